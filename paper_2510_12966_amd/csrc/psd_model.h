@@ -121,6 +121,9 @@ struct Model {
     void* xbw = nullptr;      // the same three for prompt-ingestion passes: operands with 32 column tiles, [d/16][512] partials
     void* xbw2 = nullptr;
     float* ssw = nullptr;
+    void* panel_mem = nullptr;   // wide passes: an allocation of its own, freed with the context, holding
+    float* panel_rs = nullptr;   //   [512] rms scale per column
+    void* panel_part = nullptr;  //   sums of the K quarters of a projection
     float* qkv = nullptr;     // [512][nqkv]
     float* gu = nullptr;      // [32][2F]
     float* attn_part = nullptr;  // [nsplit_max][512][H][hd + 2]
@@ -144,7 +147,7 @@ int model_init(Model& M, const psd_model_desc& desc, const char* tag, int max_se
 int model_map_pages(Model& M, int keep, int upto, int* first_changed, int* n_changed, char* err);
 
 // Enqueues one pass described by *M.desc (already on the device).  wmax: one of kNarrowClasses = widest pass the launch must cover;
-// 128, 256, 384 or 512 (bf16 models, logits == nullptr): prompt ingestion.
+// 128, 256, 384 or 512 (bf16 models, logits == nullptr, at most ingest_max): prompt ingestion.
 // logits: device [rows][V] destination (may be null when the pass produces none).
 int model_forward(Model& M, int wmax, float* logits, hipStream_t stream, Profiler* prof, char* err);
 

@@ -13,6 +13,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace psd {
 
@@ -361,6 +362,7 @@ struct GemmArgs {
     const float* ss_in;
     int ss_tiles;
     float inv_d, eps;
+    const float* rs_in;    // wide passes, EPI_SWIGLU: the columns' rms scales, from panel_scale
     // outputs
     float* Y;              // RESID: residual stream [32][ldy]; LOGITS: logits [rows][ldy]; QKV: query buffer [32][ldy]
     int ldy;
@@ -512,6 +514,48 @@ __device__ inline void epilogue(const GemmArgs& a, const DescVals& dv, int tile,
     }
 }
 
+// 16-byte load from a wave-uniform base plus a 32-bit lane offset: the address arithmetic stays in scalar registers
+__device__ inline u32x4 load16_at(const u32x4* uniform, uint32_t lane_bytes) {
+    return *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(uniform) + lane_bytes);
+}
+
+// Order of the sum over a projection's NW K ranges, the same for every pass width: the q/k/v, o and down projections
+// (EPI_QKV, EPI_RESID) add the ranges of each quarter of K in order and then the four quarters in order, so that a wide
+// pass can give a quarter to a workgroup of its own; the others add all ranges in order.
+template <int EPI>
+constexpr bool kGrouped = EPI == EPI_QKV || EPI == EPI_RESID;
+template <int NW, int EPI, typename F>
+__device__ inline f32x4 group_sum(F range) {
+    constexpr int NG = kGrouped<EPI> ? 4 : 1, PER = NW / NG;
+    static_assert(NW % NG == 0, "ranges per group");
+    f32x4 sum;
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        f32x4 gs = range(j * PER);
+#pragma unroll
+        for (int v = 1; v < PER; ++v) gs += range(j * PER + v);
+        sum = j == 0 ? gs : sum + gs;
+    }
+    return sum;
+}
+
+// rms scale of a column in a wide pass: the narrow kernels' 4 NW strided partial sums of the input's sums of squares,
+// folded as there: (0 + 1) + (2 + 3) within each group of four, the groups added in order
+template <int NW>
+__device__ inline float ss_slot(const GemmArgs& a, int slot, int col) {
+    float sum = 0.f;
+#pragma unroll 8
+    for (int st = slot; st < a.ss_tiles; st += 4 * NW) sum += a.ss_in[st * (16 * kWideCT) + col];
+    return sum;
+}
+template <int NW, int GC>
+__device__ inline float ss_scale(const GemmArgs& a, const float (*ssp)[GC], int col) {
+    float ssum = 0.f;
+#pragma unroll
+    for (int u = 0; u < NW; ++u) ssum += (ssp[4 * u][col] + ssp[4 * u + 1][col]) + (ssp[4 * u + 2][col] + ssp[4 * u + 3][col]);
+    return rsqrtf(ssum * a.inv_d + a.eps);
+}
+
 // One workgroup of NW waves per RT tiles of 16 output rows; the waves split K and are summed in wave order.
 // A wave multiplies RT row tiles by the same activation operand, which is loaded once per K step (the operand
 // comes from L2 and would otherwise cost twice the weight bytes) and only by the lanes whose column is in use.
@@ -527,18 +571,16 @@ template <int NT, int NW, int RT, int EPI, int CT, bool LB = false, bool SK = fa
 __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
     static_assert(!LB || NT == 1, "LDS staging of the operand is for one column tile");
     extern __shared__ u32x4 lb_buf[];
-    constexpr int TG = NT > 2 ? 2 : NT;   // column tiles whose partials cross LDS together
     static_assert(RT <= NW, "one finishing wave per row tile");
-    __shared__ f32x4 red[NW][RT][TG][64];
+    __shared__ f32x4 red[NW][RT][NT][64];
     constexpr bool kScaled = (EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LOGITS);
     __shared__ float ssp[kScaled ? NW : 1][16 * NT];
     const int tile0 = blockIdx.x * RT, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int k0 = (int)(((long)a.KS * wave) / NW), k1 = (int)(((long)a.KS * (wave + 1)) / NW);
     const int g = lane >> 4, cc = lane & 15;
     const DescVals dv = load_desc(a.desc);
-    // the epilogue's own reads: the narrow kernels' finishing wave asks for them once its first weights are on the way
-    constexpr bool kEarly = NT <= 2;
-    EpiPre<EPI> pre[kEarly ? NT : 1];   // wave r finishes row tile r
+    // the epilogue's own reads: the finishing wave asks for them once its first weights are on the way
+    EpiPre<EPI> pre[NT];   // wave r finishes row tile r
     float ss_mine[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) ss_mine[t] = 0.f;
@@ -555,12 +597,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
                 for (int st = gi; st < a.ss_tiles; st += 4 * NW) ss_mine[t] += a.ss_in[st * (16 * CT) + t * 16 + cc];
             }
         }
-        if constexpr (kEarly) {
-            if (wave >= RT) return;
+        if (wave >= RT) return;
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-                if (t * 16 + cc < dv.w) epi_prefetch<EPI>(a, dv, tile0 + wave, g, t * 16 + cc, pre[t]);
-        }
+        for (int t = 0; t < NT; ++t)
+            if (t * 16 + cc < dv.w) epi_prefetch<EPI>(a, dv, tile0 + wave, g, t * 16 + cc, pre[t]);
     };
     const u32x4* a_ptr = a.Wt + ((size_t)tile0 * a.KS + k0) * 64 + lane;
     const size_t tile_stride = (size_t)a.KS * 64;
@@ -578,7 +618,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
     // K steps per batch: about 16 weight loads of 16 bytes in flight per lane; 28 with seven row tiles per wave (one
     // workgroup per CU, so registers do not limit residency there; measured: 71 -> 67 ms per 1504 launches); for the
     // four-tile variant 24 or 32 in flight were slower than 16
-    constexpr int U = RT == 7 ? 4 : (NT > 2 ? (NW > 8 ? 4 : 8) : 16) / RT;
+    constexpr int U = RT == 7 ? 4 : 16 / RT;
     static_assert(U >= 1, "too many row tiles per wave");
     const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
     auto mfma_step = [&](const u32x4 (&wv)[RT], int t, const u32x4 bh, const u32x4 bl) {
@@ -815,177 +855,227 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
             if (g == 0) ssp[wave][t * 16 + cc] = sw;
         }
     }
-    // the waves' partial sums meet in LDS TG column tiles at a time; wave r adds up row tile r in wave order and
-    // finishes it, so the RT epilogues of a workgroup run side by side
+    // the waves' partial sums meet in LDS; wave r adds up row tile r in the order of group_sum and finishes it, so the RT
+    // epilogues of a workgroup run side by side
     const int w = dv.w;
 #pragma unroll
-    for (int t0 = 0; t0 < NT; t0 += TG) {
-        if (t0 > 0) __syncthreads();   // the finishing waves have read the previous group
+    for (int r = 0; r < RT; ++r)
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
+        for (int t = 0; t < NT; ++t) red[wave][r][t][lane] = acc[r][t];
+    __syncthreads();
+    if (wave >= RT) return;
 #pragma unroll
-            for (int tt = 0; tt < TG; ++tt) red[wave][r][tt][lane] = acc[r][t0 + tt];
-        __syncthreads();
-        if (wave >= RT) continue;
+    for (int t = 0; t < NT; ++t) {
+        float rs = 1.f;
+        if constexpr (kScaled) {
+            float ssum = 0.f;
 #pragma unroll
-        for (int tt = 0; tt < TG; ++tt) {
-            const int t = t0 + tt;
-            float rs = 1.f;
-            if constexpr (kScaled) {
-                float ssum = 0.f;
+            for (int v = 0; v < NW; ++v) ssum += ssp[v][t * 16 + cc];
+            rs = rsqrtf(ssum * a.inv_d + a.eps);
+        }
+        const int c = t * 16 + cc;
+        const f32x4 sum = group_sum<NW, EPI>([&](int v) { return red[v][wave][t][lane]; });
+        // whole 16-lane groups agree on c < w, and the shuffles inside the epilogue cross g only
+        if (c < w) epilogue<EPI, CT, true>(a, dv, tile0 + wave, g, c, sum, rs, pre[t]);
+    }
+}
+
+// Projections of a prompt-ingestion pass (33..512 tokens).  A workgroup of eight waves (two per SIMD) owns 8 RTW row
+// tiles x TCW column tiles; every wave multiplies RTW row tiles of its own with all of the group's columns:
+//   - weight blocks go from memory straight into the registers of the one wave that uses them, three K steps ahead
+//     (they are stored in operand order, so nothing is gained by a detour through LDS);
+//   - the group's operand (hi and lo halves) goes through three LDS buffers: a step's blocks are asked for six steps
+//     ahead, written two steps ahead and read by all waves.  One barrier per step, and the first blocks of the next
+//     step are read before it, so a step does not begin with an LDS latency.
+// Bound: the matrix cores.  A loop of these MFMAs alone settles at 1.42-1.48 PFLOP/s on this part (a plain library
+// product of 8192^3 reaches 1.48); the draft's gate/up projection (16384 x 2048, 512 columns, hi + lo) runs at 1.11
+// PFLOP/s, 62 us.  The rest is the launch, the first loads and the epilogue (14 us of it, by extrapolating the K loop
+// to zero steps).  With the weights staged through LDS as well (4 x 4 tiles per wave) it took 75 us, with four waves of
+// 4 x 8 tiles, one per SIMD, 78 us: nothing covers a wave's barriers and folds there.
+// The arithmetic is that of gemm_bf16 with NW waves: K is cut at the same NW boundaries, each range is accumulated
+// from zero by the same MFMA sequence, and the ranges are added in the same order, so the result has the same bits as
+// the narrow kernels'.
+// EPI_QKV and EPI_RESID have too few row tiles to fill the device: K is cut into the four groups of ranges that the
+// narrow kernels add up separately (group_sum), a workgroup does one of them and leaves its sums in `part`
+// ([group][row tile][column tile][64 lanes], fp32), and panel_finish adds the groups and runs the epilogue (target's
+// down projection and o projection at 512 columns: 174 us on average as one launch, 74 + 12 us in two).
+// rms scale of every column of a wide pass, once for all workgroups of the gate/up projection (each of them would
+// otherwise read 128 KB of partial sums for its own columns: 16 us of a 95 us launch on the draft's shape).
+// grid column tiles, 256 threads.
+template <int NW>
+__global__ __launch_bounds__(256) void panel_scale(const GemmArgs a, float* __restrict__ rs_out) {
+    __shared__ float ssp[4 * NW][16];
+    const int cc = threadIdx.x & 15;
 #pragma unroll
-                for (int v = 0; v < NW; ++v) ssum += ssp[v][t * 16 + cc];
-                rs = rsqrtf(ssum * a.inv_d + a.eps);
+    for (int s = threadIdx.x >> 4; s < 4 * NW; s += 16) ssp[s][cc] = ss_slot<NW>(a, s, blockIdx.x * 16 + cc);
+    __syncthreads();
+    if (threadIdx.x < 16) rs_out[blockIdx.x * 16 + cc] = ss_scale<NW, 16>(a, ssp, cc);
+}
+
+template <int NW, int EPI, int RTW, int TCW>
+__global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int tiles, const int ncg, f32x4* __restrict__ part) {
+    constexpr int CT = kWideCT;
+    constexpr bool kSplit = kGrouped<EPI>;
+    constexpr bool kScaled = (EPI == EPI_SWIGLU);             // the grouped epilogues are scaled in panel_finish
+    constexpr int GC = 16 * TCW, GW = 2 * TCW * 64;           // columns, and operand words per K step, of a column group
+    constexpr int WV = 8, TH = 64 * WV, NB = GW / TH;                              // operand words a thread stages per K step
+    constexpr int kBStep = CT * 128;
+    __shared__ float s_rs[kScaled ? GC : 1];
+    __shared__ u32x4 sB[3][GW];                               // [column tile][hi, lo][lane]: one K step each
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, cc = lane & 15;
+    // Workgroups go to the eight XCDs (one L2 each) round-robin in launch order.  The ncg column groups of a row
+    // group take consecutive slots of one XCD, so they run side by side and its weights come from memory once.
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int unit = (slot / ncg) * 8 + xcd, cg = slot % ncg, KS = a.KS;
+    const int rgi = kSplit ? unit >> 2 : unit, grp = kSplit ? unit & 3 : 0;
+    const int tile0 = (rgi * WV + wave) * RTW;
+    if (rgi * WV * RTW >= tiles) return;
+    // the K ranges of this workgroup: all of them, or those of one group
+    int v = kSplit ? grp * (NW / 4) : 0;
+    const int v_end = kSplit ? v + NW / 4 : NW;
+    const int k0 = (int)(((long)KS * v) / NW), k1 = (int)(((long)KS * v_end) / NW);
+    const u32x4* pa[RTW];
+#pragma unroll
+    for (int r = 0; r < RTW; ++r) pa[r] = a.Wt + (size_t)min(tile0 + r, tiles - 1) * KS * 64;
+    const u32x4* pb = a.XB + (size_t)cg * GW;
+    const int k_last = min(max(k1 - 1, k0), KS - 1);   // loads past the range repeat its last step and are never used
+    u32x4 wa[4][RTW], sb[4][NB];
+    auto fetch_a1 = [&](int st, int ks, int r) {
+        wa[st][r] = load16_at(pa[r] + (size_t)min(ks, k_last) * 64, lane * 16);
+    };
+    auto fetch_b1 = [&](int st, int ks, int i) { sb[st][i] = load16_at(pb + (size_t)min(ks, k_last) * kBStep + i * TH, tid * 16); };
+    auto fetch_a = [&](int st, int ks) {
+#pragma unroll
+        for (int r = 0; r < RTW; ++r) fetch_a1(st, ks, r);
+    };
+    auto fetch_b = [&](int st, int ks) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) fetch_b1(st, ks, i);
+    };
+    auto put = [&](int st, int buf) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) sB[buf][tid + i * TH] = sb[st][i];
+    };
+    // in the order of use: the operand of steps 0 and 1 first
+    fetch_b(0, k0);
+    fetch_b(1, k0 + 1);
+    fetch_a(0, k0);
+    fetch_b(2, k0 + 2);
+    fetch_a(1, k0 + 1);
+    fetch_b(3, k0 + 3);
+    fetch_a(2, k0 + 2);
+    if (kScaled && tid < GC) s_rs[tid] = a.rs_in[cg * GC + tid];
+    put(0, 0);
+    put(1, 1);
+    fetch_b(0, k0 + 4);
+    fetch_b(1, k0 + 5);
+    f32x4 cur[RTW][TCW], tot[RTW][TCW];
+    const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < RTW; ++r)
+#pragma unroll
+        for (int t = 0; t < TCW; ++t) { cur[r][t] = zero4; tot[r][t] = zero4; }
+    __syncthreads();
+    u32x4 bh = sB[0][lane], bl = sB[0][64 + lane];
+    int buf = 0, buf1 = 1, buf2 = 2;
+    int nb = k0;   // where the current range began or ends: the first step of every range folds the one before it
+    auto step = [&](int st, int ks) {
+#pragma unroll
+        for (int t = 0; t < TCW; ++t) {
+            // the step's writes and loads are spread over its column tiles: a burst of loads would hold the wave up
+            // while the memory pipeline is full
+#pragma unroll
+            for (int i = t; i < NB; i += TCW) {
+                sB[buf2][tid + i * TH] = sb[(st + 2) & 3][i];
+                fetch_b1((st + 2) & 3, ks + 6, i);
             }
-            const int c = t * 16 + cc;
-            f32x4 sum = red[0][wave][tt][lane];
 #pragma unroll
-            for (int v = 1; v < NW; ++v) sum += red[v][wave][tt][lane];
-            // whole 16-lane groups agree on c < w, and the shuffles inside the epilogue cross g only
-            if (c < w) epilogue<EPI, CT, kEarly>(a, dv, tile0 + wave, g, c, sum, rs, pre[kEarly ? t : 0]);
+            for (int r = 0; r < RTW; ++r)
+                if (t == (NB + r) % TCW) fetch_a1((st + 3) & 3, ks + 3, r);
+            const u32x4* nx = t + 1 < TCW ? &sB[buf][(t + 1) * 128] : &sB[buf1][0];
+            const u32x4 nh = nx[lane], nl = nx[64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < RTW; ++r)
+                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[st][r]), __builtin_bit_cast(bf16x8, bh),
+                                                                    cur[r][t], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < RTW; ++r)
+                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[st][r]), __builtin_bit_cast(bf16x8, bl),
+                                                                    cur[r][t], 0, 0, 0);
+            bh = nh;
+            bl = nl;
+        }
+        __syncthreads();
+        const int b0 = buf;
+        buf = buf1; buf1 = buf2; buf2 = b0;
+    };
+    // a finished range joins the total; empty ranges (fewer K steps than ranges) add nothing
+    auto fold = [&](int ks) {
+#pragma unroll
+        for (int r = 0; r < RTW; ++r)
+#pragma unroll
+            for (int t = 0; t < TCW; ++t) {
+                tot[r][t] += cur[r][t];
+                cur[r][t] = zero4;
+            }
+        do { ++v; nb = (int)(((long)KS * v) / NW); } while (nb <= ks);
+    };
+    for (int ks = k0; ks < k1; ks += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (ks + u >= k1) break;
+            if (ks + u == nb) fold(ks + u);
+            step(u, ks + u);
+        }
+    }
+    const DescVals dv = load_desc(a.desc);
+#pragma unroll
+    for (int t = 0; t < TCW; ++t) {
+        const int c = cg * GC + t * 16 + cc;
+        const float rs = kScaled ? s_rs[kScaled ? t * 16 + cc : 0] : 1.f;
+#pragma unroll
+        for (int r = 0; r < RTW; ++r) {
+            const f32x4 sum = tot[r][t] + cur[r][t];
+            const int tile = tile0 + r;
+            if constexpr (kSplit) {
+                if (tile < tiles) part[(((size_t)grp * tiles + tile) * (ncg * TCW) + cg * TCW + t) * 64 + lane] = sum;
+            } else {
+                // whole 16-lane groups agree on c < w, and the shuffles inside the epilogue cross g only
+                if (tile < tiles && c < dv.w) epilogue<EPI, CT, false>(a, dv, tile, g, c, sum, rs, EpiPre<EPI>{});
+            }
         }
     }
 }
 
-// Projections of a prompt-ingestion pass wider than 128 tokens.  A workgroup of eight waves owns 16 row tiles x
-// 32 TC columns (ncg column groups per launch) and walks the whole of K: every K step's 16 weight blocks and
-// the column group's operand (hi and lo halves) go through LDS once, double-buffered, and each wave multiplies a
-// 4 x TC block of tiles out of it, so a weight block fetched from memory is used for 32 TC columns and an operand
-// block for 256 rows.  TC = 4 moves the fewest bytes per MFMA; TC = 2 doubles the workgroups of a projection with
-// few row tiles.  The arithmetic is that of gemm_bf16 with NW waves: K is cut at the same NW boundaries, each
-// range is accumulated from zero by the same MFMA sequence, and the ranges are added in order, so the result has
-// the same bits as the narrow kernels'.
-template <int NW, int EPI, int TC>
-__global__ __launch_bounds__(512) void gemm_panel(const GemmArgs a, const int tiles, const int ncg) {
+// Second half of a grouped projection of a wide pass: adds the four groups' sums in order and runs the epilogue.
+// grid (row tiles / 16, column tiles), 256 threads: a wave finishes four row tiles of one column tile.
+template <int NW, int EPI>
+__global__ __launch_bounds__(256) void panel_finish(const GemmArgs a, const int tiles, const f32x4* __restrict__ part) {
     constexpr int CT = kWideCT;
-    constexpr bool kScaled = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
-    constexpr int GC = 32 * TC, GW = 4 * TC * 64;             // columns, and operand words per K step, of a column group
-    static_assert(TC == 2 || TC == 4, "column tiles per wave");
-    __shared__ u32x4 smem[2 * 2 * 16 * 64];                   // 64 KB: weight blocks, then operand blocks, two buffers each
-    u32x4 (*sA)[16][64] = reinterpret_cast<u32x4 (*)[16][64]>(smem);
-    u32x4 (*sB)[16][64] = reinterpret_cast<u32x4 (*)[16][64]>(smem + 2 * 16 * 64);   // [column tile][hi, lo][lane] flattened
+    __shared__ float ssp[4 * NW][16];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4, cc = lane & 15;
-    const int wr = wave >> 1, wc = wave & 1;     // rows 4 wr .. + 4 of the 16 tiles, column tiles TC wc .. + TC of the group's
-    // Workgroups go to the eight XCDs (one L2 each) round-robin in launch order.  The ncg column groups of a row
-    // group take consecutive slots of one XCD, so they run side by side and its weights come from memory once.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int rgi = (slot / ncg) * 8 + xcd, cg = slot % ncg, KS = a.KS;
-    if (rgi * 16 >= tiles) return;
-    const int tile0 = rgi * 16;
-    constexpr int kBStep = CT * 128;
-    // what this thread stages per K step: two weight words and two operand words
-    const int ta = tile0 + (tid >> 6);
-    const u32x4* pa0 = a.Wt + (size_t)(ta < tiles ? ta : tiles - 1) * KS * 64 + lane;
-    const u32x4* pa1 = a.Wt + (size_t)(ta + 8 < tiles ? ta + 8 : tiles - 1) * KS * 64 + lane;
-    const u32x4* pb = a.XB + (size_t)cg * GW + tid;
-    struct Stage { u32x4 a0, a1, b0, b1; };
-    auto fetch = [&](Stage& s, int ks) {
-        s.a0 = __builtin_nontemporal_load(pa0 + (size_t)ks * 64);
-        s.a1 = __builtin_nontemporal_load(pa1 + (size_t)ks * 64);
-        s.b0 = pb[(size_t)ks * kBStep];
-        if constexpr (GW > 512) s.b1 = pb[(size_t)ks * kBStep + 512];
-    };
-    Stage s0, s1;
-    fetch(s0, 0);
-    if (KS > 1) fetch(s1, 1);
-    float rs[TC];
+    const int ct = blockIdx.y, nct = gridDim.y, c = ct * 16 + cc;
+    const int tile0 = blockIdx.x * 16 + wave * 4;
+    f32x4 p[4][4];
 #pragma unroll
-    for (int t = 0; t < TC; ++t) rs[t] = 1.f;
-    if constexpr (kScaled) {
-        // the narrow kernels' 4 NW strided partial sums of the input's sums of squares, per column, folded as there:
-        // (0 + 1) + (2 + 3) within each group of four, the groups added in order
-        float (*ssp)[GC] = reinterpret_cast<float (*)[GC]>(smem);
-        const int col = tid % GC;
-        for (int slot = tid / GC; slot < 4 * NW; slot += 512 / GC) {
-            float sum = 0.f;
-            for (int st = slot; st < a.ss_tiles; st += 4 * NW) sum += a.ss_in[st * (16 * CT) + cg * GC + col];
-            ssp[slot][col] = sum;
-        }
-        __syncthreads();
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int t = 0; t < TC; ++t) {
-            float ssum = 0.f;
-#pragma unroll
-            for (int u = 0; u < NW; ++u) {
-                const int col = (wc * TC + t) * 16 + cc;
-                ssum += (ssp[4 * u][col] + ssp[4 * u + 1][col]) + (ssp[4 * u + 2][col] + ssp[4 * u + 3][col]);
-            }
-            rs[t] = rsqrtf(ssum * a.inv_d + a.eps);
-        }
-        __syncthreads();
-    }
-    f32x4 cur[4][TC], tot[4][TC];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int t = 0; t < TC; ++t) { cur[r][t] = f32x4{0.f, 0.f, 0.f, 0.f}; tot[r][t] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    // K ranges end at KS (v + 1) / NW; the launcher guarantees KS >= NW, so none is empty.  A range's sum starts from
-    // +0 and can therefore never be -0: adding it to a zero total leaves its bits as they are.
-    int v = 0, nb = KS / NW;
-    auto fold = [&]() {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int t = 0; t < TC; ++t) {
-                tot[r][t] += cur[r][t];
-                cur[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        ++v;
-        nb = (int)(((long)KS * (v + 1)) / NW);
-    };
-    auto put = [&](const Stage& s, int buf) {
-        sA[buf][tid >> 6][lane] = s.a0;
-        sA[buf][8 + (tid >> 6)][lane] = s.a1;
-        (&sB[buf][0][0])[tid] = s.b0;
-        if constexpr (GW > 512) (&sB[buf][0][0])[tid + 512] = s.b1;
-    };
-    auto multiply = [&](int buf) {
-        u32x4 wv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) wv[r] = sA[buf][wr * 4 + r][lane];
-#pragma unroll
-        for (int t = 0; t < TC; ++t) {
-            const u32x4 bh = sB[buf][(wc * TC + t) * 2][lane], bl = sB[buf][(wc * TC + t) * 2 + 1][lane];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[r]),
-                                                                    __builtin_bit_cast(bf16x8, bh), cur[r][t], 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[r]),
-                                                                    __builtin_bit_cast(bf16x8, bl), cur[r][t], 0, 0, 0);
-        }
-    };
-    // K step ks is multiplied out of LDS buffer ks & 1 while step ks + 1 is written to the other buffer and
-    // steps ks + 2, ks + 3 are in flight in registers
-    put(s0, 0);
-    if (KS > 2) fetch(s0, 2);
-    __syncthreads();
-    for (int ks = 0; ks < KS; ks += 2) {
-        if (ks == nb) fold();
-        if (ks + 1 < KS) put(s1, 1);
-        if (ks + 3 < KS) fetch(s1, ks + 3);
-        multiply(0);
-        __syncthreads();
-        if (ks + 1 >= KS) break;
-        if (ks + 1 == nb) fold();
-        if (ks + 2 < KS) put(s0, 0);
-        if (ks + 4 < KS) fetch(s0, ks + 4);
-        multiply(1);
-        __syncthreads();
-    }
-    fold();
+        for (int j = 0; j < 4; ++j)
+            p[i][j] = part[(((size_t)j * tiles + min(tile0 + i, tiles - 1)) * nct + ct) * 64 + lane];
     const DescVals dv = load_desc(a.desc);
-    const int w = dv.w;
+    float rs = 1.f;
+    if constexpr (EPI == EPI_QKV) {
+        for (int s = tid >> 4; s < 4 * NW; s += 16) ssp[s][cc] = ss_slot<NW>(a, s, c);
+        __syncthreads();
+        rs = ss_scale<NW, 16>(a, ssp, cc);
+    }
+    if (c >= dv.w) return;   // whole 16-lane groups agree, and the shuffles inside the epilogue cross g only
 #pragma unroll
-    for (int t = 0; t < TC; ++t) {
-        const int c = cg * GC + (wc * TC + t) * 16 + cc;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int tile = tile0 + wr * 4 + r;
-            // whole 16-lane groups agree on c < w, and the shuffles inside the epilogue cross g only
-            if (tile < tiles && c < w) epilogue<EPI, CT, false>(a, dv, tile, g, c, tot[r][t], rs[t], EpiPre<EPI>{});
-        }
+    for (int i = 0; i < 4; ++i) {
+        if (tile0 + i >= tiles) break;
+        const f32x4 sum = ((p[i][0] + p[i][1]) + p[i][2]) + p[i][3];
+        epilogue<EPI, CT, false>(a, dv, tile0 + i, g, c, sum, rs, EpiPre<EPI>{});
     }
 }
 
@@ -1037,8 +1127,7 @@ __global__ __launch_bounds__(1024) void gemm_o_narrow(const GemmArgs a, const fl
     if (wave > 0) red[wave - 1][lane] = acc;
     __syncthreads();
     if (wave != 0) return;
-#pragma unroll
-    for (int v = 0; v < NW - 1; ++v) acc += red[v][lane];
+    acc = group_sum<NW, EPI_RESID>([&](int v) { return v == 0 ? acc : red[v - 1][lane]; });
     if (cc < w) epilogue<EPI_RESID, 2, true>(a, dv, tile, g, cc, acc, 1.f, pre);
 }
 
@@ -1470,10 +1559,10 @@ static void model_shape(Model& M, const psd_model_desc& m, int max_seq) {
     M.max_seq = max_seq;
     M.n_pages = (max_seq + kPage - 1) / kPage;
     M.nsplit_max = (max_seq + kAttnSplit - 1) / kAttnSplit;
-    // the panel kernel of the widest passes wants every K range of every projection non-empty
-    auto panel_ok = [](int n, int k) { return k / 32 >= (round16(n) / 16 <= 256 ? 16 : 8); };
-    M.ingest_max = m.dtype != PSD_BF16 ? kMaxW
-                   : (panel_ok(M.nqkv, M.d) && panel_ok(M.d, M.H * M.hd) && panel_ok(2 * M.F, M.d) && panel_ok(M.d, M.F)) ? kCols : 128;
+    // what the interface takes: 512 tokens per ingestion pass where no K range of any projection is empty, else 128
+    auto ranges_ok = [](int n, int k) { return k / 32 >= (round16(n) / 16 <= 256 ? 16 : 8); };
+    M.ingest_max = M.dtype != PSD_BF16 ? kMaxW
+                   : (ranges_ok(M.nqkv, M.d) && ranges_ok(M.d, M.H * M.hd) && ranges_ok(2 * M.F, M.d) && ranges_ok(M.d, M.F)) ? kCols : 128;
 }
 
 size_t model_pool_bytes(const psd_model_desc& m, int max_seq) {
@@ -1575,6 +1664,12 @@ int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, 
         PSD_HIP(hipMemsetAsync(M.xbw, 0, kmax * 4 * kCols, stream), err);
         PSD_HIP(hipMemsetAsync(M.xbw2, 0, kmax * 4 * kCols, stream), err);
         PSD_HIP(hipMemsetAsync(M.ssw, 0, (size_t)(M.d / 16) * kCols * sizeof(float), stream), err);
+    }
+    if (bf) {   // wide passes: the columns' rms scales, then the sums of the four K quarters of a grouped projection
+        const size_t rs_bytes = kCols * sizeof(float);
+        PSD_HIP(hipMalloc(&M.panel_mem, rs_bytes + (size_t)4 * (round16(std::max(M.nqkv, M.d)) / 16) * (M.ingest_max / 16) * 64 * sizeof(f32x4)), err);
+        M.panel_rs = (float*)M.panel_mem;
+        M.panel_part = (char*)M.panel_mem + rs_bytes;
     }
     // page bookkeeping: every logical block unmapped, free list in (optionally scrambled) order
     M.h_page_table.assign(M.n_pages, -1);
@@ -1688,6 +1783,25 @@ static int forward_f32(Model& M, int wmax, float* logits, Launch& L) {
     return PSD_OK;
 }
 
+// Projection of a prompt-ingestion pass.  NW: the K split of the narrow kernels.
+template <int NW, int EPI, int RTW, int TCW>
+static void launch_panel_as(Launch& L, GemmArgs a, int tiles) {
+    Model& M = L.M;
+    const int ncg = L.wcls / (16 * TCW), units = (tiles + 8 * RTW - 1) / (8 * RTW) * (kGrouped<EPI> ? 4 : 1);
+    a.rs_in = M.panel_rs;
+    if constexpr (EPI == EPI_SWIGLU) panel_scale<NW><<<L.wcls / 16, 256, 0, L.s>>>(a, M.panel_rs);
+    gemm_panel<NW, EPI, RTW, TCW><<<(units + 7) / 8 * 8 * ncg, 512, 0, L.s>>>(a, tiles, ncg, (f32x4*)M.panel_part);
+    if constexpr (kGrouped<EPI>) panel_finish<NW, EPI><<<dim3((tiles + 15) / 16, L.wcls / 16), 256, 0, L.s>>>(a, tiles, (const f32x4*)M.panel_part);
+}
+template <int NW, int EPI>
+static void launch_panel(Launch& L, const GemmArgs& a, int tiles) {
+    // 256 x 128 outputs per workgroup move the fewest bytes per MFMA; smaller tiles where those would leave CUs idle
+    const int full = (tiles + 15) / 16 * (kGrouped<EPI> ? 4 : 1) * (L.wcls / 128);
+    if (full >= 192) launch_panel_as<NW, EPI, 2, 8>(L, a, tiles);
+    else if (full >= 96) launch_panel_as<NW, EPI, 2, 4>(L, a, tiles);
+    else launch_panel_as<NW, EPI, 1, 4>(L, a, tiles);
+}
+
 // bf16 models: five or six launches per layer (q/k/v projection, attention, merge, o, gate/up, down)
 template <int EPI>
 static void launch_gemm_bf16(Launch& L, const char* family, GemmArgs a) {
@@ -1700,30 +1814,10 @@ static void launch_gemm_bf16(Launch& L, const char* family, GemmArgs a) {
     // from the pass width: a token's result must not depend on the width of the pass that computes it.  Row tiles
     // per wave do not change the arithmetic and are picked per width class.
 #define PSD_GEMM(NT_, NW_, RT_, CT_) gemm_bf16<NT_, NW_, RT_, EPI, CT_><<<tiles / RT_, 64 * NW_, 0, L.s>>>(a)
-    if (L.wcls > 128) {   // several column groups of 128: weights and operand shared through LDS
+    if (L.wcls > kMaxW) {   // prompt ingestion
         if constexpr (EPI != EPI_LOGITS) {
-            // NW: the K split of the narrow kernels.  Column groups of 64 where groups of 128 would leave CUs idle.
-            const int rg = (tiles + 15) / 16, rg8 = (rg + 7) / 8 * 8;
-            if (rg * (L.wcls / 128) >= 192) {
-                const int ncg = L.wcls / 128;
-                if (tiles <= 256) gemm_panel<16, EPI, 4><<<rg8 * ncg, 512, 0, L.s>>>(a, tiles, ncg);
-                else gemm_panel<8, EPI, 4><<<rg8 * ncg, 512, 0, L.s>>>(a, tiles, ncg);
-            } else {
-                const int ncg = L.wcls / 64;
-                if (tiles <= 256) gemm_panel<16, EPI, 2><<<rg8 * ncg, 512, 0, L.s>>>(a, tiles, ncg);
-                else gemm_panel<8, EPI, 2><<<rg8 * ncg, 512, 0, L.s>>>(a, tiles, ncg);
-            }
-        }
-    } else if (L.wcls > 32) {   // 128 columns: every weight block is used 8 times as often, so more row tiles share an operand load
-        if (tiles <= 256) {
-            // two row tiles per wave only where the workgroup's LDS stays under 64 KB (no sum-of-squares table)
-            if (EPI == EPI_RESID && tiles % 2 == 0) PSD_GEMM(8, 16, 2, kWideCT); else PSD_GEMM(8, 16, 1, kWideCT);
-        } else if (tiles % 4 == 0) {
-            PSD_GEMM(8, 8, 4, kWideCT);
-        } else if (tiles % 2 == 0) {
-            PSD_GEMM(8, 8, 2, kWideCT);
-        } else {
-            PSD_GEMM(8, 8, 1, kWideCT);
+            if (tiles <= 256) launch_panel<16, EPI>(L, a, tiles);
+            else launch_panel<8, EPI>(L, a, tiles);
         }
     } else {
         const bool wide = L.wcls > 16;

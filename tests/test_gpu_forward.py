@@ -155,6 +155,29 @@ def test_bf16_prompt_ingestion_in_512_token_passes_is_bit_exact():
     ctx.close()
 
 
+# one shape per tile size and K split of the wide projection kernel that the models above do not reach: 256 x 128
+# workgroup tiles for q/k/v with 16 K ranges (30 K steps: ranges of one and two) and with 8 (44 steps), and for gate/up,
+# each with a last row group that is not full
+PANEL = (ModelShape(1, 960, 15, 15, 2848, 1000), ModelShape(1, 512, 8, 8, 6176, 1000), ModelShape(1, 1408, 11, 11, 608, 1000))
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+@pytest.mark.parametrize("n", [509, 512, 385])
+def test_bf16_wide_projection_tiles_are_bit_exact(which, n):
+    blobs = [synth.target_weights(s, 60 + i, synth.DTYPE_BF16, sigma=0.03) for i, s in enumerate(PANEL)]
+    ctx = _ctx(PANEL, blobs, synth.DTYPE_BF16, 10000.0, 576)
+    toks = synth.tokens(13, 0, n + 3, 1000)
+    out = []
+    for step in (512, 32):
+        for pos in range(0, n, step):
+            ctx.forward(which, toks[pos:min(pos + step, n)], pos, want_logits=False)
+        out.append(ctx.forward(which, toks[n:n + 3], n))
+    ctx.close()
+    assert np.array_equal(out[0], out[1])
+    ref = oracle.Model(PANEL[which], blobs[which], synth.DTYPE_BF16, 10000.0, 576).forward(toks, 0)[n:]
+    assert np.abs(out[0] - ref).max() <= TOL_BF16
+
+
 def test_bf16_ingestion_at_page_split_and_pass_boundaries():
     # prompt lengths around the KV page (64), the attention key range (128) and the pass widths (128, 512):
     # the widest passes, 32-token passes and a ragged mix leave identical logits for the tokens that follow
