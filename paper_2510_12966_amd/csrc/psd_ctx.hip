@@ -211,7 +211,7 @@ static int map_pages(psd_ctx* c, Model& M, int keep, int upto) {
     int32_t tmp[kPerSlot];
     for (int done = 0; done < n; done += kPerSlot) {
         const int cnt = std::min(kPerSlot, n - done);
-        for (int i = 0; i < cnt; ++i) tmp[i] = std::max(M.h_page_table[first + done + i], 0);   // unmapped: page 0, never read
+        for (int i = 0; i < cnt; ++i) tmp[i] = std::max(M.h_page_table[first + done + i], 0);   // unmapped: page 0
         if ((rc = upload(c, M.page_table + first + done, tmp, (size_t)cnt * sizeof(int32_t))) != PSD_OK) return rc;
     }
     return PSD_OK;

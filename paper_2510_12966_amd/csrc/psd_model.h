@@ -143,7 +143,7 @@ int model_init(Model& M, const psd_model_desc& desc, const char* tag, int max_se
 
 // Makes sure KV pages exist for positions < upto and frees pages wholly beyond `keep`, in the host mirror of the page
 // table; reports which entries changed ([*first_changed, +*n_changed), none: 0 entries) so that the caller can upload
-// just those (device entries of unmapped blocks are never read: attention stops at the pass's last position).
+// just those (the caller sends page 0 for unmapped blocks: every device entry names a valid page at all times).
 int model_map_pages(Model& M, int keep, int upto, int* first_changed, int* n_changed, char* err);
 
 // Enqueues one pass described by *M.desc (already on the device).  wmax: one of kNarrowClasses = widest pass the launch must cover;

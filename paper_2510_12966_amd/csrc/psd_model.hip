@@ -21,7 +21,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-enum { EPI_STORE = 0, EPI_RESID = 1, EPI_LOGITS = 2 };
+enum { EPI_RESID = 1, EPI_LOGITS = 2 };
 
 // ---- operand packing ----------------------------------------------------------------------------
 // GEMM input X[c][f] (c < 16 CT tokens, f < K features), bf16 path: [K/32][CT col tiles][hi, lo][64 lanes][8]
@@ -43,47 +43,12 @@ __device__ inline void pack_store(void* xb, int K, int c, int f, float v) {
 }
 
 // ---- small kernels ------------------------------------------------------------------------------
-template <bool BF16>
-__global__ __launch_bounds__(256) void embed_rows(const void* embed, const PassDesc* desc, float* x, int d, int V) {
+__global__ __launch_bounds__(256) void embed_rows(const float* embed, const PassDesc* desc, float* x, int d, int V) {
     const int c = blockIdx.x;
     if (c >= desc->w) return;
     int tok = desc->tok[c];
     tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);  // ids are validated on the host; never index outside the table
-    for (int f = threadIdx.x; f < d; f += 256) {
-        float v;
-        if constexpr (BF16) {
-            const int KS = d >> 5;
-            const size_t idx = ((((size_t)(tok >> 4) * KS + (f >> 5)) * 64) + ((f & 31) >> 3) * 16 + (tok & 15)) * 8 + (f & 7);
-            v = bf16_to_f32(((const uint16_t*)embed)[idx]);
-        } else {
-            v = ((const float*)embed)[(size_t)tok * d + f];
-        }
-        x[(size_t)c * d + f] = v;
-    }
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(256) void rmsnorm_pack(const float* x, const float* gain, const PassDesc* desc, void* xb,
-                                                    int d, float eps) {
-    __shared__ float sm[4];
-    const int c = blockIdx.x;
-    if (c >= desc->w) return;
-    const float* row = x + (size_t)c * d;
-    float ss = 0.f;
-    for (int f = threadIdx.x; f < d; f += 256) ss += row[f] * row[f];
-    ss = block_sum<4>(ss, sm);
-    const float r = rsqrtf(ss / (float)d + eps);
-    for (int f = threadIdx.x; f < d; f += 256) pack_store<BF16>(xb, d, c, f, row[f] * r * gain[f]);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(256) void swiglu_pack(const float* gu, const PassDesc* desc, void* xb, int F) {
-    const int c = blockIdx.x;
-    if (c >= desc->w) return;
-    const int f = blockIdx.y * 256 + threadIdx.x;
-    if (f >= F) return;
-    const float g = gu[(size_t)c * 2 * F + f], u = gu[(size_t)c * 2 * F + F + f];
-    pack_store<BF16>(xb, F, c, f, g / (1.f + expf(-g)) * u);
+    for (int f = threadIdx.x; f < d; f += 256) x[(size_t)c * d + f] = embed[(size_t)tok * d + f];
 }
 
 __global__ void rope_table(float2* tab, int max_seq, int half, double theta) {
@@ -158,34 +123,6 @@ __device__ inline int kv_v_off(int slot, int dim) {
 
 __device__ inline size_t kv_base(int page, int layer, int L, int g, int KV, int which, int hd) {
     return ((((size_t)page * L + layer) * KV + g) * 2 + which) * (size_t)kPage * hd;
-}
-
-// grid (wmax, H + 2 KV), block hd/2: q heads are rotated in place, k heads rotated into the cache, v copied
-template <typename KVT>
-__global__ void rope_kv(float* qkv, const PassDesc* desc, const float2* rope, KVT* kv, const int32_t* page_table,
-                        int layer, int L, int H, int KV, int hd, int nqkv) {
-    const int c = blockIdx.x, h = blockIdx.y, i = threadIdx.x, half = hd >> 1;
-    if (c >= desc->w) return;
-    const int pos = desc->pos0 + c;
-    float* v = qkv + (size_t)c * nqkv + (size_t)h * hd;
-    const int page = page_table[pos / kPage], slot = pos % kPage;
-    if (h < H + KV) {
-        const float2 cs = rope[(size_t)pos * half + i];
-        const float a = v[i], b = v[i + half];
-        const float ra = a * cs.x - b * cs.y, rb = b * cs.x + a * cs.y;
-        if (h < H) {
-            v[i] = ra;
-            v[i + half] = rb;
-        } else {
-            KVT* dst = kv + kv_base(page, layer, L, h - H, KV, 0, hd) + (size_t)slot * hd;
-            kv_store<KVT>(dst + i, ra);
-            kv_store<KVT>(dst + i + half, rb);
-        }
-    } else {
-        KVT* dst = kv + kv_base(page, layer, L, h - H - KV, KV, 1, hd) + (size_t)slot * hd;
-        kv_store<KVT>(dst + i, v[i]);
-        kv_store<KVT>(dst + i + half, v[i + half]);
-    }
 }
 
 // ---- attention -------------------------------------------------------------------------------------
@@ -1416,32 +1353,280 @@ __global__ __launch_bounds__(256) void attn_combine_long(const float* part, cons
     }
 }
 
-// fp32 weights, row-major [N][K]; X fp32 rows [c][K].  One wave per output row.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ W, const float* __restrict__ X,
-                                                float* __restrict__ Y, int N, int K, int ldy,
-                                                const PassDesc* __restrict__ desc) {
-    const int n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (n >= N) return;
-    const int w = desc->w;
-    const float* wr = W + (size_t)n * K;
-    for (int c = 0; c < w; ++c) {
-        int row = c;
-        if constexpr (EPI == EPI_LOGITS) {
-            const int first = w - desc->n_logit;
-            if (c < first) continue;
-            row = desc->logit_row0 + c - first;
-        }
-        const float* xr = X + (size_t)c * K;
-        float acc = 0.f;
-        for (int k = lane; k < K; k += 64) acc += wr[k] * xr[k];
-        acc = wave_sum(acc);
-        if (lane == 0) {
-            float* dst = Y + (size_t)row * ldy + n;
-            if constexpr (EPI == EPI_RESID) *dst += acc;
-            else *dst = acc;
-        }
+// ---- fp32 models -------------------------------------------------------------------------------------------
+// Projection Y[c][n] = sum_k W[n][k] X[c][k] of a pass of up to 32 tokens, plain VALU, weights row-major [N][K].  These
+// models are small, so a pass is a chain of launches of a few microseconds each and what counts is how many there are
+// and how long a dependent chain each one holds: the norm in front and the rotation / cache append / SwiGLU / residual
+// behind a projection are part of it (5 launches per layer; as kernels of their own they were 10).
+// LP lanes share a pair of output rows (n1, n2): a rotary pair, a gate row and its up row, or two neighbours.  A lane
+// takes 4 adjacent k of every 4 LP, its sums over NC columns stay in registers and are folded across the LP lanes at
+// the end, so the weights are read 16 bytes per lane and the serial part is K / (4 LP) steps.  grid.y workgroups take the
+// column groups in turn.  Every column's
+// arithmetic is the same whatever NC and the pass width.
+enum { F32_QKV, F32_RESID, F32_SWIGLU, F32_LOGITS };
+struct F32Args {
+    const float* W;
+    const float* X;      // [32][K]
+    const float* gain;   // RMSNorm of X in front (null: none)
+    float* Y;            // QKV: query buffer [32][ldy]; RESID: residual stream; SWIGLU: [32][N / 2]; LOGITS: rows
+    int N, K, ldy;
+    float eps;
+    const PassDesc* desc;
+    const float2* rope;  // QKV only, from here
+    float* kv;
+    const int32_t* page_table;
+    int layer, L, H, KV, hd;
+};
+constexpr int kF32Chunk = 1024;   // K entries of X staged in LDS at a time
+
+// sum over LP lanes (16 or 64), every lane gets it; fixed tree
+template <int LP>
+__device__ inline float lanes_sum(float v) {
+    auto dpp = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v += dpp(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+    v += dpp(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+    v += dpp(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror
+    if constexpr (LP == 64) {
+        v += __shfl_xor(v, 16, kWave);
+        v += __shfl_xor(v, 32, kWave);
     }
+    return v;
+}
+
+template <int EPI, int LP, int NC>
+__global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
+    __shared__ float xs[NC][kF32Chunk];
+    __shared__ float gs[kF32Chunk];
+    __shared__ float rsc[NC];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, sub = tid % LP;
+    const int K = a.K, npairs = (a.N + 1) >> 1, pair = blockIdx.x * (256 / LP) + tid / LP, pc = min(pair, npairs - 1);
+    int n1, n2;
+    if constexpr (EPI == F32_QKV) {
+        const int half = a.hd >> 1;
+        n1 = (pc / half) * a.hd + pc % half;
+        n2 = n1 + half;
+    } else if constexpr (EPI == F32_SWIGLU) {
+        n1 = pc;
+        n2 = (a.N >> 1) + pc;
+    } else {
+        n1 = 2 * pc;
+        n2 = min(n1 + 1, a.N - 1);
+    }
+    const float* w1 = a.W + (size_t)n1 * K;
+    const float* w2 = a.W + (size_t)n2 * K;
+    // nothing of this depends on the pass descriptor: the first steps' weights and the gains are asked for at once
+    constexpr int U = 4;
+    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 p0[U], q0[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = sub * 4 + u * 4 * LP;
+        p0[u] = k < K ? *reinterpret_cast<const float4*>(w1 + k) : zero4;
+        q0[u] = k < K ? *reinterpret_cast<const float4*>(w2 + k) : zero4;
+    }
+    const bool once = K <= kF32Chunk;   // X is staged once per column group
+    if (a.gain && once)
+        for (int k = tid * 4; k < K; k += 1024) *reinterpret_cast<float4*>(gs + k) = *reinterpret_cast<const float4*>(a.gain + k);
+    const int w = a.desc->w, pos0 = a.desc->pos0;
+    const int first = EPI == F32_LOGITS ? w - a.desc->n_logit : 0, row0 = EPI == F32_LOGITS ? a.desc->logit_row0 : 0;
+    for (int c0 = first + (int)blockIdx.y * NC; c0 < w; c0 += NC * (int)gridDim.y) {
+        const int nc = min(NC, w - c0);
+        const float* x0 = a.X + (size_t)c0 * K;
+        auto square_sum = [&](const float* row) {   // one wave
+            float ss = 0.f;
+            for (int k = lane * 4; k < K; k += 256) {
+                const float4 v = *reinterpret_cast<const float4*>(row + k);
+                ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+            }
+            return lanes_sum<64>(ss);
+        };
+        if (a.gain && !once) {
+            for (int c = wave; c < nc; c += 4) {
+                const float ss = square_sum(x0 + (size_t)c * K);
+                if (lane == 0) rsc[c] = rsqrtf(ss / (float)K + a.eps);
+            }
+            __syncthreads();
+        }
+        float acc1[NC], acc2[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) { acc1[c] = 0.f; acc2[c] = 0.f; }
+        auto step = [&](const float4 p, const float4 q, int k) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {   // columns past nc: whatever LDS holds, never stored
+                const float4 x = *reinterpret_cast<const float4*>(&xs[c][k]);
+                acc1[c] = fmaf(p.x, x.x, acc1[c]); acc1[c] = fmaf(p.y, x.y, acc1[c]);
+                acc1[c] = fmaf(p.z, x.z, acc1[c]); acc1[c] = fmaf(p.w, x.w, acc1[c]);
+                acc2[c] = fmaf(q.x, x.x, acc2[c]); acc2[c] = fmaf(q.y, x.y, acc2[c]);
+                acc2[c] = fmaf(q.z, x.z, acc2[c]); acc2[c] = fmaf(q.w, x.w, acc2[c]);
+            }
+        };
+        for (int kc = 0; kc < K; kc += kF32Chunk) {
+            const int kn = min(kF32Chunk, K - kc), kq = kn >> 2;
+            if (kc > 0) __syncthreads();   // the previous chunk has been read
+            auto normalised = [&](float4 v, int c, int k) {
+                const float r = rsc[c];
+                const float4 gn = *reinterpret_cast<const float4*>(once ? gs + k : a.gain + kc + k);
+                return make_float4(v.x * r * gn.x, v.y * r * gn.y, v.z * r * gn.z, v.w * r * gn.w);
+            };
+            for (int i = tid; i < nc * kq; i += 256) {
+                const int c = i / kq, k = (i - c * kq) * 4;
+                const float4 v = *reinterpret_cast<const float4*>(x0 + (size_t)c * K + kc + k);
+                *reinterpret_cast<float4*>(&xs[c][k]) = a.gain && !once ? normalised(v, c, k) : v;
+            }
+            __syncthreads();
+            if (a.gain && once) {   // squares and scaling out of LDS: X makes one trip from memory
+                for (int c = wave; c < nc; c += 4) {
+                    const float ss = square_sum(xs[c]);
+                    if (lane == 0) rsc[c] = rsqrtf(ss / (float)K + a.eps);
+                }
+                __syncthreads();
+                for (int i = tid; i < nc * kq; i += 256) {
+                    const int c = i / kq, k = (i - c * kq) * 4;
+                    float4* x = reinterpret_cast<float4*>(&xs[c][k]);
+                    *x = normalised(*x, c, k);
+                }
+                __syncthreads();
+            }
+            int k = sub * 4;
+            if (kc == 0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u, k += 4 * LP)
+                    if (k < kn) step(p0[u], q0[u], k);
+            }
+#pragma unroll 4
+            for (; k < kn; k += 4 * LP)
+                step(*reinterpret_cast<const float4*>(w1 + kc + k), *reinterpret_cast<const float4*>(w2 + kc + k), k);
+        }
+        // lane c of a pair's LP lanes finishes column c
+        float v1 = 0.f, v2 = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const float s1 = lanes_sum<LP>(acc1[c]), s2 = lanes_sum<LP>(acc2[c]);
+            if (sub == c) { v1 = s1; v2 = s2; }
+        }
+        if (sub < nc && pair < npairs) {
+            const int c = c0 + sub;
+            if constexpr (EPI == F32_RESID) {
+                float* y = a.Y + (size_t)c * a.ldy;
+                y[n1] += v1;
+                if (n2 != n1) y[n2] += v2;
+            } else if constexpr (EPI == F32_SWIGLU) {
+                a.Y[(size_t)c * a.ldy + n1] = v1 / (1.f + expf(-v1)) * v2;
+            } else if constexpr (EPI == F32_LOGITS) {
+                float* y = a.Y + (size_t)(row0 + c - first) * a.ldy;
+                y[n1] = v1;
+                if (n2 != n1) y[n2] = v2;
+            } else {
+                const int hd = a.hd, head = n1 / hd, i = n1 % hd, pos = pos0 + c;
+                if (head < a.H + a.KV) {
+                    const float2 cs = a.rope[(size_t)pos * (hd >> 1) + i];
+                    const float r1 = v1 * cs.x - v2 * cs.y, r2 = v2 * cs.x + v1 * cs.y;
+                    v1 = r1; v2 = r2;
+                }
+                float* y;
+                if (head < a.H) {
+                    y = a.Y + (size_t)c * a.ldy + (size_t)head * hd;
+                } else {
+                    const int g = head - a.H, which = g >= a.KV;
+                    y = a.kv + kv_base(a.page_table[pos / kPage], a.layer, a.L, which ? g - a.KV : g, a.KV, which, hd) + (size_t)(pos % kPage) * hd;
+                }
+                y[i] = v1;
+                y[i + (hd >> 1)] = v2;
+            }
+        }
+        if (c0 + NC * (int)gridDim.y < w) __syncthreads();   // xs and rsc are written again
+    }
+}
+
+// Attention of an fp32 model at contexts of at most kF32OneSplits key ranges: one workgroup per (head, query) takes all
+// of them, wave v the ranges v, v + 4, and merges them in order; the arithmetic is that of attn_partial and
+// attn_combine_pack, so a token's output does not depend on which route its launch takes.
+// grid (H, wmax), 256 threads, writes the o projection's input [c][H hd].
+constexpr int kF32OneSplits = 8;
+__global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qkv, const PassDesc* desc, const float* __restrict__ kv,
+                                                    const int32_t* __restrict__ page_table, int n_pages, float* __restrict__ out, int layer,
+                                                    int L, int H, int KV, int hd, int nqkv) {
+    __shared__ float s_q[128], s_p[4][kAttnSplit], s_m[kF32OneSplits], s_l[kF32OneSplits], s_o[kF32OneSplits][128];
+    const int h = blockIdx.x, c = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int g = h / (H / KV);
+    if ((int)threadIdx.x < hd) s_q[threadIdx.x] = qkv[(size_t)c * nqkv + (size_t)h * hd + threadIdx.x];
+    __syncthreads();
+    const float scale = rsqrtf((float)hd);
+    // a key range is two pages; lane j takes keys j and j + 64 of it.  Any page of the table can be read (keys that are not
+    // there are masked afterwards), so a wave's first range is on its way before the pass descriptor has arrived
+    auto plane = [&](int sp, int half, int which) {
+        return kv + kv_base(page_table[min(2 * sp + half, n_pages - 1)], layer, L, g, KV, which, hd);
+    };
+    auto dot = [&](int sp, int half) {
+        const float* kr = plane(sp, half, 0) + (size_t)lane * hd;
+        float acc = 0.f;
+#pragma unroll 8
+        for (int i = 0; i < hd; i += 4) {
+            const float4 k4 = *reinterpret_cast<const float4*>(kr + i);
+            acc = fmaf(s_q[i], k4.x, acc); acc = fmaf(s_q[i + 1], k4.y, acc);
+            acc = fmaf(s_q[i + 2], k4.z, acc); acc = fmaf(s_q[i + 3], k4.w, acc);
+        }
+        return acc * scale;
+    };
+    float v0[32];   // the first 32 values of head dim `lane` of the first range
+    {
+        const float* vp = plane(wave, 0, 1) + min(lane, hd - 1);
+#pragma unroll
+        for (int u = 0; u < 32; ++u) v0[u] = vp[(size_t)u * hd];
+    }
+    float s0 = dot(wave, 0), s1 = dot(wave, 1);
+    if (c >= desc->w) return;
+    const int nkeys = desc->pos0 + c + 1, nsp = min((nkeys + kAttnSplit - 1) / kAttnSplit, kF32OneSplits);
+    float* p = s_p[wave];
+    for (int sp = wave; sp < nsp; sp += 4) {
+        const int visible = min(kAttnSplit, nkeys - sp * kAttnSplit);
+        if (sp != wave) { s0 = dot(sp, 0); s1 = dot(sp, 1); }
+        if (lane >= visible) s0 = -INFINITY;
+        if (lane + 64 >= visible) s1 = -INFINITY;
+        const float m = wave_max(fmaxf(s0, s1));
+        const float p0 = expf(s0 - m), p1 = expf(s1 - m);  // exp(-inf) = 0 for masked keys
+        const float l = wave_sum(p0 + p1);
+        p[lane] = p0;
+        p[lane + 64] = p1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < hd; i += 64) {
+            float acc = 0.f;
+            for (int b = 0; b < visible; b += kPage) {
+                const float* vp = plane(sp, b / kPage, 1) + i;
+                const int n = min(kPage, visible - b);
+#pragma unroll
+                for (int j0 = 0; j0 < kPage; j0 += 32) {   // 32 loads in flight; keys past the last one add 0 * 0
+                    if (j0 >= n) break;
+                    const bool held = sp == wave && b == 0 && j0 == 0 && i == lane;
+                    float vv[32];
+#pragma unroll
+                    for (int u = 0; u < 32; ++u) vv[u] = j0 + u >= n ? 0.f : held ? v0[u] : vp[(size_t)(j0 + u) * hd];
+#pragma unroll
+                    for (int u = 0; u < 32; ++u) acc = fmaf(p[b + j0 + u], vv[u], acc);
+                }
+            }
+            s_o[sp][i] = acc;
+        }
+        if (lane == 0) { s_m[sp] = m; s_l[sp] = l; }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    const int i = threadIdx.x;
+    if (i >= hd) return;
+    float M = -INFINITY;
+    for (int sp = 0; sp < nsp; ++sp) M = fmaxf(M, s_m[sp]);
+    float Lsum = 0.f, o = 0.f;
+    for (int sp = 0; sp < nsp; ++sp) {
+        const float f = expf(s_m[sp] - M);
+        Lsum = fmaf(s_l[sp], f, Lsum);
+        o = fmaf(s_o[sp][i], f, o);
+    }
+    out[(size_t)c * H * hd + h * hd + i] = o / Lsum;
 }
 
 // ---- profiler ---------------------------------------------------------------------------------------
@@ -1656,6 +1841,9 @@ int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, 
     PSD_HIP(hipMemsetAsync(M.qkv, 0, (size_t)kCols * M.nqkv * sizeof(float), stream), err);
     PSD_HIP(hipMemsetAsync(M.gu, 0, (size_t)kMaxW * 2 * F * sizeof(float), stream), err);
     PSD_HIP(hipMemsetAsync(M.desc, 0, sizeof(PassDesc), stream), err);
+    // every page-table entry is a valid page at all times (blocks without one name page 0): attention kernels may read, and
+    // then mask, a block that is not mapped
+    PSD_HIP(hipMemsetAsync(M.page_table, 0, (size_t)M.n_pages * sizeof(int32_t), stream), err);
     // KV pages start as zeros: attention may read (and mask) slots of a page that were never written
     PSD_HIP(hipMemsetAsync(M.kv, 0, (size_t)M.n_pages * M.L * M.KV * 2 * kPage * M.hd * 4, stream), err);
     if (bf) {
@@ -1732,12 +1920,25 @@ struct Launch {
 };
 }  // namespace
 
-// fp32 models: unfused pipeline, plain VALU GEMM
+// fp32 models: five launches per layer
 template <int EPI>
-static void launch_gemm_f32(Launch& L, const char* family, const void* W, float* Y, int N, int K, int ldy) {
-    Model& M = L.M;
-    L.begin(family, (double)N * K * 4);
-    gemm_f32<EPI><<<(N + 3) / 4, 256, 0, L.s>>>((const float*)W, (const float*)M.xb, Y, N, K, ldy, M.desc);
+static void launch_proj_f32(Launch& L, const char* family, F32Args a) {
+    const int npairs = (a.N + 1) / 2;
+    a.desc = L.M.desc;
+    L.begin(family, (double)a.N * a.K * 4);
+    // Lanes per row pair: 64 where K feeds them (more workgroups and fewer serial steps), 16 for K up to 256; K decides the
+    // summation order, the pass width does not.  Columns: a workgroup takes up to 4, the pass's others go to workgroups of
+    // their own, which read the weights again; where that is more than L2 likes (over 2 M weights) 8 columns at a time
+    // and one workgroup after the other.  (Tiny target, 9 tokens: 7.5 us with 8 columns in turn, 4.5 us side by side.)
+    const bool big = (size_t)a.N * a.K > ((size_t)2 << 20);
+    const dim3 grid16((npairs + 15) / 16, big || L.wcls <= 4 ? 1 : (L.wcls + 3) / 4), grid64((npairs + 3) / 4, grid16.y);
+#define PSD_F32(LP_, NC_) proj_f32<EPI, LP_, NC_><<<LP_ == 16 ? grid16 : grid64, 256, 0, L.s>>>(a)
+    if (a.K > 256) {
+        if (L.wcls == 1) PSD_F32(64, 1); else if (L.wcls <= 4 || !big) PSD_F32(64, 4); else PSD_F32(64, 8);
+    } else {
+        if (L.wcls == 1) PSD_F32(16, 1); else if (L.wcls <= 4 || !big) PSD_F32(16, 4); else PSD_F32(16, 8);
+    }
+#undef PSD_F32
     L.end();
 }
 
@@ -1745,41 +1946,38 @@ static int forward_f32(Model& M, int wmax, float* logits, Launch& L) {
     hipStream_t stream = L.s;
     const int d = M.d, F = M.F, H = M.H, KV = M.KV, hd = M.hd;
     const double act = (double)wmax * d * 4;
+    float* attn = (float*)M.xb;
     L.begin("embed", act);
-    embed_rows<false><<<wmax, 256, 0, stream>>>(M.embed, M.desc, M.x, d, M.V);
+    embed_rows<<<wmax, 256, 0, stream>>>((const float*)M.embed, M.desc, M.x, d, M.V);
     L.end();
-    const int lds = attn_lds_bytes(hd);
+    const int nsplit = std::min(M.nsplit_max, kCtxBuckets[M.ctx_bucket]);   // key ranges this launch covers
+    F32Args base{};
+    base.eps = M.eps;
+    base.rope = M.rope; base.kv = (float*)M.kv; base.page_table = M.page_table;
+    base.L = M.L; base.H = H; base.KV = KV; base.hd = hd;
+    auto args = [&](const void* W, const float* X, const float* gain, float* Y, int N, int K, int ldy) {
+        F32Args a = base;
+        a.W = (const float*)W; a.X = X; a.gain = gain; a.Y = Y; a.N = N; a.K = K; a.ldy = ldy;
+        return a;
+    };
     for (int l = 0; l < M.L; ++l) {
         const LayerW& w = M.layers[l];
-        L.begin("rmsnorm", act);
-        rmsnorm_pack<false><<<wmax, 256, 0, stream>>>(M.x, w.attn_norm, M.desc, M.xb, d, M.eps);
-        L.end();
-        launch_gemm_f32<EPI_STORE>(L, "gemm_qkv", w.wqkv, M.qkv, M.nqkv, d, M.nqkv);
-        L.begin("rope_kv", (double)wmax * M.nqkv * 4);
-        rope_kv<float><<<dim3(wmax, H + 2 * KV), hd / 2, 0, stream>>>(M.qkv, M.desc, M.rope, (float*)M.kv, M.page_table, l, M.L, H, KV, hd, M.nqkv);
-        L.end();
+        base.layer = l;
+        launch_proj_f32<F32_QKV>(L, "gemm_qkv", args(w.wqkv, M.x, w.attn_norm, M.qkv, M.nqkv, d, M.nqkv));
         L.begin("attn", (double)std::min(M.max_seq, M.len + wmax) * KV * hd * 2 * 4 + (double)wmax * H * hd * 4 * 2);
-        attn_partial<float><<<dim3(H, M.nsplit_max), 256, lds, stream>>>(M.qkv, M.desc, (const float*)M.kv, M.page_table, M.attn_part, l, M.L, H, KV, hd, M.nqkv);
+        // short contexts: one launch; longer ones spread the key ranges over workgroups and merge in a second
+        if (nsplit <= kF32OneSplits) {
+            attn_one_f32<<<dim3(H, wmax), 256, 0, stream>>>(M.qkv, M.desc, (const float*)M.kv, M.page_table, M.n_pages, attn, l, M.L, H, KV, hd, M.nqkv);
+        } else {
+            attn_partial<float><<<dim3(H, nsplit), 256, attn_lds_bytes(hd), stream>>>(M.qkv, M.desc, (const float*)M.kv, M.page_table, M.attn_part, l, M.L, H, KV, hd, M.nqkv);
+            attn_combine_pack<false><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, attn, H, hd);
+        }
         L.end();
-        L.begin("attn_combine", act);
-        attn_combine_pack<false><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, M.xb, H, hd);
-        L.end();
-        launch_gemm_f32<EPI_RESID>(L, "gemm_o", w.wo, M.x, d, H * hd, d);
-        L.begin("rmsnorm", act);
-        rmsnorm_pack<false><<<wmax, 256, 0, stream>>>(M.x, w.ffn_norm, M.desc, M.xb, d, M.eps);
-        L.end();
-        launch_gemm_f32<EPI_STORE>(L, "gemm_gate_up", w.wgu, M.gu, 2 * F, d, 2 * F);
-        L.begin("swiglu", (double)wmax * 2 * F * 4);
-        swiglu_pack<false><<<dim3(wmax, (F + 255) / 256), 256, 0, stream>>>(M.gu, M.desc, M.xb, F);
-        L.end();
-        launch_gemm_f32<EPI_RESID>(L, "gemm_down", w.wd, M.x, d, F, d);
+        launch_proj_f32<F32_RESID>(L, "gemm_o", args(w.wo, attn, nullptr, M.x, d, H * hd, d));
+        launch_proj_f32<F32_SWIGLU>(L, "gemm_gate_up", args(w.wgu, M.x, w.ffn_norm, M.gu, 2 * F, d, F));
+        launch_proj_f32<F32_RESID>(L, "gemm_down", args(w.wd, M.gu, nullptr, M.x, d, F, d));
     }
-    if (logits) {
-        L.begin("rmsnorm", act);
-        rmsnorm_pack<false><<<wmax, 256, 0, stream>>>(M.x, M.final_norm, M.desc, M.xb, d, M.eps);
-        L.end();
-        launch_gemm_f32<EPI_LOGITS>(L, "gemm_lm_head", M.embed, logits, M.V, d, M.V);
-    }
+    if (logits) launch_proj_f32<F32_LOGITS>(L, "gemm_lm_head", args(M.embed, M.x, M.final_norm, logits, M.V, d, M.V));
     return PSD_OK;
 }
 
