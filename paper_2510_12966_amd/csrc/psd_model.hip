@@ -113,7 +113,7 @@ __device__ inline size_t kv_plane(int page, int layer, int L, int g, int KV, int
 // Inside a plane the elements sit in the order the attention MFMAs consume them, so that a wave's operand load is one
 // contiguous block (1 KiB for K, 512 bytes for V) instead of sixteen strided pieces:
 //   K planes: A-operand tiles of v_mfma_f32_16x16x32_bf16, [slot / 16][hd / 32][64 lanes][8], lane = (dim % 32) / 8 * 16 + slot % 16
-//   V planes: B-operand tiles of v_mfma_f32_16x16x16_bf16, [hd / 16][slot / 16][64 lanes][4], lane = (slot % 16) / 4 * 16 + dim % 16
+//   V planes: half B-operand tiles of v_mfma_f32_16x16x32_bf16 (16 keys each), [hd / 16][slot / 16][64 lanes][4], lane = (slot % 16) / 4 * 16 + dim % 16
 __device__ inline int kv_k_off(int slot, int dim, int hd) {
     return ((((slot >> 4) * (hd >> 5) + (dim >> 5)) * 64 + ((dim & 31) >> 3) * 16 + (slot & 15)) << 3) + (dim & 7);
 }
@@ -211,9 +211,20 @@ __global__ void attn_combine_pack(const float* part, const PassDesc* desc, void*
     pack_store<BF16>(xb, H * hd, c, h * hd + i, o / Lsum);
 }
 
-// Merge of the split partials of one (token, head): the same arithmetic wherever it is done, so that a token's
-// attention output has the same bits whichever kernel merges it.  Returns the normalised output of head dims
-// i .. i + N - 1.
+// Softmax of the bf16 models' attention works in base 2 (the query carries log2 e, exponentials are the hardware exp2).
+// Key ranges are merged in order with a running maximum, the same arithmetic wherever it is done (attn_merge,
+// attn_combine_long, attn_wide), so that a token's attention output has the same bits whichever kernel merges it:
+// the state (M, Lsum, o) takes range (m, l, o_s) as
+//   M' = max(M, m),  al = 2^(M - M'),  be = 2^(m - M'),  Lsum = Lsum al + l be,  o = o al + o_s be.
+__device__ inline float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+struct MergeFac { float M, al, be; };
+__device__ inline MergeFac merge_fac(float M, float m) {
+    const float Mn = fmaxf(M, m);
+    return MergeFac{Mn, M == -INFINITY ? 0.f : exp2_hw(M - Mn), m == -INFINITY ? 0.f : exp2_hw(m - Mn)};
+}
+__device__ inline float merge_add(float acc, float x, const MergeFac& f) { return fmaf(acc, f.al, x * f.be); }
+
+// Merge of the split partials of one (token, head).  Returns the normalised output of head dims i .. i + N - 1.
 template <int N>
 __device__ inline void attn_merge(const float* part, int nsp, int c, int head, int H, int hd, int i, float out[N]) {
     const size_t stride = (size_t)kCols * H * (hd + 2);
@@ -221,13 +232,12 @@ __device__ inline void attn_merge(const float* part, int nsp, int c, int head, i
     float M = -INFINITY, Lsum = 0.f;
 #pragma unroll
     for (int e = 0; e < N; ++e) out[e] = 0.f;
-    if (nsp <= 8) {
-        // all partials in flight at once (one memory round trip); the arithmetic below is the general loop's
+    for (int s0 = 0; s0 < nsp; s0 += 8) {   // eight partials in flight at a time
         float m[8], l[8], o[8][N];
 #pragma unroll
         for (int s = 0; s < 8; ++s)
-            if (s < nsp) {
-                const float* pr = p0 + s * stride;
+            if (s0 + s < nsp) {
+                const float* pr = p0 + (size_t)(s0 + s) * stride;
                 m[s] = pr[0];
                 l[s] = pr[1];
 #pragma unroll
@@ -235,44 +245,13 @@ __device__ inline void attn_merge(const float* part, int nsp, int c, int head, i
             }
 #pragma unroll
         for (int s = 0; s < 8; ++s)
-            if (s < nsp) M = fmaxf(M, m[s]);
+            if (s0 + s < nsp) {
+                const MergeFac f = merge_fac(M, m[s]);
+                M = f.M;
+                Lsum = merge_add(Lsum, l[s], f);
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-            if (s < nsp) {
-                const float f = expf(m[s] - M);
-                Lsum = fmaf(l[s], f, Lsum);
-#pragma unroll
-                for (int e = 0; e < N; ++e) out[e] = fmaf(o[s][e], f, out[e]);
+                for (int e = 0; e < N; ++e) out[e] = merge_add(out[e], o[s][e], f);
             }
-    } else {
-        // long contexts: the same arithmetic in the same order, with the loads of 16 / 8 partials issued together
-        for (int s0 = 0; s0 < nsp; s0 += 16) {
-            float m[16];
-#pragma unroll
-            for (int s = 0; s < 16; ++s) m[s] = (s0 + s < nsp) ? p0[(size_t)(s0 + s) * stride] : -INFINITY;
-#pragma unroll
-            for (int s = 0; s < 16; ++s) M = fmaxf(M, m[s]);
-        }
-        for (int s0 = 0; s0 < nsp; s0 += 8) {
-            float m[8], l[8], o[8][N];
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                if (s0 + s < nsp) {
-                    const float* pr = p0 + (size_t)(s0 + s) * stride;
-                    m[s] = pr[0];
-                    l[s] = pr[1];
-#pragma unroll
-                    for (int e = 0; e < N; ++e) o[s][e] = pr[2 + i + e];
-                }
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                if (s0 + s < nsp) {
-                    const float f = expf(m[s] - M);
-                    Lsum = fmaf(l[s], f, Lsum);
-#pragma unroll
-                    for (int e = 0; e < N; ++e) out[e] = fmaf(o[s][e], f, out[e]);
-                }
-        }
     }
 #pragma unroll
     for (int e = 0; e < N; ++e) out[e] = out[e] / Lsum;
@@ -1068,31 +1047,28 @@ __global__ __launch_bounds__(1024) void gemm_o_narrow(const GemmArgs a, const fl
     if (cc < w) epilogue<EPI_RESID, 2, true>(a, dv, tile, g, cc, acc, 1.f, pre);
 }
 
-// token embedding: x = E[token]; also the first RMSNorm's operand and sum-of-squares partials.  grid d/16, 64 threads
-template <int NT, int CT>
+// token embedding: x = E[token]; also the first RMSNorm's operand and sum-of-squares partials.  grid (d/16, column tiles),
+// 64 threads
+template <int CT>
 __global__ __launch_bounds__(64) void embed_pack(const uint16_t* embed, const PassDesc* desc, float* x, void* xb,
                                                  const float* gain, float* ss_out, int d, int V) {
     const int tile = blockIdx.x, lane = threadIdx.x, g = lane >> 4, cc = lane & 15;
-    const int w = desc->w, KS = d >> 5;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int c = t * 16 + cc;
-        if (c >= w) continue;
-        int tok = desc->tok[c];
-        tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
-        const int n = tile * 16 + g * 4;
-        const size_t idx = ((((size_t)(tok >> 4) * KS + (n >> 5)) * 64) + ((n & 31) >> 3) * 16 + (tok & 15)) * 8 + (n & 7);
-        const uint2 raw = *reinterpret_cast<const uint2*>(embed + idx);
-        const float v[4] = {bf16_to_f32(raw.x & 0xffff), bf16_to_f32(raw.x >> 16), bf16_to_f32(raw.y & 0xffff), bf16_to_f32(raw.y >> 16)};
-        *reinterpret_cast<float4*>(x + (size_t)c * d + n) = make_float4(v[0], v[1], v[2], v[3]);
-        const float4 gn = *reinterpret_cast<const float4*>(gain + n);
-        const float pk[4] = {v[0] * gn.x, v[1] * gn.y, v[2] * gn.z, v[3] * gn.w};
-        pack4<CT>(xb, c, n, pk);
-        float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-        ss += __shfl_xor(ss, 16, kWave);
-        ss += __shfl_xor(ss, 32, kWave);
-        if (g == 0) ss_out[tile * (16 * CT) + c] = ss;
-    }
+    const int w = desc->w, KS = d >> 5, c = blockIdx.y * 16 + cc;
+    if (c >= w) return;   // whole 16-lane groups agree on it, and the shuffles below cross g only
+    int tok = desc->tok[c];
+    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
+    const int n = tile * 16 + g * 4;
+    const size_t idx = ((((size_t)(tok >> 4) * KS + (n >> 5)) * 64) + ((n & 31) >> 3) * 16 + (tok & 15)) * 8 + (n & 7);
+    const uint2 raw = *reinterpret_cast<const uint2*>(embed + idx);
+    const float v[4] = {bf16_to_f32(raw.x & 0xffff), bf16_to_f32(raw.x >> 16), bf16_to_f32(raw.y & 0xffff), bf16_to_f32(raw.y >> 16)};
+    *reinterpret_cast<float4*>(x + (size_t)c * d + n) = make_float4(v[0], v[1], v[2], v[3]);
+    const float4 gn = *reinterpret_cast<const float4*>(gain + n);
+    const float pk[4] = {v[0] * gn.x, v[1] * gn.y, v[2] * gn.z, v[3] * gn.w};
+    pack4<CT>(xb, c, n, pk);
+    float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    ss += __shfl_xor(ss, 16, kWave);
+    ss += __shfl_xor(ss, 32, kWave);
+    if (g == 0) ss_out[tile * (16 * CT) + c] = ss;
 }
 
 // ---- attention, bf16 KV cache, MFMA ---------------------------------------------------------------------
@@ -1101,15 +1077,51 @@ __global__ __launch_bounds__(64) void embed_pack(const uint16_t* embed, const Pa
 // [split * 128 + 32 j, +32):
 //   S^T = K Q^T    v_mfma_f32_16x16x32_bf16, A = 16 keys x 32 head dims: one contiguous 1 KiB tile of the K planes
 //                  (hi, lo), B = queries as bf16 hi + lo built in registers; result lane (g, c): keys 4g..4g+3 of query c
-//   P   = exp(S - max) per query over the wave's 32 keys (masked causally), kept in registers: the result
-//         layout of S^T is exactly the A operand layout of v_mfma_f32_16x16x16bf16_1k
-//   O   = P V      B = 4 consecutive keys of one head dim: one contiguous 512-byte tile of the V planes
+//   P   = 2^(S - max) per query over the wave's 32 keys (masked causally), kept in registers: the result
+//         layout of S^T is an A operand layout of v_mfma_f32_16x16x32_bf16 (attn_probs)
+//   O   = P V      B = 2 x 4 consecutive keys of one head dim: two contiguous 512-byte tiles of the V planes
 // The four waves' (max, sum, O) are merged through LDS in wave order and written as one partial per split.
 // Memory round trips on the critical path: the pass descriptor and the page-table entry travel together, then the
 // queries (from L2), keys and values go out back to back; the kernel is latency-bound, so that is what counts.
 // Two waves per SIMD are asked for (at head dim 128 the kernel would otherwise take 284 registers and run one workgroup
 // per CU): with dozens of key ranges a launch has several workgroups per CU, and their round trips then overlap.
-typedef __attribute__((ext_vector_type(4))) short s16x4;
+template <int HD>
+__device__ inline float attn_scale() { return rsqrtf((float)HD) * 1.4426950408889634f; }   // scores come out in base 2
+
+// Probabilities of one wave's 32 keys (two 16-key score tiles, lane (g, c): keys 4 g + r of query c) relative to `msafe`, as the
+// A operand of v_mfma_f32_16x16x32_bf16 in hi and lo halves, and the query's sum over the 32 keys.  The instruction's k
+// index is free as long as both operands agree on it: lane group g's eight entries are keys 4 g .. 4 g + 3 of the first tile,
+// then of the second, which is how the scores lie already and how two 8-byte pieces of the V planes fit together.
+__device__ inline void attn_probs(const f32x4 (&S)[2], float msafe, u32x4& Ph, u32x4& Pl, float& l) {
+    l = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+        float p[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = exp2_hw(S[kt][r] - msafe);   // 2^(-inf) = 0 for masked keys
+            l += p[r];
+        }
+        uint32_t h0, l0, h1, l1;
+        f32x2_split(p[0], p[1], h0, l0);
+        f32x2_split(p[2], p[3], h1, l1);
+        Ph[2 * kt] = h0; Ph[2 * kt + 1] = h1;
+        Pl[2 * kt] = l0; Pl[2 * kt + 1] = l1;
+    }
+    l += __shfl_xor(l, 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+}
+// (p_hi + p_lo)(v_hi + v_lo) without the lo * lo term, 16 queries x 16 JT head dims over 32 keys; the head dims' chains side
+// by side
+template <int JT>
+__device__ inline void attn_pv(u32x4 Ph, u32x4 Pl, const u32x4 (&vh)[JT], const u32x4 (&vl)[JT], f32x4 (&O)[JT]) {
+#pragma unroll
+    for (int t3 = 0; t3 < 3; ++t3)
+#pragma unroll
+        for (int j = 0; j < JT; ++j)
+            O[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t3 == 1 ? Pl : Ph), __builtin_bit_cast(bf16x8, t3 < 2 ? vh[j] : vl[j]),
+                                                           t3 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : O[j], 0, 0, 0);
+}
 
 template <int HD>
 __global__ __launch_bounds__(256, 2) void attn_mfma(const float* qkv, const PassDesc* desc, const uint16_t* kv,
@@ -1127,7 +1139,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma(const float* qkv, const Pass
     const int G = H / KV, R = w * G;
     if (key0 >= kv_max || (int)blockIdx.z * qt_per_wg * 16 >= R) return;
     const bool wave_live = wkey0 < kv_max;
-    const float scale = rsqrtf((float)HD);
+    const float scale = attn_scale<HD>();
     // query rows of the first tile, as they come from the q/k/v projection (fp32); converted when they are used
     auto load_q = [&](int qt, float (&v)[KSQ][8]) {
         const int rho = qt * 16 + cq;
@@ -1225,32 +1237,15 @@ __global__ __launch_bounds__(256, 2) void attn_mfma(const float* qkv, const Pass
         m = fmaxf(m, __shfl_xor(m, 16, kWave));
         m = fmaxf(m, __shfl_xor(m, 32, kWave));
         const float msafe = m == -INFINITY ? 0.f : m;
-        s16x4 Ph[2], Pl[2];
+        u32x4 Ph, Pl;
+        attn_probs(Sx, msafe, Ph, Pl, l);
+        u32x4 vh[JT], vl[JT];
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            float p[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                p[r] = expf(Sx[kt][r] - msafe);   // exp(-inf) = 0 for masked keys
-                l += p[r];
-            }
-            uint2 ph, pl;
-            f32x2_split(p[0], p[1], ph.x, pl.x);
-            f32x2_split(p[2], p[3], ph.y, pl.y);
-            Ph[kt] = __builtin_bit_cast(s16x4, ph);
-            Pl[kt] = __builtin_bit_cast(s16x4, pl);
+        for (int j = 0; j < JT; ++j) {
+            vh[j] = u32x4{vraw[j][0].x, vraw[j][0].y, vraw[j][1].x, vraw[j][1].y};
+            vl[j] = u32x4{vlow[j][0].x, vlow[j][0].y, vlow[j][1].x, vlow[j][1].y};
         }
-        l += __shfl_xor(l, 16, kWave);
-        l += __shfl_xor(l, 32, kWave);
-#pragma unroll
-        for (int j = 0; j < JT; ++j)
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt) {
-                const s16x4 vb = __builtin_bit_cast(s16x4, vraw[j][kt]), vl = __builtin_bit_cast(s16x4, vlow[j][kt]);
-                O[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ph[kt], vb, O[j], 0, 0, 0);
-                O[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Pl[kt], vb, O[j], 0, 0, 0);
-                O[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ph[kt], vl, O[j], 0, 0, 0);
-            }
+        attn_pv<JT>(Ph, Pl, vh, vl, O);
     }
     // merge the four waves: O lane (g, c) holds queries 4g + r, head dim 16 j + c
     if (g == 0) { mrg[wave][cq][0] = m; mrg[wave][cq][1] = l; }
@@ -1271,7 +1266,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma(const float* qkv, const Pass
             float fac[4], Ls = 0.f;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                fac[v] = mrg[v][qr][0] == -INFINITY ? 0.f : expf(mrg[v][qr][0] - M);
+                fac[v] = mrg[v][qr][0] == -INFINITY ? 0.f : exp2_hw(mrg[v][qr][0] - M);
                 Ls = fmaf(mrg[v][qr][1], fac[v], Ls);
             }
             const int rh = (rr / G) * H + gkv * G + rr % G;
@@ -1304,13 +1299,12 @@ __global__ void attn_combine_bf16(const float* part, const PassDesc* desc, void*
 
 // The same merge for long contexts (more than eight key ranges): one workgroup per (token, head) brings the partials of
 // all its ranges into LDS with one round of loads (the thread-per-head-dim form above walks them in dependent rounds of
-// sixteen: 9-11 us at 36 ranges), then takes the maximum (exact, so any order), the rescaling factors (one thread per
-// range) and the sums in range order: the arithmetic, hence the bits, of attn_merge.
-// grid (wmax, H), 256 threads, dynamic LDS: nsplit * (hd + 3) floats.
+// eight), works out every range's factors (one thread per range, from the maxima before it) and then sums in range
+// order: the arithmetic, hence the bits, of attn_merge.
+// grid (wmax, H), 256 threads, dynamic LDS: nsplit * (hd + 4) floats.
 template <int CT>
 __global__ __launch_bounds__(256) void attn_combine_long(const float* part, const PassDesc* desc, void* xb, int H, int hd, int nsp_cap) {
     extern __shared__ float cmb[];
-    __shared__ float red[4];
     const int c = blockIdx.x, h = blockIdx.y;
     if (c >= desc->w) return;
     // splits holding keys <= pos0 + c; never more than the launch covers (the LDS area is sized for those)
@@ -1335,21 +1329,209 @@ __global__ __launch_bounds__(256) void attn_combine_long(const float* part, cons
         }
     }
     __syncthreads();
-    float m = -INFINITY;
-    for (int sp = threadIdx.x; sp < nsp; sp += 256) m = fmaxf(m, cmb[sp * row]);
-    const float M = block_max<4>(m, red);
-    float* fac = cmb + nsp * row;
-    for (int sp = threadIdx.x; sp < nsp; sp += 256) fac[sp] = expf(cmb[sp * row] - M);
+    float2* fac = reinterpret_cast<float2*>(cmb + ((nsp * row + 1) & ~1));
+    for (int sp = threadIdx.x; sp < nsp; sp += 256) {
+        float M = -INFINITY;
+        for (int i = 0; i < sp; ++i) M = fmaxf(M, cmb[i * row]);
+        const MergeFac f = merge_fac(M, cmb[sp * row]);
+        fac[sp] = make_float2(f.al, f.be);
+    }
     __syncthreads();
     if ((int)threadIdx.x < hd) {
         const int i = threadIdx.x;
         float Lsum = 0.f, o = 0.f;
         for (int sp = 0; sp < nsp; ++sp) {
-            const float f = fac[sp];
-            Lsum = fmaf(cmb[sp * row + 1], f, Lsum);
-            o = fmaf(cmb[sp * row + 2 + i], f, o);
+            const MergeFac f{0.f, fac[sp].x, fac[sp].y};
+            Lsum = merge_add(Lsum, cmb[sp * row + 1], f);
+            o = merge_add(o, cmb[sp * row + 2 + i], f);
         }
         pack_store<true, CT>(xb, H * hd, c, h * hd + i, o / Lsum);
+    }
+}
+
+// Attention of a prompt-ingestion pass in one sweep: a workgroup of four waves owns four consecutive 16-row query tiles of
+// one kv head, one per wave, and walks the key ranges from the first to the last one its queries see.  A range's K planes
+// (hi, lo), then its V planes, go through LDS for the four waves, asked for a whole range ahead;
+// every wave keeps its tile's running (M, Lsum, o) in registers and writes the o projection's operand itself, so no
+// partials go to memory and there is no merge kernel.  Within a range the arithmetic is that of attn_mfma: four groups of
+// 32 keys (its four waves), each from its own maximum, added in order; ranges are merged as attn_merge does: same bits.
+// With a workgroup per (kv head, range, four tiles) the draft's passes over a 3000-token prompt spent 59 us per layer here
+// and 30 us in the merge, waiting on loads and barriers per 16-row tile, against 10 us worth of MFMAs.
+// grid ceil(query tiles / 4) * KV; 128 KB of LDS at head dim 128 (one workgroup per CU).
+template <int HD>
+constexpr int kAttnWideLds = 8 * kPage * HD * 2;   // two pages x (K or V: hi, lo) each for K and V, bytes
+template <int HD>
+__global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qkv, const PassDesc* desc, const uint16_t* __restrict__ kv,
+                                                    const int32_t* __restrict__ page_table, int n_pages, void* xb, int layer, int L, int H,
+                                                    int KV, int nqkv) {
+    constexpr int KSQ = HD / 32, JT = HD / 16, PW = kPage * HD / 8;   // PW: 16-byte words of one plane of one page
+    constexpr int NS = 4 * PW / 256;                                  // words per thread of half a range (K or V)
+    static_assert(kAttnSplit == 2 * kPage, "a key range is two pages");
+    extern __shared__ u32x4 aw_lds[];
+    u32x4* sK = aw_lds;            // [2 pages][hi, lo][plane]
+    u32x4* sV = aw_lds + 4 * PW;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, cq = lane & 15;
+    // consecutive workgroups go round the eight XCDs: with eight kv heads each head's keys and values stay in one L2
+    const int gkv = blockIdx.x % KV, grp = gridDim.x / KV - 1 - blockIdx.x / KV;   // the groups with the most ranges first
+    const int w = desc->w, pos0 = desc->pos0, G = H / KV, R = w * G;
+    if (grp * 64 >= R) return;
+    const int tile = grp * 4 + wave, row0 = tile * 16;
+    const int nsp = (pos0 + (min(R, grp * 64 + 64) - 1) / G) / kAttnSplit + 1;                        // ranges of the workgroup
+    const int my_nsp = row0 < R ? (pos0 + (min(R, row0 + 16) - 1) / G) / kAttnSplit + 1 : 0;   // and of this wave's tile
+    u32x4 stk[NS], stv[NS];
+    auto load_half = [&](u32x4 (&st)[NS], int s, int half) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int page = page_table[min(2 * s + p, n_pages - 1)];
+            const u32x4* src = reinterpret_cast<const u32x4*>(kv + kv_plane(page, layer, L, gkv, KV, 2 * half, HD));   // hi and lo planes are adjacent
+#pragma unroll
+            for (int i = 0; i < NS / 2; ++i) st[p * (NS / 2) + i] = src[tid + i * 256];
+        }
+    };
+    auto put_half = [&](const u32x4 (&st)[NS], u32x4* dst) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int i = 0; i < NS / 2; ++i) dst[p * 2 * PW + tid + i * 256] = st[p * (NS / 2) + i];
+    };
+    load_half(stk, 0, 0);
+    load_half(stv, 0, 1);
+    // the tile's queries as B operand, scaled: lane (g, c) holds head dims 32 ks + 8 g .. + 8 of row c
+    const int rho = row0 + cq;
+    const float scale = attn_scale<HD>();
+    u32x4 qh[KSQ], ql[KSQ];
+#pragma unroll
+    for (int ks = 0; ks < KSQ; ++ks) {
+        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (rho < R) {
+            const float* qrow = qkv + (size_t)(rho / G) * nqkv + (size_t)(gkv * G + rho % G) * HD + ks * 32 + g * 8;
+            const float4 a0 = *reinterpret_cast<const float4*>(qrow), a1 = *reinterpret_cast<const float4*>(qrow + 4);
+            v[0] = a0.x; v[1] = a0.y; v[2] = a0.z; v[3] = a0.w; v[4] = a1.x; v[5] = a1.y; v[6] = a1.z; v[7] = a1.w;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t hi, lo;
+            f32x2_split(v[2 * e] * scale, v[2 * e + 1] * scale, hi, lo);
+            qh[ks][e] = hi;
+            ql[ks][e] = lo;
+        }
+    }
+    const int qpos = rho < R ? pos0 + rho / G : -1, qpos_first = pos0 + row0 / G;
+    float M = -INFINITY, Lsum = 0.f;
+    f32x4 o[JT];
+#pragma unroll
+    for (int j = 0; j < JT; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // a per-query value, held by the lanes of column c, for the four queries 4 g + r of the P V layout
+    auto to_rows = [&](float v, float (&out)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[r] = __shfl(v, 4 * g + r, kWave);
+    };
+    put_half(stk, sK);
+    if (nsp > 1) load_half(stk, 1, 0);
+    __syncthreads();
+    for (int s = 0; s < nsp; ++s) {
+        const int key0 = s * kAttnSplit;
+        const bool live = s < my_nsp;
+        f32x4 S[4][2];
+        float mv[4], fac[4], Ms = -INFINITY;
+        if (live) {
+// (k_hi + k_lo)(q_hi + q_lo) without the lo * lo term (2^-18 relative); eight independent chains side by side
+#pragma unroll
+            for (int kt = 0; kt < 8; ++kt) S[kt >> 1][kt & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KSQ; ++ks) {
+                u32x4 kh[8], kl[8];
+#pragma unroll
+                for (int kt = 0; kt < 8; ++kt) {
+                    const u32x4* kp = sK + (kt >> 2) * 2 * PW + ((kt & 3) * KSQ + ks) * 64 + lane;
+                    kh[kt] = kp[0];
+                    kl[kt] = kp[PW];
+                }
+#pragma unroll
+                for (int t3 = 0; t3 < 3; ++t3)
+#pragma unroll
+                    for (int kt = 0; kt < 8; ++kt)
+                        S[kt >> 1][kt & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, t3 < 2 ? kh[kt] : kl[kt]), __builtin_bit_cast(bf16x8, t3 == 1 ? ql[ks] : qh[ks]),
+                            S[kt >> 1][kt & 1], 0, 0, 0);
+            }
+            if (key0 + kAttnSplit - 1 > qpos_first) {   // causal mask: key position <= query position
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (key0 + v * 32 + k2 * 16 + g * 4 + r > qpos) S[v][k2][r] = -INFINITY;
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float m = -INFINITY;
+#pragma unroll
+                for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) m = fmaxf(m, S[v][k2][r]);
+                m = fmaxf(m, __shfl_xor(m, 16, kWave));
+                mv[v] = fmaxf(m, __shfl_xor(m, 32, kWave));
+                Ms = fmaxf(Ms, mv[v]);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) fac[v] = mv[v] == -INFINITY ? 0.f : exp2_hw(mv[v] - Ms);
+        }
+        put_half(stv, sV);
+        if (s + 1 < nsp) load_half(stv, s + 1, 1);
+        __syncthreads();
+        if (live) {
+            float Ls = 0.f;
+            f32x4 os[JT];
+#pragma unroll
+            for (int j = 0; j < JT; ++j) os[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                u32x4 Ph, Pl;
+                float l, fr[4];
+                attn_probs(S[v], mv[v] == -INFINITY ? 0.f : mv[v], Ph, Pl, l);
+                Ls = fmaf(l, fac[v], Ls);
+                to_rows(fac[v], fr);
+                const uint2* vp = reinterpret_cast<const uint2*>(sV + (v >> 1) * 2 * PW) + ((v & 1) * 2) * 64 + lane;
+u32x4 vh[JT], vl[JT];
+                f32x4 O[JT];
+#pragma unroll
+                for (int j = 0; j < JT; ++j) {
+                    const uint2 h0 = vp[j * 256], h1 = vp[j * 256 + 64], l0 = vp[2 * PW + j * 256], l1 = vp[2 * PW + j * 256 + 64];
+                    vh[j] = u32x4{h0.x, h0.y, h1.x, h1.y};
+                    vl[j] = u32x4{l0.x, l0.y, l1.x, l1.y};
+                }
+                attn_pv<JT>(Ph, Pl, vh, vl, O);
+#pragma unroll
+                for (int j = 0; j < JT; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) os[j][r] = fmaf(O[j][r], fr[r], os[j][r]);
+            }
+            const MergeFac f = merge_fac(M, Ms);
+            M = f.M;
+            Lsum = merge_add(Lsum, Ls, f);
+            float al[4], be[4];
+            to_rows(f.al, al);
+            to_rows(f.be, be);
+#pragma unroll
+            for (int j = 0; j < JT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[j][r] = merge_add(o[j][r], os[j][r], MergeFac{0.f, al[r], be[r]});
+        }
+        if (s + 1 < nsp) put_half(stk, sK);   // everybody is past this range's K since the barrier above
+        if (s + 2 < nsp) load_half(stk, s + 2, 0);
+        __syncthreads();
+    }
+    float Lr[4];
+    to_rows(Lsum, Lr);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int rr = row0 + 4 * g + r;
+        if (rr >= R) continue;
+        const int c = rr / G, f0 = (gkv * G + rr % G) * HD + cq;
+#pragma unroll
+        for (int j = 0; j < JT; ++j) pack_store<true, kWideCT>(xb, H * HD, c, f0 + 16 * j, o[j][r] / Lr[r]);
     }
 }
 
@@ -1692,6 +1874,8 @@ int model_kernels_init(char* err) {
     // attention stages two pages of K and V as fp32 in LDS: up to ~135 KB of the 160 KB a gfx950 CU has
     PSD_HIP(hipFuncSetAttribute((const void*)attn_partial<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 attn_lds_bytes(128)), err);
+    PSD_HIP(hipFuncSetAttribute((const void*)attn_wide<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnWideLds<128>), err);
+    PSD_HIP(hipFuncSetAttribute((const void*)attn_wide<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnWideLds<64>), err);
     int rc;
     if ((rc = lb_kernels_init<EPI_RESID>(err)) != PSD_OK) return rc;
     if ((rc = lb_kernels_init<EPI_LOGITS>(err)) != PSD_OK) return rc;
@@ -2074,9 +2258,9 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
     void* xb2 = c128 ? M.xbw2 : M.xb2;
     float* ss = c128 ? M.ssw : M.ss;
     L.begin("embed", act);
-    if (c128) embed_pack<kWideCT, kWideCT><<<d / 16, 64, 0, stream>>>((const uint16_t*)M.embed, M.desc, M.x, xb, M.layers[0].attn_norm, ss, d, M.V);
-    else if (wmax <= 16) embed_pack<1, 2><<<d / 16, 64, 0, stream>>>((const uint16_t*)M.embed, M.desc, M.x, xb, M.layers[0].attn_norm, ss, d, M.V);
-    else embed_pack<2, 2><<<d / 16, 64, 0, stream>>>((const uint16_t*)M.embed, M.desc, M.x, xb, M.layers[0].attn_norm, ss, d, M.V);
+    const dim3 egrid(d / 16, (wmax + 15) / 16);
+    if (c128) embed_pack<kWideCT><<<egrid, 64, 0, stream>>>((const uint16_t*)M.embed, M.desc, M.x, xb, M.layers[0].attn_norm, ss, d, M.V);
+    else embed_pack<2><<<egrid, 64, 0, stream>>>((const uint16_t*)M.embed, M.desc, M.x, xb, M.layers[0].attn_norm, ss, d, M.V);
     L.end();
     // key ranges this launch covers: the bucket of the pass's last position (the caller's bound), never beyond the cache
     const int nsplit = std::min(M.nsplit_max, kCtxBuckets[M.ctx_bucket]);
@@ -2092,6 +2276,9 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
     // algorithmic bytes of one layer's attention: K and V of every key the pass can see, as bf16 (the cache holds a hi and a
     // lo plane per value, so the kernels move twice that), plus the queries in and the outputs back
     const double kv_bytes = (double)std::min(M.max_seq, M.len + wmax) * KV * hd * 2 * 2 + (double)wmax * H * hd * 4 * 2;
+    // Wide passes: one sweep per query tile (attn_wide) where there are enough tiles to fill the device or few key ranges to
+    // walk; few tiles over a long context keep a workgroup per key range and the merge kernel.
+    const bool sweep = c128 && (KV * ((wmax * G + 15) / 16) >= 512 || nsplit <= 8);
     const bool fold_merge = wmax <= 4 && d <= 2048 && d / 16 <= 256 && H * hd == d && nsplit <= kFoldSplits;
     GemmArgs base{};
     base.ss_in = ss; base.ss_tiles = d / 16; base.inv_d = inv_d; base.eps = M.eps;
@@ -2106,9 +2293,14 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
         launch_gemm_bf16<EPI_QKV>(L, "gemm_qkv", a);
         L.begin("attn", kv_bytes);
         const dim3 agrid(KV, nsplit, qt_max);
-        if (hd == 128) attn_mfma<128><<<agrid, 256, 0, stream>>>(M.qkv, M.desc, (const uint16_t*)M.kv, M.page_table, M.n_pages, M.attn_part, l, M.L, H, KV, M.nqkv, qt_per_wg);
-        else if (hd == 64) attn_mfma<64><<<agrid, 256, 0, stream>>>(M.qkv, M.desc, (const uint16_t*)M.kv, M.page_table, M.n_pages, M.attn_part, l, M.L, H, KV, M.nqkv, qt_per_wg);
-        else attn_mfma<32><<<agrid, 256, 0, stream>>>(M.qkv, M.desc, (const uint16_t*)M.kv, M.page_table, M.n_pages, M.attn_part, l, M.L, H, KV, M.nqkv, qt_per_wg);
+        const uint16_t* kvp = (const uint16_t*)M.kv;
+#define PSD_ATTN(HD_)                                                                                                            \
+    do {                                                                                                                         \
+        if (sweep) attn_wide<HD_><<<((wmax * G + 63) / 64) * KV, 256, kAttnWideLds<HD_>, stream>>>(M.qkv, M.desc, kvp, M.page_table, M.n_pages, xb2, l, M.L, H, KV, M.nqkv); \
+        else attn_mfma<HD_><<<agrid, 256, 0, stream>>>(M.qkv, M.desc, kvp, M.page_table, M.n_pages, M.attn_part, l, M.L, H, KV, M.nqkv, qt_per_wg); \
+    } while (0)
+        if (hd == 128) PSD_ATTN(128); else if (hd == 64) PSD_ATTN(64); else PSD_ATTN(32);
+#undef PSD_ATTN
         L.end();
         a = base;
         a.Wt = (const u32x4*)w.wo; a.XB = (const u32x4*)xb2; a.N = d; a.KS = (H * hd) / 32;
@@ -2119,10 +2311,11 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
             gemm_o_narrow<<<d / 16, 1024, 0, stream>>>(a, M.attn_part);
             L.end();
         } else {
+            if (!sweep) {
             L.begin("attn_combine", act);
             // more than eight key ranges: the form that fetches a row's partials in one round (its LDS need grows with the
             // ranges; the dependent-rounds form takes over where that no longer fits)
-            const size_t cmb_lds = (size_t)nsplit * (hd + 3) * sizeof(float);
+            const size_t cmb_lds = ((size_t)nsplit * (hd + 4) + 1) * sizeof(float);
             if (nsplit > 8 && cmb_lds <= 64 * 1024) {
                 if (c128) attn_combine_long<kWideCT><<<dim3(wmax, H), 256, cmb_lds, stream>>>(M.attn_part, M.desc, xb2, H, hd, nsplit);
                 else attn_combine_long<2><<<dim3(wmax, H), 256, cmb_lds, stream>>>(M.attn_part, M.desc, xb2, H, hd, nsplit);
@@ -2132,6 +2325,7 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
                 attn_combine_bf16<2><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, xb2, H, hd);
             }
             L.end();
+            }
             launch_gemm_bf16<EPI_RESID>(L, "gemm_o", a);
         }
         a = base;

@@ -178,6 +178,71 @@ def test_bf16_wide_projection_tiles_are_bit_exact(which, n):
     assert np.abs(out[0] - ref).max() <= TOL_BF16
 
 
+# head dims 32 / 64 / 128 with query groups of 4, 3 and 1: the first has enough query tiles for the one-sweep attention at any
+# context, the others change over to a workgroup per key range beyond eight ranges
+SWEEP = (ModelShape(1, 1024, 32, 8, 512, 200), ModelShape(1, 384, 6, 2, 256, 200), ModelShape(1, 512, 4, 4, 512, 200))
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+@pytest.mark.parametrize("n", [130, 1023, 1301])
+def test_bf16_wide_attention_is_bit_exact(which, n):
+    # ragged last query tile, causal tiles that end inside a key range, tokens of one tile that see different ranges
+    blobs = [synth.target_weights(s, 70 + i, synth.DTYPE_BF16, sigma=0.05) for i, s in enumerate(SWEEP)]
+    ctx = _ctx(SWEEP, blobs, synth.DTYPE_BF16, 10000.0, 1408, flags=0x100)
+    toks = synth.tokens(17, 0, n + 3, 200)
+    widest = 512 if SWEEP[which].d_model >= 512 else 128
+    out = []
+    for step in (widest, 100, 32):
+        for pos in range(0, n, step):
+            ctx.forward(which, toks[pos:min(pos + step, n)], pos, want_logits=False)
+        out.append(ctx.forward(which, toks[n:n + 3], n))
+    ctx.close()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+    ref = oracle.Model(SWEEP[which], blobs[which], synth.DTYPE_BF16, 10000.0, 1408).forward(toks, 0)[n:]
+    assert np.abs(out[0] - ref).max() <= TOL_BF16
+
+
+def test_fp32_attention_routes_agree():
+    # up to eight key ranges one launch attends and merges, beyond that two do: the same arithmetic, so a token at the
+    # change-over has the same logits whichever bucket of contexts its pass was launched for; and both match the oracle
+    shape = ModelShape(2, 64, 4, 2, 96, 131)
+    blobs = [synth.target_weights(shape, 80 + i, synth.DTYPE_F32, sigma=0.1) for i in range(3)]
+    n = 1100
+    toks = synth.tokens(19, 0, n, 131)
+    ref = oracle.Model(shape, blobs[0], synth.DTYPE_F32, 10000.0, 1200).forward(toks, 0)
+    got = []
+    for widths in ((32,), (7,)):   # 32-token passes are launched for the longer bucket 25 tokens earlier
+        ctx = _ctx((shape,) * 3, blobs, synth.DTYPE_F32, 10000.0, 1200, flags=0x100)
+        out, pos = [], 0
+        while pos < n:
+            w = min(widths[0], n - pos)
+            out.append(ctx.forward(0, toks[pos:pos + w], pos))
+            pos += w
+        got.append(np.concatenate(out))
+        ctx.close()
+    assert np.array_equal(got[0], got[1])
+    assert np.abs(got[0] - ref).max() <= TOL_F32
+
+
+@pytest.mark.parametrize("d,h,kv,f", [(32, 2, 1, 32), (256, 4, 4, 288), (288, 9, 3, 1056), (2048, 16, 4, 1120)])
+def test_fp32_projection_shapes(d, h, kv, f):
+    # 16 and 64 lanes per row pair (K up to 256 and beyond), K over one LDS chunk, weights over the size where columns go one
+    # group after the other, an odd vocabulary, every launch class; each column's result does not depend on the width
+    shape = ModelShape(1, d, h, kv, f, 77)
+    blobs = [synth.target_weights(shape, 90 + i, synth.DTYPE_F32, sigma=0.05) for i in range(3)]
+    ctx = _ctx((shape,) * 3, blobs, synth.DTYPE_F32, 10000.0, 96)
+    toks = synth.tokens(21, 0, 90, 77)
+    ref = oracle.Model(shape, blobs[0], synth.DTYPE_F32, 10000.0, 96).forward(toks, 0)
+    one = np.concatenate([ctx.forward(0, toks[i:i + 1], i) for i in range(90)])
+    out, pos = [], 0
+    for w in (32, 2, 4, 6, 8, 3, 12, 23):
+        out.append(ctx.forward(0, toks[pos:pos + w], pos))
+        pos += w
+    ctx.close()
+    assert pos == 90 and np.array_equal(np.concatenate(out), one)
+    assert np.abs(one - ref).max() <= TOL_F32
+
+
 def test_bf16_ingestion_at_page_split_and_pass_boundaries():
     # prompt lengths around the KV page (64), the attention key range (128) and the pass widths (128, 512):
     # the widest passes, 32-token passes and a ragged mix leave identical logits for the tokens that follow
