@@ -3,17 +3,20 @@
 // replacement draw (Sections 3.1-3.2 and the fallback rule named in Section 3.4).
 //
 // Every logit of the k judged positions is read from HBM once.  Kernels, per call:
-//   accept_clear   marks the per-chunk result slots "not written"
+//   accept_clear   marks the result slots that workgroups wait for "not written"
 //   accept_sweep   one workgroup per (trial, position, chunk).  It keeps its chunk of both rows in
 //                  registers, publishes the chunk's (max, sum of exponentials), waits until the other
 //                  chunks of the same row have done so (they are launched next to it, so the wait is
 //                  short; it is bounded by a clock and reports expiry instead of spinning on), then
-//                  finishes the divergence partial from the registers.
-//   accept_decide  per trial: divergence per position (fixed-order sums), coins, first-reject scan
+//                  finishes the divergence partial from the registers.  One more workgroup per trial,
+//                  launched after them, waits for the trial's partials in the same bounded way and decides:
+//                  divergence per position (fixed-order sums), coins, first-reject scan.
 //   accept_race    per (trial, chunk): exponential race over the ONE row that needs a replacement
 //                  token: the residual max(0, p - q) of the first rejected position, or the verifier's
 //                  last row for the bonus token.  Only this kernel draws vocabulary-wide random numbers.
-//   accept_pick    per trial: winner of the race
+//   accept_pick    per trial: winner of the race; in small calls the race's last workgroup does it
+// The decision behind a one-launch sweep and the pick of a small call were launches of their own: a stage of one trial, k =
+// 10, took 19.8 us with five launches and takes 17.9 us with three.
 // Bulk arithmetic runs in base 2 on the hardware exp2 / log2 units; the two probabilities the coin
 // compares are evaluated with the accurate library functions.  No floating-point atomics: every
 // partial has its own slot, reductions run in a fixed order, so results never depend on scheduling.
@@ -22,6 +25,7 @@
 // The assisted stage (Section 3.4) needs no softmax at all: accept_top finds the verifier's top prediction
 // per position, accept_decide_assisted compares tokens, and the replacement draw races over the verifier's
 // own row in log form.
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -127,6 +131,7 @@ struct AcceptShape {
     float inv_temp;
     int nsl;                // result slots per row of the sweep kernel: one per wave, 4 per workgroup
     unsigned long long wait_ticks;  // bound of the wait for the other chunks of a row, in wall-clock ticks
+    int few;                // few enough workgroups that polling often disturbs nobody
 };
 
 struct AcceptWs {  // carved out of the caller's workspace
@@ -136,12 +141,19 @@ struct AcceptWs {  // carved out of the caller's workspace
     RacePart* race;      // [B][nch]
     KeyIdx* top;         // [B*(k+1)][nch] per-chunk maximum logit of the verifier rows (assisted and greedy stages)
     uint32_t* expired;   // [1] set when a bounded wait ran out
+    uint32_t* raced;     // [B] race workgroups that are done (in the space of `top`, which the stages that race this way do not use)
 };
 
 __device__ inline void st_agent64(void* p, float lo, float hi) {
     __hip_atomic_store(reinterpret_cast<unsigned long long*>(p),
                        (unsigned long long)__float_as_uint(lo) | ((unsigned long long)__float_as_uint(hi) << 32),
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void st_agent32(float* p, float v) {
+    __hip_atomic_store(reinterpret_cast<uint32_t*>(p), __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline float ld_agent32(const float* p) {
+    return __uint_as_float(__hip_atomic_load(reinterpret_cast<const uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 __device__ inline unsigned long long ld_agent64(const void* p) {
     return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -153,7 +165,7 @@ __device__ inline unsigned long long ld_agent64(const void* p) {
 // WAIT: the partials come from workgroups of the running kernel; each thread polls its slot until both
 // halves are written, or the clock runs out: then false is returned in every thread.  One barrier.
 template <bool WAIT, int T>
-__device__ inline bool row_stats(const RowPart* parts, int nsl, unsigned long long wait_ticks, float4* lds, RowStats& r) {
+__device__ inline bool row_stats(const RowPart* parts, int nsl, unsigned long long wait_ticks, int few, float4* lds, RowStats& r) {
     constexpr int NW = T / 64;
     float mp = -INFINITY, mq = -INFINITY, sp = 0.f, sq = 0.f;
     const int wave = threadIdx.x >> 6;
@@ -170,7 +182,7 @@ __device__ inline bool row_stats(const RowPart* parts, int nsl, unsigned long lo
                     break;
                 }
                 if (wall_clock64() - t0 >= wait_ticks) { me.mp = INFINITY; break; }  // +inf marks the expiry
-                __builtin_amdgcn_s_sleep(32);
+                if (few) __builtin_amdgcn_s_sleep(2); else __builtin_amdgcn_s_sleep(32);
             }
         }
         if (wave * 64 < nsl) {
@@ -207,17 +219,21 @@ __device__ inline bool row_stats(const RowPart* parts, int nsl, unsigned long lo
     return true;
 }
 
-__global__ void accept_clear(AcceptWs w, size_t n_parts) {
+__global__ void accept_clear(AcceptWs w, size_t n_parts, size_t n_trials) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_parts) w.part[i] = RowPart{__uint_as_float(kUnwritten), 0.f, __uint_as_float(kUnwritten), 0.f};
+    if (i < n_parts) {
+        w.part[i] = RowPart{__uint_as_float(kUnwritten), 0.f, __uint_as_float(kUnwritten), 0.f};
+        w.jsd[i] = __uint_as_float(kUnwritten);
+    }
+    if (i < n_trials) w.raced[i] = 0u;
     if (i == 0) *w.expired = 0u;
 }
 
 enum { SWEEP_ONE_LAUNCH = 0, SWEEP_PARTIALS = 1, SWEEP_DIVERGENCE = 2 };
 
 // ---- the sweep, in pieces -----------------------------------------------------------------------------------
-// A work item is one chunk of kSweepChunk entries of one judged position: item = (trial * k + position) * chunks
-// + chunk, so the chunks of a row are neighbours in item order.  kSweepQuads quads of 4 logits per thread and row
+// A work item is one chunk of kSweepChunk entries of one judged position: item = position * chunks + chunk within a
+// trial, so the chunks of a row are neighbours in item order.  kSweepQuads quads of 4 logits per thread and row
 // stay in registers between the two halves (40 registers); the exponentials of the first half are evaluated
 // again in the second.  Every wave keeps its own maximum, sum and divergence partial: the only barrier is the
 // one inside row_stats.
@@ -225,12 +241,12 @@ struct SweepItem {
     const float *prow, *qrow;
     int pair, ch;
 };
-__device__ inline SweepItem sweep_item(const AcceptShape& s, int item) {
+__device__ inline SweepItem sweep_item(const AcceptShape& s, int b, int item) {
     const int nsw = s.nsl / kSweepWaves;
     SweepItem it;
     it.ch = item % nsw;
-    it.pair = item / nsw;  // trial * k + position
-    const int b = it.pair / s.k, i = it.pair - b * s.k;
+    const int i = item / nsw;
+    it.pair = b * s.k + i;  // trial * k + position
     it.prow = s.lp + ((size_t)b * (s.k + 1) + i) * s.V;
     it.qrow = s.lq + (size_t)it.pair * s.V;
     return it;
@@ -305,9 +321,11 @@ __device__ inline bool sweep_second(const AcceptShape& s, const AcceptWs& w, con
                                     const float a[kSweepQuads][4], const float c[kSweepQuads][4], float4* lds) {
     const float c2 = s.inv_temp * kLog2e;
     RowStats R;
-    if (!row_stats<WAIT, kAccThreads>(w.part + (size_t)it.pair * s.nsl, s.nsl, s.wait_ticks, lds, R)) {
+    if (!row_stats<WAIT, kAccThreads>(w.part + (size_t)it.pair * s.nsl, s.nsl, s.wait_ticks, s.few, lds, R)) {
         // the decision kernel reports the expiry; nothing below is waited for by anyone
         if (threadIdx.x == 0) __hip_atomic_store(w.expired, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // whoever waits for this chunk's divergence learns of it at once
+        if (WAIT && (threadIdx.x & 63) == 0) st_agent32(w.jsd + (size_t)it.pair * s.nsl + it.ch * kSweepWaves + (threadIdx.x >> 6), INFINITY);
         return false;
     }
     // With xp = log2 p_v = a_v c2 - lp and xq = log2 q_v = c_v c2 - lq, call the larger probability B = 2^max(xp, xq) and
@@ -332,21 +350,136 @@ __device__ inline bool sweep_second(const AcceptShape& s, const AcceptWs& w, con
             acc = fmaf(big, u, acc);
             acc = fmaf(big * e, u - A, acc);
         }
-    acc = wave_sum_dpp(acc);
+    acc = (0.5f * kLn2) * wave_sum_dpp(acc);
+    if (it.ch == 0 && threadIdx.x == 0) {
+        st_agent64(&w.stats[it.pair].Mp, R.Mp, R.Sp);
+        st_agent64(&w.stats[it.pair].Mq, R.Mq, R.Sq);
+    }
+    // written last and only when everything of this thread before it has been acknowledged: a reader that sees the partials
+    // of a row sees the row's statistics too.  (A NaN out of NaN logits must not look like the unwritten pattern.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if ((threadIdx.x & 63) == 0)
-        w.jsd[(size_t)it.pair * s.nsl + it.ch * kSweepWaves + (threadIdx.x >> 6)] = (0.5f * kLn2) * acc;
-    if (it.ch == 0 && threadIdx.x == 0) w.stats[it.pair] = R;
+        st_agent32(w.jsd + (size_t)it.pair * s.nsl + it.ch * kSweepWaves + (threadIdx.x >> 6), acc != acc ? __uint_as_float(0x7fc00000u) : acc);
     return true;
 }
 
-// One workgroup per item.  SWEEP_ONE_LAUNCH: publish, wait for the row, finish.  Two launches: SWEEP_PARTIALS stops
-// after the first half, SWEEP_DIVERGENCE repeats the first half without publishing and reads the finished partials.
+// What the decision of a stage writes, and what it needs besides the sweep's results
+struct DecideArgs {
+    float T;
+    uint64_t seed;
+    uint32_t position0, stage;
+    AcceptOut* out;
+    float* div_out;
+    int32_t *n_out, *tok_out;
+};
+
+// The decision of trial b by a workgroup of NW waves: wave r sums the divergence partials of positions r, r + NW, ... (lane c
+// takes slots c, c + 64, ... in increasing order, then a fixed tree), thread i tosses the coin of position i.
+// WAIT: the partials come from workgroups of the running kernel; the wait is bounded as theirs is.
+template <bool WAIT, int NW>
+__device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const DecideArgs& a, int b) {
+    __shared__ float s_div[PSD_MAX_WIDTH];
+    __shared__ int s_pass[PSD_MAX_WIDTH];
+    __shared__ int s_bad;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = threadIdx.x;
+    // the coin's inputs do not depend on the sweep: asked for first.  The coin compares p(x) and q(x); an id outside the
+    // vocabulary has probability 0 under the verifier -> rejected.
+    const size_t pair = (size_t)b * s.k + i;
+    float zp = 0.f, zq = 0.f;
+    bool known = false;
+    if (i < s.k) {
+        const int x = s.tokens[pair];
+        known = x >= 0 && x < s.V;
+        if (known) {
+            zp = s.lp[((size_t)b * (s.k + 1) + i) * s.V + x];
+            zq = s.lq[pair * s.V + x];
+        }
+    }
+    if (i == 0) s_bad = WAIT ? 0 : (int)*w.expired;
+    __syncthreads();
+    const unsigned long long t0 = WAIT ? wall_clock64() : 0ull;
+    for (int r = wave; r < s.k; r += NW) {
+        const float* pr = w.jsd + ((size_t)b * s.k + r) * s.nsl;
+        float d = 0.f;
+        if constexpr (WAIT) {
+            constexpr int kPer = kSweepMaxSlots / 64;
+            float v[kPer];
+            bool good = true;
+            for (;;) {
+                bool missing = false;
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    const int c = lane + 64 * u;
+                    v[u] = c < s.nsl ? ld_agent32(pr + c) : 0.f;
+                    missing |= __float_as_uint(v[u]) == kUnwritten;
+                    good &= v[u] != INFINITY;
+                }
+                if (!__any(missing)) break;
+                if (wall_clock64() - t0 >= s.wait_ticks) { good = false; break; }
+                __builtin_amdgcn_s_sleep(8);
+            }
+            if (!__all(good) && lane == 0) {
+                s_bad = 1;
+                __hip_atomic_store(w.expired, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // accept_race tells every trial
+            }
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (lane + 64 * u < s.nsl) d = d + v[u];
+        } else {
+            for (int c = lane; c < s.nsl; c += 64) d = d + pr[c];
+        }
+        d = wave_sum_dpp(d);
+        if (lane == 0) s_div[r] = d;
+    }
+    __syncthreads();
+    if (i < s.k) {
+        const float d = s_div[i];
+        if (a.div_out) a.div_out[pair] = d;
+        int pass = 2;  // 2: within the threshold, 1: the coin accepted, 0: rejected
+        if (!(d <= a.T)) {
+            const uint64_t sd = a.seed + (uint64_t)b;
+            U4 r = philox4x32_10(U4{0u, a.position0 + (uint32_t)i, DRAW_COIN, a.stage}, (uint32_t)sd, (uint32_t)(sd >> 32));
+            TokProb tp{0.f, 1.f};
+            if (known) {   // accurate exponentials of the natural-log probabilities
+                const unsigned long long up = ld_agent64(&w.stats[pair].Mp), uq = ld_agent64(&w.stats[pair].Mq);
+                const float Mp = __uint_as_float((uint32_t)up), Sp = __uint_as_float((uint32_t)(up >> 32));
+                const float Mq = __uint_as_float((uint32_t)uq), Sq = __uint_as_float((uint32_t)(uq >> 32));
+                const float lse_p = (Mp + log2f(Sp)) * kLn2, lse_q = (Mq + log2f(Sq)) * kLn2;
+                tp = TokProb{expf(fmaxf(zp, -kBig) * s.inv_temp - lse_p), expf(fmaxf(zq, -kBig) * s.inv_temp - lse_q)};
+            }
+            pass = (u01(r.x) * tp.qx < tp.px) ? 1 : 0;  // u < p(x)/q(x)
+        }
+        s_pass[i] = pass;
+    }
+    __syncthreads();
+    if (i == 0) {
+        int n = 0, fuzzy = 0;
+        for (; n < s.k && s_pass[n]; ++n) fuzzy += s_pass[n] == 2;
+        AcceptOut o;
+        o.n_accepted = s_bad ? -1 : n;  // -1: a bounded wait expired
+        o.n_fuzzy = fuzzy;
+        o.pad = 0;
+        o.next_token = -1;
+        a.out[b] = o;
+        if (a.n_out) { a.n_out[b] = o.n_accepted; a.tok_out[b] = -1; }
+    }
+}
+
+// One workgroup per item.  SWEEP_ONE_LAUNCH: publish, wait for the row, finish; a trial's items are followed by the
+// workgroup that decides it.  Two launches: SWEEP_PARTIALS stops after the first half, SWEEP_DIVERGENCE repeats the first
+// half without publishing and reads the finished partials.
 // The workgroups of a row are neighbours in launch order and consecutive ids go round the 8 accelerator dies, so
 // the chunks a workgroup waits for are resident with it.
 template <int MODE, bool VEC>
-__global__ __launch_bounds__(kAccThreads, (MODE == SWEEP_ONE_LAUNCH && VEC) ? 8 : 6) void accept_sweep(AcceptShape s, AcceptWs w) {
+__global__ __launch_bounds__(kAccThreads, (MODE == SWEEP_ONE_LAUNCH && VEC) ? 8 : 6) void accept_sweep(AcceptShape s, AcceptWs w, DecideArgs da) {
     __shared__ float4 lds[kSweepWaves];
-    const SweepItem it = sweep_item(s, blockIdx.x);
+    const int items = s.k * (s.nsl / kSweepWaves), per = items + (MODE == SWEEP_ONE_LAUNCH ? 1 : 0);
+    const int b = blockIdx.x / per, item = blockIdx.x - b * per;
+    if (MODE == SWEEP_ONE_LAUNCH && item == items) {
+        decide<true, kAccThreads / 64>(s, w, da, b);
+        return;
+    }
+    const SweepItem it = sweep_item(s, b, item);
     float a[kSweepQuads][4], c[kSweepQuads][4];
     if (VEC) sweep_load(s, it, a, c);
     else sweep_load_any(s, it, a, c);
@@ -355,58 +488,8 @@ __global__ __launch_bounds__(kAccThreads, (MODE == SWEEP_ONE_LAUNCH && VEC) ? 8 
     sweep_second<MODE == SWEEP_ONE_LAUNCH>(s, w, it, a, c, lds);
 }
 
-// One workgroup of 16 waves per trial: wave r sums the divergence partials of positions r, r + 16 (lane c
-// takes chunks c, c + 64, ... in increasing order, then a fixed tree), thread i tosses the coin of position i.
-__global__ __launch_bounds__(1024) void accept_decide(AcceptShape s, AcceptWs w, float T, uint64_t seed,
-                                                      uint32_t position0, uint32_t stage, AcceptOut* out,
-                                                      float* div_out, int32_t* n_out, int32_t* tok_out) {
-    __shared__ float s_div[PSD_MAX_WIDTH];
-    __shared__ int s_pass[PSD_MAX_WIDTH];
-    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = wave; i < s.k; i += 16) {
-        const float* pr = w.jsd + ((size_t)b * s.k + i) * s.nsl;
-        float d = 0.f;
-        for (int c = lane; c < s.nsl; c += 64) d = d + pr[c];
-        d = wave_sum_dpp(d);
-        if (lane == 0) s_div[i] = d;
-    }
-    __syncthreads();
-    const int i = threadIdx.x;
-    if (i < s.k) {
-        const float d = s_div[i];
-        if (div_out) div_out[(size_t)b * s.k + i] = d;
-        int pass = 2;  // 2: within the threshold, 1: the coin accepted, 0: rejected
-        if (!(d <= T)) {
-            const uint64_t sd = seed + (uint64_t)b;
-            U4 r = philox4x32_10(U4{0u, position0 + (uint32_t)i, DRAW_COIN, stage}, (uint32_t)sd, (uint32_t)(sd >> 32));
-            // The coin compares p(x) and q(x): accurate exponentials of the natural-log probabilities.
-            // An id outside the vocabulary has probability 0 under the verifier -> rejected.
-            const size_t pair = (size_t)b * s.k + i;
-            const int x = s.tokens[pair];
-            TokProb tp{0.f, 1.f};
-            if (x >= 0 && x < s.V) {
-                const RowStats R = w.stats[pair];
-                const float lse_p = (R.Mp + log2f(R.Sp)) * kLn2, lse_q = (R.Mq + log2f(R.Sq)) * kLn2;
-                const float zp = s.lp[((size_t)b * (s.k + 1) + i) * s.V + x], zq = s.lq[pair * s.V + x];
-                tp = TokProb{expf(fmaxf(zp, -kBig) * s.inv_temp - lse_p), expf(fmaxf(zq, -kBig) * s.inv_temp - lse_q)};
-            }
-            pass = (u01(r.x) * tp.qx < tp.px) ? 1 : 0;  // u < p(x)/q(x)
-        }
-        s_pass[i] = pass;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int n = 0, fuzzy = 0;
-        for (; n < s.k && s_pass[n]; ++n) fuzzy += s_pass[n] == 2;
-        AcceptOut o;
-        o.n_accepted = *w.expired ? -1 : n;  // -1: the sweep's bounded wait expired
-        o.n_fuzzy = fuzzy;
-        o.pad = 0;
-        o.next_token = -1;
-        out[b] = o;
-        if (n_out) { n_out[b] = o.n_accepted; tok_out[b] = -1; }
-    }
-}
+// the decision as a kernel of its own: behind the two-launch sweep, and where nothing is judged (k = 0)
+__global__ __launch_bounds__(1024) void accept_decide(AcceptShape s, AcceptWs w, DecideArgs a) { decide<false, 16>(s, w, a, blockIdx.x); }
 
 // ---- assisted stage: strict match against the verifier's top prediction ---------------------------------
 __global__ __launch_bounds__(kAccThreads) void accept_top(AcceptShape s, AcceptWs w) {
@@ -458,18 +541,49 @@ __global__ __launch_bounds__(1024) void accept_decide_assisted(AcceptShape s, Ac
     }
 }
 
+// Winner of trial b's race among its chunks (whose results are all there), by a whole workgroup
+__device__ inline void pick(const AcceptShape& s, const AcceptWs& w, int b, int n, int assisted, AcceptOut* out, int32_t* tok_out) {
+    __shared__ KeyIdx smp[4];
+    const bool bonus_row = n == s.k || assisted;  // keys in log form: any sign, and never without mass
+    KeyIdx best{bonus_row ? -INFINITY : -1.f, 0x7fffffff}, fb{-1.f, 0x7fffffff};
+    for (int c = threadIdx.x; c < s.nch; c += kAccThreads) {
+        const RacePart* src = w.race + (size_t)b * s.nch + c;
+        const unsigned long long u0 = ld_agent64(&src->key), u1 = ld_agent64(&src->key_fb);
+        best = better(best, KeyIdx{__uint_as_float((uint32_t)u0), (int)(u0 >> 32)});
+        fb = better(fb, KeyIdx{__uint_as_float((uint32_t)u1), (int)(u1 >> 32)});
+    }
+    best = block_best<4>(best, smp);
+    __syncthreads();
+    fb = block_best<4>(fb, smp);
+    // no residual mass at all (cannot happen in exact arithmetic): draw from p instead
+    if (!bonus_row && !(best.key > 0.f)) best = fb;
+    if (threadIdx.x == 0) {
+        const int tok = best.idx == 0x7fffffff ? -1 : best.idx;
+        out[b].next_token = tok;
+        if (tok_out) tok_out[b] = tok;
+    }
+}
+
 // Replacement draw, one row per trial.  First rejected position n < k: race r_v / E_v over the residual
 // r = max(0, p - q) (and p_v / E_v beside it, used when the residual has no mass at all).  n == k and a
 // bonus token is wanted: race over the verifier's last row in log form, z_v / temperature - ln E_v, which
 // needs no normalisation.  E_v = -ln u_v.  Assisted stage: the draw at a rejection is from the verifier's
 // row itself, in the same log form but with the replacement stream's random numbers.
-__global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, AcceptWs w, const AcceptOut* out,
+template <bool PICK>
+__global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, AcceptWs w, AcceptOut* out,
                                                            uint64_t seed, uint32_t position0, uint32_t stage,
-                                                           int take_bonus, int assisted) {
+                                                           int take_bonus, int assisted, int32_t* n_out, int32_t* tok_out) {
     __shared__ KeyIdx smk[4];
     const int ch = blockIdx.x, b = blockIdx.y;
+    if (!assisted && *w.expired) {   // some wait of the sweep ran out: no trial of the call is valid
+        if (ch == 0 && threadIdx.x == 0) {
+            out[b].n_accepted = -1;
+            if (n_out) n_out[b] = -1;
+        }
+        return;
+    }
     const int n = out[b].n_accepted;
-    if (n < 0 || (n == s.k && !take_bonus)) return;
+    if (n < 0 || (n == s.k && !take_bonus)) return;   // next_token stays -1
     const uint64_t sd = seed + (uint64_t)b;
     const uint32_t pos = position0 + (uint32_t)n;
     const float* prow = s.lp + ((size_t)b * (s.k + 1) + n) * s.V;
@@ -519,31 +633,29 @@ __global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, Accept
     }
     best = block_best<4>(best, smk);
     best_fb = block_best<4>(best_fb, smk);
-    if (threadIdx.x == 0) w.race[(size_t)b * s.nch + ch] = RacePart{best.key, best.idx, best_fb.key, best_fb.idx};
+    __shared__ int s_last;
+    if (threadIdx.x == 0) {
+        RacePart* dst = w.race + (size_t)b * s.nch + ch;
+        st_agent64(&dst->key, best.key, __int_as_float(best.idx));
+        st_agent64(&dst->key_fb, best_fb.key, __int_as_float(best_fb.idx));
+        if (PICK) {
+            // counted once the stores have been acknowledged: who counts last finds every chunk's result
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            s_last = __hip_atomic_fetch_add(w.raced + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(s.nch - 1);
+        }
+    }
+    if (PICK) {
+        __syncthreads();
+        if (s_last) pick(s, w, b, n, assisted, out, tok_out);
+    }
 }
 
+// the winner as a kernel of its own
 __global__ __launch_bounds__(kAccThreads) void accept_pick(AcceptShape s, AcceptWs w, int take_bonus, int assisted,
                                                            AcceptOut* out, int32_t* tok_out) {
-    __shared__ KeyIdx smk[4];
-    const int b = blockIdx.x;
-    const int n = out[b].n_accepted;
+    const int b = blockIdx.x, n = out[b].n_accepted;
     if (n < 0 || (n == s.k && !take_bonus)) return;  // next_token stays -1
-    const bool bonus_row = n == s.k || assisted;  // keys in log form: any sign, and never without mass
-    KeyIdx best{bonus_row ? -INFINITY : -1.f, 0x7fffffff}, fb{-1.f, 0x7fffffff};
-    for (int c = threadIdx.x; c < s.nch; c += kAccThreads) {
-        const RacePart r = w.race[(size_t)b * s.nch + c];
-        best = better(best, KeyIdx{r.key, r.idx});
-        fb = better(fb, KeyIdx{r.key_fb, r.idx_fb});
-    }
-    best = block_best<4>(best, smk);
-    fb = block_best<4>(fb, smk);
-    // no residual mass at all (cannot happen in exact arithmetic): draw from p instead
-    if (!bonus_row && !(best.key > 0.f)) best = fb;
-    if (threadIdx.x == 0) {
-        const int tok = best.idx == 0x7fffffff ? -1 : best.idx;
-        out[b].next_token = tok;
-        if (tok_out) tok_out[b] = tok;
-    }
+    pick(s, w, b, n, assisted, out, tok_out);
 }
 
 static inline size_t align16(size_t n) { return (n + 15) & ~(size_t)15; }
@@ -561,7 +673,7 @@ static size_t carve(AcceptWs* w, void* base, int n_trials, int k, int vocab) {
     RacePart* race = (RacePart*)take((size_t)n_trials * nch * sizeof(RacePart));
     KeyIdx* top = (KeyIdx*)take((pairs + n_trials) * nch * sizeof(KeyIdx));
     uint32_t* expired = (uint32_t*)take(sizeof(uint32_t));
-    if (w) *w = AcceptWs{part, jsd, st, race, top, expired};
+    if (w) *w = AcceptWs{part, jsd, st, race, top, expired, reinterpret_cast<uint32_t*>(top)};
     return off;
 }
 
@@ -588,7 +700,8 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
     if ((long long)pairs * nsw > 0x7fffffffLL) PSD_FAIL(PSD_EINVAL, errbuf, "accept: n_trials * k * chunks overflows the grid");
     AcceptWs w;
     carve(&w, workspace, n_trials, k, vocab);
-    AcceptShape s{logits_p, logits_q, tokens, k, vocab, nch, 1.0f / temperature, kSweepWaves * nsw, g_wait_ticks.load()};
+    AcceptShape s{logits_p, logits_q, tokens, k, vocab, nch, 1.0f / temperature, kSweepWaves * nsw, g_wait_ticks.load(),
+                  (long long)pairs * nsw <= 1024};
     const size_t n_parts = (size_t)pairs * nsw * kSweepWaves;
     if (assisted) {   // 1: assisted stage, 2: greedy stage
         const int greedy = assisted == 2, rows = greedy ? k + 1 : k;
@@ -596,32 +709,41 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
         accept_decide_assisted<<<n_trials, 1024, 0, stream>>>(s, w, greedy, take_bonus, out, div_out, n_accepted_out,
                                                                next_token_out);
         if (!greedy) {
-            accept_race<<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 1);
+            accept_race<false><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 1, nullptr, nullptr);
             accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 1, out, next_token_out);
         }
         PSD_HIP(hipGetLastError(), errbuf);
         return PSD_OK;
     }
-    accept_clear<<<(unsigned)((n_parts + 256) / 256), 256, 0, stream>>>(w, n_parts);
-    if (pairs > 0) {
-        const int n_items = pairs * nsw;
-        const bool vec = (vocab & 3) == 0;  // rows are then 16-byte aligned and hold whole quads
-        const bool one_launch = g_accept_path.load() != 1 && kSweepWaves * nsw <= kSweepMaxSlots;
-        if (one_launch) {
-            if (vec) accept_sweep<SWEEP_ONE_LAUNCH, true><<<n_items, kAccThreads, 0, stream>>>(s, w);
-            else accept_sweep<SWEEP_ONE_LAUNCH, false><<<n_items, kAccThreads, 0, stream>>>(s, w);
-        } else if (vec) {
-            accept_sweep<SWEEP_PARTIALS, true><<<n_items, kAccThreads, 0, stream>>>(s, w);
-            accept_sweep<SWEEP_DIVERGENCE, true><<<n_items, kAccThreads, 0, stream>>>(s, w);
-        } else {
-            accept_sweep<SWEEP_PARTIALS, false><<<n_items, kAccThreads, 0, stream>>>(s, w);
-            accept_sweep<SWEEP_DIVERGENCE, false><<<n_items, kAccThreads, 0, stream>>>(s, w);
+    const DecideArgs da{T, seed, position0, stage, out, div_out, n_accepted_out, next_token_out};
+    const size_t n_clear = std::max(n_parts, (size_t)n_trials);
+    // a row's workgroups may wait for each other while there are few enough of them to be resident together
+    const bool one_launch = pairs > 0 && g_accept_path.load() != 1 && kSweepWaves * nsw <= kSweepMaxSlots &&
+                            (long long)pairs * nsw + n_trials <= 0x7fffffffLL;
+    accept_clear<<<(unsigned)((n_clear + 256) / 256), 256, 0, stream>>>(w, n_parts, n_trials);
+    const int n_items = pairs * nsw;
+    const bool vec = (vocab & 3) == 0;  // rows are then 16-byte aligned and hold whole quads
+    if (one_launch) {
+        if (vec) accept_sweep<SWEEP_ONE_LAUNCH, true><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
+        else accept_sweep<SWEEP_ONE_LAUNCH, false><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
+    } else {
+        if (pairs > 0 && vec) {
+            accept_sweep<SWEEP_PARTIALS, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
+            accept_sweep<SWEEP_DIVERGENCE, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
+        } else if (pairs > 0) {
+            accept_sweep<SWEEP_PARTIALS, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
+            accept_sweep<SWEEP_DIVERGENCE, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
         }
+        accept_decide<<<n_trials, 1024, 0, stream>>>(s, w, da);
     }
-    accept_decide<<<n_trials, 1024, 0, stream>>>(s, w, T, seed, position0, stage, out, div_out, n_accepted_out,
-                                                 next_token_out);
-    accept_race<<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0);
-    accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 0, out, next_token_out);
+    // The last workgroup of a trial's race picks where they are few: every one of them pays an atomic's round trip for it, which
+    // a big launch notices (48 trials: 126 us instead of 107) and a launch of 63 workgroups does not (one launch less: 2 us)
+    if ((long long)nch * n_trials <= 1024) {
+        accept_race<true><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0, n_accepted_out, next_token_out);
+    } else {
+        accept_race<false><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0, n_accepted_out, next_token_out);
+        accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 0, out, next_token_out);
+    }
     PSD_HIP(hipGetLastError(), errbuf);
     return PSD_OK;
 }

@@ -173,6 +173,30 @@ def test_one_launch_and_two_launch_sweeps_agree_bit_for_bit(V, k, B):
             assert res.margin_div < TIE_DIV or res.margin_coin < TIE_COIN or res.margin_race < TIE_RACE
 
 
+@pytest.mark.parametrize("B,k,V", [(1, 1, 1), (1, 32, 5120), (3, 32, 5121), (16, 2, 128256), (17, 2, 128256), (2, 2, 327680),
+                                   (2, 1, 327681), (1030, 1, 33), (2, 0, 4097)])
+def test_deciding_and_picking_workgroups_agree_with_their_own_launches(B, k, V):
+    # the decision inside the one-launch sweep against the launch behind the two-launch one: one slot, 256 slots (all the wait
+    # covers), one vocabulary entry more (two launches on both paths), k = 0; the pick by the race's last workgroup (1008
+    # workgroups) and as a launch (1071); judged, rejected and bonus rows
+    stages = [_stage_inputs(23, b % 4, max(k, 1), V, 0.9, 2) for b in range(min(B, 4))]
+    P = [stages[b % len(stages)][0][:k + 1] for b in range(B)]
+    Q = [stages[b % len(stages)][1][:k] for b in range(B)]
+    X = [stages[b % len(stages)][2][:k] for b in range(B)]
+    for T, bonus in ((0.05, True), (0.0, False), (1.0, True)):
+        got = _batched(P, Q, X, T, 1.0, 31, 40, 2, bonus)
+        try:
+            psd.set_accept_path(1)
+            ref = _batched(P, Q, X, T, 1.0, 31, 40, 2, bonus)
+        finally:
+            psd.set_accept_path(0)
+        for a, b in zip(got, ref):
+            assert np.array_equal(a, b)
+        if B <= 4:
+            for b in range(B):
+                _compare(P[b], Q[b], X[b], T, 1.0, 31 + b, 40, 2, bonus)
+
+
 def test_accept_masked_entries():
     """-inf logits carry probability zero, in one row or in both."""
     rng = np.random.default_rng(9)
