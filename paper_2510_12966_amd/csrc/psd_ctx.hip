@@ -5,12 +5,13 @@
 // has not cached; a rollback is nothing more than lowering that count (and returning whole KV pages).
 // The draft's chain of single-token steps stays on the device: the sampling kernels write the new token
 // into the next draft pass descriptor and into the qualifier's, so the host synchronises once per
-// qualifier round and once per target pass, when it reads the ACCEPT result.
+// qualifier round and once per target pass, when it reads the ACCEPT result (from its own memory: fetch_round).
 #include <stddef.h>
 #include <math.h>
 #include <string.h>
 
 #include <algorithm>
+#include <initializer_list>
 #include <vector>
 
 #include "psd_device.h"
@@ -21,10 +22,11 @@ namespace psd {
 constexpr int kStageSlots = 64;
 constexpr int kStageSlotBytes = 2304;  // a pass descriptor with 512 token ids fits
 
-struct RoundResult {  // pinned host mirror of what a round leaves on the device
+struct RoundResult {  // pinned host memory that publish_round fills with what a round leaves on the device
     AcceptOut acc;
     int32_t tok[kMaxW];
     float div[kMaxW];
+    uint32_t seq;     // written last: the result with this number is there
 };
 
 // Adaptive controller (the header states the rule).  Pure host arithmetic on accept counts between outer iterations.
@@ -81,9 +83,10 @@ struct GraphSlot {
     hipGraphExec_t exec = nullptr;
 };
 
-// device time per stage of the loop: event pairs recorded in stream order, read once at the end of a call
+// device time per stage of the loop: events recorded in stream order, read once at the end of a call.  A stage that begins
+// where another ends shares its event (every record is a packet the device has to work through).
 struct StageTimer {
-    struct Span { int kind; hipEvent_t a, b; };
+    struct Span { int kind; hipEvent_t a, b; bool shared; };   // shared: `a` is the previous span's `b`
     std::vector<Span> spans;
     std::vector<hipEvent_t> pool;
     hipEvent_t get() {
@@ -92,13 +95,14 @@ struct StageTimer {
         (void)hipEventCreate(&e);
         return e;
     }
-    void begin(hipStream_t s, int kind) { spans.push_back({kind, get(), get()}); (void)hipEventRecord(spans.back().a, s); }
+    void begin(hipStream_t s, int kind) { spans.push_back({kind, get(), get(), false}); (void)hipEventRecord(spans.back().a, s); }
     void end(hipStream_t s) { (void)hipEventRecord(spans.back().b, s); }
+    void follow(int kind) { spans.push_back({kind, spans.back().b, get(), true}); }   // nothing was enqueued since the last end()
     void collect(double ms[4]) {  // call after the stream has been synchronised
         for (auto& sp : spans) {
             float t = 0.f;
             if (hipEventElapsedTime(&t, sp.a, sp.b) == hipSuccess) ms[sp.kind] += t;
-            pool.push_back(sp.a);
+            if (!sp.shared) pool.push_back(sp.a);
             pool.push_back(sp.b);
         }
         spans.clear();
@@ -144,6 +148,9 @@ struct psd_ctx {
     char* stage = nullptr;  // kStageSlots * kStageSlotBytes
     int stage_next = 0, stage_since_sync = 0;
     RoundResult* res = nullptr;
+    char* stage_dev = nullptr;       // the same two as the device addresses them
+    RoundResult* res_dev = nullptr;
+    uint32_t res_seq = 0;
     // graphs: [model][width class 4 / 16 / 32]
     GraphSlot graphs[3][kNumNarrowClasses][kNumCtxBuckets];   // [model][launch class][context bucket]
     GraphSlot chain_graphs[3][3][kNumNarrowClasses][kNumCtxBuckets];  // sampling steps: [proposer][model whose pass descriptor receives the tokens][launch class][context bucket]
@@ -180,6 +187,31 @@ __global__ __launch_bounds__(64) void draft_pick_advance(const KeyIdx* parts, in
     chain->position += 1;
 }
 
+// Host data into device memory: up to four pieces of one pinned staging slot, read across the bus by one small launch.  A
+// round's descriptors and chain state travelled as three stream copies, each a launch of its own with 8-10 us around it.
+struct Pieces {
+    uint32_t* dst[4];
+    int end[4];   // words, cumulative
+};
+__global__ __launch_bounds__(256) void scatter_pieces(const uint32_t* __restrict__ src, Pieces p) {
+    for (int i = threadIdx.x; i < p.end[3]; i += 256) {
+        int k = 0;
+        while (i >= p.end[k]) ++k;
+        p.dst[k][i - (k ? p.end[k - 1] : 0)] = src[i];
+    }
+}
+
+// what the host needs of a round, into pinned host memory; its number goes last.  One wave.
+__global__ __launch_bounds__(64) void publish_round(const AcceptOut* acc, const int32_t* tok, int n_tok, const float* div, int n_div,
+                                                    RoundResult* res, uint32_t seq) {
+    const int i = threadIdx.x;
+    if (i < n_tok) res->tok[i] = tok[i];
+    if (i < n_div) res->div[i] = div[i];
+    if (acc && i == 0) res->acc = *acc;
+    __threadfence_system();   // all of the wave's stores
+    if (i == 0) __hip_atomic_store(&res->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 static int stage_sync(psd_ctx* c) {
     PSD_HIP(hipStreamSynchronize(c->stream), c->err);
     c->stage_since_sync = 0;
@@ -198,6 +230,54 @@ static int upload(psd_ctx* c, void* dst, const void* src, size_t bytes) {
     c->stage_since_sync++;
     memcpy(slot, src, bytes);
     PSD_HIP(hipMemcpyAsync(dst, slot, bytes, hipMemcpyHostToDevice, c->stream), c->err);
+    return PSD_OK;
+}
+
+struct Piece { void* dst; const void* src; size_t bytes; };   // whole 4-byte words, destinations 4-byte aligned
+
+// copies up to four pieces of host data to device memory in stream order through one pinned ring slot and one launch
+static int upload_pieces(psd_ctx* c, std::initializer_list<Piece> pieces) {
+    if (c->stage_since_sync >= kStageSlots - 1) {
+        int rc = stage_sync(c);
+        if (rc != PSD_OK) return rc;
+    }
+    const size_t off = (size_t)c->stage_next * kStageSlotBytes;
+    size_t used = 0;
+    int k = 0;
+    Pieces p{};
+    for (const Piece& q : pieces) {
+        if (k == 4 || used + q.bytes > kStageSlotBytes || (q.bytes & 3) || ((uintptr_t)q.dst & 3))
+            PSD_FAIL(PSD_EINVAL, c->err, "internal: staging pieces");
+        memcpy(c->stage + off + used, q.src, q.bytes);
+        used += q.bytes;
+        p.dst[k] = (uint32_t*)q.dst;
+        p.end[k++] = (int)(used / 4);
+    }
+    for (; k < 4; ++k) p.end[k] = (int)(used / 4);
+    c->stage_next = (c->stage_next + 1) % kStageSlots;
+    c->stage_since_sync++;
+    scatter_pieces<<<1, 256, 0, c->stream>>>((const uint32_t*)(c->stage_dev + off), p);
+    PSD_HIP(hipGetLastError(), c->err);
+    return PSD_OK;
+}
+
+// Enqueues the round's result for the host and waits for it: the host watches its own memory (a stream synchronisation costs
+// 10-20 us more per round) and asks the stream now and then, so that an error or a result that never comes ends the wait.
+// Everything enqueued before is then done.
+static int fetch_round(psd_ctx* c, const AcceptOut* acc, const int32_t* tok, int n_tok, int n_div) {
+    const uint32_t seq = ++c->res_seq;
+    publish_round<<<1, 64, 0, c->stream>>>(acc, tok, n_tok, c->acc_div, n_div, c->res_dev, seq);
+    PSD_HIP(hipGetLastError(), c->err);
+    auto there = [&] { return __atomic_load_n(&c->res->seq, __ATOMIC_ACQUIRE) == seq; };
+    for (unsigned spin = 1; !there(); ++spin) {
+        if (spin % 4096 == 0) {
+            if (hipStreamQuery(c->stream) != hipErrorNotReady) break;   // finished, or failed
+            (void)hipGetLastError();                                    // "not ready" is no error to be found later
+        }
+        __builtin_ia32_pause();
+    }
+    if (!there() || c->trace) return stage_sync(c);   // reports the error; a trace copies rows behind the stream's back
+    c->stage_since_sync = 0;
     return PSD_OK;
 }
 
@@ -359,24 +439,21 @@ static int note_rows(psd_ctx* c, int mi, const float* rows, int n) {
     return row_stats_launch(rows, n, c->V, c->prm.temperature, nullptr, nullptr, c->rs_acc + 3 * mi, c->rs_ws, c->stream, c->err);
 }
 
-// One ACCEPT stage on the stream, its result in c->res after one synchronisation.  n_tok: how many of the round's
-// draft tokens to bring back as well.  The kernels of a row wait for each other under a clock; should that wait
+// One ACCEPT stage on the stream, its result in c->res.  n_tok: how many of the round's draft tokens to bring back as
+// well.  follows: the verifier's pass ended the last timer span and nothing was enqueued since.  The kernels of a row wait for each other under a clock; should that wait
 // ever expire (n_accepted = -1: the launch was not resident as a whole), the library switches to the two-launch
 // sweep for good and the stage is run again.
 static int accept_sync(psd_ctx* c, const char* prof_row, const float* lp, const float* lq, const int32_t* toks, int k,
-                       float T, uint64_t seed, uint32_t pos0, uint32_t stage, int bonus, int assisted, int n_tok) {
+                       float T, uint64_t seed, uint32_t pos0, uint32_t stage, int bonus, int assisted, int n_tok, bool follows) {
     for (int attempt = 0; attempt < 2; ++attempt) {
         if (c->prof.on) c->prof.begin(c->stream, c->prof.row_of(prof_row), (double)(2 * k + 1) * c->V * 4);
-        c->timer.begin(c->stream, 3);
+        if (follows && attempt == 0) c->timer.follow(3); else c->timer.begin(c->stream, 3);
         int rc = accept_launch(lp, lq, toks, 1, k, c->V, T, c->prm.temperature, seed, pos0, stage, bonus, c->acc_out,
                                c->acc_div, c->acc_ws, c->acc_ws_bytes, c->stream, c->err, nullptr, nullptr, assisted);
         if (rc != PSD_OK) return rc;
         c->timer.end(c->stream);
         if (c->prof.on) c->prof.end(c->stream);
-        PSD_HIP(hipMemcpyAsync(&c->res->acc, c->acc_out, sizeof(AcceptOut), hipMemcpyDeviceToHost, c->stream), c->err);
-        if (n_tok > 0) PSD_HIP(hipMemcpyAsync(c->res->tok, c->round_tok, n_tok * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream), c->err);
-        if (c->trace && k > 0) PSD_HIP(hipMemcpyAsync(c->res->div, c->acc_div, k * sizeof(float), hipMemcpyDeviceToHost, c->stream), c->err);
-        if ((rc = stage_sync(c)) != PSD_OK) return rc;
+        if ((rc = fetch_round(c, c->acc_out, c->round_tok, n_tok, c->trace ? k : 0)) != PSD_OK) return rc;
         if (c->res->acc.n_accepted >= 0) return PSD_OK;
         accept_wait_expired();
     }
@@ -499,6 +576,9 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     if (!ok) { set_error(c->err, "psd_create: device pool too small"); return fail(PSD_ENOMEM); }
     CK(hipHostMalloc((void**)&c->stage, (size_t)kStageSlots * kStageSlotBytes, hipHostMallocDefault));
     CK(hipHostMalloc((void**)&c->res, sizeof(RoundResult), hipHostMallocDefault));
+    c->res->seq = 0;
+    CK(hipHostGetDevicePointer((void**)&c->stage_dev, c->stage, 0));
+    CK(hipHostGetDevicePointer((void**)&c->res_dev, c->res, 0));
     for (auto& e : c->ev) CK(hipEventCreate(&e));
     for (auto& st : c->aux) CK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
     for (auto& e : c->aux_ready) CK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -601,6 +681,7 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
     if (!prompt || n_prompt < 1 || n_new < 0 || (n_new > 0 && !out_tokens)) PSD_FAIL(PSD_EINVAL, c->err, "psd_generate: bad argument");
     const int V = c->V;
     const int greedy = (c->prm.flags & PSD_FLAG_GREEDY) ? 1 : 0;
+    const bool row_stats = (c->prm.flags & PSD_FLAG_ROW_STATS) != 0;
     const int assisted = greedy ? 2 : (c->prm.flags & PSD_FLAG_ASSISTED) ? 1 : 0;  // rule of the qualifier stage
     // thresholds and window lengths of the current outer iteration: fixed, or moved by the adaptive controller
     Controller& ctl = c->ctl;
@@ -652,16 +733,14 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
             fill_desc(dd, seq.data(), D.len, L, 0, 1, 0);
             fill_desc(qd, seq.data(), Q.len, L, m, m + 1, nbuf);
             SampleCtl sc{seed, L, 0, hq, 0};
-            if ((rc = upload(c, D.desc, &dd, desc_bytes(dd))) != PSD_OK) return rc;
-            if ((rc = upload(c, Q.desc, &qd, desc_bytes(qd))) != PSD_OK) return rc;
-            if ((rc = upload(c, c->chain, &sc, sizeof(sc))) != PSD_OK) return rc;
+            if ((rc = upload_pieces(c, {{D.desc, &dd, desc_bytes(dd)}, {Q.desc, &qd, desc_bytes(qd)}, {c->chain, &sc, sizeof(sc)}})) != PSD_OK) return rc;
             c->timer.begin(c->stream, 0);
             // the first step also ingests what the draft has not cached (1 to 3 tokens), the others one token each
             for (int i = 0; i < m; ++i)
                 if ((rc = run_pass(c, 0, wclass(i == 0 ? L - D.len : 1), c->DL, true, true)) != PSD_OK) return rc;
             c->timer.end(c->stream);
             st.passes_d += m;
-            c->timer.begin(c->stream, 1);
+            c->timer.follow(1);
             if ((rc = run_pass(c, 1, wclass(hq + m), c->QL, false, true)) != PSD_OK) return rc;
             c->timer.end(c->stream);
             st.passes_q++;
@@ -669,7 +748,7 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
             if ((rc = note_rows(c, 1, c->QL + (size_t)nbuf * V, m + 1)) != PSD_OK) return rc;
             const int bonus = nbuf + m < k2;
             if ((rc = accept_sync(c, "accept stage1", c->QL + (size_t)nbuf * V, c->DL, c->round_tok, m, T_q, seed,
-                                  (uint32_t)L, 1u, bonus, assisted, m)) != PSD_OK) return rc;
+                                  (uint32_t)L, 1u, bonus, assisted, m, !row_stats)) != PSD_OK) return rc;
             const int n = c->res->acc.n_accepted, y = c->res->acc.next_token, has_y = y >= 0;
             if (n < 0 || n > m || (!has_y && (n < m || bonus))) PSD_FAIL(PSD_EHIP, c->err, "internal: impossible ACCEPT result (n=%d y=%d)", n, y);
             if (c->trace) {
@@ -695,15 +774,14 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
         if ((rc = map_pages(c, T, T.len, C + k2)) != PSD_OK) return rc;
         PassDesc td;
         fill_desc(td, seq.data(), T.len, C + k2, 0, k2 + 1, 0);
-        if ((rc = upload(c, T.desc, &td, desc_bytes(td))) != PSD_OK) return rc;
-        if ((rc = upload(c, c->win_tok, seq.data() + C, k2 * sizeof(int32_t))) != PSD_OK) return rc;
+        if ((rc = upload_pieces(c, {{T.desc, &td, desc_bytes(td)}, {c->win_tok, seq.data() + C, k2 * sizeof(int32_t)}})) != PSD_OK) return rc;
         c->timer.begin(c->stream, 2);
         if ((rc = run_pass(c, 2, wclass(wT), c->TL, false, true)) != PSD_OK) return rc;
         c->timer.end(c->stream);
         st.passes_t++;
         if ((rc = note_rows(c, 2, c->TL, k2 + 1)) != PSD_OK) return rc;
         if ((rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->win_tok, k2, T_t, seed, (uint32_t)C, 2u, 1,
-                              greedy ? 2 : 0, 0)) != PSD_OK) return rc;
+                              greedy ? 2 : 0, 0, !row_stats)) != PSD_OK) return rc;
         const int n = c->res->acc.n_accepted, y = c->res->acc.next_token;
         if (n < 0 || n > k2 || y < 0) PSD_FAIL(PSD_EHIP, c->err, "internal: impossible ACCEPT result (n=%d y=%d)", n, y);
         if (c->trace) {
@@ -838,22 +916,20 @@ extern "C" int psd_generate_sd(psd_ctx* c, int32_t proposer, int32_t k, float ta
         fill_desc(pd, seq.data(), P.len, C, 0, 1, 0);
         fill_desc(td, seq.data(), T.len, C, k, k + 1, 0);
         SampleCtl sc{seed, C, 0, ht, 0};
-        if ((rc = upload(c, P.desc, &pd, desc_bytes(pd))) != PSD_OK) return rc;
-        if ((rc = upload(c, T.desc, &td, desc_bytes(td))) != PSD_OK) return rc;
-        if ((rc = upload(c, c->chain, &sc, sizeof(sc))) != PSD_OK) return rc;
+        if ((rc = upload_pieces(c, {{P.desc, &pd, desc_bytes(pd)}, {T.desc, &td, desc_bytes(td)}, {c->chain, &sc, sizeof(sc)}})) != PSD_OK) return rc;
         c->timer.begin(c->stream, proposer);
         for (int i = 0; i < k; ++i)
             if ((rc = run_pass(c, proposer, wclass(i == 0 ? C - P.len : 1), c->QL, true, true, 2)) != PSD_OK) return rc;
         c->timer.end(c->stream);
         (proposer == 0 ? st.passes_d : st.passes_q) += k;
-        c->timer.begin(c->stream, 2);
+        c->timer.follow(2);
         if ((rc = run_pass(c, 2, wclass(ht + k), c->TL, false, true)) != PSD_OK) return rc;
         c->timer.end(c->stream);
         st.passes_t++;
         if ((rc = note_rows(c, proposer, c->QL, k)) != PSD_OK) return rc;
         if ((rc = note_rows(c, 2, c->TL, k + 1)) != PSD_OK) return rc;
         if ((rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->round_tok, k, tau, seed, (uint32_t)C, 2u, 1,
-                              greedy ? 2 : 0, k)) != PSD_OK)
+                              greedy ? 2 : 0, k, !(c->prm.flags & PSD_FLAG_ROW_STATS))) != PSD_OK)
             return rc;
         const int n = c->res->acc.n_accepted, y = c->res->acc.next_token;
         if (n < 0 || n > k || y < 0) PSD_FAIL(PSD_EHIP, c->err, "internal: impossible ACCEPT result (n=%d y=%d)", n, y);
@@ -911,12 +987,11 @@ extern "C" int psd_generate_plain(psd_ctx* c, int32_t which, const int32_t* prom
         if ((rc = map_pages(c, M, M.len, L)) != PSD_OK) return rc;
         PassDesc d;
         fill_desc(d, seq.data(), M.len, L, 0, 1, 0);
-        if ((rc = upload(c, M.desc, &d, desc_bytes(d))) != PSD_OK) return rc;
+        if ((rc = upload_pieces(c, {{M.desc, &d, desc_bytes(d)}})) != PSD_OK) return rc;
         if ((rc = run_pass(c, which, wclass(L - M.len), c->HL, false)) != PSD_OK) return rc;
         if ((rc = sample_launch(c->HL, 1, c->V, c->prm.temperature, seed, (uint32_t)L, nullptr, c->samp_tok, c->samp_part, c->stream, c->err,
                                 (c->prm.flags & PSD_FLAG_GREEDY) ? 1 : 0)) != PSD_OK) return rc;
-        PSD_HIP(hipMemcpyAsync(c->res->tok, c->samp_tok, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream), c->err);
-        if ((rc = stage_sync(c)) != PSD_OK) return rc;
+        if ((rc = fetch_round(c, nullptr, c->samp_tok, 1, 0)) != PSD_OK) return rc;
         seq[L] = c->res->tok[0];
         M.len = L;
         (which == 0 ? st.passes_d : which == 1 ? st.passes_q : st.passes_t)++;
