@@ -23,6 +23,21 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 enum { EPI_RESID = 1, EPI_LOGITS = 2 };
 
+// v combined over the four 16-lane rows of a wave, (row 0 with 1, 2 with 3), then the two results; every lane gets it.  The
+// swaps of two equal registers leave a row and its partner side by side: no trip through LDS.
+__device__ inline float rows_sum(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ inline float rows_max(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // ---- operand packing ----------------------------------------------------------------------------
 // GEMM input X[c][f] (c < 16 CT tokens, f < K features), bf16 path: [K/32][CT col tiles][hi, lo][64 lanes][8]
 // (CT = 2 for passes of up to 32 tokens, 32 for the passes of up to 512 tokens that ingest a prompt),
@@ -368,8 +383,7 @@ __device__ inline void epilogue(const GemmArgs& a, const DescVals& dv, int tile,
         const float pk[4] = {o.x * gn.x, o.y * gn.y, o.z * gn.z, o.w * gn.w};
         pack4<CT>(a.xb_out, c, n, pk);
         float ss = o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
-        ss += __shfl_xor(ss, 16, kWave);
-        ss += __shfl_xor(ss, 32, kWave);
+        ss = rows_sum(ss);
         if (g == 0) a.ss_out[tile * (16 * CT) + c] = ss;
     } else if constexpr (EPI == EPI_SWIGLU) {
         // weight rows are interleaved: tile row 2e = gate of feature 8 tile + e, tile row 2e + 1 = its up row
@@ -766,8 +780,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
         // wave order by whoever needs the scale
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            float sw = ss_mine[t] + __shfl_xor(ss_mine[t], 16, kWave);
-            sw = sw + __shfl_xor(sw, 32, kWave);
+            const float sw = rows_sum(ss_mine[t]);
             if (g == 0) ssp[wave][t * 16 + cc] = sw;
         }
     }
@@ -1066,8 +1079,7 @@ __global__ __launch_bounds__(64) void embed_pack(const uint16_t* embed, const Pa
     const float pk[4] = {v[0] * gn.x, v[1] * gn.y, v[2] * gn.z, v[3] * gn.w};
     pack4<CT>(xb, c, n, pk);
     float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-    ss += __shfl_xor(ss, 16, kWave);
-    ss += __shfl_xor(ss, 32, kWave);
+    ss = rows_sum(ss);
     if (g == 0) ss_out[tile * (16 * CT) + c] = ss;
 }
 
@@ -1108,8 +1120,7 @@ __device__ inline void attn_probs(const f32x4 (&S)[2], float msafe, u32x4& Ph, u
         Ph[2 * kt] = h0; Ph[2 * kt + 1] = h1;
         Pl[2 * kt] = l0; Pl[2 * kt + 1] = l1;
     }
-    l += __shfl_xor(l, 16, kWave);
-    l += __shfl_xor(l, 32, kWave);
+    l = rows_sum(l);
 }
 // (p_hi + p_lo)(v_hi + v_lo) without the lo * lo term, 16 queries x 16 JT head dims over 32 keys; the head dims' chains side
 // by side
@@ -1234,8 +1245,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma(const float* qkv, const Pass
                 if (kp > qpos) Sx[kt][r] = -INFINITY;
                 m = fmaxf(m, Sx[kt][r]);
             }
-        m = fmaxf(m, __shfl_xor(m, 16, kWave));
-        m = fmaxf(m, __shfl_xor(m, 32, kWave));
+        m = rows_max(m);
         const float msafe = m == -INFINITY ? 0.f : m;
         u32x4 Ph, Pl;
         attn_probs(Sx, msafe, Ph, Pl, l);
@@ -1351,12 +1361,13 @@ __global__ __launch_bounds__(256) void attn_combine_long(const float* part, cons
 
 // Attention of a prompt-ingestion pass in one sweep: a workgroup of four waves owns four consecutive 16-row query tiles of
 // one kv head, one per wave, and walks the key ranges from the first to the last one its queries see.  A range's K planes
-// (hi, lo), then its V planes, go through LDS for the four waves, asked for a whole range ahead;
+// (hi, lo), then its V planes, go through LDS for the four waves (K of the next range travels during P V, V during Q K^T);
 // every wave keeps its tile's running (M, Lsum, o) in registers and writes the o projection's operand itself, so no
 // partials go to memory and there is no merge kernel.  Within a range the arithmetic is that of attn_mfma: four groups of
 // 32 keys (its four waves), each from its own maximum, added in order; ranges are merged as attn_merge does: same bits.
 // With a workgroup per (kv head, range, four tiles) the draft's passes over a 3000-token prompt spent 59 us per layer here
-// and 30 us in the merge, waiting on loads and barriers per 16-row tile, against 10 us worth of MFMAs.
+// and 30 us in the merge, waiting on loads and barriers per 16-row tile; this takes 52 us (10 us worth of MFMAs and 19 us of
+// vector instructions a wave, one wave per SIMD, so little of that overlaps).
 // grid ceil(query tiles / 4) * KV; 128 KB of LDS at head dim 128 (one workgroup per CU).
 template <int HD>
 constexpr int kAttnWideLds = 8 * kPage * HD * 2;   // two pages x (K or V: hi, lo) each for K and V, bytes
@@ -1378,7 +1389,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qk
     const int tile = grp * 4 + wave, row0 = tile * 16;
     const int nsp = (pos0 + (min(R, grp * 64 + 64) - 1) / G) / kAttnSplit + 1;                        // ranges of the workgroup
     const int my_nsp = row0 < R ? (pos0 + (min(R, row0 + 16) - 1) / G) / kAttnSplit + 1 : 0;   // and of this wave's tile
-    u32x4 stk[NS], stv[NS];
+    u32x4 st[NS];
     auto load_half = [&](u32x4 (&st)[NS], int s, int half) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
@@ -1394,8 +1405,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qk
 #pragma unroll
             for (int i = 0; i < NS / 2; ++i) dst[p * 2 * PW + tid + i * 256] = st[p * (NS / 2) + i];
     };
-    load_half(stk, 0, 0);
-    load_half(stv, 0, 1);
+    load_half(st, 0, 0);
     // the tile's queries as B operand, scaled: lane (g, c) holds head dims 32 ks + 8 g .. + 8 of row c
     const int rho = row0 + cq;
     const float scale = attn_scale<HD>();
@@ -1426,10 +1436,10 @@ __global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qk
 #pragma unroll
         for (int r = 0; r < 4; ++r) out[r] = __shfl(v, 4 * g + r, kWave);
     };
-    put_half(stk, sK);
-    if (nsp > 1) load_half(stk, 1, 0);
+    put_half(st, sK);
     __syncthreads();
     for (int s = 0; s < nsp; ++s) {
+        load_half(st, s, 1);
         const int key0 = s * kAttnSplit;
         const bool live = s < my_nsp;
         f32x4 S[4][2];
@@ -1471,16 +1481,15 @@ __global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qk
                 for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) m = fmaxf(m, S[v][k2][r]);
-                m = fmaxf(m, __shfl_xor(m, 16, kWave));
-                mv[v] = fmaxf(m, __shfl_xor(m, 32, kWave));
+                mv[v] = rows_max(m);
                 Ms = fmaxf(Ms, mv[v]);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) fac[v] = mv[v] == -INFINITY ? 0.f : exp2_hw(mv[v] - Ms);
         }
-        put_half(stv, sV);
-        if (s + 1 < nsp) load_half(stv, s + 1, 1);
+        put_half(st, sV);
         __syncthreads();
+        if (s + 1 < nsp) load_half(st, s + 1, 0);
         if (live) {
             float Ls = 0.f;
             f32x4 os[JT];
@@ -1519,8 +1528,7 @@ u32x4 vh[JT], vl[JT];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) o[j][r] = merge_add(o[j][r], os[j][r], MergeFac{0.f, al[r], be[r]});
         }
-        if (s + 1 < nsp) put_half(stk, sK);   // everybody is past this range's K since the barrier above
-        if (s + 2 < nsp) load_half(stk, s + 2, 0);
+        if (s + 1 < nsp) put_half(st, sK);   // everybody is past this range's K since the barrier above
         __syncthreads();
     }
     float Lr[4];
