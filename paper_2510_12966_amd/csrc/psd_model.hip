@@ -814,8 +814,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
 //   - weight blocks go from memory straight into the registers of the one wave that uses them, three K steps ahead
 //     (they are stored in operand order, so nothing is gained by a detour through LDS);
 //   - the group's operand (hi and lo halves) goes through three LDS buffers: a step's blocks are asked for six steps
-//     ahead, written two steps ahead and read by all waves.  One barrier per step, and the first blocks of the next
-//     step are read before it, so a step does not begin with an LDS latency.
+//     ahead, written two steps ahead and read by all waves.  One barrier per step (per KB steps where a step is few MFMAs),
+//     and the first blocks of the next step are read before it, so a step does not begin with an LDS latency.
 // Bound: the matrix cores.  A loop of these MFMAs alone settles at 1.42-1.48 PFLOP/s on this part (a plain library
 // product of 8192^3 reaches 1.48); the draft's gate/up projection (16384 x 2048, 512 columns, hi + lo) runs at 1.11
 // PFLOP/s, 62 us.  The rest is the launch, the first loads and the epilogue (14 us of it, by extrapolating the K loop
@@ -841,16 +841,16 @@ __global__ __launch_bounds__(256) void panel_scale(const GemmArgs a, float* __re
     if (threadIdx.x < 16) rs_out[blockIdx.x * 16 + cc] = ss_scale<NW, 16>(a, ssp, cc);
 }
 
-template <int NW, int EPI, int RTW, int TCW>
+template <int NW, int EPI, int RTW, int TCW, int KB>
 __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int tiles, const int ncg, f32x4* __restrict__ part) {
     constexpr int CT = kWideCT;
     constexpr bool kSplit = kGrouped<EPI>;
     constexpr bool kScaled = (EPI == EPI_SWIGLU);             // the grouped epilogues are scaled in panel_finish
     constexpr int GC = 16 * TCW, GW = 2 * TCW * 64;           // columns, and operand words per K step, of a column group
-    constexpr int WV = 8, TH = 64 * WV, NB = GW / TH;                              // operand words a thread stages per K step
+    constexpr int WV = 8, TH = 64 * WV, NB = KB * GW / TH;                             // operand words a thread stages per KB steps
     constexpr int kBStep = CT * 128;
     __shared__ float s_rs[kScaled ? GC : 1];
-    __shared__ u32x4 sB[3][GW];                               // [column tile][hi, lo][lane]: one K step each
+    __shared__ u32x4 sB[3][KB * GW];                          // [K step][column tile][hi, lo][lane]
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, cc = lane & 15;
     // Workgroups go to the eight XCDs (one L2 each) round-robin in launch order.  The ncg column groups of a row
     // group take consecutive slots of one XCD, so they run side by side and its weights come from memory once.
@@ -868,36 +868,40 @@ __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int
     for (int r = 0; r < RTW; ++r) pa[r] = a.Wt + (size_t)min(tile0 + r, tiles - 1) * KS * 64;
     const u32x4* pb = a.XB + (size_t)cg * GW;
     const int k_last = min(max(k1 - 1, k0), KS - 1);   // loads past the range repeat its last step and are never used
-    u32x4 wa[4][RTW], sb[4][NB];
-    auto fetch_a1 = [&](int st, int ks, int r) {
-        wa[st][r] = load16_at(pa[r] + (size_t)min(ks, k_last) * 64, lane * 16);
+    // chunk q: the KB steps from k0 + KB q on
+    u32x4 wa[4][KB][RTW], sb[4][NB];
+    auto fetch_a1 = [&](int st, int q, int e, int r) { wa[st][e][r] = load16_at(pa[r] + (size_t)min(k0 + q * KB + e, k_last) * 64, lane * 16); };
+    auto fetch_b1 = [&](int st, int q, int i) {
+        const int e = i * TH / GW;   // GW is a multiple of the threads' words or the other way round: a word's step is uniform
+        sb[st][i] = load16_at(pb + (size_t)min(k0 + q * KB + e, k_last) * kBStep + (i * TH - e * GW), tid * 16);
     };
-    auto fetch_b1 = [&](int st, int ks, int i) { sb[st][i] = load16_at(pb + (size_t)min(ks, k_last) * kBStep + i * TH, tid * 16); };
-    auto fetch_a = [&](int st, int ks) {
+    auto fetch_a = [&](int st, int q) {
 #pragma unroll
-        for (int r = 0; r < RTW; ++r) fetch_a1(st, ks, r);
+        for (int e = 0; e < KB; ++e)
+#pragma unroll
+            for (int r = 0; r < RTW; ++r) fetch_a1(st, q, e, r);
     };
-    auto fetch_b = [&](int st, int ks) {
+    auto fetch_b = [&](int st, int q) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) fetch_b1(st, ks, i);
+        for (int i = 0; i < NB; ++i) fetch_b1(st, q, i);
     };
     auto put = [&](int st, int buf) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) sB[buf][tid + i * TH] = sb[st][i];
     };
-    // in the order of use: the operand of steps 0 and 1 first
-    fetch_b(0, k0);
-    fetch_b(1, k0 + 1);
-    fetch_a(0, k0);
-    fetch_b(2, k0 + 2);
-    fetch_a(1, k0 + 1);
-    fetch_b(3, k0 + 3);
-    fetch_a(2, k0 + 2);
+    // in the order of use: the operand of the first two chunks first
+    fetch_b(0, 0);
+    fetch_b(1, 1);
+    fetch_a(0, 0);
+    fetch_b(2, 2);
+    fetch_a(1, 1);
+    fetch_b(3, 3);
+    fetch_a(2, 2);
     if (kScaled && tid < GC) s_rs[tid] = a.rs_in[cg * GC + tid];
     put(0, 0);
     put(1, 1);
-    fetch_b(0, k0 + 4);
-    fetch_b(1, k0 + 5);
+    fetch_b(0, 4);
+    fetch_b(1, 5);
     f32x4 cur[RTW][TCW], tot[RTW][TCW];
     const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -908,33 +912,36 @@ __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int
     u32x4 bh = sB[0][lane], bl = sB[0][64 + lane];
     int buf = 0, buf1 = 1, buf2 = 2;
     int nb = k0;   // where the current range began or ends: the first step of every range folds the one before it
-    auto step = [&](int st, int ks) {
+    auto step = [&](int st, int q, int e) {
+        constexpr int kSlots = KB * TCW;   // the chunk's writes and loads are spread over its column tiles: a burst of loads
+                                           // would hold the wave up while the memory pipeline is full
 #pragma unroll
         for (int t = 0; t < TCW; ++t) {
-            // the step's writes and loads are spread over its column tiles: a burst of loads would hold the wave up
-            // while the memory pipeline is full
+            const int slot = e * TCW + t;
 #pragma unroll
-            for (int i = t; i < NB; i += TCW) {
+            for (int i = slot; i < NB; i += kSlots) {
                 sB[buf2][tid + i * TH] = sb[(st + 2) & 3][i];
-                fetch_b1((st + 2) & 3, ks + 6, i);
+                fetch_b1((st + 2) & 3, q + 6, i);
             }
 #pragma unroll
-            for (int r = 0; r < RTW; ++r)
-                if (t == (NB + r) % TCW) fetch_a1((st + 3) & 3, ks + 3, r);
-            const u32x4* nx = t + 1 < TCW ? &sB[buf][(t + 1) * 128] : &sB[buf1][0];
+            for (int x = 0; x < KB * RTW; ++x)
+                if (slot == (NB + x) % kSlots) fetch_a1((st + 3) & 3, q + 3, x / RTW, x % RTW);
+            const u32x4* nx = slot + 1 < kSlots ? &sB[buf][(slot + 1) * 128] : &sB[buf1][0];
             const u32x4 nh = nx[lane], nl = nx[64 + lane];
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int r = 0; r < RTW; ++r)
-                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[st][r]), __builtin_bit_cast(bf16x8, bh),
+                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[st][e][r]), __builtin_bit_cast(bf16x8, bh),
                                                                     cur[r][t], 0, 0, 0);
 #pragma unroll
             for (int r = 0; r < RTW; ++r)
-                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[st][r]), __builtin_bit_cast(bf16x8, bl),
+                cur[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wa[st][e][r]), __builtin_bit_cast(bf16x8, bl),
                                                                     cur[r][t], 0, 0, 0);
             bh = nh;
             bl = nl;
         }
+    };
+    auto next_chunk = [&]() {
         __syncthreads();
         const int b0 = buf;
         buf = buf1; buf1 = buf2; buf2 = b0;
@@ -950,12 +957,18 @@ __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int
             }
         do { ++v; nb = (int)(((long)KS * v) / NW); } while (nb <= ks);
     };
-    for (int ks = k0; ks < k1; ks += 4) {
+    for (int q0 = 0, ks = k0; ks < k1; q0 += 4) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (ks + u >= k1) break;
-            if (ks + u == nb) fold(ks + u);
-            step(u, ks + u);
+            if (ks >= k1) break;
+#pragma unroll
+            for (int e = 0; e < KB; ++e) {
+                if (KB > 1 && ks >= k1) break;   // a last chunk that is not full (nothing after it reads LDS)
+                if (ks == nb) fold(ks);
+                step(u, q0 + u, e);
+                ++ks;
+            }
+            next_chunk();
         }
     }
     const DescVals dv = load_desc(a.desc);
@@ -2174,22 +2187,26 @@ static int forward_f32(Model& M, int wmax, float* logits, Launch& L) {
 }
 
 // Projection of a prompt-ingestion pass.  NW: the K split of the narrow kernels.
-template <int NW, int EPI, int RTW, int TCW>
+template <int NW, int EPI, int RTW, int TCW, int KB>
 static void launch_panel_as(Launch& L, GemmArgs a, int tiles) {
     Model& M = L.M;
     const int ncg = L.wcls / (16 * TCW), units = (tiles + 8 * RTW - 1) / (8 * RTW) * (kGrouped<EPI> ? 4 : 1);
     a.rs_in = M.panel_rs;
     if constexpr (EPI == EPI_SWIGLU) panel_scale<NW><<<L.wcls / 16, 256, 0, L.s>>>(a, M.panel_rs);
-    gemm_panel<NW, EPI, RTW, TCW><<<(units + 7) / 8 * 8 * ncg, 512, 0, L.s>>>(a, tiles, ncg, (f32x4*)M.panel_part);
+    gemm_panel<NW, EPI, RTW, TCW, KB><<<(units + 7) / 8 * 8 * ncg, 512, 0, L.s>>>(a, tiles, ncg, (f32x4*)M.panel_part);
     if constexpr (kGrouped<EPI>) panel_finish<NW, EPI><<<dim3((tiles + 15) / 16, L.wcls / 16), 256, 0, L.s>>>(a, tiles, (const f32x4*)M.panel_part);
 }
 template <int NW, int EPI>
 static void launch_panel(Launch& L, const GemmArgs& a, int tiles) {
     // 256 x 128 outputs per workgroup move the fewest bytes per MFMA; smaller tiles where those would leave CUs idle
     const int full = (tiles + 15) / 16 * (kGrouped<EPI> ? 4 : 1) * (L.wcls / 128);
-    if (full >= 192) launch_panel_as<NW, EPI, 2, 8>(L, a, tiles);
-    else if (full >= 96) launch_panel_as<NW, EPI, 2, 4>(L, a, tiles);
-    else launch_panel_as<NW, EPI, 1, 4>(L, a, tiles);
+    // KB: a small tile's step is few MFMAs (64 x 64 outputs per SIMD: 128 cycles), so two of them share a barrier; where more
+    // smallest tiles than CUs are launched two workgroups share a CU instead, which the second step's registers would prevent
+    // (qualifier shape, 100 tokens: o + down 21.0 -> 18.6 us, gate/up 40.5 -> 36.8; q/k/v with 320 workgroups 19.6 -> 21.2)
+    if (full >= 192) launch_panel_as<NW, EPI, 2, 8, 1>(L, a, tiles);
+    else if (full >= 96) launch_panel_as<NW, EPI, 2, 4, 2>(L, a, tiles);
+    else if ((tiles + 7) / 8 * (kGrouped<EPI> ? 4 : 1) * (L.wcls / 64) <= 256) launch_panel_as<NW, EPI, 1, 4, 2>(L, a, tiles);
+    else launch_panel_as<NW, EPI, 1, 4, 1>(L, a, tiles);
 }
 
 // bf16 models: five or six launches per layer (q/k/v projection, attention, merge, o, gate/up, down)
