@@ -1330,51 +1330,67 @@ __global__ void attn_combine_bf16(const float* part, const PassDesc* desc, void*
 
 // The same merge for long contexts (more than eight key ranges): one workgroup per (token, head) brings the partials of
 // all its ranges into LDS with one round of loads (the thread-per-head-dim form above walks them in dependent rounds of
-// eight), works out every range's factors (one thread per range, from the maxima before it) and then sums in range
-// order: the arithmetic, hence the bits, of attn_merge.
+// eight), works out every range's factors (a lane per range, from the maximum before it by a scan over the lanes) and
+// then sums in range order: the arithmetic, hence the bits, of attn_merge.
+// Latency, at thousands of tokens of context: 5.9 -> 4.45 us on average over the three models' passes at 4.1 K (32 ranges; the
+// factors from a walk over all maxima before a range, single floats loaded with a division each: 5.9; the scan alone: 5.6).
 // grid (wmax, H), 256 threads, dynamic LDS: nsplit * (hd + 4) floats.
 template <int CT>
 __global__ __launch_bounds__(256) void attn_combine_long(const float* part, const PassDesc* desc, void* xb, int H, int hd, int nsp_cap) {
-    extern __shared__ float cmb[];
+    extern __shared__ __align__(16) float cmb[];
     const int c = blockIdx.x, h = blockIdx.y;
     if (c >= desc->w) return;
     // splits holding keys <= pos0 + c; never more than the launch covers (the LDS area is sized for those)
     const int nsp = min((desc->pos0 + c + kAttnSplit) / kAttnSplit, nsp_cap);
-    const int row = hd + 2;
+    const int row = hd + 2, hp = hd >> 1, nr = 256 / hp, tid = threadIdx.x, lane = tid & 63;
     const size_t stride = (size_t)kCols * H * row;
-    const float* p0 = part + ((size_t)c * H + h) * row;
-    // batches of 24 loads per thread, all of a batch in flight together (one batch covers 47 ranges at head dim 128)
-    constexpr int kBatch = 24;
-    for (int base = 0; base < nsp * row; base += kBatch * 256) {
-        float v[kBatch];
+    const float* p0 = part + ((size_t)c * H + h) * row;   // even: pairs of floats are aligned
+    float4* fac = reinterpret_cast<float4*>(cmb + nsp * hd);   // al, be, l be of every range
+    auto max_sum = [&](int sp) { return sp < nsp ? *reinterpret_cast<const float2*>(p0 + (size_t)sp * stride) : make_float2(-INFINITY, 0.f); };
+    float2 ml = make_float2(-INFINITY, 0.f);
+    if (tid < 64) ml = max_sum(lane);
+    // batches of 12 pairs per thread, all of a batch in flight together (one batch covers 48 ranges at head dim 128)
+    constexpr int kBatch = 12;
+    const int sub = tid / hp, pair = tid - sub * hp;
+    for (int base = 0; base < nsp; base += kBatch * nr) {
+        float2 v[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const int idx = base + u * 256 + (int)threadIdx.x;
-            const int sp = idx / row, i = idx - sp * row;
-            v[u] = idx < nsp * row ? p0[(size_t)sp * stride + i] : 0.f;
+            const int sp = base + u * nr + sub;
+            v[u] = sub < nr && sp < nsp ? *reinterpret_cast<const float2*>(p0 + (size_t)sp * stride + 2 + 2 * pair) : make_float2(0.f, 0.f);
         }
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const int idx = base + u * 256 + (int)threadIdx.x;
-            if (idx < nsp * row) cmb[idx] = v[u];
+            const int sp = base + u * nr + sub;
+            if (sub < nr && sp < nsp) *reinterpret_cast<float2*>(cmb + sp * hd + 2 * pair) = v[u];
+        }
+    }
+    if (tid < 64) {   // the maximum before every range: an inclusive scan over the lanes, shifted by one
+        float carry = -INFINITY;
+        for (int s0 = 0; s0 < nsp; s0 += 64) {
+            if (s0) ml = max_sum(s0 + lane);
+            float run = ml.x;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const float up = __shfl_up(run, d);
+                if (lane >= d) run = fmaxf(run, up);
+            }
+            run = fmaxf(run, carry);
+            const float up = __shfl_up(run, 1);
+            const MergeFac f = merge_fac(lane ? up : carry, ml.x);
+            if (s0 + lane < nsp) fac[s0 + lane] = make_float4(f.al, f.be, ml.y * f.be, 0.f);
+            carry = __shfl(run, 63);
         }
     }
     __syncthreads();
-    float2* fac = reinterpret_cast<float2*>(cmb + ((nsp * row + 1) & ~1));
-    for (int sp = threadIdx.x; sp < nsp; sp += 256) {
-        float M = -INFINITY;
-        for (int i = 0; i < sp; ++i) M = fmaxf(M, cmb[i * row]);
-        const MergeFac f = merge_fac(M, cmb[sp * row]);
-        fac[sp] = make_float2(f.al, f.be);
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < hd) {
-        const int i = threadIdx.x;
+    if (tid < hd) {
+        const int i = tid;
         float Lsum = 0.f, o = 0.f;
+#pragma unroll 8
         for (int sp = 0; sp < nsp; ++sp) {
-            const MergeFac f{0.f, fac[sp].x, fac[sp].y};
-            Lsum = merge_add(Lsum, cmb[sp * row + 1], f);
-            o = merge_add(o, cmb[sp * row + 2 + i], f);
+            const float4 f = fac[sp];
+            Lsum = fmaf(Lsum, f.x, f.z);                                          // merge_add
+            o = merge_add(o, cmb[sp * hd + i], MergeFac{0.f, f.x, f.y});
         }
         pack_store<true, CT>(xb, H * hd, c, h * hd + i, o / Lsum);
     }

@@ -201,6 +201,26 @@ def test_bf16_wide_attention_is_bit_exact(which, n):
     ref = oracle.Model(SWEEP[which], blobs[which], synth.DTYPE_BF16, 10000.0, 1408).forward(toks, 0)[n:]
     assert np.abs(out[0] - ref).max() <= TOL_BF16
 
+# more than 64 key ranges: narrow passes then merge their partials in two turns of a wave's lanes, wide ones merge range by range
+MANY = (ModelShape(2, 1024, 32, 8, 512, 200), ModelShape(2, 1024, 16, 16, 512, 200), ModelShape(2, 2048, 16, 16, 512, 200))
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+def test_bf16_merge_of_many_key_ranges_is_bit_exact(which):
+    n, m = 8000, 8512
+    blobs = [synth.target_weights(s, 80 + i, synth.DTYPE_BF16, sigma=0.03) for i, s in enumerate(MANY)]
+    ctx = _ctx(MANY, blobs, synth.DTYPE_BF16, 10000.0, 8640)
+    toks = synth.tokens(15, 0, m + 3, 200)
+    for pos in range(0, n, 500):
+        ctx.forward(which, toks[pos:pos + 500], pos, want_logits=False)
+    out = []
+    for step in (512, 32):
+        for pos in range(n, m, step):
+            ctx.forward(which, toks[pos:pos + step], pos, want_logits=False)
+        out.append(ctx.forward(which, toks[m:m + 3], m))
+    ctx.close()
+    assert np.array_equal(out[0], out[1])
+
 
 def test_fp32_attention_routes_agree():
     # up to eight key ranges one launch attends and merges, beyond that two do: the same arithmetic, so a token at the
