@@ -574,11 +574,14 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     c->rs_ws = take(row_stats_workspace_bytes(kMaxW, V));
     c->rs_acc = (double*)take(9 * sizeof(double));
     if (!ok) { set_error(c->err, "psd_create: device pool too small"); return fail(PSD_ENOMEM); }
-    CK(hipHostMalloc((void**)&c->stage, (size_t)kStageSlots * kStageSlotBytes, hipHostMallocDefault));
-    CK(hipHostMalloc((void**)&c->res, sizeof(RoundResult), hipHostMallocDefault));
-    c->res->seq = 0;
+    // one pinned allocation: the staging ring, then the round's result
+    constexpr size_t kRingBytes = (size_t)kStageSlots * kStageSlotBytes;
+    static_assert(kRingBytes % 128 == 0, "the result starts on a cache line of its own");
+    CK(hipHostMalloc((void**)&c->stage, kRingBytes + sizeof(RoundResult), hipHostMallocDefault));
     CK(hipHostGetDevicePointer((void**)&c->stage_dev, c->stage, 0));
-    CK(hipHostGetDevicePointer((void**)&c->res_dev, c->res, 0));
+    c->res = (RoundResult*)(c->stage + kRingBytes);
+    c->res_dev = (RoundResult*)(c->stage_dev + kRingBytes);
+    c->res->seq = 0;
     for (auto& e : c->ev) CK(hipEventCreate(&e));
     for (auto& st : c->aux) CK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
     for (auto& e : c->aux_ready) CK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -600,7 +603,6 @@ extern "C" void psd_destroy(psd_ctx* c) {
     for (auto& e : c->aux_ready) if (e) (void)hipEventDestroy(e);
     for (auto& e : c->aux_done) if (e) (void)hipEventDestroy(e);
     if (c->stage) (void)hipHostFree(c->stage);
-    if (c->res) (void)hipHostFree(c->res);
     for (auto& M : c->M) if (M.panel_mem) (void)hipFree(M.panel_mem);
     if (c->pool_mem) (void)hipFree(c->pool_mem);
     if (c->stream) (void)hipStreamDestroy(c->stream);
