@@ -120,8 +120,7 @@ typedef struct {
 } psd_stats;
 
 /* Builds a context: one device pool holding the three models' re-tiled weights,
- * their paged KV caches and their scratch (what prompt passes of more than 32 tokens
- * need besides is allocated beside the pool).  The three models must share `vocab`
+ * their paged KV caches and all scratch.  The three models must share `vocab`
  * (the method compares their distributions entry by entry).
  * Errors: PSD_EINVAL (null pointer, unsupported shape, k1/k2/threshold/temperature out of range,
  * vocab mismatch, wrong weights_bytes), PSD_ENOMEM (pool_bytes too small), PSD_EHIP. */

@@ -603,7 +603,6 @@ extern "C" void psd_destroy(psd_ctx* c) {
     for (auto& e : c->aux_ready) if (e) (void)hipEventDestroy(e);
     for (auto& e : c->aux_done) if (e) (void)hipEventDestroy(e);
     if (c->stage) (void)hipHostFree(c->stage);
-    for (auto& M : c->M) if (M.panel_mem) (void)hipFree(M.panel_mem);
     if (c->pool_mem) (void)hipFree(c->pool_mem);
     if (c->stream) (void)hipStreamDestroy(c->stream);
     delete c;

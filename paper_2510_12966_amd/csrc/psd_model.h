@@ -73,6 +73,11 @@ struct Pool {
     }
 };
 
+struct PanelScratch {   // memory of other buffers that a projection may use while they hold nothing
+    void* mem = nullptr;
+    size_t bytes = 0;
+};
+
 struct KernelAcc {  // profiling row
     char name[48];
     int64_t launches = 0;
@@ -121,12 +126,11 @@ struct Model {
     void* xbw = nullptr;      // the same three for prompt-ingestion passes: operands with 32 column tiles, [d/16][512] partials
     void* xbw2 = nullptr;
     float* ssw = nullptr;
-    void* panel_mem = nullptr;   // wide passes: an allocation of its own, freed with the context, holding
-    float* panel_rs = nullptr;   //   [512] rms scale per column
-    void* panel_part = nullptr;  //   sums of the K quarters of a projection
-    float* qkv = nullptr;     // [512][nqkv]
-    float* gu = nullptr;      // [32][2F]
     float* attn_part = nullptr;  // [nsplit_max][512][H][hd + 2]
+    float* qkv = nullptr;     // [512][nqkv]
+    PanelScratch panel_qkv, panel_res;   // wide passes, sums of the K quarters of the q/k/v, and of the o and down, projections
+    float* panel_rs = nullptr;   // wide passes: [512] rms scale per column, for gate/up (in attn_part)
+    float* gu = nullptr;      // [32][2F]
     PassDesc* desc = nullptr;
     // host mirror
     int len = 0;  // valid KV rows

@@ -826,7 +826,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
 // the narrow kernels'.
 // EPI_QKV and EPI_RESID have too few row tiles to fill the device: K is cut into the four groups of ranges that the
 // narrow kernels add up separately (group_sum), a workgroup does one of them and leaves its sums in `part`
-// ([group][row tile][column tile][64 lanes], fp32), and panel_finish adds the groups and runs the epilogue (target's
+// ([group][row tile][column tile of the launch][64 lanes], fp32), and panel_finish adds the groups and runs the epilogue (target's
 // down projection and o projection at 512 columns: 174 us on average as one launch, 74 + 12 us in two).
 // rms scale of every column of a wide pass, once for all workgroups of the gate/up projection (each of them would
 // otherwise read 128 KB of partial sums for its own columns: 16 us of a 95 us launch on the draft's shape).
@@ -842,7 +842,7 @@ __global__ __launch_bounds__(256) void panel_scale(const GemmArgs a, float* __re
 }
 
 template <int NW, int EPI, int RTW, int TCW, int KB>
-__global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int tiles, const int ncg, f32x4* __restrict__ part) {
+__global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int tiles, const int ncg, const int cg0, f32x4* __restrict__ part) {
     constexpr int CT = kWideCT;
     constexpr bool kSplit = kGrouped<EPI>;
     constexpr bool kScaled = (EPI == EPI_SWIGLU);             // the grouped epilogues are scaled in panel_finish
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int
     const u32x4* pa[RTW];
 #pragma unroll
     for (int r = 0; r < RTW; ++r) pa[r] = a.Wt + (size_t)min(tile0 + r, tiles - 1) * KS * 64;
-    const u32x4* pb = a.XB + (size_t)cg * GW;
+    const u32x4* pb = a.XB + (size_t)(cg0 + cg) * GW;
     const int k_last = min(max(k1 - 1, k0), KS - 1);   // loads past the range repeat its last step and are never used
     // chunk q: the KB steps from k0 + KB q on
     u32x4 wa[4][KB][RTW], sb[4][NB];
@@ -897,7 +897,7 @@ __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int
     fetch_a(1, 1);
     fetch_b(3, 3);
     fetch_a(2, 2);
-    if (kScaled && tid < GC) s_rs[tid] = a.rs_in[cg * GC + tid];
+    if (kScaled && tid < GC) s_rs[tid] = a.rs_in[(cg0 + cg) * GC + tid];
     put(0, 0);
     put(1, 1);
     fetch_b(0, 4);
@@ -974,7 +974,7 @@ __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int
     const DescVals dv = load_desc(a.desc);
 #pragma unroll
     for (int t = 0; t < TCW; ++t) {
-        const int c = cg * GC + t * 16 + cc;
+        const int c = (cg0 + cg) * GC + t * 16 + cc;
         const float rs = kScaled ? s_rs[kScaled ? t * 16 + cc : 0] : 1.f;
 #pragma unroll
         for (int r = 0; r < RTW; ++r) {
@@ -991,16 +991,16 @@ __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int
 }
 
 // Second half of a grouped projection of a wide pass: adds the four groups' sums in order and runs the epilogue.
-// grid (row tiles / 8, column tiles), 256 threads: a wave finishes two row tiles of one column tile.  Latency: everything
+// grid (row tiles / 8, column tiles of the gemm_panel launch, the first of which is ct0), 256 threads: a wave finishes two row tiles of one column tile.  Latency: everything
 // it reads is asked for at once, the epilogue's inputs beside the partial sums (512 columns of the draft's shape: q/k/v 12.5 ->
 // 10.5 us, o and down 7.2 -> 6.4; 100 columns of the qualifier's: 10.0 -> 8.3, 5.6 -> 4.8).  Four row tiles per wave: 11.2 /
 // 6.4 and 9.4 / 5.0, one: 10.6 / 6.3 and 8.2 / 4.9.
 template <int NW, int EPI>
-__global__ __launch_bounds__(256) void panel_finish(const GemmArgs a, const int tiles, const f32x4* __restrict__ part) {
+__global__ __launch_bounds__(256) void panel_finish(const GemmArgs a, const int tiles, const int ct0, const f32x4* __restrict__ part) {
     constexpr int CT = kWideCT;
     __shared__ float ssp[4 * NW][16];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4, cc = lane & 15;
-    const int ct = blockIdx.y, nct = gridDim.y, c = ct * 16 + cc;
+    const int ct = blockIdx.y, nct = gridDim.y, c = (ct0 + ct) * 16 + cc;
     const int tile0 = blockIdx.x * 8 + wave * 2;
     f32x4 p[2][4];
 #pragma unroll
@@ -1955,12 +1955,23 @@ static int model_carve(Model& M, Pool& pool) {
         M.xb2 = take(kmax * 128);
         M.ss = (float*)take((size_t)(M.d / 16) * 32 * sizeof(float));
         M.xbw = take(kmax * 4 * kCols);
-        M.xbw2 = take(kmax * 4 * kCols);
         M.ssw = (float*)take((size_t)(M.d / 16) * kCols * sizeof(float));
+        M.xbw2 = take(kmax * 4 * kCols);
     }
-    M.qkv = (float*)take((size_t)kCols * M.nqkv * sizeof(float));
-    M.gu = (float*)take((size_t)kMaxW * 2 * M.F * sizeof(float));
+    // A wide pass's q/k/v projection finds xbw2 and attn_part free (the attention that writes them comes next), its o and down
+    // projections attn_part and qkv (the attention that read them is done): the sums of their K quarters lie there, which is
+    // why the three follow each other.  gemm_panel may leave any bits in operand columns that the pass does not have; every
+    // column of a matrix product is on its own, and no kernel stores those.
+    const size_t xbw2_end = pool.used;
     M.attn_part = (float*)take((size_t)M.nsplit_max * kCols * M.H * (M.hd + 2) * sizeof(float));
+    const size_t part_end = pool.used, part_bytes = (size_t)M.nsplit_max * kCols * M.H * (M.hd + 2) * sizeof(float);
+    M.qkv = (float*)take((size_t)kCols * M.nqkv * sizeof(float));
+    if (M.dtype == PSD_BF16) {
+        M.panel_qkv = PanelScratch{M.xbw2, part_end - (xbw2_end - kmax * 4 * kCols)};
+        M.panel_res = PanelScratch{M.attn_part, pool.used - (part_end - part_bytes)};
+        M.panel_rs = M.attn_part;
+    }
+    M.gu = (float*)take((size_t)kMaxW * 2 * M.F * sizeof(float));
     M.desc = (PassDesc*)take(sizeof(PassDesc));
     return ok ? PSD_OK : PSD_ENOMEM;
 }
@@ -2081,12 +2092,6 @@ int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, 
         PSD_HIP(hipMemsetAsync(M.xbw, 0, kmax * 4 * kCols, stream), err);
         PSD_HIP(hipMemsetAsync(M.xbw2, 0, kmax * 4 * kCols, stream), err);
         PSD_HIP(hipMemsetAsync(M.ssw, 0, (size_t)(M.d / 16) * kCols * sizeof(float), stream), err);
-    }
-    if (bf) {   // wide passes: the columns' rms scales, then the sums of the four K quarters of a grouped projection
-        const size_t rs_bytes = kCols * sizeof(float);
-        PSD_HIP(hipMalloc(&M.panel_mem, rs_bytes + (size_t)4 * (round16(std::max(M.nqkv, M.d)) / 16) * (M.ingest_max / 16) * 64 * sizeof(f32x4)), err);
-        M.panel_rs = (float*)M.panel_mem;
-        M.panel_part = (char*)M.panel_mem + rs_bytes;
     }
     // page bookkeeping: every logical block unmapped, free list in (optionally scrambled) order
     M.h_page_table.assign(M.n_pages, -1);
@@ -2210,15 +2215,30 @@ static int forward_f32(Model& M, int wmax, float* logits, Launch& L) {
     return PSD_OK;
 }
 
+// bytes of the four K quarters' sums of one group of tcw column tiles
+static size_t panel_group_bytes(int tiles, int tcw) { return (size_t)4 * tiles * tcw * 64 * sizeof(f32x4); }
+
 // Projection of a prompt-ingestion pass.  NW: the K split of the narrow kernels.
 template <int NW, int EPI, int RTW, int TCW, int KB>
 static void launch_panel_as(Launch& L, GemmArgs a, int tiles) {
     Model& M = L.M;
     const int ncg = L.wcls / (16 * TCW), units = (tiles + 8 * RTW - 1) / (8 * RTW) * (kGrouped<EPI> ? 4 : 1);
-    a.rs_in = M.panel_rs;
-    if constexpr (EPI == EPI_SWIGLU) panel_scale<NW><<<L.wcls / 16, 256, 0, L.s>>>(a, M.panel_rs);
-    gemm_panel<NW, EPI, RTW, TCW, KB><<<(units + 7) / 8 * 8 * ncg, 512, 0, L.s>>>(a, tiles, ncg, (f32x4*)M.panel_part);
-    if constexpr (kGrouped<EPI>) panel_finish<NW, EPI><<<dim3((tiles + 7) / 8, L.wcls / 16), 256, 0, L.s>>>(a, tiles, (const f32x4*)M.panel_part);
+    if constexpr (kGrouped<EPI>) {
+        // as many column groups per launch as the scratch has room for: all of them unless the cache is short and the model
+        // has as many kv heads as heads
+        const PanelScratch& sc = EPI == EPI_QKV ? M.panel_qkv : M.panel_res;
+        const int room = (int)std::min((size_t)ncg, sc.bytes / panel_group_bytes(tiles, TCW)), turns = (ncg + room - 1) / room;
+        f32x4* part = (f32x4*)sc.mem;
+        for (int cg0 = 0, n = (ncg + turns - 1) / turns; cg0 < ncg; cg0 += n) {
+            n = std::min(n, ncg - cg0);
+            gemm_panel<NW, EPI, RTW, TCW, KB><<<(units + 7) / 8 * 8 * n, 512, 0, L.s>>>(a, tiles, n, cg0, part);
+            panel_finish<NW, EPI><<<dim3((tiles + 7) / 8, n * TCW), 256, 0, L.s>>>(a, tiles, cg0 * TCW, part);
+        }
+    } else {
+        a.rs_in = M.panel_rs;
+        panel_scale<NW><<<L.wcls / 16, 256, 0, L.s>>>(a, M.panel_rs);
+        gemm_panel<NW, EPI, RTW, TCW, KB><<<(units + 7) / 8 * 8 * ncg, 512, 0, L.s>>>(a, tiles, ncg, 0, nullptr);
+    }
 }
 template <int NW, int EPI>
 static void launch_panel(Launch& L, const GemmArgs& a, int tiles) {
@@ -2227,7 +2247,10 @@ static void launch_panel(Launch& L, const GemmArgs& a, int tiles) {
     // KB: a small tile's step is few MFMAs (64 x 64 outputs per SIMD: 128 cycles), so two of them share a barrier; where more
     // smallest tiles than CUs are launched two workgroups share a CU instead, which the second step's registers would prevent
     // (qualifier shape, 100 tokens: o + down 21.0 -> 18.6 us, gate/up 40.5 -> 36.8; q/k/v with 320 workgroups 19.6 -> 21.2)
-    if (full >= 192) launch_panel_as<NW, EPI, 2, 8, 1>(L, a, tiles);
+    // The scratch always has room for one group of 64 columns: q/k/v, 1024 nqkv <= 3072 d bytes of 2048 (max(d, F) +
+    // nsplit_max (d + 2 H)); o and down, 1024 d of 2048 (nsplit_max (d + 2 H) + nqkv).
+    const size_t scratch = EPI == EPI_QKV ? L.M.panel_qkv.bytes : EPI == EPI_RESID ? L.M.panel_res.bytes : SIZE_MAX;
+    if (full >= 192 && panel_group_bytes(tiles, 8) <= scratch) launch_panel_as<NW, EPI, 2, 8, 1>(L, a, tiles);
     else if (full >= 96) launch_panel_as<NW, EPI, 2, 4, 2>(L, a, tiles);
     else if ((tiles + 7) / 8 * (kGrouped<EPI> ? 4 : 1) * (L.wcls / 64) <= 256) launch_panel_as<NW, EPI, 1, 4, 2>(L, a, tiles);
     else launch_panel_as<NW, EPI, 1, 4, 1>(L, a, tiles);

@@ -178,6 +178,31 @@ def test_bf16_wide_projection_tiles_are_bit_exact(which, n):
     assert np.abs(out[0] - ref).max() <= TOL_BF16
 
 
+# as many kv heads as heads and a short cache: the sums of the q/k/v projection's K quarters find room for some of the pass's
+# column groups at a time only: 2 + 1 groups of 128 columns, 3 + 3 of 64, and 64 columns where 128 would fill the device
+ROOM = ((ModelShape(1, 1408, 11, 11, 608, 1000), 576, 380), (ModelShape(1, 960, 15, 15, 2848, 1000), 448, 380),
+        (ModelShape(1, 4096, 32, 32, 64, 1000), 128, 121))
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+def test_bf16_wide_projections_in_several_launches_are_bit_exact(which):
+    shape, max_seq, n = ROOM[which]
+    blob = synth.target_weights(shape, 65, synth.DTYPE_BF16, sigma=0.03)
+    stub = ModelShape(1, 64, 2, 1, 64, 1000)
+    small = synth.target_weights(stub, 66, synth.DTYPE_BF16, sigma=0.03)
+    ctx = _ctx((stub, stub, shape), (small, small, blob), synth.DTYPE_BF16, 10000.0, max_seq, k1=1, k2=1)
+    toks = synth.tokens(14, 0, n + 3, 1000)
+    out = []
+    for step in (512 if n > 128 else 128, 32):
+        for pos in range(0, n, step):
+            ctx.forward(2, toks[pos:min(pos + step, n)], pos, want_logits=False)
+        out.append(ctx.forward(2, toks[n:n + 3], n))
+    ctx.close()
+    assert np.array_equal(out[0], out[1])
+    ref = oracle.Model(shape, blob, synth.DTYPE_BF16, 10000.0, max_seq).forward(toks, 0)[n:]
+    assert np.abs(out[0] - ref).max() <= TOL_BF16
+
+
 # head dims 32 / 64 / 128 with query groups of 4, 3 and 1: the first has enough query tiles for the one-sweep attention at any
 # context, the others change over to a workgroup per key range beyond eight ranges
 SWEEP = (ModelShape(1, 1024, 32, 8, 512, 200), ModelShape(1, 384, 6, 2, 256, 200), ModelShape(1, 512, 4, 4, 512, 200))

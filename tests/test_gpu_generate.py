@@ -195,6 +195,37 @@ def test_create_with_a_pool_too_small_is_enomem(tiny_stack):
     ctx.close()
 
 
+def test_a_context_takes_no_device_memory_beside_its_pool():
+    # also after the widest passes: what they need beyond the models has to lie in the pool that the caller was told of
+    import ctypes as C
+    from paper_2510_12966_amd import binding as b
+    from paper_2510_12966_amd.synth import ModelShape
+
+    def free_bytes():
+        free, total = C.c_size_t(), C.c_size_t()
+        assert b.lib().hipMemGetInfo(C.byref(free), C.byref(total)) == 0   # of the runtime that the library itself uses
+        return free.value
+
+    def beside(shape, w):
+        """Device bytes that a context of three such models holds beyond its pool after passes of w tokens."""
+        blob = synth.target_weights(shape, 5, synth.DTYPE_BF16)
+        descs = [_desc(shape, blob, synth.DTYPE_BF16, 10000.0)] * 3
+        cd = [d.c() for d in descs]
+        need = b.lib().psd_pool_bytes_needed(C.byref(cd[0]), C.byref(cd[1]), C.byref(cd[2]), C.byref(b._Params(0.3, 0.2, 1.0, 4, 8, 640, 0, 0, 0)))
+        before = free_bytes()
+        ctx = psd.Context(*descs, 0.3, 0.2, 4, 8, 640, pool_bytes=need)
+        for which in range(3):
+            ctx.forward(which, synth.tokens(5, 0, w, 64), 0, want_logits=False)
+        taken = before - free_bytes()
+        ctx.close()
+        return taken - need
+
+    small, big = ModelShape(1, 64, 2, 1, 64, 64), ModelShape(1, 1024, 8, 8, 1408, 64)
+    beside(small, 64)   # the process's first context also loads the kernels
+    # what the runtime gives every context's streams is the same for both; it hands memory out in pieces of 2 MiB
+    assert beside(big, 512) <= beside(small, 64) + (4 << 20)
+
+
 def test_paper_shapes_sampled_parity():
     """Full-size models (1B / 3B / 8B shapes, vocabulary 128256) in the launch configuration bench.py times
     (graph replay): every ACCEPT and every draft sample of a short run is replayed through the oracle on the GPU's
