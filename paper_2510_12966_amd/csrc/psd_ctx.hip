@@ -574,10 +574,12 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     c->rs_ws = take(row_stats_workspace_bytes(kMaxW, V));
     c->rs_acc = (double*)take(9 * sizeof(double));
     if (!ok) { set_error(c->err, "psd_create: device pool too small"); return fail(PSD_ENOMEM); }
-    // one pinned allocation: the staging ring, then the round's result
+    // One pinned allocation: the staging ring, then the round's result.  Coherent by request: kernels read ring slots that the
+    // host has rewritten, and the host polls a result that a running kernel writes; without the flag that rests on the
+    // process's HIP_HOST_COHERENT.
     constexpr size_t kRingBytes = (size_t)kStageSlots * kStageSlotBytes;
     static_assert(kRingBytes % 128 == 0, "the result starts on a cache line of its own");
-    CK(hipHostMalloc((void**)&c->stage, kRingBytes + sizeof(RoundResult), hipHostMallocDefault));
+    CK(hipHostMalloc((void**)&c->stage, kRingBytes + sizeof(RoundResult), hipHostMallocCoherent | hipHostMallocMapped));
     CK(hipHostGetDevicePointer((void**)&c->stage_dev, c->stage, 0));
     c->res = (RoundResult*)(c->stage + kRingBytes);
     c->res_dev = (RoundResult*)(c->stage_dev + kRingBytes);

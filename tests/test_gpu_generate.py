@@ -195,6 +195,16 @@ def test_create_with_a_pool_too_small_is_enomem(tiny_stack):
     ctx.close()
 
 
+def test_rounds_do_not_rest_on_the_default_coherence_of_pinned_memory():
+    # the tiny stack's generation against the oracle, in a process whose pinned memory is not coherent unless asked for
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    subprocess.run([sys.executable, "-c", "import __graft_entry__ as g; g.smoke()"], cwd=root, timeout=100, check=True,
+                   env=dict(os.environ, HIP_HOST_COHERENT="0"))
+
+
 def test_a_context_takes_no_device_memory_beside_its_pool():
     # also after the widest passes: what they need beyond the models has to lie in the pool that the caller was told of
     import ctypes as C
