@@ -141,8 +141,12 @@ struct AcceptWs {  // carved out of the caller's workspace
     RacePart* race;      // [B][nch]
     KeyIdx* top;         // [B*(k+1)][nch] per-chunk maximum logit of the verifier rows (assisted and greedy stages)
     uint32_t* expired;   // [1] set when a bounded wait ran out
-    uint32_t* raced;     // [B] race workgroups that are done (in the space of `top`, which the stages that race this way do not use)
+    uint32_t* raced;     // [B][raced_step] race workgroups that are done (in the space of `top`, which the stages that race this way do not use)
 };
+// Words between the counters of two trials: a cache line where a trial's share of `top`, (k + 1) nch entries of two words, is that
+// long.  An atomic waits for the others on its line (side by side: 16 trials of k = 3 at V 128256, 1008 workgroups, 36.7 us a
+// call against 28.9).
+__host__ __device__ inline int raced_step(int k, int nch) { return 2 * (k + 1) * nch < 32 ? 2 * (k + 1) * nch : 32; }
 
 __device__ inline void st_agent64(void* p, float lo, float hi) {
     __hip_atomic_store(reinterpret_cast<unsigned long long*>(p),
@@ -219,14 +223,16 @@ __device__ inline bool row_stats(const RowPart* parts, int nsl, unsigned long lo
     return true;
 }
 
-__global__ void accept_clear(AcceptWs w, size_t n_parts, size_t n_trials) {
+// the arguments that every thread needs lie together: one trip for them (a stage of one trial: 18.2 us against 18.7 with the
+// workspace struct and more arguments behind it)
+__global__ void accept_clear(RowPart* part, float* jsd, uint32_t* expired, uint32_t* raced, size_t n_parts, uint32_t n_trials, uint32_t step) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n_parts) {
-        w.part[i] = RowPart{__uint_as_float(kUnwritten), 0.f, __uint_as_float(kUnwritten), 0.f};
-        w.jsd[i] = __uint_as_float(kUnwritten);
+        part[i] = RowPart{__uint_as_float(kUnwritten), 0.f, __uint_as_float(kUnwritten), 0.f};
+        jsd[i] = __uint_as_float(kUnwritten);
     }
-    if (i < n_trials) w.raced[i] = 0u;
-    if (i == 0) *w.expired = 0u;
+    if (i < n_trials) raced[i * step] = 0u;
+    if (i == 0) *expired = 0u;
 }
 
 enum { SWEEP_ONE_LAUNCH = 0, SWEEP_PARTIALS = 1, SWEEP_DIVERGENCE = 2 };
@@ -641,7 +647,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, Accept
         if (PICK) {
             // counted once the stores have been acknowledged: who counts last finds every chunk's result
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            s_last = __hip_atomic_fetch_add(w.raced + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(s.nch - 1);
+            s_last = __hip_atomic_fetch_add(w.raced + b * raced_step(s.k, s.nch), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(s.nch - 1);
         }
     }
     if (PICK) {
@@ -720,7 +726,7 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
     // a row's workgroups may wait for each other while there are few enough of them to be resident together
     const bool one_launch = pairs > 0 && g_accept_path.load() != 1 && kSweepWaves * nsw <= kSweepMaxSlots &&
                             (long long)pairs * nsw + n_trials <= 0x7fffffffLL;
-    accept_clear<<<(unsigned)((n_clear + 256) / 256), 256, 0, stream>>>(w, n_parts, n_trials);
+    accept_clear<<<(unsigned)((n_clear + 256) / 256), 256, 0, stream>>>(w.part, w.jsd, w.expired, w.raced, n_parts, (uint32_t)n_trials, (uint32_t)raced_step(k, nch));
     const int n_items = pairs * nsw;
     const bool vec = (vocab & 3) == 0;  // rows are then 16-byte aligned and hold whole quads
     if (one_launch) {
@@ -737,7 +743,8 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
         accept_decide<<<n_trials, 1024, 0, stream>>>(s, w, da);
     }
     // The last workgroup of a trial's race picks where they are few: every one of them pays an atomic's round trip for it, which
-    // a big launch notices (48 trials: 126 us instead of 107) and a launch of 63 workgroups does not (one launch less: 2 us)
+    // a launch of thousands notices (48 trials of 63 workgroups: 126 us instead of 107, with the counters side by side) and up to
+    // 1024 do not (one launch less: 63 workgroups 16.8 us against 17.4, 252 18.8 / 19.7, 1008 29.0 / 30.0, 768 of 256 trials 23.8 / 25.1)
     if ((long long)nch * n_trials <= 1024) {
         accept_race<true><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0, n_accepted_out, next_token_out);
     } else {

@@ -174,11 +174,11 @@ def test_one_launch_and_two_launch_sweeps_agree_bit_for_bit(V, k, B):
 
 
 @pytest.mark.parametrize("B,k,V", [(1, 1, 1), (1, 32, 5120), (3, 32, 5121), (16, 2, 128256), (17, 2, 128256), (2, 2, 327680),
-                                   (2, 1, 327681), (1030, 1, 33), (2, 0, 4097)])
+                                   (2, 1, 327681), (1030, 1, 33), (2, 0, 4097), (1024, 1, 33), (64, 0, 2000), (340, 2, 5000)])
 def test_deciding_and_picking_workgroups_agree_with_their_own_launches(B, k, V):
     # the decision inside the one-launch sweep against the launch behind the two-launch one: one slot, 256 slots (all the wait
     # covers), one vocabulary entry more (two launches on both paths), k = 0; the pick by the race's last workgroup (1008
-    # workgroups) and as a launch (1071); judged, rejected and bonus rows
+    # workgroups) and as a launch (1071), trials' counters 2, 4 and 32 words apart; judged, rejected and bonus rows
     stages = [_stage_inputs(23, b % 4, max(k, 1), V, 0.9, 2) for b in range(min(B, 4))]
     P = [stages[b % len(stages)][0][:k + 1] for b in range(B)]
     Q = [stages[b % len(stages)][1][:k] for b in range(B)]
