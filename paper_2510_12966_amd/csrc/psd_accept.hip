@@ -8,15 +8,15 @@
 //                  registers, publishes the chunk's (max, sum of exponentials), waits until the other
 //                  chunks of the same row have done so (they are launched next to it, so the wait is
 //                  short; it is bounded by a clock and reports expiry instead of spinning on), then
-//                  finishes the divergence partial from the registers.  One more workgroup per trial,
-//                  launched after them, waits for the trial's partials in the same bounded way and decides:
-//                  divergence per position (fixed-order sums), coins, first-reject scan.
+//                  finishes the divergence partial from the registers.  In calls of few trials one more
+//                  workgroup per trial, launched after them, waits for the trial's partials in the same bounded
+//                  way and decides: divergence per position (fixed-order sums), coins, first-reject scan.
+//   accept_decide  the decision as a launch of its own, in calls of many trials
 //   accept_race    per (trial, chunk): exponential race over the ONE row that needs a replacement
 //                  token: the residual max(0, p - q) of the first rejected position, or the verifier's
 //                  last row for the bonus token.  Only this kernel draws vocabulary-wide random numbers.
 //   accept_pick    per trial: winner of the race; in small calls the race's last workgroup does it
-// The decision behind a one-launch sweep and the pick of a small call were launches of their own: a stage of one trial, k =
-// 10, took 19.8 us with five launches and takes 17.9 us with three.
+// A stage of one trial, k = 10, takes 18 us with three launches; with the decision and the pick as launches of their own, 19.8.
 // Bulk arithmetic runs in base 2 on the hardware exp2 / log2 units; the two probabilities the coin
 // compares are evaluated with the accurate library functions.  No floating-point atomics: every
 // partial has its own slot, reductions run in a fixed order, so results never depend on scheduling.
@@ -235,7 +235,7 @@ __global__ void accept_clear(RowPart* part, float* jsd, uint32_t* expired, uint3
     if (i == 0) *expired = 0u;
 }
 
-enum { SWEEP_ONE_LAUNCH = 0, SWEEP_PARTIALS = 1, SWEEP_DIVERGENCE = 2 };
+enum { SWEEP_ONE_LAUNCH = 0, SWEEP_PARTIALS = 1, SWEEP_DIVERGENCE = 2, SWEEP_AND_DECIDE = 3 };
 
 // ---- the sweep, in pieces -----------------------------------------------------------------------------------
 // A work item is one chunk of kSweepChunk entries of one judged position: item = position * chunks + chunk within a
@@ -322,16 +322,17 @@ __device__ inline void sweep_first(const AcceptShape& s, const AcceptWs& w, cons
 
 // second half: row statistics from everybody's partials (WAIT: polled), then the divergence partial of the chunk.
 // Returns false in every thread when the bounded wait expired.
-template <bool WAIT>
+// DECIDE: a workgroup of the same launch waits for the results.
+template <bool WAIT, bool DECIDE>
 __device__ inline bool sweep_second(const AcceptShape& s, const AcceptWs& w, const SweepItem& it,
                                     const float a[kSweepQuads][4], const float c[kSweepQuads][4], float4* lds) {
     const float c2 = s.inv_temp * kLog2e;
     RowStats R;
     if (!row_stats<WAIT, kAccThreads>(w.part + (size_t)it.pair * s.nsl, s.nsl, s.wait_ticks, s.few, lds, R)) {
-        // the decision kernel reports the expiry; nothing below is waited for by anyone
+        // the decision reports the expiry
         if (threadIdx.x == 0) __hip_atomic_store(w.expired, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // whoever waits for this chunk's divergence learns of it at once
-        if (WAIT && (threadIdx.x & 63) == 0) st_agent32(w.jsd + (size_t)it.pair * s.nsl + it.ch * kSweepWaves + (threadIdx.x >> 6), INFINITY);
+        // a workgroup that waits for this chunk's divergence learns of it at once
+        if (DECIDE && (threadIdx.x & 63) == 0) st_agent32(w.jsd + (size_t)it.pair * s.nsl + it.ch * kSweepWaves + (threadIdx.x >> 6), INFINITY);
         return false;
     }
     // With xp = log2 p_v = a_v c2 - lp and xq = log2 q_v = c_v c2 - lq, call the larger probability B = 2^max(xp, xq) and
@@ -357,6 +358,12 @@ __device__ inline bool sweep_second(const AcceptShape& s, const AcceptWs& w, con
             acc = fmaf(big * e, u - A, acc);
         }
     acc = (0.5f * kLn2) * wave_sum_dpp(acc);
+    float* slot = w.jsd + (size_t)it.pair * s.nsl + it.ch * kSweepWaves + (threadIdx.x >> 6);
+    if (!DECIDE) {   // a later kernel reads them
+        if ((threadIdx.x & 63) == 0) *slot = acc;
+        if (it.ch == 0 && threadIdx.x == 0) w.stats[it.pair] = R;
+        return true;
+    }
     if (it.ch == 0 && threadIdx.x == 0) {
         st_agent64(&w.stats[it.pair].Mp, R.Mp, R.Sp);
         st_agent64(&w.stats[it.pair].Mq, R.Mq, R.Sq);
@@ -365,7 +372,7 @@ __device__ inline bool sweep_second(const AcceptShape& s, const AcceptWs& w, con
     // of a row sees the row's statistics too.  (A NaN out of NaN logits must not look like the unwritten pattern.)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if ((threadIdx.x & 63) == 0)
-        st_agent32(w.jsd + (size_t)it.pair * s.nsl + it.ch * kSweepWaves + (threadIdx.x >> 6), acc != acc ? __uint_as_float(0x7fc00000u) : acc);
+        st_agent32(slot, acc != acc ? __uint_as_float(0x7fc00000u) : acc);
     return true;
 }
 
@@ -388,21 +395,27 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
     __shared__ int s_pass[PSD_MAX_WIDTH];
     __shared__ int s_bad;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = threadIdx.x;
-    // the coin's inputs do not depend on the sweep: asked for first.  The coin compares p(x) and q(x); an id outside the
-    // vocabulary has probability 0 under the verifier -> rejected.
+    // The coin compares p(x) and q(x); an id outside the vocabulary has probability 0 under the verifier -> rejected.  Its inputs
+    // do not depend on the sweep: asked for while that is awaited, otherwise only where a coin is tossed (2048 trials, k = 1:
+    // 9.6 us against 11.4).
     const size_t pair = (size_t)b * s.k + i;
     float zp = 0.f, zq = 0.f;
     bool known = false;
-    if (i < s.k) {
+    auto coin_inputs = [&] {
         const int x = s.tokens[pair];
         known = x >= 0 && x < s.V;
         if (known) {
             zp = s.lp[((size_t)b * (s.k + 1) + i) * s.V + x];
             zq = s.lq[pair * s.V + x];
         }
+    };
+    if (WAIT && i < s.k) coin_inputs();
+    uint32_t bad = 0;   // of thread 0
+    if (!WAIT && i == 0) bad = *w.expired;
+    if (WAIT) {
+        if (i == 0) s_bad = 0;
+        __syncthreads();
     }
-    if (i == 0) s_bad = WAIT ? 0 : (int)*w.expired;
-    __syncthreads();
     const unsigned long long t0 = WAIT ? wall_clock64() : 0ull;
     for (int r = wave; r < s.k; r += NW) {
         const float* pr = w.jsd + ((size_t)b * s.k + r) * s.nsl;
@@ -446,11 +459,17 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
             const uint64_t sd = a.seed + (uint64_t)b;
             U4 r = philox4x32_10(U4{0u, a.position0 + (uint32_t)i, DRAW_COIN, a.stage}, (uint32_t)sd, (uint32_t)(sd >> 32));
             TokProb tp{0.f, 1.f};
+            if (!WAIT) coin_inputs();
             if (known) {   // accurate exponentials of the natural-log probabilities
-                const unsigned long long up = ld_agent64(&w.stats[pair].Mp), uq = ld_agent64(&w.stats[pair].Mq);
-                const float Mp = __uint_as_float((uint32_t)up), Sp = __uint_as_float((uint32_t)(up >> 32));
-                const float Mq = __uint_as_float((uint32_t)uq), Sq = __uint_as_float((uint32_t)(uq >> 32));
-                const float lse_p = (Mp + log2f(Sp)) * kLn2, lse_q = (Mq + log2f(Sq)) * kLn2;
+                RowStats R;
+                if (WAIT) {
+                    const unsigned long long up = ld_agent64(&w.stats[pair].Mp), uq = ld_agent64(&w.stats[pair].Mq);
+                    R.Mp = __uint_as_float((uint32_t)up); R.Sp = __uint_as_float((uint32_t)(up >> 32));
+                    R.Mq = __uint_as_float((uint32_t)uq); R.Sq = __uint_as_float((uint32_t)(uq >> 32));
+                } else {
+                    R = w.stats[pair];
+                }
+                const float lse_p = (R.Mp + log2f(R.Sp)) * kLn2, lse_q = (R.Mq + log2f(R.Sq)) * kLn2;
                 tp = TokProb{expf(fmaxf(zp, -kBig) * s.inv_temp - lse_p), expf(fmaxf(zq, -kBig) * s.inv_temp - lse_q)};
             }
             pass = (u01(r.x) * tp.qx < tp.px) ? 1 : 0;  // u < p(x)/q(x)
@@ -462,7 +481,8 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
         int n = 0, fuzzy = 0;
         for (; n < s.k && s_pass[n]; ++n) fuzzy += s_pass[n] == 2;
         AcceptOut o;
-        o.n_accepted = s_bad ? -1 : n;  // -1: a bounded wait expired
+        if (WAIT) bad = s_bad;
+        o.n_accepted = bad ? -1 : n;  // -1: a bounded wait expired
         o.n_fuzzy = fuzzy;
         o.pad = 0;
         o.next_token = -1;
@@ -471,17 +491,18 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
     }
 }
 
-// One workgroup per item.  SWEEP_ONE_LAUNCH: publish, wait for the row, finish; a trial's items are followed by the
-// workgroup that decides it.  Two launches: SWEEP_PARTIALS stops after the first half, SWEEP_DIVERGENCE repeats the first
+// One workgroup per item.  SWEEP_ONE_LAUNCH: publish, wait for the row, finish; SWEEP_AND_DECIDE: a trial's items are followed by
+// the workgroup that decides it.  Two launches: SWEEP_PARTIALS stops after the first half, SWEEP_DIVERGENCE repeats the first
 // half without publishing and reads the finished partials.
 // The workgroups of a row are neighbours in launch order and consecutive ids go round the 8 accelerator dies, so
 // the chunks a workgroup waits for are resident with it.
 template <int MODE, bool VEC>
-__global__ __launch_bounds__(kAccThreads, (MODE == SWEEP_ONE_LAUNCH && VEC) ? 8 : 6) void accept_sweep(AcceptShape s, AcceptWs w, DecideArgs da) {
+__global__ __launch_bounds__(kAccThreads, ((MODE == SWEEP_ONE_LAUNCH || MODE == SWEEP_AND_DECIDE) && VEC) ? 8 : 6) void accept_sweep(AcceptShape s, AcceptWs w, DecideArgs da) {
     __shared__ float4 lds[kSweepWaves];
-    const int items = s.k * (s.nsl / kSweepWaves), per = items + (MODE == SWEEP_ONE_LAUNCH ? 1 : 0);
+    constexpr bool kDecide = MODE == SWEEP_AND_DECIDE, kWait = MODE == SWEEP_ONE_LAUNCH || kDecide;
+    const int items = s.k * (s.nsl / kSweepWaves), per = items + (kDecide ? 1 : 0);
     const int b = blockIdx.x / per, item = blockIdx.x - b * per;
-    if (MODE == SWEEP_ONE_LAUNCH && item == items) {
+    if (kDecide && item == items) {
         decide<true, kAccThreads / 64>(s, w, da, b);
         return;
     }
@@ -491,10 +512,10 @@ __global__ __launch_bounds__(kAccThreads, (MODE == SWEEP_ONE_LAUNCH && VEC) ? 8 
     else sweep_load_any(s, it, a, c);
     sweep_first<MODE != SWEEP_DIVERGENCE>(s, w, it, a, c);
     if (MODE == SWEEP_PARTIALS) return;
-    sweep_second<MODE == SWEEP_ONE_LAUNCH>(s, w, it, a, c, lds);
+    sweep_second<kWait, kDecide>(s, w, it, a, c, lds);
 }
 
-// the decision as a kernel of its own: behind the two-launch sweep, and where nothing is judged (k = 0)
+// the decision as a kernel of its own: in calls of many trials, behind the two-launch sweep, and where nothing is judged (k = 0)
 __global__ __launch_bounds__(1024) void accept_decide(AcceptShape s, AcceptWs w, DecideArgs a) { decide<false, 16>(s, w, a, blockIdx.x); }
 
 // ---- assisted stage: strict match against the verifier's top prediction ---------------------------------
@@ -570,6 +591,11 @@ __device__ inline void pick(const AcceptShape& s, const AcceptWs& w, int b, int 
     }
 }
 
+__device__ inline void void_trial(AcceptOut* out, int32_t* n_out, int b) {
+    out[b].n_accepted = -1;
+    if (n_out) n_out[b] = -1;
+}
+
 // Replacement draw, one row per trial.  First rejected position n < k: race r_v / E_v over the residual
 // r = max(0, p - q) (and p_v / E_v beside it, used when the residual has no mass at all).  n == k and a
 // bonus token is wanted: race over the verifier's last row in log form, z_v / temperature - ln E_v, which
@@ -581,11 +607,10 @@ __global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, Accept
                                                            int take_bonus, int assisted, int32_t* n_out, int32_t* tok_out) {
     __shared__ KeyIdx smk[4];
     const int ch = blockIdx.x, b = blockIdx.y;
-    if (!assisted && *w.expired) {   // some wait of the sweep ran out: no trial of the call is valid
-        if (ch == 0 && threadIdx.x == 0) {
-            out[b].n_accepted = -1;
-            if (n_out) n_out[b] = -1;
-        }
+    // some wait of the sweep ran out: no trial of the call is valid.  (A big race leaves the check to accept_pick: in each of
+    // 64 K workgroups it cost 5 us of 162.)
+    if (PICK && !assisted && *w.expired) {
+        if (ch == 0 && threadIdx.x == 0) void_trial(out, n_out, b);
         return;
     }
     const int n = out[b].n_accepted;
@@ -642,9 +667,11 @@ __global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, Accept
     __shared__ int s_last;
     if (threadIdx.x == 0) {
         RacePart* dst = w.race + (size_t)b * s.nch + ch;
-        st_agent64(&dst->key, best.key, __int_as_float(best.idx));
-        st_agent64(&dst->key_fb, best_fb.key, __int_as_float(best_fb.idx));
-        if (PICK) {
+        if (!PICK) {   // a later kernel reads it
+            *dst = RacePart{best.key, best.idx, best_fb.key, best_fb.idx};
+        } else {
+            st_agent64(&dst->key, best.key, __int_as_float(best.idx));
+            st_agent64(&dst->key_fb, best_fb.key, __int_as_float(best_fb.idx));
             // counted once the stores have been acknowledged: who counts last finds every chunk's result
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             s_last = __hip_atomic_fetch_add(w.raced + b * raced_step(s.k, s.nch), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(s.nch - 1);
@@ -658,8 +685,13 @@ __global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, Accept
 
 // the winner as a kernel of its own
 __global__ __launch_bounds__(kAccThreads) void accept_pick(AcceptShape s, AcceptWs w, int take_bonus, int assisted,
-                                                           AcceptOut* out, int32_t* tok_out) {
-    const int b = blockIdx.x, n = out[b].n_accepted;
+                                                           AcceptOut* out, int32_t* n_out, int32_t* tok_out) {
+    const int b = blockIdx.x;
+    if (!assisted && *w.expired) {
+        if (threadIdx.x == 0) void_trial(out, n_out, b);
+        return;
+    }
+    const int n = out[b].n_accepted;
     if (n < 0 || (n == s.k && !take_bonus)) return;  // next_token stays -1
     pick(s, w, b, n, assisted, out, tok_out);
 }
@@ -716,22 +748,28 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
                                                                next_token_out);
         if (!greedy) {
             accept_race<false><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 1, nullptr, nullptr);
-            accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 1, out, next_token_out);
+            accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 1, out, nullptr, next_token_out);
         }
         PSD_HIP(hipGetLastError(), errbuf);
         return PSD_OK;
     }
-    const DecideArgs da{T, seed, position0, stage, out, div_out, n_accepted_out, next_token_out};
     const size_t n_clear = std::max(n_parts, (size_t)n_trials);
     // a row's workgroups may wait for each other while there are few enough of them to be resident together
-    const bool one_launch = pairs > 0 && g_accept_path.load() != 1 && kSweepWaves * nsw <= kSweepMaxSlots &&
-                            (long long)pairs * nsw + n_trials <= 0x7fffffffLL;
+    const bool one_launch = pairs > 0 && g_accept_path.load() != 1 && kSweepWaves * nsw <= kSweepMaxSlots;
+    // Deciding inside the sweep saves a launch; a deciding workgroup takes room from the sweep's.  Inside / outside, k = 1, us a
+    // call: 128 trials 28.2 / 30.5 at V 32000 (7 items a trial), 62.7 / 65.1 at V 128256 (26); 256: 40.3 / 40.7, 106.6 / 107.6, 19.8 /
+    // 20.1 at V 5000 (one item); 384: 50.7 / 50.3 at V 32000; 512: 61.5 / 60.2, 25.3 / 23.3 at V 5000; 1024: 102.9 / 100.7.
+    const bool inside = one_launch && n_trials <= 256;
+    const DecideArgs da{T, seed, position0, stage, out, div_out, n_accepted_out, next_token_out};
     accept_clear<<<(unsigned)((n_clear + 256) / 256), 256, 0, stream>>>(w.part, w.jsd, w.expired, w.raced, n_parts, (uint32_t)n_trials, (uint32_t)raced_step(k, nch));
     const int n_items = pairs * nsw;
     const bool vec = (vocab & 3) == 0;  // rows are then 16-byte aligned and hold whole quads
-    if (one_launch) {
-        if (vec) accept_sweep<SWEEP_ONE_LAUNCH, true><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
-        else accept_sweep<SWEEP_ONE_LAUNCH, false><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
+    if (inside) {
+        if (vec) accept_sweep<SWEEP_AND_DECIDE, true><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
+        else accept_sweep<SWEEP_AND_DECIDE, false><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
+    } else if (one_launch) {
+        if (vec) accept_sweep<SWEEP_ONE_LAUNCH, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
+        else accept_sweep<SWEEP_ONE_LAUNCH, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
     } else {
         if (pairs > 0 && vec) {
             accept_sweep<SWEEP_PARTIALS, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
@@ -740,8 +778,8 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
             accept_sweep<SWEEP_PARTIALS, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
             accept_sweep<SWEEP_DIVERGENCE, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
         }
-        accept_decide<<<n_trials, 1024, 0, stream>>>(s, w, da);
     }
+    if (!inside) accept_decide<<<n_trials, 1024, 0, stream>>>(s, w, da);
     // The last workgroup of a trial's race picks where they are few: every one of them pays an atomic's round trip for it, which
     // a launch of thousands notices (48 trials of 63 workgroups: 126 us instead of 107, with the counters side by side) and up to
     // 1024 do not (one launch less: 63 workgroups 16.8 us against 17.4, 252 18.8 / 19.7, 1008 29.0 / 30.0, 768 of 256 trials 23.8 / 25.1)
@@ -749,7 +787,7 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
         accept_race<true><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0, n_accepted_out, next_token_out);
     } else {
         accept_race<false><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0, n_accepted_out, next_token_out);
-        accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 0, out, next_token_out);
+        accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 0, out, n_accepted_out, next_token_out);
     }
     PSD_HIP(hipGetLastError(), errbuf);
     return PSD_OK;
