@@ -129,7 +129,9 @@ int psd_create(const psd_model_desc* draft, const psd_model_desc* qualifier, con
 
 void psd_destroy(psd_ctx* ctx);
 
-/* Device bytes a pool must have for these models and parameters. */
+/* Device bytes of a pool for these models and parameters: all that a context takes beside its streams.  Where max_seq is
+ * under about 1500 tokens a pool that is smaller by some MB per model may do as well: psd_create takes it, and the q/k/v
+ * projections of prompt ingestion then run in more launches. */
 size_t psd_pool_bytes_needed(const psd_model_desc* draft, const psd_model_desc* qualifier,
                              const psd_model_desc* target, const psd_params* params);
 

@@ -505,12 +505,17 @@ static size_t ctx_extra_bytes(int V, int k1, int k2) {
     return b + 4096;
 }
 
-extern "C" size_t psd_pool_bytes_needed(const psd_model_desc* draft, const psd_model_desc* qualifier,
-                                        const psd_model_desc* target, const psd_params* params) {
+static size_t pool_bytes_for(const psd_model_desc* draft, const psd_model_desc* qualifier, const psd_model_desc* target,
+                             const psd_params* params, bool roomy) {
     if (!draft || !qualifier || !target || !params) return 0;
     if (draft->n_heads < 1 || qualifier->n_heads < 1 || target->n_heads < 1 || params->max_seq < 1) return 0;
-    return model_pool_bytes(*draft, params->max_seq) + model_pool_bytes(*qualifier, params->max_seq) +
-           model_pool_bytes(*target, params->max_seq) + ctx_extra_bytes(target->vocab, params->k1, params->k2);
+    return model_pool_bytes(*draft, params->max_seq, roomy) + model_pool_bytes(*qualifier, params->max_seq, roomy) +
+           model_pool_bytes(*target, params->max_seq, roomy) + ctx_extra_bytes(target->vocab, params->k1, params->k2);
+}
+
+extern "C" size_t psd_pool_bytes_needed(const psd_model_desc* draft, const psd_model_desc* qualifier,
+                                        const psd_model_desc* target, const psd_params* params) {
+    return pool_bytes_for(draft, qualifier, target, params, true);
 }
 
 extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qualifier, const psd_model_desc* target,
@@ -537,10 +542,10 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     c->k1cap = params->k1;
     c->k2cap = params->k2;
     c->V = target->vocab;
-    const size_t need = psd_pool_bytes_needed(draft, qualifier, target, params);
-    const size_t pool_bytes = params->pool_bytes ? params->pool_bytes : need;
-    if (pool_bytes < need) {
-        set_error(c->err, "psd_create: pool_bytes %zu < %zu needed", pool_bytes, need);
+    const size_t full = psd_pool_bytes_needed(draft, qualifier, target, params), least = pool_bytes_for(draft, qualifier, target, params, false);
+    const size_t pool_bytes = params->pool_bytes ? params->pool_bytes : full;
+    if (pool_bytes < least) {
+        set_error(c->err, "psd_create: pool_bytes %zu < %zu needed", pool_bytes, least);
         return fail(PSD_ENOMEM);
     }
 #define CK(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { set_error(c->err, "%s: %s", #call, hipGetErrorString(e_)); return fail(PSD_EHIP); } } while (0)
@@ -553,7 +558,7 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     const char* tags[3] = {"draft", "qualifier", "target"};
     const bool scramble = (params->flags & 0x100) != 0;  // test aid: physical KV pages out of logical order
     for (int i = 0; i < 3; ++i)
-        if ((rc = model_init(c->M[i], *descs[i], tags[i], params->max_seq, scramble, c->pool, c->stream, c->err)) != PSD_OK)
+        if ((rc = model_init(c->M[i], *descs[i], tags[i], params->max_seq, scramble, c->pool, pool_bytes >= full, c->stream, c->err)) != PSD_OK)
             return fail(rc);
     const int V = c->V;
     bool ok = true;

@@ -139,10 +139,11 @@ struct Model {
     size_t weight_bytes = 0;  // bytes one pass streams (all matrices once)
 };
 
-size_t model_pool_bytes(const psd_model_desc& m, int max_seq);
+// roomy: as much as a wide pass needs to run every projection in one launch; without, as little as a model runs with
+size_t model_pool_bytes(const psd_model_desc& m, int max_seq, bool roomy);
 
 // Carves a model out of the pool and uploads + re-tiles its weights (synchronous; uses a temporary staging buffer).
-int model_init(Model& M, const psd_model_desc& desc, const char* tag, int max_seq, bool scramble_pages, Pool& pool,
+int model_init(Model& M, const psd_model_desc& desc, const char* tag, int max_seq, bool scramble_pages, Pool& pool, bool roomy,
                hipStream_t stream, char* err);
 
 // Makes sure KV pages exist for positions < upto and frees pages wholly beyond `keep`, in the host mirror of the page

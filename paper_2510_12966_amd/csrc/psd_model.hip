@@ -1927,8 +1927,12 @@ int model_kernels_init(char* err) {
     return PSD_OK;
 }
 
-// walks the allocation sequence; with a dry pool this only measures
-static int model_carve(Model& M, Pool& pool) {
+// bytes of the four K quarters' sums of one group of tcw column tiles
+static size_t panel_group_bytes(int tiles, int tcw) { return (size_t)4 * tiles * tcw * 64 * sizeof(f32x4); }
+
+// walks the allocation sequence; with a dry pool this only measures.  roomy: with what wide passes need to run every projection
+// in one launch
+static int model_carve(Model& M, Pool& pool, bool roomy) {
     const size_t es = esize(M.dtype);
     const size_t q = (size_t)M.H * M.hd;
     bool ok = true;
@@ -1958,19 +1962,25 @@ static int model_carve(Model& M, Pool& pool) {
         M.ssw = (float*)take((size_t)(M.d / 16) * kCols * sizeof(float));
         M.xbw2 = take(kmax * 4 * kCols);
     }
-    // A wide pass's q/k/v projection finds xbw2 and attn_part free (the attention that writes them comes next), its o and down
-    // projections attn_part and qkv (the attention that read them is done): the sums of their K quarters lie there, which is
-    // why the three follow each other.  gemm_panel may leave any bits in operand columns that the pass does not have; every
-    // column of a matrix product is on its own, and no kernel stores those.
-    const size_t xbw2_end = pool.used;
-    M.attn_part = (float*)take((size_t)M.nsplit_max * kCols * M.H * (M.hd + 2) * sizeof(float));
-    const size_t part_end = pool.used, part_bytes = (size_t)M.nsplit_max * kCols * M.H * (M.hd + 2) * sizeof(float);
-    M.qkv = (float*)take((size_t)kCols * M.nqkv * sizeof(float));
+    // The sums of a wide pass's K quarters lie in the attention partials, which hold nothing while a projection runs, at their end
+    // first, and go on in a piece behind them where the cache is too short for that (under 770 to 1500 tokens; o and down always
+    // fit).  Without that piece the q/k/v projection also has xbw2 in front, which the attention behind it writes, and runs in
+    // as many launches as it then takes.  (Lines that every die's L2 has read shortly before, as xbw2's, take longer to write:
+    // 512 columns, d 512, 4 heads and kv heads: q/k/v 16.5 us a launch, 20.1 from the start of xbw2 on.)  gemm_panel may
+    // leave any bits in operand columns that the pass does not have; every column of a product is on its own, and no kernel
+    // stores those.
+    const size_t xbw2_at = pool.used - kmax * 4 * kCols, part_bytes = (size_t)M.nsplit_max * kCols * M.H * (M.hd + 2) * sizeof(float);
+    M.attn_part = (float*)take(part_bytes);
+    const size_t part_at = pool.used - part_bytes;
     if (M.dtype == PSD_BF16) {
-        M.panel_qkv = PanelScratch{M.xbw2, part_end - (xbw2_end - kmax * 4 * kCols)};
-        M.panel_res = PanelScratch{M.attn_part, pool.used - (part_end - part_bytes)};
+        const int widest = std::min(M.ingest_max, M.nsplit_max * 128);
+        const size_t sums = panel_group_bytes(round16(M.nqkv) / 16, widest / 16);
+        if (roomy && sums > part_bytes) (void)take(sums - part_bytes);
+        M.panel_qkv = PanelScratch{M.xbw2, pool.used - xbw2_at};
+        M.panel_res = PanelScratch{M.attn_part, pool.used - part_at};
         M.panel_rs = M.attn_part;
     }
+    M.qkv = (float*)take((size_t)kCols * M.nqkv * sizeof(float));
     M.gu = (float*)take((size_t)kMaxW * 2 * M.F * sizeof(float));
     M.desc = (PassDesc*)take(sizeof(PassDesc));
     return ok ? PSD_OK : PSD_ENOMEM;
@@ -1990,12 +2000,12 @@ static void model_shape(Model& M, const psd_model_desc& m, int max_seq) {
                    : (ranges_ok(M.nqkv, M.d) && ranges_ok(M.d, M.H * M.hd) && ranges_ok(2 * M.F, M.d) && ranges_ok(M.d, M.F)) ? kCols : 128;
 }
 
-size_t model_pool_bytes(const psd_model_desc& m, int max_seq) {
+size_t model_pool_bytes(const psd_model_desc& m, int max_seq, bool roomy) {
     Model M;
     model_shape(M, m, max_seq);
     Pool p;
     p.dry = true;
-    model_carve(M, p);
+    model_carve(M, p, roomy);
     return p.used + 256;
 }
 
@@ -2004,7 +2014,7 @@ static size_t blob_elems(const psd_model_desc& m) {
     return (size_t)m.vocab * d + (size_t)m.n_layers * (d + q * d + 2 * kv * d + d * q + d + 2 * F * d + d * F) + d;
 }
 
-int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, bool scramble_pages, Pool& pool,
+int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, bool scramble_pages, Pool& pool, bool roomy,
                hipStream_t stream, char* err) {
     if (!m.weights) PSD_FAIL(PSD_EINVAL, err, "%s: weights pointer is null", tag);
     if (m.dtype != PSD_F32 && m.dtype != PSD_BF16) PSD_FAIL(PSD_EINVAL, err, "%s: dtype %d", tag, m.dtype);
@@ -2020,7 +2030,7 @@ int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, 
         PSD_FAIL(PSD_EINVAL, err, "%s: weights_bytes %zu, shape implies %zu", tag, m.weights_bytes, blob_elems(m) * esize(m.dtype));
     model_shape(M, m, max_seq);
     M.tag = tag;
-    int rc = model_carve(M, pool);
+    int rc = model_carve(M, pool, roomy);
     if (rc != PSD_OK) PSD_FAIL(PSD_ENOMEM, err, "%s: device pool too small (%zu bytes needed so far)", tag, pool.used);
 
     const bool bf = M.dtype == PSD_BF16;
@@ -2215,21 +2225,18 @@ static int forward_f32(Model& M, int wmax, float* logits, Launch& L) {
     return PSD_OK;
 }
 
-// bytes of the four K quarters' sums of one group of tcw column tiles
-static size_t panel_group_bytes(int tiles, int tcw) { return (size_t)4 * tiles * tcw * 64 * sizeof(f32x4); }
-
 // Projection of a prompt-ingestion pass.  NW: the K split of the narrow kernels.
 template <int NW, int EPI, int RTW, int TCW, int KB>
 static void launch_panel_as(Launch& L, GemmArgs a, int tiles) {
     Model& M = L.M;
     const int ncg = L.wcls / (16 * TCW), units = (tiles + 8 * RTW - 1) / (8 * RTW) * (kGrouped<EPI> ? 4 : 1);
     if constexpr (kGrouped<EPI>) {
-        // as many column groups per launch as the scratch has room for: all of them unless the cache is short and the model
-        // has as many kv heads as heads
+        // as many column groups per launch as the scratch has room for: all of them in a pool of the full size
         const PanelScratch& sc = EPI == EPI_QKV ? M.panel_qkv : M.panel_res;
         const int room = (int)std::min((size_t)ncg, sc.bytes / panel_group_bytes(tiles, TCW)), turns = (ncg + room - 1) / room;
-        f32x4* part = (f32x4*)sc.mem;
-        for (int cg0 = 0, n = (ncg + turns - 1) / turns; cg0 < ncg; cg0 += n) {
+        int n = (ncg + turns - 1) / turns;
+        f32x4* part = (f32x4*)((char*)sc.mem + (sc.bytes - n * panel_group_bytes(tiles, TCW)) / 256 * 256);   // at its end
+        for (int cg0 = 0; cg0 < ncg; cg0 += n) {
             n = std::min(n, ncg - cg0);
             gemm_panel<NW, EPI, RTW, TCW, KB><<<(units + 7) / 8 * 8 * n, 512, 0, L.s>>>(a, tiles, n, cg0, part);
             panel_finish<NW, EPI><<<dim3((tiles + 7) / 8, n * TCW), 256, 0, L.s>>>(a, tiles, cg0 * TCW, part);
@@ -2248,7 +2255,7 @@ static void launch_panel(Launch& L, const GemmArgs& a, int tiles) {
     // smallest tiles than CUs are launched two workgroups share a CU instead, which the second step's registers would prevent
     // (qualifier shape, 100 tokens: o + down 21.0 -> 18.6 us, gate/up 40.5 -> 36.8; q/k/v with 320 workgroups 19.6 -> 21.2)
     // The scratch always has room for one group of 64 columns: q/k/v, 1024 nqkv <= 3072 d bytes of 2048 (max(d, F) +
-    // nsplit_max (d + 2 H)); o and down, 1024 d of 2048 (nsplit_max (d + 2 H) + nqkv).
+    // nsplit_max (d + 2 H)); o and down, 1024 d of 2048 nsplit_max (d + 2 H).
     const size_t scratch = EPI == EPI_QKV ? L.M.panel_qkv.bytes : EPI == EPI_RESID ? L.M.panel_res.bytes : SIZE_MAX;
     if (full >= 192 && panel_group_bytes(tiles, 8) <= scratch) launch_panel_as<NW, EPI, 2, 8, 1>(L, a, tiles);
     else if (full >= 96) launch_panel_as<NW, EPI, 2, 4, 2>(L, a, tiles);

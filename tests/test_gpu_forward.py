@@ -178,27 +178,44 @@ def test_bf16_wide_projection_tiles_are_bit_exact(which, n):
     assert np.abs(out[0] - ref).max() <= TOL_BF16
 
 
-# as many kv heads as heads and a short cache: the sums of the q/k/v projection's K quarters find room for some of the pass's
-# column groups at a time only: 2 + 1 groups of 128 columns, 3 + 3 of 64, and 64 columns where 128 would fill the device
+# as many kv heads as heads, a short cache and the smallest pool that is accepted: the sums of the q/k/v projection's K quarters find
+# room for some of the pass's column groups at a time only: 2 + 1 groups of 128 columns, 3 + 3 of 64, and 64 columns where 128
+# would fill the device
 ROOM = ((ModelShape(1, 1408, 11, 11, 608, 1000), 576, 380), (ModelShape(1, 960, 15, 15, 2848, 1000), 448, 380),
         (ModelShape(1, 4096, 32, 32, 64, 1000), 128, 121))
 
 
 @pytest.mark.parametrize("which", [0, 1, 2])
 def test_bf16_wide_projections_in_several_launches_are_bit_exact(which):
+    import ctypes as C
+    from paper_2510_12966_amd import binding as b
     shape, max_seq, n = ROOM[which]
     blob = synth.target_weights(shape, 65, synth.DTYPE_BF16, sigma=0.03)
     stub = ModelShape(1, 64, 2, 1, 64, 1000)
     small = synth.target_weights(stub, 66, synth.DTYPE_BF16, sigma=0.03)
-    ctx = _ctx((stub, stub, shape), (small, small, blob), synth.DTYPE_BF16, 10000.0, max_seq, k1=1, k2=1)
+    descs = [_desc(s, w, synth.DTYPE_BF16, 10000.0) for s, w in ((stub, small), (stub, small), (shape, blob))]
+    cd = [d.c() for d in descs]
+    full = b.lib().psd_pool_bytes_needed(C.byref(cd[0]), C.byref(cd[1]), C.byref(cd[2]), C.byref(b._Params(0.3, 0.2, 1.0, 1, 1, max_seq, 0, 0, 0)))
+
+    def beyond_the_attention_partials(s, widest):   # of a q/k/v projection's sums, in 256-byte pieces
+        nsplit, hd = (max_seq + 127) // 128, s.d_model // s.n_heads
+        sums = 4 * (s.n_heads + 2 * s.n_kv_heads) * hd * min(widest, 128 * nsplit) * 4
+        return max(0, sums - nsplit * 512 * s.n_heads * (hd + 2) * 4 + 255) // 256 * 256
+
+    least = full - 2 * beyond_the_attention_partials(stub, 128) - beyond_the_attention_partials(shape, 512 if n > 128 else 128)
+    assert least < full
+    with pytest.raises(psd.PsdError):
+        psd.Context(*descs, 0.3, 0.2, 1, 1, max_seq, pool_bytes=least - 1)
     toks = synth.tokens(14, 0, n + 3, 1000)
     out = []
-    for step in (512 if n > 128 else 128, 32):
+    for pool, step in ((full, 512), (least, 512), (least, 32)):
+        ctx = psd.Context(*descs, 0.3, 0.2, 1, 1, max_seq, pool_bytes=pool)
+        step = min(step, 512 if n > 128 else 128)
         for pos in range(0, n, step):
             ctx.forward(2, toks[pos:min(pos + step, n)], pos, want_logits=False)
         out.append(ctx.forward(2, toks[n:n + 3], n))
-    ctx.close()
-    assert np.array_equal(out[0], out[1])
+        ctx.close()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
     ref = oracle.Model(shape, blob, synth.DTYPE_BF16, 10000.0, max_seq).forward(toks, 0)[n:]
     assert np.abs(out[0] - ref).max() <= TOL_BF16
 
