@@ -671,6 +671,7 @@ extern "C" int psd_forward(psd_ctx* c, int32_t which, const int32_t* tokens, int
     int rc = check_tokens(c, tokens, w);
     if (rc != PSD_OK) return rc;
     PSD_HIP(hipSetDevice(c->device), c->err);
+    M.len = pos0;   // rows beyond are about to be replaced: the launch is sized for what the pass can see
     if ((rc = map_pages(c, M, pos0, pos0 + w)) != PSD_OK) return rc;
     PassDesc d;
     fill_desc(d, tokens, 0, w, 0, logits_out ? w : 0, 0);

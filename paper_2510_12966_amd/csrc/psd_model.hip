@@ -2356,8 +2356,17 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
     // lo plane per value, so the kernels move twice that), plus the queries in and the outputs back
     const double kv_bytes = (double)std::min(M.max_seq, M.len + wmax) * KV * hd * 2 * 2 + (double)wmax * H * hd * 4 * 2;
     // Wide passes: one sweep per query tile (attn_wide) where there are enough tiles to fill the device or few key ranges to
-    // walk; few tiles over a long context keep a workgroup per key range and the merge kernel.
-    const bool sweep = c128 && (KV * ((wmax * G + 15) / 16) >= 512 || nsplit <= 8);
+    // walk; few tiles over a long context keep a workgroup per key range and the merge kernel.  us a layer, ranges + merge / sweep,
+    // head dim 64 | 128, over the key ranges that the pass's last position has:
+    //    64 tiles   1: 18 / 10 | 23 / 13    2: 18 / 13 | 23 / 19    3: 18 / 16 | 23 / 23    4: 18 / 19 | 23 / 28    8: 19 / 31 | 23 / 48
+    //   256 tiles   3: 21 / 16 | 29 / 25    4: 21 / 19 | 29 / 30    5: 21 / 22 | 30 / 34    8: 22 / 31 | 32 / 50
+    //   384 tiles   5: 26 / 22 | 39 / 34    6: 26 / 25 | 44 / 39    7: 26 / 29 | 46 / 43    8: 26 / 32 | 46 / 48
+    //   512 tiles   7: 33 / 28 |           14: 55 / 50 | 91 / 82   25: 75 / 84 | 137 / 138
+    //   768 tiles  27: 104 / 86 | 205 / 145
+    // (a sweep takes 10 us and 3 for every range after the first | 13 and 5; the other route starts at 18-23 us and grows with
+    // tiles times ranges).
+    const int tiles = KV * ((wmax * G + 15) / 16), ranges = (std::min(M.max_seq, M.len + wmax) + kAttnSplit - 1) / kAttnSplit;
+    const bool sweep = c128 && (tiles >= 512 || ranges <= (tiles >= 384 ? 6 : tiles >= 256 ? 4 : 3));
     const bool fold_merge = wmax <= 4 && d <= 2048 && d / 16 <= 256 && H * hd == d && nsplit <= kFoldSplits;
     GemmArgs base{};
     base.ss_in = ss; base.ss_tiles = d / 16; base.inv_d = inv_d; base.eps = M.eps;

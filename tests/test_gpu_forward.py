@@ -221,7 +221,8 @@ def test_bf16_wide_projections_in_several_launches_are_bit_exact(which):
 
 
 # head dims 32 / 64 / 128 with query groups of 4, 3 and 1: the first has enough query tiles for the one-sweep attention at any
-# context, the others change over to a workgroup per key range beyond eight ranges
+# context in 512-token passes and changes over to a workgroup per key range beyond four ranges in 100-token ones, the others
+# beyond three
 SWEEP = (ModelShape(1, 1024, 32, 8, 512, 200), ModelShape(1, 384, 6, 2, 256, 200), ModelShape(1, 512, 4, 4, 512, 200))
 
 
