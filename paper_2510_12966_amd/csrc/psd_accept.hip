@@ -131,7 +131,9 @@ struct AcceptShape {
     float inv_temp;
     int nsl;                // result slots per row of the sweep kernel: one per wave, 4 per workgroup
     unsigned long long wait_ticks;  // bound of the wait for the other chunks of a row, in wall-clock ticks
-    int few;                // few enough workgroups that polling often disturbs nobody
+    // Few enough workgroups that polling often disturbs nobody.  us a call, polling every 2 / 32 sleeps: 3 positions of 26 chunks 16.0 /
+    // 17.6, 1008 workgroups 21.5 / 21.9, 1664 41.7 / 41.4, 13312 141 / 136; 1792 of 7 chunks a row 39.8 / 40.4
+    int few;
 };
 
 struct AcceptWs {  // carved out of the caller's workspace

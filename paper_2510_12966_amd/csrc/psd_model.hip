@@ -2249,15 +2249,20 @@ static void launch_panel_as(Launch& L, GemmArgs a, int tiles) {
 }
 template <int NW, int EPI>
 static void launch_panel(Launch& L, const GemmArgs& a, int tiles) {
-    // 256 x 128 outputs per workgroup move the fewest bytes per MFMA; smaller tiles where those would leave CUs idle
+    // 256 x 128 outputs per workgroup move the fewest bytes per MFMA; smaller tiles where those would leave CUs idle.  us of a
+    // projection with 256 x 128 / 256 x 64 / 128 x 64 tiles, over the number `full` of the first:
+    //   160: 36.6 / 43.8 / 43.1    144: 30.0 / 32.5 / 33.7, 59.4 / 65.4 / 69.8    128: 58.2 / 41.9 / 50.3, 38.0 / 30.5 / 36.3
+    //   112: 102 / 82 / 95          96: 38.3 / 32.5 / 35.8, 54.6 / 38.6 / 48.4      64: 55.8 / 38.4 / 31.0, 35.0 / 26.9 / 22.8
     const int full = (tiles + 15) / 16 * (kGrouped<EPI> ? 4 : 1) * (L.wcls / 128);
     // KB: a small tile's step is few MFMAs (64 x 64 outputs per SIMD: 128 cycles), so two of them share a barrier; where more
-    // smallest tiles than CUs are launched two workgroups share a CU instead, which the second step's registers would prevent
-    // (qualifier shape, 100 tokens: o + down 21.0 -> 18.6 us, gate/up 40.5 -> 36.8; q/k/v with 320 workgroups 19.6 -> 21.2)
+    // smallest tiles than CUs are launched (`full` from 64 to 96) two workgroups share a CU instead, which the second step's
+    // registers would prevent (qualifier shape, 100 tokens: o + down 21.0 -> 18.6 us, gate/up 40.5 -> 36.8; q/k/v with 320 workgroups
+    // 19.6 -> 21.2).  There the 256 x 64 tiles are no clear choice either: one step / two steps / those, 30.7 / 31.9 / 28.0 at 80,
+    // 20.3 / 22.7 / 21.3 at 72
     // The scratch always has room for one group of 64 columns: q/k/v, 1024 nqkv <= 3072 d bytes of 2048 (max(d, F) +
     // nsplit_max (d + 2 H)); o and down, 1024 d of 2048 nsplit_max (d + 2 H).
     const size_t scratch = EPI == EPI_QKV ? L.M.panel_qkv.bytes : EPI == EPI_RESID ? L.M.panel_res.bytes : SIZE_MAX;
-    if (full >= 192 && panel_group_bytes(tiles, 8) <= scratch) launch_panel_as<NW, EPI, 2, 8, 1>(L, a, tiles);
+    if (full >= 144 && panel_group_bytes(tiles, 8) <= scratch) launch_panel_as<NW, EPI, 2, 8, 1>(L, a, tiles);
     else if (full >= 96) launch_panel_as<NW, EPI, 2, 4, 2>(L, a, tiles);
     else if ((tiles + 7) / 8 * (kGrouped<EPI> ? 4 : 1) * (L.wcls / 64) <= 256) launch_panel_as<NW, EPI, 1, 4, 2>(L, a, tiles);
     else launch_panel_as<NW, EPI, 1, 4, 1>(L, a, tiles);
