@@ -130,7 +130,7 @@ struct Model {
     float* qkv = nullptr;     // [512][nqkv]
     PanelScratch panel_qkv, panel_res;   // wide passes, sums of the K quarters of the q/k/v, and of the o and down, projections
     float* panel_rs = nullptr;   // wide passes: [512] rms scale per column, for gate/up (in attn_part)
-    float* gu = nullptr;      // [32][2F]
+    float* gu = nullptr;      // fp32 models: [32][F], the SwiGLU's output
     PassDesc* desc = nullptr;
     // host mirror
     int len = 0;  // valid KV rows

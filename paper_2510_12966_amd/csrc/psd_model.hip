@@ -39,22 +39,18 @@ __device__ inline float rows_max(float v) {
 }
 
 // ---- operand packing ----------------------------------------------------------------------------
-// GEMM input X[c][f] (c < 16 CT tokens, f < K features), bf16 path: [K/32][CT col tiles][hi, lo][64 lanes][8]
+// GEMM input X[c][f] (c < 16 CT tokens, f < K features) of bf16 models: [K/32][CT col tiles][hi, lo][64 lanes][8]
 // (CT = 2 for passes of up to 32 tokens, 32 for the passes of up to 512 tokens that ingest a prompt),
 // lane = ((f % 32) / 8) * 16 + c % 16: exactly the B operand of v_mfma_f32_16x16x32_bf16.
-// fp32 path: plain rows [c][K].
-template <bool BF16, int CT = 2>
-__device__ inline void pack_store(void* xb, int K, int c, int f, float v) {
-    if constexpr (BF16) {
-        const int ks = f >> 5, g = (f & 31) >> 3, e = f & 7, t = c >> 4, cc = c & 15;
-        uint16_t* p = (uint16_t*)xb;
-        const size_t base = ((((size_t)ks * CT + t) * 2) * 64 + g * 16 + cc) * 8 + e;
-        const uint16_t hi = f32_to_bf16(v);
-        p[base] = hi;
-        p[base + 64 * 8] = f32_to_bf16(v - bf16_to_f32(hi));
-    } else {
-        ((float*)xb)[(size_t)c * K + f] = v;
-    }
+// fp32 models: plain rows [c][K].
+template <int CT>
+__device__ inline void pack_store(void* xb, int c, int f, float v) {
+    const int ks = f >> 5, g = (f & 31) >> 3, e = f & 7, t = c >> 4, cc = c & 15;
+    uint16_t* p = (uint16_t*)xb;
+    const size_t base = ((((size_t)ks * CT + t) * 2) * 64 + g * 16 + cc) * 8 + e;
+    const uint16_t hi = f32_to_bf16(v);
+    p[base] = hi;
+    p[base + 64 * 8] = f32_to_bf16(v - bf16_to_f32(hi));
 }
 
 // ---- small kernels ------------------------------------------------------------------------------
@@ -105,18 +101,6 @@ __global__ __launch_bounds__(256) void tile_bf16(const uint4* src, uint4* dst, i
 }
 
 // ---- rotary embedding + KV append ------------------------------------------------------------------
-template <typename KVT>
-__device__ inline void kv_store(KVT* p, float v);
-template <>
-__device__ inline void kv_store<float>(float* p, float v) { *p = v; }
-template <>
-__device__ inline void kv_store<uint16_t>(uint16_t* p, float v) { *p = f32_to_bf16(v); }
-template <typename KVT>
-__device__ inline float kv_load(const KVT* p);
-template <>
-__device__ inline float kv_load<float>(const float* p) { return *p; }
-template <>
-__device__ inline float kv_load<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
 
 // bf16 models keep every K and V element as a bf16 hi + lo pair (value = hi + lo to 2^-17) in four planes per
 // (page, layer, kv head): K hi, K lo, V hi, V lo, each of kPage x hd elements.  One bf16 rounding of the
@@ -145,8 +129,7 @@ __device__ inline size_t kv_base(int page, int layer, int L, int g, int KV, int 
 // [split * 128, split * 128 + 128); wave j takes the queries c = j, j + 4, ...  Partial result per
 // (split, query, head): running max m, sum l and the un-normalised output, merged by attn_combine in
 // split order.  The arithmetic for a query at a given position is the same whatever the pass width.
-template <typename KVT>
-__global__ __launch_bounds__(256) void attn_partial(const float* qkv, const PassDesc* desc, const KVT* kv,
+__global__ __launch_bounds__(256) void attn_partial(const float* qkv, const PassDesc* desc, const float* kv,
                                                     const int32_t* page_table, float* part, int layer, int L, int H,
                                                     int KV, int hd, int nqkv) {
     extern __shared__ float lds[];
@@ -163,8 +146,8 @@ __global__ __launch_bounds__(256) void attn_partial(const float* qkv, const Pass
     for (int idx = threadIdx.x; idx < nkeys * hd; idx += 256) {
         const int j = idx / hd, i = idx % hd, pos = key0 + j;
         const int page = page_table[pos / kPage], slot = pos % kPage;
-        Ks[j * ld + i] = kv_load<KVT>(kv + kv_base(page, layer, L, g, KV, 0, hd) + (size_t)slot * hd + i);
-        Vs[j * ld + i] = kv_load<KVT>(kv + kv_base(page, layer, L, g, KV, 1, hd) + (size_t)slot * hd + i);
+        Ks[j * ld + i] = kv[kv_base(page, layer, L, g, KV, 0, hd) + (size_t)slot * hd + i];
+        Vs[j * ld + i] = kv[kv_base(page, layer, L, g, KV, 1, hd) + (size_t)slot * hd + i];
     }
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -208,9 +191,8 @@ __global__ __launch_bounds__(256) void attn_partial(const float* qkv, const Pass
     }
 }
 
-// grid (wmax, H), block hd: merges the split partials in order and writes the O-projection's input operand
-template <bool BF16>
-__global__ void attn_combine_pack(const float* part, const PassDesc* desc, void* xb, int H, int hd) {
+// grid (wmax, H), block hd: merges the split partials in order and writes the O-projection's input row
+__global__ void attn_combine_f32(const float* part, const PassDesc* desc, float* out, int H, int hd) {
     const int c = blockIdx.x, h = blockIdx.y, i = threadIdx.x;
     if (c >= desc->w) return;
     const int nsp = (desc->pos0 + c + kAttnSplit) / kAttnSplit;  // splits holding keys <= pos0 + c
@@ -223,7 +205,7 @@ __global__ void attn_combine_pack(const float* part, const PassDesc* desc, void*
         Lsum += pr[1] * f;
         o += pr[2 + i] * f;
     }
-    pack_store<BF16>(xb, H * hd, c, h * hd + i, o / Lsum);
+    out[(size_t)c * H * hd + h * hd + i] = o / Lsum;
 }
 
 // Softmax of the bf16 models' attention works in base 2 (the query carries log2 e, exponentials are the hardware exp2).
@@ -497,9 +479,10 @@ __device__ inline float ss_scale(const GemmArgs& a, const float (*ssp)[GC], int 
 // live blocks (4 columns x 4 k groups x hi, lo) of two K steps per instruction, no registers.  Loads return in order, so
 // the staged blocks are there before the first weight block, and a K step then reads its operand from LDS (~100
 // cycles) instead of L2 (~1400 cycles, of which a wave's two MFMAs per step hide nothing).
-template <int NT, int NW, int RT, int EPI, int CT, bool LB = false, bool SK = false>
+template <int NT, int NW, int RT, int EPI, bool LB = false, bool SK = false>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
     static_assert(!LB || NT == 1, "LDS staging of the operand is for one column tile");
+    constexpr int CT = 2;   // column tiles of the operand
     extern __shared__ u32x4 lb_buf[];
     static_assert(RT <= NW, "one finishing wave per row tile");
     __shared__ f32x4 red[NW][RT][NT][64];
@@ -1325,7 +1308,7 @@ __global__ void attn_combine_bf16(const float* part, const PassDesc* desc, void*
     const int nsp = (desc->pos0 + c + kAttnSplit) / kAttnSplit;  // splits holding keys <= pos0 + c
     float o[1];
     attn_merge<1>(part, nsp, c, h, H, hd, i, o);
-    pack_store<true, CT>(xb, H * hd, c, h * hd + i, o[0]);
+    pack_store<CT>(xb, c, h * hd + i, o[0]);
 }
 
 // The same merge for long contexts (more than eight key ranges): one workgroup per (token, head) brings the partials of
@@ -1392,7 +1375,7 @@ __global__ __launch_bounds__(256) void attn_combine_long(const float* part, cons
             Lsum = fmaf(Lsum, f.x, f.z);                                          // merge_add
             o = merge_add(o, cmb[sp * hd + i], MergeFac{0.f, f.x, f.y});
         }
-        pack_store<true, CT>(xb, H * hd, c, h * hd + i, o / Lsum);
+        pack_store<CT>(xb, c, h * hd + i, o / Lsum);
     }
 }
 
@@ -1482,7 +1465,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qk
         f32x4 S[4][2];
         float mv[4], fac[4], Ms = -INFINITY;
         if (live) {
-// (k_hi + k_lo)(q_hi + q_lo) without the lo * lo term (2^-18 relative); eight independent chains side by side
+            // (k_hi + k_lo)(q_hi + q_lo) without the lo * lo term (2^-18 relative); eight independent chains side by side
 #pragma unroll
             for (int kt = 0; kt < 8; ++kt) S[kt >> 1][kt & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1540,7 +1523,7 @@ __global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qk
                 Ls = fmaf(l, fac[v], Ls);
                 to_rows(fac[v], fr);
                 const uint2* vp = reinterpret_cast<const uint2*>(sV + (v >> 1) * 2 * PW) + ((v & 1) * 2) * 64 + lane;
-u32x4 vh[JT], vl[JT];
+                u32x4 vh[JT], vl[JT];
                 f32x4 O[JT];
 #pragma unroll
                 for (int j = 0; j < JT; ++j) {
@@ -1576,7 +1559,7 @@ u32x4 vh[JT], vl[JT];
         if (rr >= R) continue;
         const int c = rr / G, f0 = (gkv * G + rr % G) * HD + cq;
 #pragma unroll
-        for (int j = 0; j < JT; ++j) pack_store<true, kWideCT>(xb, H * HD, c, f0 + 16 * j, o[j][r] / Lr[r]);
+        for (int j = 0; j < JT; ++j) pack_store<kWideCT>(xb, c, f0 + 16 * j, o[j][r] / Lr[r]);
     }
 }
 
@@ -1770,7 +1753,7 @@ __global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
 
 // Attention of an fp32 model at contexts of at most kF32OneSplits key ranges: one workgroup per (head, query) takes all
 // of them, wave v the ranges v, v + 4, and merges them in order; the arithmetic is that of attn_partial and
-// attn_combine_pack, so a token's output does not depend on which route its launch takes.
+// attn_combine_f32, so a token's output does not depend on which route its launch takes.
 // grid (H, wmax), 256 threads, writes the o projection's input [c][H hd].
 constexpr int kF32OneSplits = 8;
 __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qkv, const PassDesc* desc, const float* __restrict__ kv,
@@ -1909,15 +1892,15 @@ constexpr size_t kLbMaxBytes = 128 * 1024;
 
 template <int EPI>
 static int lb_kernels_init(char* err) {
-    PSD_HIP(hipFuncSetAttribute((const void*)gemm_bf16<1, 16, 1, EPI, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbMaxBytes), err);
-    PSD_HIP(hipFuncSetAttribute((const void*)gemm_bf16<1, 8, 2, EPI, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbMaxBytes), err);
-    PSD_HIP(hipFuncSetAttribute((const void*)gemm_bf16<1, 8, 1, EPI, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbMaxBytes), err);
+    PSD_HIP(hipFuncSetAttribute((const void*)gemm_bf16<1, 16, 1, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbMaxBytes), err);
+    PSD_HIP(hipFuncSetAttribute((const void*)gemm_bf16<1, 8, 2, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbMaxBytes), err);
+    PSD_HIP(hipFuncSetAttribute((const void*)gemm_bf16<1, 8, 1, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLbMaxBytes), err);
     return PSD_OK;
 }
 
 int model_kernels_init(char* err) {
     // attention stages two pages of K and V as fp32 in LDS: up to ~135 KB of the 160 KB a gfx950 CU has
-    PSD_HIP(hipFuncSetAttribute((const void*)attn_partial<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    PSD_HIP(hipFuncSetAttribute((const void*)attn_partial, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 attn_lds_bytes(128)), err);
     PSD_HIP(hipFuncSetAttribute((const void*)attn_wide<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnWideLds<128>), err);
     PSD_HIP(hipFuncSetAttribute((const void*)attn_wide<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnWideLds<64>), err);
@@ -1982,7 +1965,7 @@ static int model_carve(Model& M, Pool& pool, bool roomy) {
         M.panel_rs = M.attn_part;
     }
     M.qkv = (float*)take((size_t)kCols * M.nqkv * sizeof(float));
-    M.gu = (float*)take((size_t)kMaxW * 2 * M.F * sizeof(float));
+    if (M.dtype == PSD_F32) M.gu = (float*)take((size_t)kMaxW * M.F * sizeof(float));
     // the page table behind the pass descriptor, so that creation clears them in one go (70 us of the 1.4 ms of a tiny stack each)
     char* desc = (char*)take(kDescBytes + (size_t)M.n_pages * sizeof(int32_t));
     M.desc = (PassDesc*)desc;
@@ -2093,7 +2076,6 @@ int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, 
     PSD_HIP(hipMemsetAsync(M.xb, 0, kmax * 128, stream), err);
     PSD_HIP(hipMemsetAsync(M.x, 0, (size_t)kCols * d * sizeof(float), stream), err);
     PSD_HIP(hipMemsetAsync(M.qkv, 0, (size_t)kCols * M.nqkv * sizeof(float), stream), err);
-    PSD_HIP(hipMemsetAsync(M.gu, 0, (size_t)kMaxW * 2 * F * sizeof(float), stream), err);
     // the descriptor and the page table: every entry is a valid page at all times (blocks without one name page 0), so that
     // attention kernels may read, and then mask, a block that is not mapped
     PSD_HIP(hipMemsetAsync(M.desc, 0, kDescBytes + (size_t)M.n_pages * sizeof(int32_t), stream), err);
@@ -2216,8 +2198,8 @@ static int forward_f32(Model& M, int wmax, float* logits, Launch& L) {
         if (nsplit <= kF32OneSplits) {
             attn_one_f32<<<dim3(H, wmax), 256, 0, stream>>>(M.qkv, M.desc, (const float*)M.kv, M.page_table, M.n_pages, attn, l, M.L, H, KV, hd, M.nqkv);
         } else {
-            attn_partial<float><<<dim3(H, nsplit), 256, attn_lds_bytes(hd), stream>>>(M.qkv, M.desc, (const float*)M.kv, M.page_table, M.attn_part, l, M.L, H, KV, hd, M.nqkv);
-            attn_combine_pack<false><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, attn, H, hd);
+            attn_partial<<<dim3(H, nsplit), 256, attn_lds_bytes(hd), stream>>>(M.qkv, M.desc, (const float*)M.kv, M.page_table, M.attn_part, l, M.L, H, KV, hd, M.nqkv);
+            attn_combine_f32<<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, attn, H, hd);
         }
         L.end();
         launch_proj_f32<F32_RESID>(L, "gemm_o", args(w.wo, attn, nullptr, M.x, d, H * hd, d));
@@ -2282,7 +2264,7 @@ static void launch_gemm_bf16(Launch& L, const char* family, GemmArgs a) {
     // Waves per workgroup (the K split, hence the summation order) follow from the number of row tiles only, never
     // from the pass width: a token's result must not depend on the width of the pass that computes it.  Row tiles
     // per wave do not change the arithmetic and are picked per width class.
-#define PSD_GEMM(NT_, NW_, RT_, CT_) gemm_bf16<NT_, NW_, RT_, EPI, CT_><<<tiles / RT_, 64 * NW_, 0, L.s>>>(a)
+#define PSD_GEMM(NT_, NW_, RT_) gemm_bf16<NT_, NW_, RT_, EPI><<<tiles / RT_, 64 * NW_, 0, L.s>>>(a)
     if (L.wcls > kMaxW) {   // prompt ingestion
         if constexpr (EPI != EPI_LOGITS) {
             if (tiles <= 256) launch_panel<16, EPI>(L, a, tiles);
@@ -2294,10 +2276,10 @@ static void launch_gemm_bf16(Launch& L, const char* family, GemmArgs a) {
         if constexpr (EPI == EPI_SWIGLU) {   // shapes measured one by one; only the gate/up kernels have such variants
             if (tiles % 7 == 0 && tiles / 7 >= 256) {
                 // one workgroup per CU for the target's gate/up projection (1792 tiles): 44 us against 47
-                if (wide) PSD_GEMM(2, 8, 7, 2); else PSD_GEMM(1, 8, 7, 2);
+                if (wide) PSD_GEMM(2, 8, 7); else PSD_GEMM(1, 8, 7);
                 done = true;
             } else if (!wide && tiles == 1024 && a.KS >= 96) {
-                PSD_GEMM(1, 8, 4, 2);   // likewise the qualifier's (1024 tiles, K 3072): 20.2 us against 21.1; not for K 2048
+                PSD_GEMM(1, 8, 4);   // likewise the qualifier's (1024 tiles, K 3072): 20.2 us against 21.1; not for K 2048
                 done = true;
             }
         }
@@ -2312,22 +2294,22 @@ static void launch_gemm_bf16(Launch& L, const char* family, GemmArgs a) {
         a.lb_slots = lb_slots;
 #define PSD_GEMM_LB(NW_, RT_)                                                                                      \
     do {                                                                                                           \
-        if constexpr (kHasLb) gemm_bf16<1, NW_, RT_, EPI, 2, true><<<tiles / RT_, 64 * NW_, lb_bytes, L.s>>>(a);   \
+        if constexpr (kHasLb) gemm_bf16<1, NW_, RT_, EPI, true><<<tiles / RT_, 64 * NW_, lb_bytes, L.s>>>(a);   \
     } while (0)
         // one column tile, at most 7 K steps per wave: the variant that asks for a wave's whole range at once
         const bool short_k = !wide && !lb && (a.KS + 15) / 16 <= 7 && (EPI == EPI_RESID || EPI == EPI_QKV);
         if (done) {
         } else if (tiles <= 256) {
             if (lb) PSD_GEMM_LB(16, 1);
-            else if (wide) PSD_GEMM(2, 16, 1, 2);
+            else if (wide) PSD_GEMM(2, 16, 1);
             else if (short_k) {
-                if constexpr (EPI == EPI_RESID || EPI == EPI_QKV) gemm_bf16<1, 16, 1, EPI, 2, false, true><<<tiles, 64 * 16, 0, L.s>>>(a);
+                if constexpr (EPI == EPI_RESID || EPI == EPI_QKV) gemm_bf16<1, 16, 1, EPI, false, true><<<tiles, 64 * 16, 0, L.s>>>(a);
             }
-            else PSD_GEMM(1, 16, 1, 2);
+            else PSD_GEMM(1, 16, 1);
         } else if (tiles % 2 == 0) {
-            if (lb) PSD_GEMM_LB(8, 2); else if (wide) PSD_GEMM(2, 8, 2, 2); else PSD_GEMM(1, 8, 2, 2);
+            if (lb) PSD_GEMM_LB(8, 2); else if (wide) PSD_GEMM(2, 8, 2); else PSD_GEMM(1, 8, 2);
         } else {
-            if (lb) PSD_GEMM_LB(8, 1); else if (wide) PSD_GEMM(2, 8, 1, 2); else PSD_GEMM(1, 8, 1, 2);
+            if (lb) PSD_GEMM_LB(8, 1); else if (wide) PSD_GEMM(2, 8, 1); else PSD_GEMM(1, 8, 1);
         }
 #undef PSD_GEMM_LB
     }
@@ -2408,19 +2390,19 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
             L.end();
         } else {
             if (!sweep) {
-            L.begin("attn_combine", act);
-            // more than eight key ranges: the form that fetches a row's partials in one round (its LDS need grows with the
-            // ranges; the dependent-rounds form takes over where that no longer fits)
-            const size_t cmb_lds = ((size_t)nsplit * (hd + 4) + 1) * sizeof(float);
-            if (nsplit > 8 && cmb_lds <= 64 * 1024) {
-                if (c128) attn_combine_long<kWideCT><<<dim3(wmax, H), 256, cmb_lds, stream>>>(M.attn_part, M.desc, xb2, H, hd, nsplit);
-                else attn_combine_long<2><<<dim3(wmax, H), 256, cmb_lds, stream>>>(M.attn_part, M.desc, xb2, H, hd, nsplit);
-            } else if (c128) {
-                attn_combine_bf16<kWideCT><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, xb2, H, hd);
-            } else {
-                attn_combine_bf16<2><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, xb2, H, hd);
-            }
-            L.end();
+                L.begin("attn_combine", act);
+                // more than eight key ranges: the form that fetches a row's partials in one round (its LDS need grows with the
+                // ranges; the dependent-rounds form takes over where that no longer fits)
+                const size_t cmb_lds = ((size_t)nsplit * (hd + 4) + 1) * sizeof(float);
+                if (nsplit > 8 && cmb_lds <= 64 * 1024) {
+                    if (c128) attn_combine_long<kWideCT><<<dim3(wmax, H), 256, cmb_lds, stream>>>(M.attn_part, M.desc, xb2, H, hd, nsplit);
+                    else attn_combine_long<2><<<dim3(wmax, H), 256, cmb_lds, stream>>>(M.attn_part, M.desc, xb2, H, hd, nsplit);
+                } else if (c128) {
+                    attn_combine_bf16<kWideCT><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, xb2, H, hd);
+                } else {
+                    attn_combine_bf16<2><<<dim3(wmax, H), hd, 0, stream>>>(M.attn_part, M.desc, xb2, H, hd);
+                }
+                L.end();
             }
             launch_gemm_bf16<EPI_RESID>(L, "gemm_o", a);
         }
