@@ -265,6 +265,27 @@ def test_bf16_merge_of_many_key_ranges_is_bit_exact(which):
     assert np.array_equal(out[0], out[1])
 
 
+# few query tiles: passes of every width merge partials, beyond 64 ranges in two turns of a wave's lanes, and beyond 124 ranges at
+# head dim 128 range by range from memory; with 16 heads the 512-token passes of the same model sweep
+@pytest.mark.parametrize("shape,n", [(ModelShape(1, 512, 4, 4, 512, 200), 8300), (ModelShape(1, 512, 4, 4, 512, 200), 16100),
+                                     (ModelShape(1, 2048, 16, 16, 512, 200), 16100)])
+def test_bf16_merge_routes_over_many_key_ranges_are_bit_exact(shape, n):
+    stub = ModelShape(1, 64, 2, 1, 64, 200)
+    small = synth.target_weights(stub, 83, synth.DTYPE_BF16, sigma=0.03)
+    blob = synth.target_weights(shape, 84, synth.DTYPE_BF16, sigma=0.03)
+    ctx = _ctx((stub, stub, shape), (small, small, blob), synth.DTYPE_BF16, 10000.0, n + 540, k1=1, k2=1)
+    toks = synth.tokens(16, 0, n + 515, 200)
+    for pos in range(0, n, 500):
+        ctx.forward(2, toks[pos:min(pos + 500, n)], pos, want_logits=False)
+    out = []
+    for step in (512, 128, 32):
+        for pos in range(n, n + 512, step):
+            ctx.forward(2, toks[pos:pos + step], pos, want_logits=False)
+        out.append(ctx.forward(2, toks[n + 512:n + 515], n + 512))
+    ctx.close()
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
 def test_fp32_attention_routes_agree():
     # up to eight key ranges one launch attends and merges, beyond that two do: the same arithmetic, so a token at the
     # change-over has the same logits whichever bucket of contexts its pass was launched for; and both match the oracle
@@ -274,7 +295,7 @@ def test_fp32_attention_routes_agree():
     toks = synth.tokens(19, 0, n, 131)
     ref = oracle.Model(shape, blobs[0], synth.DTYPE_F32, 10000.0, 1200).forward(toks, 0)
     got = []
-    for widths in ((32,), (7,)):   # 32-token passes are launched for the longer bucket 25 tokens earlier
+    for widths in ((32,), (7,)):   # launched for the longer bucket from the first pass behind 960 tokens on: at 992 and at 966
         ctx = _ctx((shape,) * 3, blobs, synth.DTYPE_F32, 10000.0, 1200, flags=0x100)
         out, pos = [], 0
         while pos < n:

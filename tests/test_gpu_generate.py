@@ -299,10 +299,12 @@ def test_generation_survives_expired_waits(tiny_stack):
     cfg, d, q, t, prompt = tiny_stack
     ctx = _ctx(cfg, (d, q, t), 16 + 32 + 10, 0.004, 0.012, 4, 8)
     ref, _ = ctx.generate(prompt, 32, 3)
+    before = psd.get_accept_expiries()
     try:
-        psd.set_accept_path(3)     # waits expire at once; vocabulary 512 is a single chunk, so nothing ever waits
+        psd.set_accept_path(3)     # waits expire at once: no row waits (one chunk), but the decision does, for its row
         out, _ = ctx.generate(prompt, 32, 3)
         assert np.array_equal(out, ref)
+        assert psd.get_accept_expiries() > before   # the stage has been run again behind the two-launch sweep
     finally:
         psd.set_accept_path(0)
     ctx.close()
