@@ -792,25 +792,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16(const GemmArgs a) {
     }
 }
 
-// Projections of a prompt-ingestion pass (33..512 tokens).  A workgroup of eight waves (two per SIMD) owns 8 RTW row
-// tiles x TCW column tiles; every wave multiplies RTW row tiles of its own with all of the group's columns:
-//   - weight blocks go from memory straight into the registers of the one wave that uses them, three K steps ahead
-//     (they are stored in operand order, so nothing is gained by a detour through LDS);
-//   - the group's operand (hi and lo halves) goes through three LDS buffers: a step's blocks are asked for six steps
-//     ahead, written two steps ahead and read by all waves.  One barrier per step (per KB steps where a step is few MFMAs),
-//     and the first blocks of the next step are read before it, so a step does not begin with an LDS latency.
-// Bound: the matrix cores.  A loop of these MFMAs alone settles at 1.42-1.48 PFLOP/s on this part (a plain library
-// product of 8192^3 reaches 1.48); the draft's gate/up projection (16384 x 2048, 512 columns, hi + lo) runs at 1.11
-// PFLOP/s, 62 us.  The rest is the launch, the first loads and the epilogue (14 us of it, by extrapolating the K loop
-// to zero steps).  With the weights staged through LDS as well (4 x 4 tiles per wave) it took 75 us, with four waves of
-// 4 x 8 tiles, one per SIMD, 78 us: nothing covers a wave's barriers and folds there.
-// The arithmetic is that of gemm_bf16 with NW waves: K is cut at the same NW boundaries, each range is accumulated
-// from zero by the same MFMA sequence, and the ranges are added in the same order, so the result has the same bits as
-// the narrow kernels'.
-// EPI_QKV and EPI_RESID have too few row tiles to fill the device: K is cut into the four groups of ranges that the
-// narrow kernels add up separately (group_sum), a workgroup does one of them and leaves its sums in `part`
-// ([group][row tile][column tile of the launch][64 lanes], fp32), and panel_finish adds the groups and runs the epilogue (target's
-// down projection and o projection at 512 columns: 174 us on average as one launch, 74 + 12 us in two).
 // rms scale of every column of a wide pass, once for all workgroups of the gate/up projection (each of them would
 // otherwise read 128 KB of partial sums for its own columns: 16 us of a 95 us launch on the draft's shape).
 // grid column tiles, 256 threads.
@@ -824,6 +805,25 @@ __global__ __launch_bounds__(256) void panel_scale(const GemmArgs a, float* __re
     if (threadIdx.x < 16) rs_out[blockIdx.x * 16 + cc] = ss_scale<NW, 16>(a, ssp, cc);
 }
 
+// Projections of a prompt-ingestion pass (33..512 tokens).  A workgroup of eight waves (two per SIMD) owns 8 RTW row
+// tiles x TCW column tiles; every wave multiplies RTW row tiles of its own with all of the group's columns:
+//   - weight blocks go from memory straight into the registers of the one wave that uses them, three chunks ahead
+//     (they are stored in operand order, so nothing is gained by a detour through LDS);
+//   - the group's operand (hi and lo halves) goes through three LDS buffers of one chunk, KB K steps, each: a chunk's blocks are
+//     asked for six chunks ahead, written two ahead and read by all waves.  One barrier per chunk (two steps where a step is
+//     few MFMAs), and the first blocks of the next chunk are read before it, so none begins with an LDS latency.
+// Bound: the matrix cores.  A loop of these MFMAs alone settles at 1.42-1.48 PFLOP/s on this part (a plain library
+// product of 8192^3 reaches 1.48); the draft's gate/up projection (16384 x 2048, 512 columns, hi + lo) runs at 1.11
+// PFLOP/s, 62 us.  The rest is the launch, the first loads and the epilogue (14 us of it, by extrapolating the K loop
+// to zero steps).  With the weights staged through LDS as well (4 x 4 tiles per wave) it took 75 us, with four waves of
+// 4 x 8 tiles, one per SIMD, 78 us: nothing covers a wave's barriers and folds there.
+// The arithmetic is that of gemm_bf16 with NW waves: K is cut at the same NW boundaries, each range is accumulated
+// from zero by the same MFMA sequence, and the ranges are added in the same order, so the result has the same bits as
+// the narrow kernels'.
+// EPI_QKV and EPI_RESID have too few row tiles to fill the device: K is cut into the four groups of ranges that the
+// narrow kernels add up separately (group_sum), a workgroup does one of them and leaves its sums in `part`
+// ([group][row tile][column tile of the launch][64 lanes], fp32), and panel_finish adds the groups and runs the epilogue (target's
+// down projection and o projection at 512 columns: 174 us on average as one launch, 74 + 12 us in two).
 template <int NW, int EPI, int RTW, int TCW, int KB>
 __global__ __launch_bounds__(512, 2) void gemm_panel(const GemmArgs a, const int tiles, const int ncg, const int cg0, f32x4* __restrict__ part) {
     constexpr int CT = kWideCT;
