@@ -287,16 +287,18 @@ int psd_accept_batch_noalloc(const float* logits_p, const float* logits_q, const
  *   0  automatic: one launch that reads every logit once when a row has at most 64 chunks of 5120 entries,
  *      else two launches that read the logits twice
  *   1  always two launches     2  same as 0
- *   3  test aid: as 0, but a workgroup's wait for the rest of its row expires at once unless it is already
- *      satisfied, so the expiry handling below can be exercised without a stuck kernel
+ *   3  test aid: as 0, but a workgroup's wait for others of its launch (in the sweep, and in the one-launch passes of small
+ *      fp32 models) expires at once unless it is already satisfied, so the expiry handling below can be exercised without
+ *      a stuck kernel
  * Both sweeps give bit-identical results.  When a wait expires, psd_accept, psd_generate and psd_generate_sd
- * switch the process to path 1 and run the stage again; psd_get_accept_path tells which path is in force.
+ * switch the process to path 1 and run the stage again; psd_get_accept_path tells which path is in force.  When one expires in a
+ * pass, the context runs that pass again, and all later ones, as a launch per projection (bit-identical as well).
  * The switch may be flipped while other threads run stages (they pick it up at their next stage).  Returns PSD_EINVAL
  * for other values. */
 int psd_set_accept_path(int32_t path);
 int psd_get_accept_path(void);
-/* How many times, in this process, a bounded wait expired and the library ran a stage again on path 1: normally 0;
- * anything else explains an ACCEPT slowdown (the two-launch sweep reads the logits twice). */
+/* How many times, in this process, a bounded wait expired and the library ran a stage again on path 1, or a pass again in many
+ * launches: normally 0; anything else explains a slowdown (the two-launch sweep reads the logits twice). */
 int64_t psd_get_accept_expiries(void);
 
 /* Fresh sample from softmax(logits / temperature) by the exponential race (how the

@@ -31,6 +31,7 @@
 
 #include "psd_device.h"
 #include "psd_host.h"
+#include "psd_model.h"
 
 // Every fused multiply-add in this file is written out: the compiler may not fuse a product into a
 // neighbouring sum on its own, so variants of one kernel round identically.
@@ -57,6 +58,8 @@ void accept_wait_expired() {
     g_accept_path.store(1);
     g_wait_expiries.fetch_add(1);
 }
+unsigned long long wait_ticks() { return g_wait_ticks.load(); }
+void note_wait_expired() { g_wait_expiries.fetch_add(1); }
 
 // base-2 maximum of a chunk and its sum of 2^(z - m), for the verifier row (p) and the proposer row (q);
 // each half is published with one 64-bit store and is valid once its m is not the unwritten pattern
@@ -799,16 +802,10 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
 // score_v = z_v / temperature - ln(-ln u_v); token = argmax (the exponential race in log form, so no
 // normalisation pass is needed)
 // greedy: the key is the logit itself (the top prediction; no random numbers)
-__global__ __launch_bounds__(kAccThreads) void sample_partial(const float* logits, int V, int nch, float inv_temp,
-                                                              uint64_t seed, uint32_t position0,
-                                                              const SampleCtl* ctl, KeyIdx* parts, int greedy) {
+// the best entry of chunk `ch` of a row, by a whole workgroup
+__device__ inline KeyIdx sample_chunk(const float* row, int V, int ch, float inv_temp, uint64_t seed, uint32_t pos, int greedy) {
     __shared__ KeyIdx smk[4];
-    const int ch = blockIdx.x, r = blockIdx.y;
-    int row0 = 0;
-    if (ctl) { seed = ctl->seed; position0 = (uint32_t)ctl->position; row0 = ctl->row; }
-    const float* row = logits + (size_t)(row0 + r) * V;
     const bool vec = (V & 3) == 0;
-    const uint32_t pos = position0 + (uint32_t)r;
     KeyIdx best{-INFINITY, 0x7fffffff};
 #pragma unroll
     for (int j = 0; j < kQuadsPerThread; ++j) {
@@ -827,29 +824,87 @@ __global__ __launch_bounds__(kAccThreads) void sample_partial(const float* logit
         for (int e = 0; e < 4; ++e)
             if (v + e < V) best = better(best, KeyIdx{a[e] * inv_temp - logf(-logf(u[e])), v + e});
     }
-    best = block_best<4>(best, smk);
+    return block_best<4>(best, smk);
+}
+
+// chain (optional): seed, position and row come from the draft chain's state
+__global__ __launch_bounds__(kAccThreads) void sample_partial(const float* logits, int V, int nch, float inv_temp,
+                                                              uint64_t seed, uint32_t position0,
+                                                              const SampleCtl* chain, KeyIdx* parts, int greedy) {
+    const int ch = blockIdx.x, r = blockIdx.y;
+    int row0 = 0;
+    if (chain) { seed = chain->seed; position0 = (uint32_t)chain->position; row0 = chain->row; }
+    const KeyIdx best = sample_chunk(logits + (size_t)(row0 + r) * V, V, ch, inv_temp, seed, position0 + (uint32_t)r, greedy);
     if (threadIdx.x == 0) parts[(size_t)r * nch + ch] = best;
 }
 
 // one wave per row; the order of the comparisons is free: equal keys always resolve to the lowest index
+__device__ inline KeyIdx sample_pick(const KeyIdx* parts, int nch) {
+    KeyIdx best{-INFINITY, 0x7fffffff};
+    for (int c = threadIdx.x; c < nch; c += kWave) best = better(best, parts[c]);
+    return wave_best(best);
+}
 __global__ __launch_bounds__(64) void sample_final(const KeyIdx* parts, int nch, int32_t* tokens_out) {
     const int r = blockIdx.x;
-    KeyIdx best{-INFINITY, 0x7fffffff};
-    for (int c = threadIdx.x; c < nch; c += kWave) best = better(best, parts[(size_t)r * nch + c]);
-    best = wave_best(best);
+    const KeyIdx best = sample_pick(parts + (size_t)r * nch, nch);
     if (threadIdx.x == 0) tokens_out[r] = best.idx;
 }
 
-int sample_launch(const float* logits, int n_rows, int vocab, float temperature, uint64_t seed, uint32_t position0,
-                  const SampleCtl* ctl, int32_t* tokens_out, void* partial, hipStream_t stream, char* errbuf, int greedy) {
+// one thread: publishes draft token t to the next draft pass and to the verifier's
+__device__ inline void chain_advance(const ChainStep& s, int t) {
+    const int step = s.chain->row;
+    s.samp_tok[0] = t;
+    if (step < kMaxW) s.round_tok[step] = t;
+    if (s.q_desc && s.chain->q_base >= 0 && s.chain->q_base + step < kMaxW) s.q_desc->tok[s.chain->q_base + step] = t;
+    s.d_desc->pos0 += s.d_desc->w;
+    s.d_desc->w = 1;
+    s.d_desc->tok[0] = t;
+    s.d_desc->logit_row0 = step + 1;
+    s.d_desc->tag0 += s.d_desc->tag_step;
+    s.chain->row = step + 1;
+    s.chain->position += 1;
+}
+// one wave: picks the winner among the per-chunk winners of the race
+__global__ __launch_bounds__(64) void draft_pick_advance(const KeyIdx* parts, int nch, const ChainStep s) {
+    const KeyIdx best = sample_pick(parts, nch);
+    if (threadIdx.x == 0) chain_advance(s, best.idx);
+}
+// Vocabularies of one chunk: the race's only workgroup has the winner, one launch of ~3.5 us less
+__global__ __launch_bounds__(kAccThreads) void draft_sample_advance(const float* logits, int V, float inv_temp, int greedy, const ChainStep s) {
+    const KeyIdx best = sample_chunk(logits + (size_t)s.chain->row * V, V, 0, inv_temp, s.chain->seed, (uint32_t)s.chain->position, greedy);
+    if (threadIdx.x == 0) chain_advance(s, best.idx);
+}
+
+static int sample_args(const float* logits, int n_rows, int vocab, float temperature, const void* partial, char* errbuf) {
     if (!logits || !partial) PSD_FAIL(PSD_EINVAL, errbuf, "sample: null pointer");
     if (n_rows < 1 || n_rows > 65535 || vocab < 1 || !(temperature > 0.f))
         PSD_FAIL(PSD_EINVAL, errbuf, "sample: n_rows=%d vocab=%d temperature=%g", n_rows, vocab, temperature);
     if ((uintptr_t)logits & ((vocab & 3) == 0 ? 15 : 3)) PSD_FAIL(PSD_EINVAL, errbuf, "sample: logits rows must be 16-byte aligned (4-byte when the vocabulary is not a multiple of 4)");
+    return PSD_OK;
+}
+
+int sample_launch(const float* logits, int n_rows, int vocab, float temperature, uint64_t seed, uint32_t position0,
+                  int32_t* tokens_out, void* partial, hipStream_t stream, char* errbuf, int greedy) {
+    int rc = sample_args(logits, n_rows, vocab, temperature, partial, errbuf);
+    if (rc != PSD_OK) return rc;
     const int nch = accept_chunks(vocab);
     sample_partial<<<dim3(nch, n_rows), kAccThreads, 0, stream>>>(logits, vocab, nch, 1.0f / temperature, seed,
-                                                                   position0, ctl, (KeyIdx*)partial, greedy);
-    if (tokens_out) sample_final<<<n_rows, 64, 0, stream>>>((const KeyIdx*)partial, nch, tokens_out);
+                                                                   position0, nullptr, (KeyIdx*)partial, greedy);
+    sample_final<<<n_rows, 64, 0, stream>>>((const KeyIdx*)partial, nch, tokens_out);
+    PSD_HIP(hipGetLastError(), errbuf);
+    return PSD_OK;
+}
+
+int draft_sample_launch(const float* logits, int vocab, float temperature, int greedy, void* partial, const ChainStep& step, hipStream_t stream, char* errbuf) {
+    int rc = sample_args(logits, 1, vocab, temperature, partial, errbuf);
+    if (rc != PSD_OK) return rc;
+    const int nch = accept_chunks(vocab);
+    if (nch == 1) {
+        draft_sample_advance<<<1, kAccThreads, 0, stream>>>(logits, vocab, 1.0f / temperature, greedy, step);
+    } else {
+        sample_partial<<<nch, kAccThreads, 0, stream>>>(logits, vocab, nch, 1.0f / temperature, 0, 0, step.chain, (KeyIdx*)partial, greedy);
+        draft_pick_advance<<<1, 64, 0, stream>>>((const KeyIdx*)partial, nch, step);
+    }
     PSD_HIP(hipGetLastError(), errbuf);
     return PSD_OK;
 }

@@ -177,7 +177,7 @@ extern "C" int psd_sample(const float* logits, int32_t n_rows, int32_t vocab, fl
         l = (const float*)dl.p;
         t = (int32_t*)dt.p;
     }
-    int rc = sample_launch(l, n_rows, vocab, temperature, seed, position0, nullptr, t, part.p, nullptr, err);
+    int rc = sample_launch(l, n_rows, vocab, temperature, seed, position0, t, part.p, nullptr, err);
     if (rc != PSD_OK) return rc;
     PSD_HIP(hipDeviceSynchronize(), err);
     if (where == 0) PSD_HIP(hipMemcpy(tokens_out, t, n_rows * sizeof(int32_t), hipMemcpyDeviceToHost), err);

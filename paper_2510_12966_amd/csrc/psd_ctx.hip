@@ -27,7 +27,9 @@ struct RoundResult {  // pinned host memory that publish_round fills with what a
     int32_t tok[kMaxW];
     float div[kMaxW];
     uint32_t seq;     // written last: the result with this number is there
+    uint32_t stuck;   // set by a one-launch pass whose bounded wait expired
 };
+constexpr int kPassExpired = 1;   // (internal) the round's passes have to be run again
 
 // Adaptive controller (the header states the rule).  Pure host arithmetic on accept counts between outer iterations.
 struct Controller {
@@ -167,26 +169,6 @@ struct psd_ctx {
 
 namespace psd {
 
-// one wave: picks the winner among the per-chunk winners of the sampling race (the comparisons of sample_final; equal
-// keys resolve to the lowest index) and publishes the token to the next draft pass and to the qualifier pass
-__global__ __launch_bounds__(64) void draft_pick_advance(const KeyIdx* parts, int nch, int32_t* samp_tok, SampleCtl* chain,
-                                                         PassDesc* d_desc, PassDesc* q_desc, int32_t* round_tok) {
-    KeyIdx best{-INFINITY, 0x7fffffff};
-    for (int ch = threadIdx.x; ch < nch; ch += kWave) best = better(best, parts[ch]);
-    best = wave_best(best);
-    if (threadIdx.x != 0) return;
-    const int t = best.idx, step = chain->row;
-    samp_tok[0] = t;
-    if (step < kMaxW) round_tok[step] = t;
-    if (q_desc && chain->q_base >= 0 && chain->q_base + step < kMaxW) q_desc->tok[chain->q_base + step] = t;
-    d_desc->pos0 += d_desc->w;
-    d_desc->w = 1;
-    d_desc->tok[0] = t;
-    d_desc->logit_row0 = step + 1;
-    chain->row = step + 1;
-    chain->position += 1;
-}
-
 // Host data into device memory: up to four pieces of one pinned staging slot, read across the bus by one small launch.  A
 // round's descriptors and chain state travelled as three stream copies, each a launch of its own with 8-10 us around it.
 struct Pieces {
@@ -261,9 +243,19 @@ static int upload_pieces(psd_ctx* c, std::initializer_list<Piece> pieces) {
     return PSD_OK;
 }
 
+// The stream has been waited for: whether the bounded wait of a one-launch pass has expired since this was last asked.  Passes are
+// chains of launches in this context from then on; nothing the host keeps has moved, so the caller runs the passes again.
+static bool passes_expired(psd_ctx* c) {
+    if (!__atomic_load_n(&c->res->stuck, __ATOMIC_ACQUIRE)) return false;
+    __atomic_store_n(&c->res->stuck, 0u, __ATOMIC_RELEASE);
+    for (auto& M : c->M) M.one_launch = false;
+    note_wait_expired();
+    return true;
+}
+
 // Enqueues the round's result for the host and waits for it: the host watches its own memory (a stream synchronisation costs
 // 10-20 us more per round) and asks the stream now and then, so that an error or a result that never comes ends the wait.
-// Everything enqueued before is then done.
+// Everything enqueued before is then done.  kPassExpired: it has to be run again.
 static int fetch_round(psd_ctx* c, const AcceptOut* acc, const int32_t* tok, int n_tok, int n_div) {
     const uint32_t seq = ++c->res_seq;
     publish_round<<<1, 64, 0, c->stream>>>(acc, tok, n_tok, c->acc_div, n_div, c->res_dev, seq);
@@ -276,9 +268,12 @@ static int fetch_round(psd_ctx* c, const AcceptOut* acc, const int32_t* tok, int
         }
         __builtin_ia32_pause();
     }
-    if (!there() || c->trace) return stage_sync(c);   // reports the error; a trace copies rows behind the stream's back
+    if (!there() || c->trace) {   // reports the error; a trace copies rows behind the stream's back
+        int rc = stage_sync(c);
+        if (rc != PSD_OK) return rc;
+    }
     c->stage_since_sync = 0;
-    return PSD_OK;
+    return passes_expired(c) ? kPassExpired : PSD_OK;
 }
 
 // KV pages for positions < upto of model M (pages wholly beyond `keep` are returned); the page-table entries that
@@ -315,18 +310,17 @@ static int run_pass(psd_ctx* c, int mi, int wcls, float* logits, bool with_sampl
     // Upper bound of the pass's last position.  The host mirror of the length moves once per round: a catch-up pass of
     // up to kMaxW tokens and up to kMaxW - 1 single-token sampling steps may be launched from one value of it.
     M.ctx_bucket = ctx_bucket_index(std::min(M.max_seq, M.len + std::max(wcls, 2 * kMaxW)));
-    // only the decoding loop's three pass shapes are captured; prefill, the test hook and plain generation stay eager
-    const bool use_graph = allow_graph && (c->prm.flags & PSD_FLAG_GRAPH) && !c->prof.on;
+    // only the decoding loop's three pass shapes are captured; prefill, the test hook and plain generation stay eager.  A pass of one
+    // launch is launched as it is: a graph costs the host 16 us to launch, a kernel 2 to 4.
+    const bool use_graph = allow_graph && (c->prm.flags & PSD_FLAG_GRAPH) && !c->prof.on && !model_one_launch(M, wcls, logits);
     auto enqueue = [&](Profiler* prof) -> int {
         int rc = model_forward(M, wcls, logits, stream, prof, c->err);
         if (rc != PSD_OK) return rc;
         if (with_sample) {
             if (prof && prof->on) prof->begin(c->stream, prof->row_of("sample draft"), (double)c->V * 4);
-            rc = sample_launch(logits, 1, c->V, c->prm.temperature, 0, 0, c->chain, nullptr, c->samp_part,
-                               c->stream, c->err, (c->prm.flags & PSD_FLAG_GREEDY) ? 1 : 0);
+            rc = draft_sample_launch(logits, c->V, c->prm.temperature, (c->prm.flags & PSD_FLAG_GREEDY) ? 1 : 0, c->samp_part,
+                                     ChainStep{c->samp_tok, c->chain, M.desc, c->M[verifier].desc, c->round_tok}, c->stream, c->err);
             if (rc != PSD_OK) return rc;
-            draft_pick_advance<<<1, 64, 0, c->stream>>>((const KeyIdx*)c->samp_part, accept_chunks(c->V), c->samp_tok, c->chain,
-                                                         M.desc, c->M[verifier].desc, c->round_tok);
             if (prof && prof->on) prof->end(c->stream);
         }
         return PSD_OK;
@@ -439,15 +433,15 @@ static int note_rows(psd_ctx* c, int mi, const float* rows, int n) {
     return row_stats_launch(rows, n, c->V, c->prm.temperature, nullptr, nullptr, c->rs_acc + 3 * mi, c->rs_ws, c->stream, c->err);
 }
 
-// One ACCEPT stage on the stream, its result in c->res.  n_tok: how many of the round's draft tokens to bring back as
-// well.  follows: the verifier's pass ended the last timer span and nothing was enqueued since.  The kernels of a row wait for each other under a clock; should that wait
+// One ACCEPT stage on the stream, its result in c->res (or kPassExpired: the logits it was to judge are no good).  n_tok: how many of the round's draft tokens to bring back as
+// well.  The verifier's pass ended the last timer span and nothing was enqueued since.  The kernels of a row wait for each other under a clock; should that wait
 // ever expire (n_accepted = -1: the launch was not resident as a whole), the library switches to the two-launch
 // sweep for good and the stage is run again.
 static int accept_sync(psd_ctx* c, const char* prof_row, const float* lp, const float* lq, const int32_t* toks, int k,
-                       float T, uint64_t seed, uint32_t pos0, uint32_t stage, int bonus, int assisted, int n_tok, bool follows) {
+                       float T, uint64_t seed, uint32_t pos0, uint32_t stage, int bonus, int assisted, int n_tok) {
     for (int attempt = 0; attempt < 2; ++attempt) {
         if (c->prof.on) c->prof.begin(c->stream, c->prof.row_of(prof_row), (double)(2 * k + 1) * c->V * 4);
-        if (follows && attempt == 0) c->timer.follow(3); else c->timer.begin(c->stream, 3);
+        if (attempt == 0) c->timer.follow(3); else c->timer.begin(c->stream, 3);
         int rc = accept_launch(lp, lq, toks, 1, k, c->V, T, c->prm.temperature, seed, pos0, stage, bonus, c->acc_out,
                                c->acc_div, c->acc_ws, c->acc_ws_bytes, c->stream, c->err, nullptr, nullptr, assisted);
         if (rc != PSD_OK) return rc;
@@ -589,6 +583,8 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     c->res = (RoundResult*)(c->stage + kRingBytes);
     c->res_dev = (RoundResult*)(c->stage_dev + kRingBytes);
     c->res->seq = 0;
+    c->res->stuck = 0;
+    for (auto& M : c->M) M.stuck = &c->res_dev->stuck;
     for (auto& e : c->ev) CK(hipEventCreate(&e));
     for (auto& st : c->aux) CK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
     for (auto& e : c->aux_ready) CK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -676,10 +672,13 @@ extern "C" int psd_forward(psd_ctx* c, int32_t which, const int32_t* tokens, int
     PassDesc d;
     fill_desc(d, tokens, 0, w, 0, logits_out ? w : 0, 0);
     d.pos0 = pos0;
-    if ((rc = upload(c, M.desc, &d, desc_bytes(d))) != PSD_OK) return rc;
-    if ((rc = run_pass(c, which, wclass(w), logits_out ? c->HL : nullptr, false)) != PSD_OK) return rc;
+    do {
+        if ((rc = model_stamp(M, d, 1, c->stream, c->err)) != PSD_OK) return rc;
+        if ((rc = upload(c, M.desc, &d, desc_bytes(d))) != PSD_OK) return rc;
+        if ((rc = run_pass(c, which, wclass(w), logits_out ? c->HL : nullptr, false)) != PSD_OK) return rc;
+        if ((rc = stage_sync(c)) != PSD_OK) return rc;
+    } while (passes_expired(c));
     M.len = pos0 + w;
-    if ((rc = stage_sync(c)) != PSD_OK) return rc;
     if (logits_out) PSD_HIP(hipMemcpy(logits_out, c->HL, (size_t)w * c->V * sizeof(float), hipMemcpyDeviceToHost), c->err);
     return PSD_OK;
 }
@@ -690,7 +689,6 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
     if (!prompt || n_prompt < 1 || n_new < 0 || (n_new > 0 && !out_tokens)) PSD_FAIL(PSD_EINVAL, c->err, "psd_generate: bad argument");
     const int V = c->V;
     const int greedy = (c->prm.flags & PSD_FLAG_GREEDY) ? 1 : 0;
-    const bool row_stats = (c->prm.flags & PSD_FLAG_ROW_STATS) != 0;
     const int assisted = greedy ? 2 : (c->prm.flags & PSD_FLAG_ASSISTED) ? 1 : 0;  // rule of the qualifier stage
     // thresholds and window lengths of the current outer iteration: fixed, or moved by the adaptive controller
     Controller& ctl = c->ctl;
@@ -742,22 +740,24 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
             fill_desc(dd, seq.data(), D.len, L, 0, 1, 0);
             fill_desc(qd, seq.data(), Q.len, L, m, m + 1, nbuf);
             SampleCtl sc{seed, L, 0, hq, 0};
+            if ((rc = model_stamp(D, dd, m, c->stream, c->err)) != PSD_OK || (rc = model_stamp(Q, qd, 1, c->stream, c->err)) != PSD_OK) return rc;
             if ((rc = upload_pieces(c, {{D.desc, &dd, desc_bytes(dd)}, {Q.desc, &qd, desc_bytes(qd)}, {c->chain, &sc, sizeof(sc)}})) != PSD_OK) return rc;
             c->timer.begin(c->stream, 0);
             // the first step also ingests what the draft has not cached (1 to 3 tokens), the others one token each
             for (int i = 0; i < m; ++i)
                 if ((rc = run_pass(c, 0, wclass(i == 0 ? L - D.len : 1), c->DL, true, true)) != PSD_OK) return rc;
             c->timer.end(c->stream);
-            st.passes_d += m;
             c->timer.follow(1);
             if ((rc = run_pass(c, 1, wclass(hq + m), c->QL, false, true)) != PSD_OK) return rc;
             c->timer.end(c->stream);
+            const int bonus = nbuf + m < k2;
+            rc = accept_sync(c, "accept stage1", c->QL + (size_t)nbuf * V, c->DL, c->round_tok, m, T_q, seed, (uint32_t)L, 1u, bonus, assisted, m);
+            if (rc == kPassExpired) continue;
+            if (rc != PSD_OK) return rc;
+            st.passes_d += m;
             st.passes_q++;
             if ((rc = note_rows(c, 0, c->DL, m)) != PSD_OK) return rc;
             if ((rc = note_rows(c, 1, c->QL + (size_t)nbuf * V, m + 1)) != PSD_OK) return rc;
-            const int bonus = nbuf + m < k2;
-            if ((rc = accept_sync(c, "accept stage1", c->QL + (size_t)nbuf * V, c->DL, c->round_tok, m, T_q, seed,
-                                  (uint32_t)L, 1u, bonus, assisted, m, !row_stats)) != PSD_OK) return rc;
             const int n = c->res->acc.n_accepted, y = c->res->acc.next_token, has_y = y >= 0;
             if (n < 0 || n > m || (!has_y && (n < m || bonus))) PSD_FAIL(PSD_EHIP, c->err, "internal: impossible ACCEPT result (n=%d y=%d)", n, y);
             if (c->trace) {
@@ -783,14 +783,17 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
         if ((rc = map_pages(c, T, T.len, C + k2)) != PSD_OK) return rc;
         PassDesc td;
         fill_desc(td, seq.data(), T.len, C + k2, 0, k2 + 1, 0);
-        if ((rc = upload_pieces(c, {{T.desc, &td, desc_bytes(td)}, {c->win_tok, seq.data() + C, k2 * sizeof(int32_t)}})) != PSD_OK) return rc;
-        c->timer.begin(c->stream, 2);
-        if ((rc = run_pass(c, 2, wclass(wT), c->TL, false, true)) != PSD_OK) return rc;
-        c->timer.end(c->stream);
+        do {
+            if ((rc = model_stamp(T, td, 1, c->stream, c->err)) != PSD_OK) return rc;
+            if ((rc = upload_pieces(c, {{T.desc, &td, desc_bytes(td)}, {c->win_tok, seq.data() + C, k2 * sizeof(int32_t)}})) != PSD_OK) return rc;
+            c->timer.begin(c->stream, 2);
+            if ((rc = run_pass(c, 2, wclass(wT), c->TL, false, true)) != PSD_OK) return rc;
+            c->timer.end(c->stream);
+            rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->win_tok, k2, T_t, seed, (uint32_t)C, 2u, 1, greedy ? 2 : 0, 0);
+        } while (rc == kPassExpired);
+        if (rc != PSD_OK) return rc;
         st.passes_t++;
         if ((rc = note_rows(c, 2, c->TL, k2 + 1)) != PSD_OK) return rc;
-        if ((rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->win_tok, k2, T_t, seed, (uint32_t)C, 2u, 1,
-                              greedy ? 2 : 0, 0, !row_stats)) != PSD_OK) return rc;
         const int n = c->res->acc.n_accepted, y = c->res->acc.next_token;
         if (n < 0 || n > k2 || y < 0) PSD_FAIL(PSD_EHIP, c->err, "internal: impossible ACCEPT result (n=%d y=%d)", n, y);
         if (c->trace) {
@@ -925,21 +928,22 @@ extern "C" int psd_generate_sd(psd_ctx* c, int32_t proposer, int32_t k, float ta
         fill_desc(pd, seq.data(), P.len, C, 0, 1, 0);
         fill_desc(td, seq.data(), T.len, C, k, k + 1, 0);
         SampleCtl sc{seed, C, 0, ht, 0};
+        if ((rc = model_stamp(P, pd, k, c->stream, c->err)) != PSD_OK || (rc = model_stamp(T, td, 1, c->stream, c->err)) != PSD_OK) return rc;
         if ((rc = upload_pieces(c, {{P.desc, &pd, desc_bytes(pd)}, {T.desc, &td, desc_bytes(td)}, {c->chain, &sc, sizeof(sc)}})) != PSD_OK) return rc;
         c->timer.begin(c->stream, proposer);
         for (int i = 0; i < k; ++i)
             if ((rc = run_pass(c, proposer, wclass(i == 0 ? C - P.len : 1), c->QL, true, true, 2)) != PSD_OK) return rc;
         c->timer.end(c->stream);
-        (proposer == 0 ? st.passes_d : st.passes_q) += k;
         c->timer.follow(2);
         if ((rc = run_pass(c, 2, wclass(ht + k), c->TL, false, true)) != PSD_OK) return rc;
         c->timer.end(c->stream);
+        rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->round_tok, k, tau, seed, (uint32_t)C, 2u, 1, greedy ? 2 : 0, k);
+        if (rc == kPassExpired) continue;
+        if (rc != PSD_OK) return rc;
+        (proposer == 0 ? st.passes_d : st.passes_q) += k;
         st.passes_t++;
         if ((rc = note_rows(c, proposer, c->QL, k)) != PSD_OK) return rc;
         if ((rc = note_rows(c, 2, c->TL, k + 1)) != PSD_OK) return rc;
-        if ((rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->round_tok, k, tau, seed, (uint32_t)C, 2u, 1,
-                              greedy ? 2 : 0, k, !(c->prm.flags & PSD_FLAG_ROW_STATS))) != PSD_OK)
-            return rc;
         const int n = c->res->acc.n_accepted, y = c->res->acc.next_token;
         if (n < 0 || n > k || y < 0) PSD_FAIL(PSD_EHIP, c->err, "internal: impossible ACCEPT result (n=%d y=%d)", n, y);
         if (c->trace) {
@@ -996,11 +1000,15 @@ extern "C" int psd_generate_plain(psd_ctx* c, int32_t which, const int32_t* prom
         if ((rc = map_pages(c, M, M.len, L)) != PSD_OK) return rc;
         PassDesc d;
         fill_desc(d, seq.data(), M.len, L, 0, 1, 0);
-        if ((rc = upload_pieces(c, {{M.desc, &d, desc_bytes(d)}})) != PSD_OK) return rc;
-        if ((rc = run_pass(c, which, wclass(L - M.len), c->HL, false)) != PSD_OK) return rc;
-        if ((rc = sample_launch(c->HL, 1, c->V, c->prm.temperature, seed, (uint32_t)L, nullptr, c->samp_tok, c->samp_part, c->stream, c->err,
-                                (c->prm.flags & PSD_FLAG_GREEDY) ? 1 : 0)) != PSD_OK) return rc;
-        if ((rc = fetch_round(c, nullptr, c->samp_tok, 1, 0)) != PSD_OK) return rc;
+        do {
+            if ((rc = model_stamp(M, d, 1, c->stream, c->err)) != PSD_OK) return rc;
+            if ((rc = upload_pieces(c, {{M.desc, &d, desc_bytes(d)}})) != PSD_OK) return rc;
+            if ((rc = run_pass(c, which, wclass(L - M.len), c->HL, false)) != PSD_OK) return rc;
+            if ((rc = sample_launch(c->HL, 1, c->V, c->prm.temperature, seed, (uint32_t)L, c->samp_tok, c->samp_part, c->stream, c->err,
+                                    (c->prm.flags & PSD_FLAG_GREEDY) ? 1 : 0)) != PSD_OK) return rc;
+            rc = fetch_round(c, nullptr, c->samp_tok, 1, 0);
+        } while (rc == kPassExpired);
+        if (rc != PSD_OK) return rc;
         seq[L] = c->res->tok[0];
         M.len = L;
         (which == 0 ? st.passes_d : which == 1 ? st.passes_q : st.passes_t)++;

@@ -54,6 +54,11 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
                   hipStream_t stream, char* errbuf, int32_t* n_accepted_out = nullptr,
                   int32_t* next_token_out = nullptr, int assisted = 0);
 
+// Bound of the waits between workgroups of one launch, in ticks of the 100 MHz clock (0: test aid)
+unsigned long long wait_ticks();
+// Counts a bounded wait outside the ACCEPT stage that ran out
+void note_wait_expired();
+
 // Called by whoever reads n_accepted = -1: from now on the sweep runs as two launches (no waiting between workgroups).
 void accept_wait_expired();
 
@@ -67,13 +72,9 @@ struct SampleCtl {
 };
 
 // Fresh samples: row r -> token for position position0 + r.  partial: n_rows * accept_chunks(vocab) * 8 bytes.
-// ctl (optional, device): when non-null, seed / position0 / first logits row come from *ctl instead.
 // greedy: the top prediction of every row instead of a sample.
-// tokens_out may be null: then the per-chunk winners stay in `partial` ([n_rows][accept_chunks(vocab)] KeyIdx) and the
-// caller picks among them (in a kernel of its own that has more to do with the token).
 int sample_launch(const float* logits, int n_rows, int vocab, float temperature, uint64_t seed, uint32_t position0,
-                  const SampleCtl* ctl, int32_t* tokens_out, void* partial, hipStream_t stream, char* errbuf,
-                  int greedy = 0);
+                  int32_t* tokens_out, void* partial, hipStream_t stream, char* errbuf, int greedy = 0);
 
 // Entropy (nats) and largest probability of softmax(row / temperature) for n_rows logits rows (device memory).
 // entropy / max_prob: optional [n_rows] outputs; acc: optional device double[3] {rows, sum H, sum p_max} that is

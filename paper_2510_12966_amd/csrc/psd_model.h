@@ -47,8 +47,20 @@ struct PassDesc {
     int32_t pos0;        // position of the first token == number of valid KV rows before the pass
     int32_t n_logit;     // the last n_logit tokens get logit rows (0 = none)
     int32_t logit_row0;  // first destination row in the logits buffer
+    uint32_t tag0;       // one-launch passes: the pass's tags are tag0 + 1 .. tag0 + tag_step (see F32Pass); the next
+    uint32_t tag_step;   // pass of a draft chain starts at tag0 + tag_step
     int32_t tok[kCols];
 };
+
+// A draft step's end: the token goes to the next draft pass and to the verifier's.
+struct ChainStep {
+    int32_t* samp_tok;
+    SampleCtl* chain;
+    PassDesc *d_desc, *q_desc;   // the drafting model's and (may be null) the verifier's
+    int32_t* round_tok;
+};
+// Samples draft token chain->row from its logits row and advances the chain.  partial: accept_chunks(vocab) * 8 bytes.
+int draft_sample_launch(const float* logits, int vocab, float temperature, int greedy, void* partial, const ChainStep& step, hipStream_t stream, char* errbuf);
 
 struct LayerW {
     const float* attn_norm;
@@ -131,6 +143,9 @@ struct Model {
     PanelScratch panel_qkv, panel_res;   // wide passes, sums of the K quarters of the q/k/v, and of the o and down, projections
     float* panel_rs = nullptr;   // wide passes: [512] rms scale per column, for gate/up (in attn_part)
     float* gu = nullptr;      // fp32 models: [32][F], the SwiGLU's output
+    bool one_launch = false;  // fp32 models small enough for it: passes with logits over few key ranges are one launch
+    uint32_t tag_last = 0;    // last tag handed out to a pass
+    uint32_t* stuck = nullptr;   // pinned host memory as the device addresses it: a one-launch pass whose bounded wait expired sets it
     PassDesc* desc = nullptr;
     // host mirror
     int len = 0;  // valid KV rows
@@ -151,10 +166,16 @@ int model_init(Model& M, const psd_model_desc& desc, const char* tag, int max_se
 // just those (the caller sends page 0 for unmapped blocks: every device entry names a valid page at all times).
 int model_map_pages(Model& M, int keep, int upto, int* first_changed, int* n_changed, char* err);
 
+// Gives a descriptor tags of its own for `passes` passes in a row (a draft chain); in stream order, before the descriptor travels.
+int model_stamp(Model& M, PassDesc& d, int passes, hipStream_t stream, char* err);
+
 // Enqueues one pass described by *M.desc (already on the device).  wmax: one of kNarrowClasses = widest pass the launch must cover;
 // 128, 256, 384 or 512 (bf16 models, logits == nullptr, at most ingest_max): prompt ingestion.
 // logits: device [rows][V] destination (may be null when the pass produces none).
 int model_forward(Model& M, int wmax, float* logits, hipStream_t stream, Profiler* prof, char* err);
+
+// Whether the pass that model_forward would enqueue now is one launch (M.ctx_bucket is set, the others as there)
+bool model_one_launch(const Model& M, int wcls, const float* logits);
 
 int model_kernels_init(char* err);  // one-time function attributes
 

@@ -124,6 +124,47 @@ __device__ inline size_t kv_base(int page, int layer, int L, int g, int KV, int 
     return ((((size_t)page * L + layer) * KV + g) * 2 + which) * (size_t)kPage * hd;
 }
 
+// sum over LP lanes (16 or 64), every lane gets it; fixed tree
+template <int LP>
+__device__ inline float lanes_sum(float v) {
+    auto dpp = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v += dpp(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+    v += dpp(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+    v += dpp(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror
+    if constexpr (LP == 64) v = rows_sum(v);
+    return v;
+}
+
+__device__ inline float lanes_max(float v) {   // over a wave
+    auto dpp = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v = fmaxf(v, dpp(v, std::integral_constant<int, 0xB1>{}));
+    v = fmaxf(v, dpp(v, std::integral_constant<int, 0x4E>{}));
+    v = fmaxf(v, dpp(v, std::integral_constant<int, 0x141>{}));
+    v = fmaxf(v, dpp(v, std::integral_constant<int, 0x140>{}));
+    return rows_max(v);
+}
+
+// Arithmetic that the routes of an fp32 pass share, with every fusion written out: the same bits wherever the compiler puts it
+__device__ inline float f32_squares(float4 v) { return fmaf(v.x, v.x, v.y * v.y) + fmaf(v.z, v.z, v.w * v.w); }
+__device__ inline void f32_rotate(float& v1, float& v2, float2 cs) {
+    const float r1 = fmaf(v1, cs.x, -(v2 * cs.y)), r2 = fmaf(v2, cs.x, v1 * cs.y);
+    v1 = r1; v2 = r2;
+}
+__device__ inline float f32_silu_up(float g, float u) {
+#pragma clang fp contract(off)
+    return g / (1.f + expf(-g)) * u;
+}
+__device__ inline float f32_rms(float squares, float inv_k, float eps) { return rsqrtf(fmaf(squares, inv_k, eps)); }
+__device__ inline float f32_score(float dot, float scale) {
+#pragma clang fp contract(off)
+    return dot * scale;
+}
+
 // ---- attention -------------------------------------------------------------------------------------
 // grid (H, nsplit_max), 256 threads.  A workgroup owns one query head and one absolute key range
 // [split * 128, split * 128 + 128); wave j takes the queries c = j, j + 4, ...  Partial result per
@@ -171,11 +212,11 @@ __global__ __launch_bounds__(256) void attn_partial(const float* qkv, const Pass
             float acc = 0.f;
             if (j < visible)
                 for (int i = 0; i < hd; ++i) acc += q[i] * Ks[j * ld + i];
-            s[r] = j < visible ? acc * scale : -INFINITY;
+            s[r] = j < visible ? f32_score(acc, scale) : -INFINITY;
         }
-        const float m = wave_max(fmaxf(s[0], s[1]));
+        const float m = lanes_max(fmaxf(s[0], s[1]));
         const float p0 = expf(s[0] - m), p1 = expf(s[1] - m);  // exp(-inf) = 0 for masked keys
-        const float l = wave_sum(p0 + p1);
+        const float l = lanes_sum<64>(p0 + p1);
         p[lane] = p0;
         p[lane + 64] = p1;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1589,23 +1630,6 @@ struct F32Args {
 };
 constexpr int kF32Chunk = 1024;   // K entries of X staged in LDS at a time
 
-// sum over LP lanes (16 or 64), every lane gets it; fixed tree
-template <int LP>
-__device__ inline float lanes_sum(float v) {
-    auto dpp = [](float x, auto ctrl) {
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
-    };
-    v += dpp(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
-    v += dpp(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
-    v += dpp(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
-    v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror
-    if constexpr (LP == 64) {
-        v += __shfl_xor(v, 16, kWave);
-        v += __shfl_xor(v, 32, kWave);
-    }
-    return v;
-}
-
 template <int EPI, int LP, int NC>
 __global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
     __shared__ float xs[NC][kF32Chunk];
@@ -1640,6 +1664,7 @@ __global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
     const bool once = K <= kF32Chunk;   // X is staged once per column group
     if (a.gain && once)
         for (int k = tid * 4; k < K; k += 1024) *reinterpret_cast<float4*>(gs + k) = *reinterpret_cast<const float4*>(a.gain + k);
+    const float inv_k = 1.f / (float)K;
     const int w = a.desc->w, pos0 = a.desc->pos0;
     const int first = EPI == F32_LOGITS ? w - a.desc->n_logit : 0, row0 = EPI == F32_LOGITS ? a.desc->logit_row0 : 0;
     for (int c0 = first + (int)blockIdx.y * NC; c0 < w; c0 += NC * (int)gridDim.y) {
@@ -1649,14 +1674,14 @@ __global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
             float ss = 0.f;
             for (int k = lane * 4; k < K; k += 256) {
                 const float4 v = *reinterpret_cast<const float4*>(row + k);
-                ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+                ss += f32_squares(v);
             }
             return lanes_sum<64>(ss);
         };
         if (a.gain && !once) {
             for (int c = wave; c < nc; c += 4) {
                 const float ss = square_sum(x0 + (size_t)c * K);
-                if (lane == 0) rsc[c] = rsqrtf(ss / (float)K + a.eps);
+                if (lane == 0) rsc[c] = f32_rms(ss, inv_k, a.eps);
             }
             __syncthreads();
         }
@@ -1690,7 +1715,7 @@ __global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
             if (a.gain && once) {   // squares and scaling out of LDS: X makes one trip from memory
                 for (int c = wave; c < nc; c += 4) {
                     const float ss = square_sum(xs[c]);
-                    if (lane == 0) rsc[c] = rsqrtf(ss / (float)K + a.eps);
+                    if (lane == 0) rsc[c] = f32_rms(ss, inv_k, a.eps);
                 }
                 __syncthreads();
                 for (int i = tid; i < nc * kq; i += 256) {
@@ -1724,7 +1749,7 @@ __global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
                 y[n1] += v1;
                 if (n2 != n1) y[n2] += v2;
             } else if constexpr (EPI == F32_SWIGLU) {
-                a.Y[(size_t)c * a.ldy + n1] = v1 / (1.f + expf(-v1)) * v2;
+                a.Y[(size_t)c * a.ldy + n1] = f32_silu_up(v1, v2);
             } else if constexpr (EPI == F32_LOGITS) {
                 float* y = a.Y + (size_t)(row0 + c - first) * a.ldy;
                 y[n1] = v1;
@@ -1733,8 +1758,7 @@ __global__ __launch_bounds__(256) void proj_f32(const F32Args a) {
                 const int hd = a.hd, head = n1 / hd, i = n1 % hd, pos = pos0 + c;
                 if (head < a.H + a.KV) {
                     const float2 cs = a.rope[(size_t)pos * (hd >> 1) + i];
-                    const float r1 = v1 * cs.x - v2 * cs.y, r2 = v2 * cs.x + v1 * cs.y;
-                    v1 = r1; v2 = r2;
+                    f32_rotate(v1, v2, cs);
                 }
                 float* y;
                 if (head < a.H) {
@@ -1779,7 +1803,7 @@ __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qk
             acc = fmaf(s_q[i], k4.x, acc); acc = fmaf(s_q[i + 1], k4.y, acc);
             acc = fmaf(s_q[i + 2], k4.z, acc); acc = fmaf(s_q[i + 3], k4.w, acc);
         }
-        return acc * scale;
+        return f32_score(acc, scale);
     };
     float v0[32];   // the first 32 values of head dim `lane` of the first range
     {
@@ -1796,9 +1820,9 @@ __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qk
         if (sp != wave) { s0 = dot(sp, 0); s1 = dot(sp, 1); }
         if (lane >= visible) s0 = -INFINITY;
         if (lane + 64 >= visible) s1 = -INFINITY;
-        const float m = wave_max(fmaxf(s0, s1));
+        const float m = lanes_max(fmaxf(s0, s1));
         const float p0 = expf(s0 - m), p1 = expf(s1 - m);  // exp(-inf) = 0 for masked keys
-        const float l = wave_sum(p0 + p1);
+        const float l = lanes_sum<64>(p0 + p1);
         p[lane] = p0;
         p[lane + 64] = p1;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1837,6 +1861,512 @@ __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qk
         o = fmaf(s_o[sp][i], f, o);
     }
     out[(size_t)c * H * hd + h * hd + i] = o / Lsum;
+}
+
+// A whole pass of a small fp32 model in one launch.  As a chain of launches (above) such a pass is 5 L + 2 of them at
+// ~4.5 us each, of which the launch boundary itself is 1.7 us and the rest the trips to memory that every kernel starts and ends
+// with; the arithmetic is next to nothing.  Here the workgroups stay and hand the activations to each other through memory: a
+// value travels as a 64-bit slot (value, tag), written and polled with agent-scope accesses, so that the poll that finds the tag
+// has the value (an all-gather of 512 slots among 32 workgroups: 1.1 us, on one die or across all eight).  A stage asks for its
+// weights first and polls its input while they travel.  The pieces of work and the arithmetic are those of proj_f32 and
+// attn_one_f32, so the results have the same bits.  Bound: the chain of exchanges and the instructions of one wave per SIMD between them, 2-4 us a
+// stage.  Tiny stack, us a pass between events: draft step with its sampling (2 layers, d 64) 61 -> 30, qualifier (4, d 128, 5 tokens)
+// 120 -> 68, target (6, d 256, 9 tokens) 201 -> 118.
+// Tags are the pass's own, one per stage (tag0 + 5 l + 1 ..: q/k/v, attention, o, SwiGLU, down), and no slot is written again
+// while somebody may still wait for its former tag:
+//   X, Q, A, G hold one row per token and are handled in groups of NC tokens by every projection.  A group's slots of one buffer are
+//   written again only by work that needs, through the all-to-all stages in between, the results of everybody who read them.
+//   The new keys and values of a layer are read by the attention of later tokens too, whose groups may lag behind: they have
+//   slots of their own for every layer.
+// Every wait is bounded by the 100 MHz clock: a workgroup whose wait expires (the launch is not resident as a whole) says so in
+// *stuck and ends, the others follow, and the host runs the pass again as a chain of launches.
+typedef unsigned long long slot_t;
+struct F32Pass {
+    const float *embed, *final_norm;
+    LayerW w;            // of layer 0; those of layer l lie l * layer_bytes further
+    size_t layer_bytes;
+    const PassDesc* desc;
+    const float2* rope;
+    float* kv;
+    const int32_t* page_table;
+    int n_pages;
+    slot_t *X, *Q, *A, *G, *KVn;   // [32][d] residual stream, [32][d] queries, [32][d] attention output, [32][F] SwiGLU output, [L][32][2 KV hd] new keys and values
+    float* logits;
+    uint32_t* stuck;
+    unsigned long long wait_ticks;
+    float eps, inv_d;
+    int L, d, H, KV, F, V, hd_log;
+    int nux[6];          // per stage: workgroups of a group of columns (attention: heads)
+};
+constexpr int kF32PassK = 1024;   // largest K of a projection: 16 weights per lane of a row
+
+__device__ inline slot_t slot_load(const slot_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void slot_store(slot_t* p, uint32_t tag, float v) {
+    __hip_atomic_store(p, (slot_t)tag << 32 | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Pairs of slots in one 16-byte load that goes past the caches, as slot_load does; either half of it is as it was stored.  Buffer
+// addressing: one register of offset per load, the base in scalar registers.
+typedef __amdgpu_buffer_rsrc_t buf_t;
+__device__ inline buf_t buf_of(const void* p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000); }
+__device__ inline u32x4 pair_load(buf_t b, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 16 | (int)0x80000000); }   // sc1, volatile
+// Waits for N pairs of slots at byte offsets off(u), until all of them carry `tag`; false when the wait expired
+template <int N, typename O>
+__device__ inline bool pairs_wait(buf_t b, O off, uint32_t tag, unsigned long long ticks, u32x4 (&v)[N]) {
+    const unsigned long long t0 = wall_clock64();
+    for (;;) {
+        uint32_t diff = 0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = pair_load(b, off(u));
+#pragma unroll
+        for (int u = 0; u < N; ++u) diff |= (v[u].y ^ tag) | (v[u].w ^ tag);
+        if (diff == 0) return true;
+        if (wall_clock64() - t0 >= ticks) return false;
+    }
+}
+// n slots (even, at least two) from the start of b into LDS, by 256 threads
+template <int N>
+__device__ inline bool slots_gather_as(int tid, buf_t b, int n, uint32_t tag, unsigned long long ticks, float* dst) {
+    u32x4 v[N];
+    const bool ok = pairs_wait<N>(b, [&](int u) { return (uint32_t)min(2 * tid + 512 * u, n - 2) * 8; }, tag, ticks, v);
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+        if (2 * tid + 512 * u < n) *reinterpret_cast<float2*>(dst + 2 * tid + 512 * u) = make_float2(__uint_as_float(v[u].x), __uint_as_float(v[u].z));
+    return ok;
+}
+__device__ inline bool slots_gather(int tid, const slot_t* p, int n, uint32_t tag, unsigned long long ticks, float* dst) {
+    if (2 * tid >= n) return true;
+    const buf_t b = buf_of(p, n * 8);
+    if (n <= 512) return slots_gather_as<1>(tid, b, n, tag, ticks, dst);
+    if (n <= 1024) return slots_gather_as<2>(tid, b, n, tag, ticks, dst);
+    bool ok = true;
+    for (int i = 0; i < n && ok; i += 4096) {
+        if (2 * tid >= n - i) break;
+        ok = slots_gather_as<8>(tid, buf_of(p + i, (n - i) * 8), n - i, tag, ticks, dst + i);
+    }
+    return ok;
+}
+
+// The thread's index, worked out anew: the compiler would otherwise keep what every stage derives from it in registers over the
+// whole pass (190 spilled registers)
+__device__ inline int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+struct F32PassVals { int w, pos0, n_logit, row0; uint32_t tag0; };
+// The stages of a layer, and the logits.  Stage k of layer l takes its input with tag tag0 + 5 l + k and leaves its result with the next.
+enum { kStQkv, kStAttn, kStO, kStGateUp, kStDown, kStLogits };
+
+// what a projection reads besides its input: asked for as soon as the products of the stage before are done
+struct F32Weights { float4 p[4], q[4], gain[4]; };   // of the lane's two rows; the norm's gains that the lane multiplies with
+
+// This workgroup's part of stage K: row pairs 256 / LP bx .., columns NC cg ..  It has one part at most, the same in every layer.
+template <int K_> struct F32Part { int bx, cg; bool mine; };
+template <int K_, int NC>
+__device__ inline F32Part<K_> f32_part(const F32Pass& a, const F32PassVals& dv) {
+    const int b = blockIdx.x, cg = b / a.nux[K_], cols = K_ == kStLogits ? dv.n_logit : dv.w;
+    return F32Part<K_>{b - cg * a.nux[K_], cg, K_ == kStAttn ? cg < dv.w : cg * NC < cols};
+}
+template <int K_>
+__device__ inline const float* f32_matrix(const F32Pass& a, int layer) {
+    const void* p = K_ == kStQkv ? a.w.wqkv : K_ == kStO ? a.w.wo : K_ == kStGateUp ? a.w.wgu : K_ == kStDown ? a.w.wd : a.embed;
+    return reinterpret_cast<const float*>(static_cast<const char*>(p) + (K_ == kStLogits ? 0 : (size_t)layer * a.layer_bytes));
+}
+template <int K_> constexpr bool kStNorm = K_ == kStQkv || K_ == kStGateUp || K_ == kStLogits;   // an RMSNorm comes first
+template <int K_> constexpr bool kStResid = K_ == kStO || K_ == kStDown;
+template <int K_>
+__device__ inline int f32_rows(const F32Pass& a) { return K_ == kStQkv ? a.d + (2 * a.KV << a.hd_log) : K_ == kStGateUp ? 2 * a.F : K_ == kStLogits ? a.V : a.d; }
+// log2 of the lanes that share a row pair, as launch_proj_f32 picks them: 16 for K up to 256, 64 beyond
+__device__ inline int f32_lp_log(int k) { return k > 256 ? 6 : 4; }
+// the rows of this thread's pair; false: no pair of the matrix (the last one stands in)
+template <int K_>
+__device__ inline bool f32_pair(const F32Pass& a, const F32Part<K_>& part, int tid, int lp_log, int& n1, int& n2) {
+    const int N = f32_rows<K_>(a), npairs = (N + 1) >> 1, pair = (part.bx << (8 - lp_log)) + (tid >> lp_log), pc = min(pair, npairs - 1);
+    if constexpr (K_ == kStQkv) {
+        const int half_log = a.hd_log - 1;
+        n1 = ((pc >> half_log) << a.hd_log) + (pc & ((1 << half_log) - 1));
+        n2 = n1 + (1 << half_log);
+    } else if constexpr (K_ == kStGateUp) {
+        n1 = pc;
+        n2 = a.F + pc;
+    } else {
+        n1 = 2 * pc;
+        n2 = K_ == kStLogits ? min(n1 + 1, N - 1) : n1 + 1;
+    }
+    return pair < npairs;
+}
+template <int K_>
+__device__ inline void f32_fetch(const F32Pass& a, const F32Part<K_>& part, int layer, F32Weights& f) {
+    if (!part.mine) return;
+    const int K = K_ == kStDown ? a.F : a.d, lp_log = f32_lp_log(K), tid = fresh_tid(), sub = tid & ((1 << lp_log) - 1), lane = tid & 63;
+    int n1, n2;
+    f32_pair<K_>(a, part, tid, lp_log, n1, n2);
+    const buf_t W = buf_of(f32_matrix<K_>(a, layer), (uint32_t)f32_rows<K_>(a) * K * 4);   // 8 MB at most
+    const uint32_t o1 = ((uint32_t)n1 * K + sub * 4) * 4, o2 = ((uint32_t)n2 * K + sub * 4) * 4;
+    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = u << (lp_log + 2);
+        f.p[u] = zero4; f.q[u] = zero4;
+        if (sub * 4 + k < K) {
+            f.p[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(W, o1, k * 4, 0));
+            f.q[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(W, o2, k * 4, 0));
+        }
+    }
+    if constexpr (kStNorm<K_>) {
+        const float* G = K_ == kStLogits ? a.final_norm : reinterpret_cast<const float*>(reinterpret_cast<const char*>(K_ == kStQkv ? a.w.attn_norm : a.w.ffn_norm) + (size_t)layer * a.layer_bytes);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (lane * 4 + u * 256 < K) f.gain[u] = *reinterpret_cast<const float4*>(G + lane * 4 + u * 256);
+    }
+}
+
+// One projection, K <= kF32PassK.  next() is called once the weights have been used.  rot, page: q/k/v, the rotation and the cache page of
+// the column that this lane finishes.  False when a wait expired.
+template <int K_, int NC, typename Next>
+__device__ inline bool f32_project(const F32Pass& a, float* xs, const float* zeros, int& bad, const F32PassVals& dv, const F32Part<K_>& part, int layer, const F32Weights& f,
+                                   float2 rot, int page, Next next) {
+    const int K = K_ == kStDown ? a.F : a.d, lp_log = f32_lp_log(K);
+    const int tid = fresh_tid(), wave = tid >> 6, lane = tid & 63, sub = tid & ((1 << lp_log) - 1);
+    const int c0 = (K_ == kStLogits ? dv.w - dv.n_logit : 0) + part.cg * NC, nc = min(NC, dv.w - c0), c = c0 + sub;
+    int n1, n2;
+    const bool fin = f32_pair<K_>(a, part, tid, lp_log, n1, n2) && sub < nc;   // lane c of a pair finishes column c
+    const uint32_t tag_in = dv.tag0 + 5 * layer + (K_ == kStLogits ? 0 : K_), tag = tag_in + 1;
+    auto token_row = [&](int col) {
+        const int tok = a.desc->tok[col];
+        return a.embed + (size_t)(tok < 0 ? 0 : (tok >= a.V ? a.V - 1 : tok)) * a.d;
+    };
+    // the residual stream's values that the result is added to: as a rule there since two stages
+    u32x4 r = u32x4{0u, 0u, 0u, 0u};
+    float y1 = 0.f, y2 = 0.f;
+    const buf_t res = buf_of(a.X, kMaxW * a.d * 8);
+    const uint32_t res_off = (uint32_t)(c * a.d + n1) * 8;   // rows n1, n1 + 1
+    const uint32_t old = K_ == kStDown ? tag_in - 1 : tag_in - 2;
+    const bool embedded = K_ == kStO && layer == 0;
+    if (kStResid<K_> && fin) {
+        if (embedded) {
+            const float* row = token_row(c);
+            y1 = row[n1]; y2 = row[n2];
+        } else {
+            r = pair_load(res, res_off);
+        }
+    }
+    __syncthreads();   // the last stage's LDS has been read
+    bool ok = true;
+    if (K_ == kStQkv && layer == 0) {
+        for (int cc = 0; cc < nc; ++cc) {
+            const float* row = token_row(c0 + cc);
+            for (int k = tid; k < K; k += 256) xs[cc * K + k] = row[k];
+        }
+    } else {
+        const slot_t* src = (K_ == kStO ? a.A : K_ == kStDown ? a.G : a.X) + c0 * K;
+        ok = slots_gather(tid, src, nc * K, tag_in, a.wait_ticks, xs);
+    }
+    if (kStResid<K_> && fin && !embedded && ok) {
+        if (r.y != old || r.w != old) {
+            u32x4 again[1];
+            ok = pairs_wait<1>(res, [&](int) { return res_off; }, old, a.wait_ticks, again);
+            r = again[0];
+        }
+        y1 = __uint_as_float(r.x);
+        y2 = __uint_as_float(r.z);
+    }
+    if (!ok) bad = 1;
+    __syncthreads();
+    if (bad) return false;
+    if constexpr (kStNorm<K_>) {   // a wave sums and scales a column of its own
+        for (int col = wave; col < nc; col += 4) {
+            float ss = 0.f;
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (lane * 4 + u * 256 < K) {
+                    v[u] = *reinterpret_cast<const float4*>(xs + col * K + lane * 4 + u * 256);
+                    ss += f32_squares(v[u]);
+                }
+            const float r = f32_rms(lanes_sum<64>(ss), a.inv_d, a.eps);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float4 gn = f.gain[u];
+                if (lane * 4 + u * 256 < K)
+                    *reinterpret_cast<float4*>(xs + col * K + lane * 4 + u * 256) = make_float4(v[u].x * r * gn.x, v[u].y * r * gn.y, v[u].z * r * gn.z, v[u].w * r * gn.w);
+            }
+        }
+        __syncthreads();
+    }
+    float acc1[NC], acc2[NC];
+#pragma unroll
+    for (int col = 0; col < NC; ++col) { acc1[col] = 0.f; acc2[col] = 0.f; }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if ((u << (lp_log + 2)) >= K) break;
+        const int k = (sub + (u << lp_log)) * 4;
+        const float4 p = f.p[u], q = f.q[u];
+        const float* x0 = k < K ? xs + k : zeros;   // lanes past the row's end: 0 * 0
+        const int step = k < K ? K : 0;
+#pragma unroll
+        for (int col = 0; col < NC; ++col) {   // columns past nc: whatever LDS holds, never stored
+            const float4 x = *reinterpret_cast<const float4*>(x0 + col * step);
+            acc1[col] = fmaf(p.x, x.x, acc1[col]); acc1[col] = fmaf(p.y, x.y, acc1[col]);
+            acc1[col] = fmaf(p.z, x.z, acc1[col]); acc1[col] = fmaf(p.w, x.w, acc1[col]);
+            acc2[col] = fmaf(q.x, x.x, acc2[col]); acc2[col] = fmaf(q.y, x.y, acc2[col]);
+            acc2[col] = fmaf(q.z, x.z, acc2[col]); acc2[col] = fmaf(q.w, x.w, acc2[col]);
+        }
+    }
+    next();
+    float v1 = 0.f, v2 = 0.f;
+#pragma unroll
+    for (int col = 0; col < NC; ++col) {
+        acc1[col] = lanes_sum<16>(acc1[col]);
+        acc2[col] = lanes_sum<16>(acc2[col]);
+    }
+    if (lp_log == 6) {
+#pragma unroll
+        for (int col = 0; col < NC; ++col) {
+            acc1[col] = rows_sum(acc1[col]);
+            acc2[col] = rows_sum(acc2[col]);
+        }
+    }
+#pragma unroll
+    for (int col = 0; col < NC; ++col)
+        if (sub == col) { v1 = acc1[col]; v2 = acc2[col]; }
+    if (!fin) return true;
+    if constexpr (kStResid<K_>) {
+        slot_store(a.X + c * a.d + n1, tag, y1 + v1);
+        slot_store(a.X + c * a.d + n2, tag, y2 + v2);
+    } else if constexpr (K_ == kStGateUp) {
+        slot_store(a.G + c * a.F + n1, tag, f32_silu_up(v1, v2));
+    } else if constexpr (K_ == kStLogits) {
+        float* y = a.logits + (size_t)(dv.row0 + part.cg * NC + sub) * a.V;
+        y[n1] = v1;
+        if (n2 != n1) y[n2] = v2;
+    } else {
+        const int half = 1 << (a.hd_log - 1), kvd = a.KV << a.hd_log;
+        if (n1 < a.d + kvd) f32_rotate(v1, v2, rot);
+        if (n1 < a.d) {
+            slot_store(a.Q + c * a.d + n1, tag, v1);
+            slot_store(a.Q + c * a.d + n1 + half, tag, v2);
+        } else {
+            const int at = n1 - a.d, which = at >= kvd;
+            slot_t* s = a.KVn + ((size_t)layer * kMaxW + c) * 2 * kvd + at;
+            slot_store(s, tag, v1);
+            slot_store(s + half, tag, v2);
+            float* y = a.kv + kv_base(page, layer, a.L, (at - which * kvd) >> a.hd_log, a.KV, which, 1 << a.hd_log) +
+                       (size_t)(((dv.pos0 + c) % kPage) << a.hd_log) + (at & ((1 << a.hd_log) - 1));   // for later passes
+            y[0] = v1;
+            y[half] = v2;
+        }
+    }
+    return true;
+}
+
+// Attention of the pass: per (head, token) what attn_one_f32 does.  Keys and values of earlier passes come from the cache (asked
+// for before the queries are there), this pass's from their slots.
+constexpr int f32_pass_attn_lds(int hd) { return hd + 4 * kAttnSplit + 2 * kF32OneSplits + kF32OneSplits * hd + 2 * kMaxW * hd; }   // floats
+template <int HD, typename Next>
+__device__ inline bool f32_attend(const F32Pass& a, float* lds, int& bad, const int* pages, const F32PassVals& dv, const F32Part<kStAttn>& part, int layer, Next next) {
+    // a wave's first range waits in registers: its keys, the values of HELD of them (as many as the registers have room for)
+    constexpr bool PRE = HD <= 32;
+    constexpr int HELD = HD == 16 ? 64 : 32;
+    float *s_q = lds, *s_p = s_q + HD, *s_m = s_p + 4 * kAttnSplit, *s_l = s_m + kF32OneSplits, *s_o = s_l + kF32OneSplits, *s_k = s_o + kF32OneSplits * HD, *s_v = s_k + kMaxW * HD;
+    const int tid = fresh_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const uint32_t tag_in = dv.tag0 + 5 * layer + kStAttn, tag = tag_in + 1;
+    const float scale = rsqrtf((float)HD);
+    const int c = part.cg, h = part.bx, g = h * a.KV / a.H;
+    const int nkeys = dv.pos0 + c + 1, nsp = min((nkeys + kAttnSplit - 1) / kAttnSplit, kF32OneSplits);
+    auto plane = [&](int sp, int half, int which) {
+        return a.kv + kv_base(__builtin_amdgcn_readfirstlane(pages[2 * sp + half]), layer, a.L, g, a.KV, which, HD);
+    };
+    float4 kr[2][PRE ? HD / 4 : 1];
+    float vr[PRE ? HELD : 1];
+    if constexpr (PRE) {
+        if (wave < nsp) {
+            const int old = dv.pos0 - wave * kAttnSplit;   // keys of the range that earlier passes left
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+                if (half * 64 + lane < old) {
+                    const float* p = plane(wave, half, 0) + (size_t)lane * HD;
+#pragma unroll
+                    for (int i = 0; i < HD / 4; ++i) kr[half][i] = *reinterpret_cast<const float4*>(p + 4 * i);
+                }
+            const float* p = plane(wave, 0, 1) + min(lane, HD - 1);
+#pragma unroll
+            for (int b = 0; b < HELD; b += 32) {
+                if (b >= old) break;
+#pragma unroll
+                for (int u = 0; u < 32; ++u) vr[b + u] = p[(size_t)(b + u) * HD];
+            }
+        }
+    }
+    __syncthreads();   // the last piece's LDS has been read
+    {
+        // [token][K, V][hd] in pairs of slots; the query
+        const int npairs = (c + 1) * HD, row = 2 * a.KV * HD * 8;   // bytes of a token's slots
+        const buf_t kn = buf_of(a.KVn + ((size_t)layer * kMaxW * 2 * a.KV + g) * HD, row * (c + 1)), q = buf_of(a.Q + c * a.d + h * HD, HD * 8);
+        u32x4 q0 = u32x4{0u, 0u, 0u, 0u};
+        if (tid < HD / 2) q0 = pair_load(q, tid * 16);
+        bool ok = true;
+        auto gather = [&](auto n, int i0) {
+            constexpr int N = decltype(n)::value;
+            u32x4 v[N];
+            if (!pairs_wait<N>(kn, [&](int u) {
+                    const int i = min(i0 + 256 * u, npairs - 1);
+                    return (uint32_t)((i / HD) * row + (i & (HD / 2) ? a.KV * HD * 8 : 0) + (i & (HD / 2 - 1)) * 16);
+                }, tag_in, a.wait_ticks, v)) ok = false;
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int i = i0 + 256 * u;
+                if (i < npairs) *reinterpret_cast<float2*>((i & (HD / 2) ? s_v : s_k) + (i / HD) * HD + 2 * (i & (HD / 2 - 1))) = make_float2(__uint_as_float(v[u].x), __uint_as_float(v[u].z));
+            }
+        };
+        if (tid < npairs) {
+            if (npairs <= 256) gather(std::integral_constant<int, 1>{}, tid);
+            else for (int i = tid; i < npairs && ok; i += 1024) gather(std::integral_constant<int, 4>{}, i);
+        }
+        if (tid < HD / 2) {
+            if (q0.y != tag_in || q0.w != tag_in) {
+                u32x4 again[1];
+                if (!pairs_wait<1>(q, [&](int) { return (uint32_t)tid * 16; }, tag_in, a.wait_ticks, again)) ok = false;
+                q0 = again[0];
+            }
+            *reinterpret_cast<float2*>(s_q + 2 * tid) = make_float2(__uint_as_float(q0.x), __uint_as_float(q0.z));
+        }
+        if (!ok) bad = 1;
+    }
+    __syncthreads();
+    if (bad) return false;
+    next();
+    for (int sp = wave; sp < nsp; sp += 4) {
+        const int visible = min(kAttnSplit, nkeys - sp * kAttnSplit), old = dv.pos0 - sp * kAttnSplit;
+        const bool held = PRE && sp == wave;
+        float* p = s_p + wave * kAttnSplit;
+        float s[2];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int j = half * 64 + lane;
+            float acc = 0.f;
+            auto dot4 = [&](int i, const float4 k4) {
+                acc = fmaf(s_q[i], k4.x, acc); acc = fmaf(s_q[i + 1], k4.y, acc);
+                acc = fmaf(s_q[i + 2], k4.z, acc); acc = fmaf(s_q[i + 3], k4.w, acc);
+            };
+            if (j < old) {
+                if (held) {
+                    if constexpr (PRE) {
+#pragma unroll
+                        for (int i = 0; i < HD / 4; ++i) dot4(4 * i, kr[half][i]);
+                    }
+                } else {
+                    const float* k = plane(sp, half, 0) + (size_t)lane * HD;
+#pragma unroll 8
+                    for (int i = 0; i < HD; i += 4) dot4(i, *reinterpret_cast<const float4*>(k + i));
+                }
+            } else if (j < visible) {
+                const float* k = s_k + (j - old) * HD;
+#pragma unroll 4
+                for (int i = 0; i < HD; i += 4) dot4(i, *reinterpret_cast<const float4*>(k + i));
+            }
+            s[half] = j < visible ? f32_score(acc, scale) : -INFINITY;
+        }
+        const float m = lanes_max(fmaxf(s[0], s[1]));
+        const float p0 = expf(s[0] - m), p1 = expf(s[1] - m);  // exp(-inf) = 0 for masked keys
+        const float l = lanes_sum<64>(p0 + p1);
+        p[lane] = p0;
+        p[lane + 64] = p1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < HD; i += 64) {
+            float acc = 0.f;
+            const int n = min(old, visible);   // keys past the last old one add p * 0
+            auto add = [&](int b, const float* v) {
+#pragma unroll
+                for (int u = 0; u < 32; ++u) acc = fmaf(p[b + u], b + u < old ? v[u] : 0.f, acc);
+            };
+            int b = 0;
+            if constexpr (PRE) {
+                if (held) {
+                    if (n > 0) { add(0, vr); b = 32; }
+                    if (HELD > 32 && n > 32) { add(32, vr + (HELD - 32)); b = 64; }
+                }
+            }
+#pragma unroll 1
+            for (; b < n; b += 32) {
+                const float* v = plane(sp, b / kPage, 1) + (size_t)(b % kPage) * HD + i;
+                float vv[32];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) vv[u] = v[(size_t)u * HD];
+                add(b, vv);
+            }
+#pragma unroll 8
+            for (int j = max(old, 0); j < visible; ++j) acc = fmaf(p[j], s_v[(j - old) * HD + i], acc);
+            if (nsp == 1) slot_store(a.A + c * a.d + h * HD + i, tag, acc / l);   // nothing to merge
+            s_o[sp * HD + i] = acc;
+        }
+        if (lane == 0) { s_m[sp] = m; s_l[sp] = l; }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (nsp == 1) return true;
+    __syncthreads();
+    if (tid < HD) {
+        float M = -INFINITY;
+        for (int sp = 0; sp < nsp; ++sp) M = fmaxf(M, s_m[sp]);
+        float Lsum = 0.f, o = 0.f;
+        for (int sp = 0; sp < nsp; ++sp) {
+            const float f = expf(s_m[sp] - M);
+            Lsum = fmaf(s_l[sp], f, Lsum);
+            o = fmaf(s_o[sp * HD + tid], f, o);
+        }
+        slot_store(a.A + (size_t)c * a.d + h * HD + tid, tag, o / Lsum);
+    }
+    return true;
+}
+
+template <int HD, int NC>
+__global__ __launch_bounds__(256, 2) void pass_f32(const F32Pass a) {
+    constexpr int kProj = NC * kF32PassK, kAttn = f32_pass_attn_lds(HD);
+    __shared__ __align__(16) float lds[kProj > kAttn ? kProj : kAttn];
+    __shared__ __align__(16) float zeros[4];
+    __shared__ int bad, pages[2 * kF32OneSplits];
+    if (threadIdx.x < 4) zeros[threadIdx.x] = 0.f;
+    const F32PassVals dv{a.desc->w, a.desc->pos0, a.desc->n_logit, a.desc->logit_row0, a.desc->tag0};
+    if (threadIdx.x == 0) bad = 0;
+    if (threadIdx.x < 2 * kF32OneSplits) pages[threadIdx.x] = a.page_table[min((int)threadIdx.x, a.n_pages - 1)];
+    const auto qkv = f32_part<kStQkv, NC>(a, dv);
+    const auto attn = f32_part<kStAttn, 1>(a, dv);
+    const auto o = f32_part<kStO, NC>(a, dv);
+    const auto gu = f32_part<kStGateUp, NC>(a, dv);
+    const auto down = f32_part<kStDown, NC>(a, dv);
+    const auto lm = f32_part<kStLogits, NC>(a, dv);
+    F32Weights f{};
+    f32_fetch(a, qkv, 0, f);
+    float2 rot = make_float2(1.f, 0.f);
+    int page = 0;
+    if (qkv.mine) {
+        const int lp_log = f32_lp_log(a.d), c = min(qkv.cg * NC + ((int)threadIdx.x & ((1 << lp_log) - 1)), dv.w - 1), pos = dv.pos0 + c;
+        int n1, n2;
+        f32_pair<kStQkv>(a, qkv, threadIdx.x, lp_log, n1, n2);
+        rot = a.rope[(size_t)pos * (HD / 2) + (n1 & (HD - 1))];   // read for the values as well, and not used
+        page = a.page_table[pos / kPage];
+    }
+    __syncthreads();
+    bool ok = true;
+    for (int l = 0; l < a.L && ok; ++l) {
+        if (qkv.mine) ok = f32_project<kStQkv, NC>(a, lds, zeros, bad, dv, qkv, l, f, rot, page, [] {});
+        auto fetch_o = [&] { f32_fetch(a, o, l, f); };
+        if (!attn.mine) fetch_o();
+        else if (ok) ok = f32_attend<HD>(a, lds, bad, pages, dv, attn, l, fetch_o);
+        auto fetch_gu = [&] { f32_fetch(a, gu, l, f); };
+        if (!o.mine) fetch_gu();
+        else if (ok) ok = f32_project<kStO, NC>(a, lds, zeros, bad, dv, o, l, f, rot, page, fetch_gu);
+        auto fetch_down = [&] { f32_fetch(a, down, l, f); };
+        if (!gu.mine) fetch_down();
+        else if (ok) ok = f32_project<kStGateUp, NC>(a, lds, zeros, bad, dv, gu, l, f, rot, page, fetch_down);
+        auto fetch_next = [&] { if (l + 1 < a.L) f32_fetch(a, qkv, l + 1, f); else f32_fetch(a, lm, 0, f); };
+        if (!down.mine) fetch_next();
+        else if (ok) ok = f32_project<kStDown, NC>(a, lds, zeros, bad, dv, down, l, f, rot, page, fetch_next);
+    }
+    if (lm.mine && ok) ok = f32_project<kStLogits, NC>(a, lds, zeros, bad, dv, lm, a.L, f, rot, page, [] {});
+    if (!ok && threadIdx.x == 0) __hip_atomic_store(a.stuck, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- profiler ---------------------------------------------------------------------------------------
@@ -1987,6 +2517,36 @@ static void model_shape(Model& M, const psd_model_desc& m, int max_seq) {
                    : (ranges_ok(M.nqkv, M.d) && ranges_ok(M.d, M.H * M.hd) && ranges_ok(2 * M.F, M.d) && ranges_ok(M.d, M.F)) ? kCols : 128;
 }
 
+// Slots of a one-launch pass lie in the rows of the residual stream and of the q/k/v buffer beyond the 32 that an fp32 pass can have:
+// nothing else ever writes them, so what they hold is zero (from the creation on) or an older tag.
+static bool f32_slots_fit(const Model& M) {
+    const size_t rows = kCols - kMaxW, kv = (size_t)M.KV * M.hd;
+    return (size_t)kMaxW * (3 * M.d + M.F) * sizeof(slot_t) <= rows * M.d * sizeof(float) &&
+           (size_t)M.L * kMaxW * 2 * kv * sizeof(slot_t) <= rows * M.nqkv * sizeof(float);
+}
+
+// workgroups per group of columns of every stage (attention: heads per token)
+static void f32_pass_parts(const Model& M, int nux[6]) {
+    auto parts = [](int n, int k) { const int pw = k > 256 ? 4 : 16; return ((n + 1) / 2 + pw - 1) / pw; };
+    nux[0] = parts(M.nqkv, M.d); nux[1] = M.H; nux[2] = parts(M.d, M.d);
+    nux[3] = parts(2 * M.F, M.d); nux[4] = parts(M.d, M.F); nux[5] = parts(M.V, M.d);
+}
+// workgroups of a one-launch pass: one for every part of the largest stage
+static int f32_pass_grid(const Model& M, int wcls) {
+    int nux[6], most = 0;
+    f32_pass_parts(M, nux);
+    const int groups = wcls == 1 ? 1 : wcls <= 16 ? (wcls + 3) / 4 : (wcls + 7) / 8;
+    for (int i = 0; i < 6; ++i) most = std::max(most, nux[i] * (i == 1 ? wcls : groups));
+    return most;
+}
+// A pass in one launch: models whose projections a workgroup per CU can hold (16 weights per lane of a row, no more than the 2 M
+// weights of a projection up to which proj_f32 gives every group of columns workgroups of its own).
+static bool f32_one_launch(const Model& M) {
+    const size_t most = (size_t)2 << 20;
+    return M.dtype == PSD_F32 && M.d <= kF32PassK && M.F <= kF32PassK && (size_t)2 * M.F * M.d <= most && (size_t)M.nqkv * M.d <= most &&
+           (size_t)M.V * M.d <= most && f32_slots_fit(M);
+}
+
 size_t model_pool_bytes(const psd_model_desc& m, int max_seq, bool roomy) {
     Model M;
     model_shape(M, m, max_seq);
@@ -2101,9 +2661,15 @@ int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, 
     }
     M.pages_mapped = 0;
     M.len = 0;
+    M.one_launch = f32_one_launch(M);
+    M.tag_last = 0;
     PSD_HIP(hipStreamSynchronize(stream), err);
     PSD_HIP(hipGetLastError(), err);
     return PSD_OK;
+}
+
+bool model_one_launch(const Model& M, int wcls, const float* logits) {
+    return M.one_launch && logits && f32_pass_grid(M, wcls) <= 256 && std::min(M.nsplit_max, kCtxBuckets[M.ctx_bucket]) <= kF32OneSplits;
 }
 
 int model_map_pages(Model& M, int keep, int upto, int* first_changed, int* n_changed, char* err) {
@@ -2171,9 +2737,60 @@ static void launch_proj_f32(Launch& L, const char* family, F32Args a) {
     L.end();
 }
 
+int model_stamp(Model& M, PassDesc& d, int passes, hipStream_t stream, char* err) {
+    if (!M.one_launch) return PSD_OK;
+    d.tag_step = 5 * M.L;
+    const uint32_t span = (uint32_t)passes * d.tag_step;
+    if (M.tag_last > 0xffffffffu - span) {   // used up: the slots forget them
+        PSD_HIP(hipMemsetAsync(M.x + (size_t)kMaxW * M.d, 0, (size_t)(kCols - kMaxW) * M.d * sizeof(float), stream), err);
+        PSD_HIP(hipMemsetAsync(M.qkv + (size_t)kMaxW * M.nqkv, 0, (size_t)(kCols - kMaxW) * M.nqkv * sizeof(float), stream), err);
+        M.tag_last = 0;
+    }
+    d.tag0 = M.tag_last;
+    M.tag_last += span;
+    return PSD_OK;
+}
+
+template <int HD>
+static void launch_pass_f32(Launch& L, float* logits) {
+    Model& M = L.M;
+    const int d = M.d, F = M.F;
+    F32Pass a{};
+    a.embed = (const float*)M.embed; a.final_norm = M.final_norm;
+    a.w = M.layers[0];
+    a.layer_bytes = M.L > 1 ? (const char*)M.layers[1].wqkv - (const char*)M.layers[0].wqkv : 0;   // the same for all: model_carve
+    a.desc = M.desc; a.rope = M.rope; a.kv = (float*)M.kv; a.page_table = M.page_table; a.n_pages = M.n_pages;
+    a.X = (slot_t*)(M.x + (size_t)kMaxW * d);
+    a.Q = a.X + (size_t)kMaxW * d;
+    a.A = a.Q + (size_t)kMaxW * d;
+    a.G = a.A + (size_t)kMaxW * d;
+    a.KVn = (slot_t*)(M.qkv + (size_t)kMaxW * M.nqkv);
+    a.logits = logits;
+    a.stuck = M.stuck;
+    a.wait_ticks = wait_ticks();
+    a.eps = M.eps;
+    a.inv_d = 1.f / (float)d;
+    a.L = M.L; a.d = d; a.H = M.H; a.KV = M.KV; a.F = F; a.V = M.V;
+    a.hd_log = HD == 16 ? 4 : HD == 32 ? 5 : HD == 64 ? 6 : 7;
+    f32_pass_parts(M, a.nux);
+    const int grid = f32_pass_grid(M, L.wcls);
+    L.begin("pass_f32", (double)M.weight_bytes);
+    if (L.wcls == 1) pass_f32<HD, 1><<<grid, 256, 0, L.s>>>(a);
+    else if (L.wcls <= 16) pass_f32<HD, 4><<<grid, 256, 0, L.s>>>(a);
+    else pass_f32<HD, 8><<<grid, 256, 0, L.s>>>(a);
+    L.end();
+}
+
 static int forward_f32(Model& M, int wmax, float* logits, Launch& L) {
     hipStream_t stream = L.s;
     const int d = M.d, F = M.F, H = M.H, KV = M.KV, hd = M.hd;
+    if (model_one_launch(M, wmax, logits)) {
+        if (hd == 16) launch_pass_f32<16>(L, logits);
+        else if (hd == 32) launch_pass_f32<32>(L, logits);
+        else if (hd == 64) launch_pass_f32<64>(L, logits);
+        else launch_pass_f32<128>(L, logits);
+        return PSD_OK;
+    }
     const double act = (double)wmax * d * 4;
     float* attn = (float*)M.xb;
     L.begin("embed", act);

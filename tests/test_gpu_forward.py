@@ -327,6 +327,42 @@ def test_fp32_projection_shapes(d, h, kv, f):
     assert np.abs(one - ref).max() <= TOL_F32
 
 
+@pytest.mark.parametrize("layers,d,h,kv,f,v", [(2, 64, 4, 2, 256, 512), (3, 128, 4, 4, 512, 131), (2, 256, 8, 1, 1024, 77), (2, 512, 4, 2, 1024, 2),
+                                               (1, 288, 9, 3, 992, 33), (1, 1024, 16, 8, 1024, 513)])
+def test_fp32_one_launch_passes_equal_the_chain_of_launches(layers, d, h, kv, f, v):
+    # small models take a pass with logits in one launch; where its bounded wait expires (at once here, for the second context) the
+    # context goes on with a launch per projection: the same bits at every launch class, context length and head dim, and where the
+    # one launch is not taken (more than eight key ranges, more parts than workgroups)
+    shape = ModelShape(layers, d, h, kv, f, v)
+    blobs = [synth.target_weights(shape, 60 + i, synth.DTYPE_F32, sigma=0.06) for i in range(3)]
+    toks = synth.tokens(23, 0, 1000, v)
+    got = []
+    for expire in (False, True):
+        ctx = _ctx((shape,) * 3, blobs, synth.DTYPE_F32, 10000.0, 1300, flags=0x100)
+        before = psd.get_accept_expiries()
+        if expire:
+            try:
+                psd.set_accept_path(3)
+                ctx.forward(0, toks[:3], 0)
+            finally:
+                psd.set_accept_path(0)
+        assert psd.get_accept_expiries() - before == (1 if expire else 0)
+        out, pos = [], 0
+        for w in (1, 2, 4, 5, 8, 11, 16, 24, 32, 1, 23, 1, 1, 3):
+            out.append(ctx.forward(0, toks[pos:pos + w], pos))
+            pos += w
+        while pos < 1000:
+            w = min(1 + pos % 32, 1000 - pos)
+            out.append(ctx.forward(0, toks[pos:pos + w], pos))
+            pos += w
+        out.append(ctx.forward(0, toks[100:117], 100))   # over rows that are there already
+        got.append(np.concatenate(out))
+        ctx.close()
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
+    ref = oracle.Model(shape, blobs[0], synth.DTYPE_F32, 10000.0, 160).forward(toks[:160], 0)
+    assert np.abs(got[0][:160] - ref).max() <= TOL_F32
+
+
 def test_bf16_ingestion_at_page_split_and_pass_boundaries():
     # prompt lengths around the KV page (64), the attention key range (128) and the pass widths (128, 512):
     # the widest passes, 32-token passes and a ragged mix leave identical logits for the tokens that follow

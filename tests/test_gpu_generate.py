@@ -310,6 +310,34 @@ def test_generation_survives_expired_waits(tiny_stack):
     ctx.close()
 
 
+@pytest.mark.parametrize("kind", ["psd", "sd", "plain", "row_stats"])
+def test_rounds_are_run_again_after_an_expired_pass(tiny_stack, kind):
+    # the first pass that waits is run again as a chain of launches: tokens and statistics are those of a context that never waited in vain
+    cfg, d, q, t, prompt = tiny_stack
+    res = []
+    for expire in (False, True):
+        ctx = _ctx(cfg, (d, q, t), 16 + 32 + 10, 0.004, 0.012, 4, 8, flags=psd.FLAG_ROW_STATS if kind == "row_stats" else 0)
+        before = psd.get_accept_expiries()
+        try:
+            if expire:
+                psd.set_accept_path(3)
+            if kind == "sd":
+                out, st = ctx.generate_sd(0, 4, 0.02, prompt, 24, 5)
+            elif kind == "plain":
+                out, st = ctx.generate_plain(2, prompt, 24, 5)
+            else:
+                out, st = ctx.generate(prompt, 24, 5)
+        finally:
+            psd.set_accept_path(0)
+        assert (psd.get_accept_expiries() > before) == expire
+        res.append((out, {k: v for k, v in st.items() if not k.startswith("ms_")}, ctx.row_stats() if kind == "row_stats" else None))
+        ctx.close()
+    assert np.array_equal(res[0][0], res[1][0]) and res[0][1] == res[1][1]
+    if kind == "row_stats":
+        for m in res[0][2]:
+            assert np.allclose(res[0][2][m], res[1][2][m], rtol=1e-12), m   # sums of the same numbers in the same order
+
+
 @pytest.mark.parametrize("case", range(18))
 def test_randomised_stacks_replay(case):
     """Seeded random shapes, windows, thresholds and prompt lengths (through the 128- and 512-token ingestion passes
