@@ -16,7 +16,11 @@
 //                  token: the residual max(0, p - q) of the first rejected position, or the verifier's
 //                  last row for the bonus token.  Only this kernel draws vocabulary-wide random numbers.
 //   accept_pick    per trial: winner of the race; in small calls the race's last workgroup does it
-// A stage of one trial, k = 10, takes 18 us with three launches; with the decision and the pick as launches of their own, 19.8.
+// In calls of one trial the race's workgroups are part of the sweep's launch too and wait for the decision, with the race over the
+// bonus row done meanwhile: two launches.  Bound: the chain loads - row exchange - divergence exchange - decision - race -
+// count - pick, 12.7 us of which 7.5 are trips through memory between workgroups (k = 10: 18.0 us a call with the race as a launch of
+// its own and reductions by shuffles, 15.1 now).  Race workgroups that read the divergences and decide for themselves instead of
+// waiting for the decision: 17.6, polls of the lines that are being written hold the writers up.
 // Bulk arithmetic runs in base 2 on the hardware exp2 / log2 units; the two probabilities the coin
 // compares are evaluated with the accurate library functions.  No floating-point atomics: every
 // partial has its own slot, reductions run in a fixed order, so results never depend on scheduling.
@@ -147,6 +151,14 @@ struct AcceptWs {  // carved out of the caller's workspace
     KeyIdx* top;         // [B*(k+1)][nch] per-chunk maximum logit of the verifier rows (assisted and greedy stages)
     uint32_t* expired;   // [1] set when a bounded wait ran out
     uint32_t* raced;     // [B][raced_step] race workgroups that are done (in the space of `top`, which the stages that race this way do not use)
+    __host__ __device__ uint32_t* decision() const { return raced + 1; }   // calls of one trial in one launch: what was decided
+};
+// (accepted, within the threshold) of a decided trial as one word
+struct Decision {
+    static constexpr uint32_t kBad = 0xfffffffeu;   // a wait expired
+    int n, fuzzy;
+    __device__ uint32_t word() const { return (uint32_t)n | (uint32_t)fuzzy << 8; }
+    __device__ static Decision of(uint32_t v) { return Decision{(int)(v & 0xff), (int)(v >> 8)}; }
 };
 // Words between the counters of two trials: a cache line where a trial's share of `top`, (k + 1) nch entries of two words, is that
 // long.  An atomic waits for the others on its line (side by side: 16 trials of k = 3 at V 128256, 1008 workgroups, 36.7 us a
@@ -166,6 +178,22 @@ __device__ inline float ld_agent32(const float* p) {
 }
 __device__ inline unsigned long long ld_agent64(const void* p) {
     return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ inline RowStats stats_agent(const RowStats* p) {
+    const unsigned long long up = ld_agent64(&p->Mp), uq = ld_agent64(&p->Mq);
+    return RowStats{__uint_as_float((uint32_t)up), __uint_as_float((uint32_t)(up >> 32)), __uint_as_float((uint32_t)uq), __uint_as_float((uint32_t)(uq >> 32))};
+}
+
+// The same while the workgroup that writes them may still be at it: the row's divergence partials are there, so these are on their
+// way.  false: not within the bound of all such waits.
+__device__ inline bool stats_wait(const RowStats* p, unsigned long long ticks, RowStats& r) {
+    const unsigned long long t0 = wall_clock64();
+    for (;;) {
+        r = stats_agent(p);
+        if (__float_as_uint(r.Mp) != kUnwritten && __float_as_uint(r.Mq) != kUnwritten) return true;
+        if (wall_clock64() - t0 >= ticks) return false;
+    }
 }
 
 // Row maxima and sums S = sum_c s_c 2^(m_c - M) of both rows from the per-wave partials.  Thread t folds
@@ -228,19 +256,32 @@ __device__ inline bool row_stats(const RowPart* parts, int nsl, unsigned long lo
     return true;
 }
 
-// the arguments that every thread needs lie together: one trip for them (a stage of one trial: 18.2 us against 18.7 with the
-// workspace struct and more arguments behind it)
-__global__ void accept_clear(RowPart* part, float* jsd, uint32_t* expired, uint32_t* raced, size_t n_parts, uint32_t n_trials, uint32_t step) {
+// one cache line of arguments: one trip for them (a stage of one trial: 18.2 us against 18.7 with more behind them)
+struct ClearArgs {
+    RowPart* part;
+    float* jsd;
+    RowStats* stats;
+    uint32_t *expired, *raced;
+    size_t n_parts;
+    uint32_t n_pairs, n_trials;
+    uint16_t step, whole;   // whole: there is a decision to clear
+};
+static_assert(sizeof(ClearArgs) <= 64, "one cache line");
+__global__ void accept_clear(ClearArgs a) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_parts) {
-        part[i] = RowPart{__uint_as_float(kUnwritten), 0.f, __uint_as_float(kUnwritten), 0.f};
-        jsd[i] = __uint_as_float(kUnwritten);
+    if (i < a.n_parts) {
+        a.part[i] = RowPart{__uint_as_float(kUnwritten), 0.f, __uint_as_float(kUnwritten), 0.f};
+        a.jsd[i] = __uint_as_float(kUnwritten);
     }
-    if (i < n_trials) raced[i * step] = 0u;
-    if (i == 0) *expired = 0u;
+    if (i < a.n_pairs) a.stats[i] = RowStats{__uint_as_float(kUnwritten), 0.f, __uint_as_float(kUnwritten), 0.f};
+    if (i < a.n_trials) a.raced[i * a.step] = 0u;
+    if (i == 0) {
+        *a.expired = 0u;
+        if (a.whole) a.raced[1] = kUnwritten;   // AcceptWs::decision
+    }
 }
 
-enum { SWEEP_ONE_LAUNCH = 0, SWEEP_PARTIALS = 1, SWEEP_DIVERGENCE = 2, SWEEP_AND_DECIDE = 3 };
+enum { SWEEP_ONE_LAUNCH = 0, SWEEP_PARTIALS = 1, SWEEP_DIVERGENCE = 2, SWEEP_AND_DECIDE = 3, SWEEP_STAGE = 4 };
 
 // ---- the sweep, in pieces -----------------------------------------------------------------------------------
 // A work item is one chunk of kSweepChunk entries of one judged position: item = position * chunks + chunk within a
@@ -369,15 +410,13 @@ __device__ inline bool sweep_second(const AcceptShape& s, const AcceptWs& w, con
         if (it.ch == 0 && threadIdx.x == 0) w.stats[it.pair] = R;
         return true;
     }
-    if (it.ch == 0 && threadIdx.x == 0) {
-        st_agent64(&w.stats[it.pair].Mp, R.Mp, R.Sp);
-        st_agent64(&w.stats[it.pair].Mq, R.Mq, R.Sq);
+    // a NaN out of NaN logits must not look like the unwritten pattern
+    auto written = [](float v) { return v != v ? __uint_as_float(0x7fc00000u) : v; };
+    if ((threadIdx.x & 63) == 0) st_agent32(slot, written(acc));
+    if (it.ch == 0 && threadIdx.x == 0) {   // for whoever sees the partials and waits for these (stats_wait)
+        st_agent64(&w.stats[it.pair].Mp, written(R.Mp), R.Sp);
+        st_agent64(&w.stats[it.pair].Mq, written(R.Mq), R.Sq);
     }
-    // written last and only when everything of this thread before it has been acknowledged: a reader that sees the partials
-    // of a row sees the row's statistics too.  (A NaN out of NaN logits must not look like the unwritten pattern.)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if ((threadIdx.x & 63) == 0)
-        st_agent32(slot, acc != acc ? __uint_as_float(0x7fc00000u) : acc);
     return true;
 }
 
@@ -394,7 +433,8 @@ struct DecideArgs {
 // The decision of trial b by a workgroup of NW waves: wave r sums the divergence partials of positions r, r + NW, ... (lane c
 // takes slots c, c + 64, ... in increasing order, then a fixed tree), thread i tosses the coin of position i.
 // WAIT: the partials come from workgroups of the running kernel; the wait is bounded as theirs is.
-template <bool WAIT, int NW>
+// PUBLISH: the result goes to the workgroups of the same launch that race for the token (Decision), and to nobody else.
+template <bool WAIT, int NW, bool PUBLISH = false>
 __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const DecideArgs& a, int b) {
     __shared__ float s_div[PSD_MAX_WIDTH];
     __shared__ int s_pass[PSD_MAX_WIDTH];
@@ -414,7 +454,12 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
             zq = s.lq[pair * s.V + x];
         }
     };
-    if (WAIT && i < s.k) coin_inputs();
+    auto toss = [&] {
+        const uint64_t sd = a.seed + (uint64_t)b;
+        return u01(philox4x32_10(U4{0u, a.position0 + (uint32_t)i, DRAW_COIN, a.stage}, (uint32_t)sd, (uint32_t)(sd >> 32)).x);
+    };
+    float coin = 0.f;
+    if (WAIT && i < s.k) { coin_inputs(); coin = toss(); }
     uint32_t bad = 0;   // of thread 0
     if (!WAIT && i == 0) bad = *w.expired;
     if (WAIT) {
@@ -440,7 +485,7 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
                 }
                 if (!__any(missing)) break;
                 if (wall_clock64() - t0 >= s.wait_ticks) { good = false; break; }
-                __builtin_amdgcn_s_sleep(8);
+                __builtin_amdgcn_s_sleep(2);
             }
             if (!__all(good) && lane == 0) {
                 s_bad = 1;
@@ -461,23 +506,22 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
         if (a.div_out) a.div_out[pair] = d;
         int pass = 2;  // 2: within the threshold, 1: the coin accepted, 0: rejected
         if (!(d <= a.T)) {
-            const uint64_t sd = a.seed + (uint64_t)b;
-            U4 r = philox4x32_10(U4{0u, a.position0 + (uint32_t)i, DRAW_COIN, a.stage}, (uint32_t)sd, (uint32_t)(sd >> 32));
             TokProb tp{0.f, 1.f};
-            if (!WAIT) coin_inputs();
+            if (!WAIT) { coin_inputs(); coin = toss(); }
             if (known) {   // accurate exponentials of the natural-log probabilities
                 RowStats R;
                 if (WAIT) {
-                    const unsigned long long up = ld_agent64(&w.stats[pair].Mp), uq = ld_agent64(&w.stats[pair].Mq);
-                    R.Mp = __uint_as_float((uint32_t)up); R.Sp = __uint_as_float((uint32_t)(up >> 32));
-                    R.Mq = __uint_as_float((uint32_t)uq); R.Sq = __uint_as_float((uint32_t)(uq >> 32));
+                    if (!stats_wait(w.stats + pair, s.wait_ticks, R)) {
+                        s_bad = 1;
+                        __hip_atomic_store(w.expired, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
                 } else {
                     R = w.stats[pair];
                 }
                 const float lse_p = (R.Mp + log2f(R.Sp)) * kLn2, lse_q = (R.Mq + log2f(R.Sq)) * kLn2;
                 tp = TokProb{expf(fmaxf(zp, -kBig) * s.inv_temp - lse_p), expf(fmaxf(zq, -kBig) * s.inv_temp - lse_q)};
             }
-            pass = (u01(r.x) * tp.qx < tp.px) ? 1 : 0;  // u < p(x)/q(x)
+            pass = (coin * tp.qx < tp.px) ? 1 : 0;  // u < p(x)/q(x)
         }
         s_pass[i] = pass;
     }
@@ -485,8 +529,12 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
     if (i == 0) {
         int n = 0, fuzzy = 0;
         for (; n < s.k && s_pass[n]; ++n) fuzzy += s_pass[n] == 2;
-        AcceptOut o;
         if (WAIT) bad = s_bad;
+        if (PUBLISH) {
+            __hip_atomic_store(w.decision(), bad ? Decision::kBad : Decision{n, fuzzy}.word(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        AcceptOut o;
         o.n_accepted = bad ? -1 : n;  // -1: a bounded wait expired
         o.n_fuzzy = fuzzy;
         o.pad = 0;
@@ -494,30 +542,6 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
         a.out[b] = o;
         if (a.n_out) { a.n_out[b] = o.n_accepted; a.tok_out[b] = -1; }
     }
-}
-
-// One workgroup per item.  SWEEP_ONE_LAUNCH: publish, wait for the row, finish; SWEEP_AND_DECIDE: a trial's items are followed by
-// the workgroup that decides it.  Two launches: SWEEP_PARTIALS stops after the first half, SWEEP_DIVERGENCE repeats the first
-// half without publishing and reads the finished partials.
-// The workgroups of a row are neighbours in launch order and consecutive ids go round the 8 accelerator dies, so
-// the chunks a workgroup waits for are resident with it.
-template <int MODE, bool VEC>
-__global__ __launch_bounds__(kAccThreads, ((MODE == SWEEP_ONE_LAUNCH || MODE == SWEEP_AND_DECIDE) && VEC) ? 8 : 6) void accept_sweep(AcceptShape s, AcceptWs w, DecideArgs da) {
-    __shared__ float4 lds[kSweepWaves];
-    constexpr bool kDecide = MODE == SWEEP_AND_DECIDE, kWait = MODE == SWEEP_ONE_LAUNCH || kDecide;
-    const int items = s.k * (s.nsl / kSweepWaves), per = items + (kDecide ? 1 : 0);
-    const int b = blockIdx.x / per, item = blockIdx.x - b * per;
-    if (kDecide && item == items) {
-        decide<true, kAccThreads / 64>(s, w, da, b);
-        return;
-    }
-    const SweepItem it = sweep_item(s, b, item);
-    float a[kSweepQuads][4], c[kSweepQuads][4];
-    if (VEC) sweep_load(s, it, a, c);
-    else sweep_load_any(s, it, a, c);
-    sweep_first<MODE != SWEEP_DIVERGENCE>(s, w, it, a, c);
-    if (MODE == SWEEP_PARTIALS) return;
-    sweep_second<kWait, kDecide>(s, w, it, a, c, lds);
 }
 
 // the decision as a kernel of its own: in calls of many trials, behind the two-launch sweep, and where nothing is judged (k = 0)
@@ -573,27 +597,24 @@ __global__ __launch_bounds__(1024) void accept_decide_assisted(AcceptShape s, Ac
     }
 }
 
-// Winner of trial b's race among its chunks (whose results are all there), by a whole workgroup
-__device__ inline void pick(const AcceptShape& s, const AcceptWs& w, int b, int n, int assisted, AcceptOut* out, int32_t* tok_out) {
-    __shared__ KeyIdx smp[4];
+// Winner of trial b's race among its chunks (whose results are all there), by one wave; every lane gets it
+__device__ inline int pick(const AcceptShape& s, const AcceptWs& w, int b, int n, int assisted) {
     const bool bonus_row = n == s.k || assisted;  // keys in log form: any sign, and never without mass
     KeyIdx best{bonus_row ? -INFINITY : -1.f, 0x7fffffff}, fb{-1.f, 0x7fffffff};
-    for (int c = threadIdx.x; c < s.nch; c += kAccThreads) {
+    for (int c = threadIdx.x & 63; c < s.nch; c += kWave) {
         const RacePart* src = w.race + (size_t)b * s.nch + c;
         const unsigned long long u0 = ld_agent64(&src->key), u1 = ld_agent64(&src->key_fb);
         best = better(best, KeyIdx{__uint_as_float((uint32_t)u0), (int)(u0 >> 32)});
         fb = better(fb, KeyIdx{__uint_as_float((uint32_t)u1), (int)(u1 >> 32)});
     }
-    best = block_best<4>(best, smp);
-    __syncthreads();
-    fb = block_best<4>(fb, smp);
+    best = wave_best(best);
     // no residual mass at all (cannot happen in exact arithmetic): draw from p instead
-    if (!bonus_row && !(best.key > 0.f)) best = fb;
-    if (threadIdx.x == 0) {
-        const int tok = best.idx == 0x7fffffff ? -1 : best.idx;
-        out[b].next_token = tok;
-        if (tok_out) tok_out[b] = tok;
-    }
+    if (!bonus_row && !(best.key > 0.f)) best = wave_best(fb);
+    return best.idx == 0x7fffffff ? -1 : best.idx;
+}
+__device__ inline void put_token(AcceptOut* out, int32_t* tok_out, int b, int tok) {
+    out[b].next_token = tok;
+    if (tok_out) tok_out[b] = tok;
 }
 
 __device__ inline void void_trial(AcceptOut* out, int32_t* n_out, int b) {
@@ -606,11 +627,86 @@ __device__ inline void void_trial(AcceptOut* out, int32_t* n_out, int b) {
 // bonus token is wanted: race over the verifier's last row in log form, z_v / temperature - ln E_v, which
 // needs no normalisation.  E_v = -ln u_v.  Assisted stage: the draw at a rejection is from the verifier's
 // row itself, in the same log form but with the replacement stream's random numbers.
+// race_log / race_residual: this thread's best of chunk ch of row n; race_put: the workgroup's, into w.race.
+__device__ inline KeyIdx race_log(const AcceptShape& s, int ch, int b, int n, uint64_t sd, uint32_t pos, uint32_t purpose, uint32_t stage) {
+    const float* prow = s.lp + ((size_t)b * (s.k + 1) + n) * s.V;
+    const bool vec = (s.V & 3) == 0;
+    KeyIdx best{-INFINITY, 0x7fffffff};
+#pragma unroll
+    for (int j = 0; j < kQuadsPerThread; ++j) {
+        const int v = ch * kAcceptChunk + 4 * (threadIdx.x + kAccThreads * j);
+        if (v >= s.V) continue;
+        float a[4], u[4];
+        load4(prow, v, s.V, vec, a);
+        draw4(sd, (uint32_t)(v >> 2), pos, purpose, stage, u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (v + e >= s.V) continue;
+            const float E = -kLn2 * fast_log2(u[e]);
+            best = better(best, KeyIdx{fmaf(a[e], s.inv_temp, -kLn2 * fast_log2(E)), v + e});
+        }
+    }
+    return best;
+}
+__device__ inline void race_residual(const AcceptShape& s, int ch, int b, int n, uint64_t sd, uint32_t pos, uint32_t stage, const RowStats& R, KeyIdx& best, KeyIdx& best_fb) {
+    const float* prow = s.lp + ((size_t)b * (s.k + 1) + n) * s.V;
+    const float* qrow = s.lq + ((size_t)b * s.k + n) * s.V;
+    const bool vec = (s.V & 3) == 0;
+    const float c2 = s.inv_temp * kLog2e, ip = 1.f / R.Sp, iq = 1.f / R.Sq;
+    best = KeyIdx{-1.f, 0x7fffffff};  // residual keys are positive
+    best_fb = best;
+#pragma unroll
+    for (int j = 0; j < kQuadsPerThread; ++j) {
+        const int v = ch * kAcceptChunk + 4 * (threadIdx.x + kAccThreads * j);
+        if (v >= s.V) continue;
+        float a[4], c[4], u[4];
+        load4(prow, v, s.V, vec, a);
+        load4(qrow, v, s.V, vec, c);
+        draw4(sd, (uint32_t)(v >> 2), pos, DRAW_RESAMPLE, stage, u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (v + e >= s.V) continue;
+            const float p = fast_exp2(fmaf(a[e], c2, -R.Mp)) * ip;  // -inf logits: 2^(-inf) = 0
+            const float q = fast_exp2(fmaf(c[e], c2, -R.Mq)) * iq;
+            const float iE = __builtin_amdgcn_rcpf(-kLn2 * fast_log2(u[e]));
+            const float r = p - q;
+            if (r > 0.f) best = better(best, KeyIdx{r * iE, v + e});
+            if (p > 0.f) best_fb = better(best_fb, KeyIdx{p * iE, v + e});
+        }
+    }
+}
+// AGENT: workgroups of the running kernel read it
+template <bool AGENT>
+__device__ inline void race_put(const AcceptShape& s, const AcceptWs& w, int ch, int b, KeyIdx best, KeyIdx best_fb) {
+    __shared__ KeyIdx smk[4], smf[4];
+    best = wave_best(best);
+    best_fb = wave_best(best_fb);
+    if ((threadIdx.x & 63) == 0) { smk[threadIdx.x >> 6] = best; smf[threadIdx.x >> 6] = best_fb; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 1; i < 4; ++i) { best = better(best, smk[i]); best_fb = better(best_fb, smf[i]); }
+        RacePart* dst = w.race + (size_t)b * s.nch + ch;
+        if (!AGENT) {   // a later kernel reads it
+            *dst = RacePart{best.key, best.idx, best_fb.key, best_fb.idx};
+        } else {
+            st_agent64(&dst->key, best.key, __int_as_float(best.idx));
+            st_agent64(&dst->key_fb, best_fb.key, __int_as_float(best_fb.idx));
+        }
+    }
+}
+// Thread 0, once its stores are out: counts this workgroup among the trial's `nch` race workgroups and says what was counted
+// before.  Counted when the stores have been acknowledged, so who counts last finds every chunk's result.
+__device__ inline uint32_t race_count(const AcceptWs& w, int b, uint32_t step, uint32_t add) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    return __hip_atomic_fetch_add(w.raced + b * step, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// the race as a kernel of its own; PICK: its last workgroup picks the winner
 template <bool PICK>
 __global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, AcceptWs w, AcceptOut* out,
                                                            uint64_t seed, uint32_t position0, uint32_t stage,
                                                            int take_bonus, int assisted, int32_t* n_out, int32_t* tok_out) {
-    __shared__ KeyIdx smk[4];
     const int ch = blockIdx.x, b = blockIdx.y;
     // some wait of the sweep ran out: no trial of the call is valid.  (A big race leaves the check to accept_pick: in each of
     // 64 K workgroups it cost 5 us of 162.)
@@ -622,74 +718,97 @@ __global__ __launch_bounds__(kAccThreads) void accept_race(AcceptShape s, Accept
     if (n < 0 || (n == s.k && !take_bonus)) return;   // next_token stays -1
     const uint64_t sd = seed + (uint64_t)b;
     const uint32_t pos = position0 + (uint32_t)n;
-    const float* prow = s.lp + ((size_t)b * (s.k + 1) + n) * s.V;
-    const bool vec = (s.V & 3) == 0;
-    KeyIdx best{-INFINITY, 0x7fffffff}, best_fb{-1.f, 0x7fffffff};
-    if (n == s.k || assisted) {
-        const uint32_t purpose = n == s.k ? (uint32_t)DRAW_SAMPLE : (uint32_t)DRAW_RESAMPLE, stg = n == s.k ? 0u : stage;
-#pragma unroll
-        for (int j = 0; j < kQuadsPerThread; ++j) {
-            const int v = ch * kAcceptChunk + 4 * (threadIdx.x + kAccThreads * j);
-            if (v >= s.V) continue;
-            float a[4], u[4];
-            load4(prow, v, s.V, vec, a);
-            draw4(sd, (uint32_t)(v >> 2), pos, purpose, stg, u);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (v + e >= s.V) continue;
-                const float E = -kLn2 * fast_log2(u[e]);
-                best = better(best, KeyIdx{fmaf(a[e], s.inv_temp, -kLn2 * fast_log2(E)), v + e});
-            }
+    KeyIdx best, best_fb{-1.f, 0x7fffffff};
+    if (n == s.k) best = race_log(s, ch, b, n, sd, pos, DRAW_SAMPLE, 0u);
+    else if (assisted) best = race_log(s, ch, b, n, sd, pos, DRAW_RESAMPLE, stage);
+    else race_residual(s, ch, b, n, sd, pos, stage, w.stats[b * s.k + n], best, best_fb);
+    race_put<PICK>(s, w, ch, b, best, best_fb);
+    if (PICK && threadIdx.x < 64) {
+        int last = 0;
+        if (threadIdx.x == 0) last = race_count(w, b, raced_step(s.k, s.nch), 1u) == (uint32_t)(s.nch - 1);
+        if (__builtin_amdgcn_readfirstlane(last)) {
+            const int tok = pick(s, w, b, n, assisted);
+            if (threadIdx.x == 0) put_token(out, tok_out, b, tok);
         }
-    } else {
-        const int pair = b * s.k + n;
-        const float* qrow = s.lq + (size_t)pair * s.V;
-        const RowStats R = w.stats[pair];
-        const float c2 = s.inv_temp * kLog2e, ip = 1.f / R.Sp, iq = 1.f / R.Sq;
-        best.key = -1.f;  // residual keys are positive
-#pragma unroll
-        for (int j = 0; j < kQuadsPerThread; ++j) {
-            const int v = ch * kAcceptChunk + 4 * (threadIdx.x + kAccThreads * j);
-            if (v >= s.V) continue;
-            float a[4], c[4], u[4];
-            load4(prow, v, s.V, vec, a);
-            load4(qrow, v, s.V, vec, c);
-            draw4(sd, (uint32_t)(v >> 2), pos, DRAW_RESAMPLE, stage, u);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (v + e >= s.V) continue;
-                const float p = fast_exp2(fmaf(a[e], c2, -R.Mp)) * ip;  // -inf logits: 2^(-inf) = 0
-                const float q = fast_exp2(fmaf(c[e], c2, -R.Mq)) * iq;
-                const float iE = __builtin_amdgcn_rcpf(-kLn2 * fast_log2(u[e]));
-                const float r = p - q;
-                if (r > 0.f) best = better(best, KeyIdx{r * iE, v + e});
-                if (p > 0.f) best_fb = better(best_fb, KeyIdx{p * iE, v + e});
-            }
-        }
-    }
-    best = block_best<4>(best, smk);
-    best_fb = block_best<4>(best_fb, smk);
-    __shared__ int s_last;
-    if (threadIdx.x == 0) {
-        RacePart* dst = w.race + (size_t)b * s.nch + ch;
-        if (!PICK) {   // a later kernel reads it
-            *dst = RacePart{best.key, best.idx, best_fb.key, best_fb.idx};
-        } else {
-            st_agent64(&dst->key, best.key, __int_as_float(best.idx));
-            st_agent64(&dst->key_fb, best_fb.key, __int_as_float(best_fb.idx));
-            // counted once the stores have been acknowledged: who counts last finds every chunk's result
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            s_last = __hip_atomic_fetch_add(w.raced + b * raced_step(s.k, s.nch), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(s.nch - 1);
-        }
-    }
-    if (PICK) {
-        __syncthreads();
-        if (s_last) pick(s, w, b, n, assisted, out, tok_out);
     }
 }
 
+// Race workgroup `ch` of a call of one trial whose sweep is part of the same launch
+__device__ inline void stage_race(const AcceptShape& s, const AcceptWs& w, const DecideArgs& a, int ch, int take_bonus) {
+    __shared__ uint32_t s_word;
+    __shared__ RowStats s_stats;
+    constexpr uint32_t kLate = 1u << 16;   // counted beside the workgroups: their wait expired
+    // while the decision is awaited: the race over the bonus row, which is the one that is wanted where everything passes
+    KeyIdx best{-INFINITY, 0x7fffffff};
+    if (take_bonus) best = race_log(s, ch, 0, s.k, a.seed, a.position0 + (uint32_t)s.k, DRAW_SAMPLE, 0u);
+    if (threadIdx.x == 0) {
+        const unsigned long long t0 = wall_clock64();
+        uint32_t v;
+        while ((v = __hip_atomic_load(w.decision(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kUnwritten) {
+            if (wall_clock64() - t0 >= s.wait_ticks) break;
+            __builtin_amdgcn_s_sleep(2);
+        }
+        // the statistics of the row that is raced over, if it is not the bonus row
+        if (v != kUnwritten && v != Decision::kBad && Decision::of(v).n < s.k && !stats_wait(w.stats + Decision::of(v).n, s.wait_ticks, s_stats)) v = kUnwritten;
+        s_word = v;
+    }
+    __syncthreads();
+    const uint32_t word = s_word;
+    const bool bad = word == kUnwritten || word == Decision::kBad;
+    const Decision d = Decision::of(word);
+    const bool wanted = !bad && (d.n < s.k || take_bonus);
+    if (wanted) {
+        KeyIdx best_fb{-1.f, 0x7fffffff};
+        if (d.n < s.k) race_residual(s, ch, 0, d.n, a.seed, a.position0 + (uint32_t)d.n, a.stage, s_stats, best, best_fb);
+        race_put<true>(s, w, ch, 0, best, best_fb);
+    }
+    if (threadIdx.x >= 64) return;
+    const uint32_t add = bad ? 1u + kLate : 1u;
+    uint32_t now = 0;
+    if (threadIdx.x == 0) now = race_count(w, 0, 0, add) + add;
+    now = __builtin_amdgcn_readfirstlane(now);
+    if ((now & (kLate - 1)) != (uint32_t)s.nch) return;
+    const bool ok = now < kLate;   // nobody's wait expired
+    const int tok = ok && wanted ? pick(s, w, 0, d.n, 0) : -1;
+    if (threadIdx.x == 0) {
+        a.out[0] = AcceptOut{ok ? d.n : -1, tok, ok ? d.fuzzy : 0, 0};
+        if (a.n_out) { a.n_out[0] = ok ? d.n : -1; a.tok_out[0] = tok; }
+    }
+}
+
+// One workgroup per item.  SWEEP_ONE_LAUNCH: publish, wait for the row, finish; SWEEP_AND_DECIDE: a trial's items are followed by
+// the workgroup that decides it.  SWEEP_STAGE, calls of one trial: the decision is followed by the race's workgroups, which wait for
+// it; the last of them to finish picks the token and is the only one to write the result.  Two launches: SWEEP_PARTIALS stops after the
+// first half, SWEEP_DIVERGENCE repeats the first half without publishing and reads the finished partials.
+// The workgroups of a row are neighbours in launch order and consecutive ids go round the 8 accelerator dies, so
+// the chunks a workgroup waits for are resident with it; nobody waits for a workgroup that is launched after it.
+template <int MODE, bool VEC>
+__global__ __launch_bounds__(kAccThreads, ((MODE == SWEEP_ONE_LAUNCH || MODE == SWEEP_AND_DECIDE || MODE == SWEEP_STAGE) && VEC) ? 8 : 6) void accept_sweep(AcceptShape s, AcceptWs w, DecideArgs da, int take_bonus) {
+    __shared__ float4 lds[kSweepWaves];
+    constexpr bool kDecide = MODE == SWEEP_AND_DECIDE || MODE == SWEEP_STAGE, kWait = MODE == SWEEP_ONE_LAUNCH || kDecide;
+    const int items = s.k * (s.nsl / kSweepWaves), per = items + (kDecide ? 1 : 0);
+    const int b = MODE == SWEEP_STAGE ? 0 : blockIdx.x / per, item = blockIdx.x - b * per;
+    if (kDecide && item == items) {
+        decide<true, kAccThreads / 64, MODE == SWEEP_STAGE>(s, w, da, b);
+        return;
+    }
+    if constexpr (MODE == SWEEP_STAGE) {
+        if (item > items) {
+            stage_race(s, w, da, item - items - 1, take_bonus);
+            return;
+        }
+    }
+    const SweepItem it = sweep_item(s, b, item);
+    float a[kSweepQuads][4], c[kSweepQuads][4];
+    if (VEC) sweep_load(s, it, a, c);
+    else sweep_load_any(s, it, a, c);
+    sweep_first<MODE != SWEEP_DIVERGENCE>(s, w, it, a, c);
+    if (MODE == SWEEP_PARTIALS) return;
+    sweep_second<kWait, kDecide>(s, w, it, a, c, lds);
+}
+
 // the winner as a kernel of its own
-__global__ __launch_bounds__(kAccThreads) void accept_pick(AcceptShape s, AcceptWs w, int take_bonus, int assisted,
+__global__ __launch_bounds__(64) void accept_pick(AcceptShape s, AcceptWs w, int take_bonus, int assisted,
                                                            AcceptOut* out, int32_t* n_out, int32_t* tok_out) {
     const int b = blockIdx.x;
     if (!assisted && *w.expired) {
@@ -698,7 +817,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_pick(AcceptShape s, Accept
     }
     const int n = out[b].n_accepted;
     if (n < 0 || (n == s.k && !take_bonus)) return;  // next_token stays -1
-    pick(s, w, b, n, assisted, out, tok_out);
+    const int tok = pick(s, w, b, n, assisted);
+    if (threadIdx.x == 0) put_token(out, tok_out, b, tok);
 }
 
 static inline size_t align16(size_t n) { return (n + 15) & ~(size_t)15; }
@@ -753,7 +873,7 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
                                                                next_token_out);
         if (!greedy) {
             accept_race<false><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 1, nullptr, nullptr);
-            accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 1, out, nullptr, next_token_out);
+            accept_pick<<<n_trials, 64, 0, stream>>>(s, w, take_bonus, 1, out, nullptr, next_token_out);
         }
         PSD_HIP(hipGetLastError(), errbuf);
         return PSD_OK;
@@ -766,22 +886,34 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
     // 20.1 at V 5000 (one item); 384: 50.7 / 50.3 at V 32000; 512: 61.5 / 60.2, 25.3 / 23.3 at V 5000; 1024: 102.9 / 100.7.
     const bool inside = one_launch && n_trials <= 256;
     const DecideArgs da{T, seed, position0, stage, out, div_out, n_accepted_out, next_token_out};
-    accept_clear<<<(unsigned)((n_clear + 256) / 256), 256, 0, stream>>>(w.part, w.jsd, w.expired, w.raced, n_parts, (uint32_t)n_trials, (uint32_t)raced_step(k, nch));
     const int n_items = pairs * nsw;
+    // One trial: the race is part of the sweep's launch as well.  In it / as a launch of its own, us a call (a position rejected, all
+    // accepted): k = 1 at V 5000 10.8, 10.8 / 13.8, 13.9; 10 at 32000 13.7, 12.1 / 14.7, 15.2; 10 at 128256 15.2, 13.7 / 16.2, 16.5; 32 at
+    // 128256 20.9, 21.0 / 22.5, 23.3; 32 at 327680, the widest rows that one launch sweeps (2048 items), 37.8, 37.8 / 38.2, 39.3.
+    const bool whole = one_launch && n_trials == 1;
+    accept_clear<<<(unsigned)((n_clear + 256) / 256), 256, 0, stream>>>(
+        ClearArgs{w.part, w.jsd, w.stats, w.expired, w.raced, n_parts, (uint32_t)pairs, (uint32_t)n_trials, (uint16_t)raced_step(k, nch), (uint16_t)whole});
     const bool vec = (vocab & 3) == 0;  // rows are then 16-byte aligned and hold whole quads
+    if (whole) {
+        const int grid = n_items + 1 + nch;
+        if (vec) accept_sweep<SWEEP_STAGE, true><<<grid, kAccThreads, 0, stream>>>(s, w, da, take_bonus);
+        else accept_sweep<SWEEP_STAGE, false><<<grid, kAccThreads, 0, stream>>>(s, w, da, take_bonus);
+        PSD_HIP(hipGetLastError(), errbuf);
+        return PSD_OK;
+    }
     if (inside) {
-        if (vec) accept_sweep<SWEEP_AND_DECIDE, true><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
-        else accept_sweep<SWEEP_AND_DECIDE, false><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da);
+        if (vec) accept_sweep<SWEEP_AND_DECIDE, true><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da, 0);
+        else accept_sweep<SWEEP_AND_DECIDE, false><<<n_items + n_trials, kAccThreads, 0, stream>>>(s, w, da, 0);
     } else if (one_launch) {
-        if (vec) accept_sweep<SWEEP_ONE_LAUNCH, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
-        else accept_sweep<SWEEP_ONE_LAUNCH, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
+        if (vec) accept_sweep<SWEEP_ONE_LAUNCH, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da, 0);
+        else accept_sweep<SWEEP_ONE_LAUNCH, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da, 0);
     } else {
         if (pairs > 0 && vec) {
-            accept_sweep<SWEEP_PARTIALS, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
-            accept_sweep<SWEEP_DIVERGENCE, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
+            accept_sweep<SWEEP_PARTIALS, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da, 0);
+            accept_sweep<SWEEP_DIVERGENCE, true><<<n_items, kAccThreads, 0, stream>>>(s, w, da, 0);
         } else if (pairs > 0) {
-            accept_sweep<SWEEP_PARTIALS, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
-            accept_sweep<SWEEP_DIVERGENCE, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da);
+            accept_sweep<SWEEP_PARTIALS, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da, 0);
+            accept_sweep<SWEEP_DIVERGENCE, false><<<n_items, kAccThreads, 0, stream>>>(s, w, da, 0);
         }
     }
     if (!inside) accept_decide<<<n_trials, 1024, 0, stream>>>(s, w, da);
@@ -792,7 +924,7 @@ int accept_launch(const float* logits_p, const float* logits_q, const int32_t* t
         accept_race<true><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0, n_accepted_out, next_token_out);
     } else {
         accept_race<false><<<dim3(nch, n_trials), kAccThreads, 0, stream>>>(s, w, out, seed, position0, stage, take_bonus, 0, n_accepted_out, next_token_out);
-        accept_pick<<<n_trials, kAccThreads, 0, stream>>>(s, w, take_bonus, 0, out, n_accepted_out, next_token_out);
+        accept_pick<<<n_trials, 64, 0, stream>>>(s, w, take_bonus, 0, out, n_accepted_out, next_token_out);
     }
     PSD_HIP(hipGetLastError(), errbuf);
     return PSD_OK;

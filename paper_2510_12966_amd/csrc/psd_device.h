@@ -57,13 +57,26 @@ __device__ inline KeyIdx better(KeyIdx a, KeyIdx b) {
     if (b.key > a.key || (b.key == a.key && b.idx < a.idx)) return b;
     return a;
 }
+// over a wave, every lane gets it: lane moves within the rows of 16, then swaps between them; no trip through LDS (six shuffles are
+// 12 such trips, 0.6 us where one wave is all there is)
+template <int CTRL>
+__device__ inline KeyIdx best_moved(KeyIdx v) {
+    return better(v, KeyIdx{__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v.key), CTRL, 0xf, 0xf, true)),
+                            __builtin_amdgcn_update_dpp(0, v.idx, CTRL, 0xf, 0xf, true)});
+}
 __device__ inline KeyIdx wave_best(KeyIdx v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        KeyIdx t{__shfl_xor(v.key, o, kWave), __shfl_xor(v.idx, o, kWave)};
-        v = better(v, t);
+    v = best_moved<0xB1>(v);    // quad_perm [1,0,3,2]
+    v = best_moved<0x4E>(v);    // quad_perm [2,3,0,1]
+    v = best_moved<0x141>(v);   // row_half_mirror
+    v = best_moved<0x140>(v);   // row_mirror
+    {
+        const auto k = __builtin_amdgcn_permlane16_swap(__float_as_uint(v.key), __float_as_uint(v.key), false, false);
+        const auto i = __builtin_amdgcn_permlane16_swap((uint32_t)v.idx, (uint32_t)v.idx, false, false);
+        v = better(KeyIdx{__uint_as_float(k[0]), (int)i[0]}, KeyIdx{__uint_as_float(k[1]), (int)i[1]});
     }
-    return v;
+    const auto k = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.key), __float_as_uint(v.key), false, false);
+    const auto i = __builtin_amdgcn_permlane32_swap((uint32_t)v.idx, (uint32_t)v.idx, false, false);
+    return better(KeyIdx{__uint_as_float(k[0]), (int)i[0]}, KeyIdx{__uint_as_float(k[1]), (int)i[1]});
 }
 
 // block-wide versions for blockDim.x = 64 * NW (NW <= 16); `sm` needs NW slots; result valid in all threads

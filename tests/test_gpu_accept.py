@@ -175,11 +175,13 @@ def test_one_launch_and_two_launch_sweeps_agree_bit_for_bit(V, k, B):
 
 @pytest.mark.parametrize("B,k,V", [(1, 1, 1), (1, 32, 5120), (3, 32, 5121), (16, 2, 128256), (17, 2, 128256), (2, 2, 327680),
                                    (2, 1, 327681), (1030, 1, 33), (2, 0, 4097), (1024, 1, 33), (64, 0, 2000), (340, 2, 5000),
-                                   (256, 1, 20001), (257, 1, 20001)])
+                                   (256, 1, 20001), (257, 1, 20001), (1, 10, 128256), (1, 32, 20003), (1, 2, 327680),
+                                   (1, 2, 327681)])
 def test_deciding_and_picking_workgroups_agree_with_their_own_launches(B, k, V):
     # the decision inside the one-launch sweep against the launch behind the two-launch one: one slot, 256 slots (all the wait
     # covers), one vocabulary entry more (two launches on both paths), k = 0, and behind the one-launch sweep (257 trials); the pick by the race's last workgroup (1008
-    # workgroups) and as a launch (1071), trials' counters 2, 4 and 32 words apart; judged, rejected and bonus rows
+    # workgroups) and as a launch (1071), trials' counters 2, 4 and 32 words apart; one trial, with the race inside the sweep; judged, rejected
+    # and bonus rows
     stages = [_stage_inputs(23, b % 4, max(k, 1), V, 0.9, 2) for b in range(min(B, 4))]
     P = [stages[b % len(stages)][0][:k + 1] for b in range(B)]
     Q = [stages[b % len(stages)][1][:k] for b in range(B)]
@@ -237,7 +239,7 @@ def test_expired_wait_falls_back_to_two_launches_and_still_matches_oracle():
     assert _compare(lp, lq, x, 0.2, 1.0, 9, 40, 2, True) in ("exact", "tie")
 
 
-@pytest.mark.parametrize("B", [3, 200, 257])
+@pytest.mark.parametrize("B", [1, 3, 200, 257])
 def test_an_expired_wait_voids_every_trial_of_a_batch(B):
     # decided inside the sweep and picked by the race, decided inside and picked by a launch, decided by a launch
     V, k = 20000, 1
