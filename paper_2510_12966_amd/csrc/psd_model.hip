@@ -1420,59 +1420,16 @@ __global__ __launch_bounds__(256) void attn_combine_long(const float* part, cons
     }
 }
 
-// Attention of a prompt-ingestion pass in one sweep: a workgroup of four waves owns four consecutive 16-row query tiles of
-// one kv head, one per wave, and walks the key ranges from the first to the last one its queries see.  A range's K planes
-// (hi, lo), then its V planes, go through LDS for the four waves (K of the next range travels during P V, V during Q K^T);
-// every wave keeps its tile's running (M, Lsum, o) in registers and writes the o projection's operand itself, so no
-// partials go to memory and there is no merge kernel.  Within a range the arithmetic is that of attn_mfma: four groups of
-// 32 keys (its four waves), each from its own maximum, added in order; ranges are merged as attn_merge does: same bits.
-// With a workgroup per (kv head, range, four tiles) the draft's passes over a 3000-token prompt spent 59 us per layer here
-// and 30 us in the merge, waiting on loads and barriers per 16-row tile; this takes 52 us (10 us worth of MFMAs and 19 us of
-// vector instructions a wave, one wave per SIMD, so little of that overlaps).
-// grid ceil(query tiles / 4) * KV; 128 KB of LDS at head dim 128 (one workgroup per CU).
+// ---- pieces of the sweeps over a tile's key ranges (attn_wide, attn_pair) ----
+// one plane pair of a page in LDS: hi, then lo, HD / 8 * kPage words each
 template <int HD>
-constexpr int kAttnWideLds = 8 * kPage * HD * 2;   // two pages x (K or V: hi, lo) each for K and V, bytes
+constexpr int kPlaneWords = kPage * HD / 8;
+// a tile's queries as B operand, scaled: lane (g, c) holds head dims 32 ks + 8 g .. + 8 of row c
 template <int HD>
-__global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qkv, const PassDesc* desc, const uint16_t* __restrict__ kv,
-                                                    const int32_t* __restrict__ page_table, int n_pages, void* xb, int layer, int L, int H,
-                                                    int KV, int nqkv) {
-    constexpr int KSQ = HD / 32, JT = HD / 16, PW = kPage * HD / 8;   // PW: 16-byte words of one plane of one page
-    constexpr int NS = 4 * PW / 256;                                  // words per thread of half a range (K or V)
-    static_assert(kAttnSplit == 2 * kPage, "a key range is two pages");
-    extern __shared__ u32x4 aw_lds[];
-    u32x4* sK = aw_lds;            // [2 pages][hi, lo][plane]
-    u32x4* sV = aw_lds + 4 * PW;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, cq = lane & 15;
-    // consecutive workgroups go round the eight XCDs: with eight kv heads each head's keys and values stay in one L2
-    const int gkv = blockIdx.x % KV, grp = gridDim.x / KV - 1 - blockIdx.x / KV;   // the groups with the most ranges first
-    const int w = desc->w, pos0 = desc->pos0, G = H / KV, R = w * G;
-    if (grp * 64 >= R) return;
-    const int tile = grp * 4 + wave, row0 = tile * 16;
-    const int nsp = (pos0 + (min(R, grp * 64 + 64) - 1) / G) / kAttnSplit + 1;                        // ranges of the workgroup
-    const int my_nsp = row0 < R ? (pos0 + (min(R, row0 + 16) - 1) / G) / kAttnSplit + 1 : 0;   // and of this wave's tile
-    u32x4 st[NS];
-    auto load_half = [&](u32x4 (&st)[NS], int s, int half) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int page = page_table[min(2 * s + p, n_pages - 1)];
-            const u32x4* src = reinterpret_cast<const u32x4*>(kv + kv_plane(page, layer, L, gkv, KV, 2 * half, HD));   // hi and lo planes are adjacent
-#pragma unroll
-            for (int i = 0; i < NS / 2; ++i) st[p * (NS / 2) + i] = src[tid + i * 256];
-        }
-    };
-    auto put_half = [&](const u32x4 (&st)[NS], u32x4* dst) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int i = 0; i < NS / 2; ++i) dst[p * 2 * PW + tid + i * 256] = st[p * (NS / 2) + i];
-    };
-    load_half(st, 0, 0);
-    // the tile's queries as B operand, scaled: lane (g, c) holds head dims 32 ks + 8 g .. + 8 of row c
-    const int rho = row0 + cq;
+__device__ inline void sweep_queries(const float* __restrict__ qkv, int nqkv, int rho, int R, int G, int gkv, int g, u32x4 (&qh)[HD / 32], u32x4 (&ql)[HD / 32]) {
     const float scale = attn_scale<HD>();
-    u32x4 qh[KSQ], ql[KSQ];
 #pragma unroll
-    for (int ks = 0; ks < KSQ; ++ks) {
+    for (int ks = 0; ks < HD / 32; ++ks) {
         float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (rho < R) {
             const float* qrow = qkv + (size_t)(rho / G) * nqkv + (size_t)(gkv * G + rho % G) * HD + ks * 32 + g * 8;
@@ -1487,121 +1444,320 @@ __global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qk
             ql[ks][e] = lo;
         }
     }
-    const int qpos = rho < R ? pos0 + rho / G : -1, qpos_first = pos0 + row0 / G;
-    float M = -INFINITY, Lsum = 0.f;
-    f32x4 o[JT];
+}
+// scores of a range's four groups of 32 keys, masked, each group's maximum per query and the range's
+template <int HD>
+__device__ inline void sweep_scores(const u32x4* sK, const u32x4 (&qh)[HD / 32], const u32x4 (&ql)[HD / 32], int key0, int qpos, int qpos_first,
+                                    f32x4 (&S)[4][2], float (&mv)[4], float& Ms) {
+    constexpr int KSQ = HD / 32, PW = kPlaneWords<HD>;
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    // (k_hi + k_lo)(q_hi + q_lo) without the lo * lo term (2^-18 relative); eight independent chains side by side
 #pragma unroll
-    for (int j = 0; j < JT; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // a per-query value, held by the lanes of column c, for the four queries 4 g + r of the P V layout
-    auto to_rows = [&](float v, float (&out)[4]) {
+    for (int kt = 0; kt < 8; ++kt) S[kt >> 1][kt & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[r] = __shfl(v, 4 * g + r, kWave);
-    };
-    put_half(st, sK);
-    __syncthreads();
-    for (int s = 0; s < nsp; ++s) {
-        load_half(st, s, 1);
-        const int key0 = s * kAttnSplit;
-        const bool live = s < my_nsp;
-        f32x4 S[4][2];
-        float mv[4], fac[4], Ms = -INFINITY;
-        if (live) {
-            // (k_hi + k_lo)(q_hi + q_lo) without the lo * lo term (2^-18 relative); eight independent chains side by side
+    for (int ks = 0; ks < KSQ; ++ks) {
+        u32x4 kh[8], kl[8];
 #pragma unroll
-            for (int kt = 0; kt < 8; ++kt) S[kt >> 1][kt & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KSQ; ++ks) {
-                u32x4 kh[8], kl[8];
-#pragma unroll
-                for (int kt = 0; kt < 8; ++kt) {
-                    const u32x4* kp = sK + (kt >> 2) * 2 * PW + ((kt & 3) * KSQ + ks) * 64 + lane;
-                    kh[kt] = kp[0];
-                    kl[kt] = kp[PW];
-                }
-#pragma unroll
-                for (int t3 = 0; t3 < 3; ++t3)
-#pragma unroll
-                    for (int kt = 0; kt < 8; ++kt)
-                        S[kt >> 1][kt & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, t3 < 2 ? kh[kt] : kl[kt]), __builtin_bit_cast(bf16x8, t3 == 1 ? ql[ks] : qh[ks]),
-                            S[kt >> 1][kt & 1], 0, 0, 0);
-            }
-            if (key0 + kAttnSplit - 1 > qpos_first) {   // causal mask: key position <= query position
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (key0 + v * 32 + k2 * 16 + g * 4 + r > qpos) S[v][k2][r] = -INFINITY;
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float m = -INFINITY;
-#pragma unroll
-                for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) m = fmaxf(m, S[v][k2][r]);
-                mv[v] = rows_max(m);
-                Ms = fmaxf(Ms, mv[v]);
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) fac[v] = mv[v] == -INFINITY ? 0.f : exp2_hw(mv[v] - Ms);
+        for (int kt = 0; kt < 8; ++kt) {
+            const u32x4* kp = sK + (kt >> 2) * 2 * PW + ((kt & 3) * KSQ + ks) * 64 + lane;
+            kh[kt] = kp[0];
+            kl[kt] = kp[PW];
         }
-        put_half(st, sV);
-        __syncthreads();
-        if (s + 1 < nsp) load_half(st, s + 1, 0);
-        if (live) {
-            float Ls = 0.f;
-            f32x4 os[JT];
 #pragma unroll
-            for (int j = 0; j < JT; ++j) os[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t3 = 0; t3 < 3; ++t3)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                u32x4 Ph, Pl;
-                float l, fr[4];
-                attn_probs(S[v], mv[v] == -INFINITY ? 0.f : mv[v], Ph, Pl, l);
-                Ls = fmaf(l, fac[v], Ls);
-                to_rows(fac[v], fr);
-                const uint2* vp = reinterpret_cast<const uint2*>(sV + (v >> 1) * 2 * PW) + ((v & 1) * 2) * 64 + lane;
-                u32x4 vh[JT], vl[JT];
-                f32x4 O[JT];
-#pragma unroll
-                for (int j = 0; j < JT; ++j) {
-                    const uint2 h0 = vp[j * 256], h1 = vp[j * 256 + 64], l0 = vp[2 * PW + j * 256], l1 = vp[2 * PW + j * 256 + 64];
-                    vh[j] = u32x4{h0.x, h0.y, h1.x, h1.y};
-                    vl[j] = u32x4{l0.x, l0.y, l1.x, l1.y};
-                }
-                attn_pv<JT>(Ph, Pl, vh, vl, O);
-#pragma unroll
-                for (int j = 0; j < JT; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) os[j][r] = fmaf(O[j][r], fr[r], os[j][r]);
-            }
-            const MergeFac f = merge_fac(M, Ms);
-            M = f.M;
-            Lsum = merge_add(Lsum, Ls, f);
-            float al[4], be[4];
-            to_rows(f.al, al);
-            to_rows(f.be, be);
-#pragma unroll
-            for (int j = 0; j < JT; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[j][r] = merge_add(o[j][r], os[j][r], MergeFac{0.f, al[r], be[r]});
-        }
-        if (s + 1 < nsp) put_half(st, sK);   // everybody is past this range's K since the barrier above
-        __syncthreads();
+            for (int kt = 0; kt < 8; ++kt)
+                S[kt >> 1][kt & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, t3 < 2 ? kh[kt] : kl[kt]), __builtin_bit_cast(bf16x8, t3 == 1 ? ql[ks] : qh[ks]),
+                    S[kt >> 1][kt & 1], 0, 0, 0);
     }
+    if (key0 + kAttnSplit - 1 > qpos_first) {   // causal mask: key position <= query position
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (key0 + v * 32 + k2 * 16 + g * 4 + r > qpos) S[v][k2][r] = -INFINITY;
+    }
+    Ms = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        float m = -INFINITY;
+#pragma unroll
+        for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m = fmaxf(m, S[v][k2][r]);
+        mv[v] = rows_max(m);
+        Ms = fmaxf(Ms, mv[v]);
+    }
+}
+// a per-query value, held by the lanes of column c, for the four queries 4 g + r of the P V layout
+__device__ inline void to_rows(float v, float (&out)[4]) {
+    const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[r] = __shfl(v, 4 * g + r, kWave);
+}
+// sum of exponentials and P V of a range, its groups added in order; probs(v, ...) as attn_probs for group v
+template <int HD, typename Probs>
+__device__ inline void sweep_values(const u32x4* sV, Probs probs, const float (&mv)[4], float Ms, float& Ls, f32x4 (&os)[HD / 16]) {
+    constexpr int JT = HD / 16, PW = kPlaneWords<HD>;
+    const int lane = threadIdx.x & 63;
+    float fac[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) fac[v] = mv[v] == -INFINITY ? 0.f : exp2_hw(mv[v] - Ms);
+    Ls = 0.f;
+#pragma unroll
+    for (int j = 0; j < JT; ++j) os[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        u32x4 Ph, Pl;
+        float l, fr[4];
+        probs(v, Ph, Pl, l);
+        Ls = fmaf(l, fac[v], Ls);
+        to_rows(fac[v], fr);
+        const uint2* vp = reinterpret_cast<const uint2*>(sV + (v >> 1) * 2 * PW) + ((v & 1) * 2) * 64 + lane;
+        u32x4 vh[JT], vl[JT];
+        f32x4 O[JT];
+#pragma unroll
+        for (int j = 0; j < JT; ++j) {
+            const uint2 h0 = vp[j * 256], h1 = vp[j * 256 + 64], l0 = vp[2 * PW + j * 256], l1 = vp[2 * PW + j * 256 + 64];
+            vh[j] = u32x4{h0.x, h0.y, h1.x, h1.y};
+            vl[j] = u32x4{l0.x, l0.y, l1.x, l1.y};
+        }
+        attn_pv<JT>(Ph, Pl, vh, vl, O);
+#pragma unroll
+        for (int j = 0; j < JT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) os[j][r] = fmaf(O[j][r], fr[r], os[j][r]);
+    }
+}
+// the running (M, Lsum, o) takes a range in
+template <int JT>
+__device__ inline void sweep_merge(float Ms, float Ls, const f32x4 (&os)[JT], float& M, float& Lsum, f32x4 (&o)[JT]) {
+    const MergeFac f = merge_fac(M, Ms);
+    M = f.M;
+    Lsum = merge_add(Lsum, Ls, f);
+    float al[4], be[4];
+    to_rows(f.al, al);
+    to_rows(f.be, be);
+#pragma unroll
+    for (int j = 0; j < JT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[j][r] = merge_add(o[j][r], os[j][r], MergeFac{0.f, al[r], be[r]});
+}
+// o projection's operand of the tile
+template <int JT>
+__device__ inline void sweep_store(void* xb, int row0, int R, int G, int gkv, float Lsum, const f32x4 (&o)[JT]) {
+    const int lane = threadIdx.x & 63, g = lane >> 4, cq = lane & 15;
     float Lr[4];
     to_rows(Lsum, Lr);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int rr = row0 + 4 * g + r;
         if (rr >= R) continue;
-        const int c = rr / G, f0 = (gkv * G + rr % G) * HD + cq;
+        const int c = rr / G, f0 = (gkv * G + rr % G) * (16 * JT) + cq;
 #pragma unroll
         for (int j = 0; j < JT; ++j) pack_store<kWideCT>(xb, c, f0 + 16 * j, o[j][r] / Lr[r]);
     }
+}
+// K (half 0) or V (half 1) planes of a range's two pages, hi and lo, by T threads through registers into LDS
+template <int HD, int T>
+struct SweepStage {
+    static constexpr int PW = kPlaneWords<HD>, NS = 4 * PW / T;   // words per thread
+    static_assert(kAttnSplit == 2 * kPage, "a key range is two pages");
+    u32x4 st[NS];
+    __device__ void load(const uint16_t* __restrict__ kv, const int32_t* __restrict__ page_table, int n_pages, int layer, int L, int gkv, int KV, int s, int half) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int page = page_table[min(2 * s + p, n_pages - 1)];
+            const u32x4* src = reinterpret_cast<const u32x4*>(kv + kv_plane(page, layer, L, gkv, KV, 2 * half, HD));   // hi and lo planes are adjacent
+#pragma unroll
+            for (int i = 0; i < NS / 2; ++i) st[p * (NS / 2) + i] = src[threadIdx.x + i * T];
+        }
+    }
+    __device__ void put(u32x4* dst) const {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int i = 0; i < NS / 2; ++i) dst[p * 2 * PW + threadIdx.x + i * T] = st[p * (NS / 2) + i];
+    }
+};
+
+// Attention of a prompt-ingestion pass in one sweep: a workgroup of four waves owns four consecutive 16-row query tiles of
+// one kv head, one per wave, and walks the key ranges from the first to the last one its queries see.  A range's K planes
+// (hi, lo), then its V planes, go through LDS for the four waves (K of the next range travels during P V, V during Q K^T);
+// every wave keeps its tile's running (M, Lsum, o) in registers and writes the o projection's operand itself, so no
+// partials go to memory and there is no merge kernel.  Within a range the arithmetic is that of attn_mfma: four groups of
+// 32 keys (its four waves), each from its own maximum, added in order; ranges are merged as attn_merge does: same bits.
+// With a workgroup per (kv head, range, four tiles) passes over a 3000-token prompt (head dim 64) spent 59 us per layer here and
+// 30 us in the merge, waiting on loads and barriers per 16-row tile; this took 52 us (10 us worth of MFMAs and 19 us of vector
+// instructions a wave, one wave per SIMD, so little of that overlaps: attn_pair overlaps them, and is taken where it fits).
+// grid ceil(query tiles / 4) * KV; 128 KB of LDS at head dim 128 (one workgroup per CU).
+template <int HD>
+constexpr int kAttnWideLds = 8 * kPage * HD * 2;   // two pages x (K or V: hi, lo) each for K and V, bytes
+template <int HD>
+__global__ __launch_bounds__(256, 1) void attn_wide(const float* __restrict__ qkv, const PassDesc* desc, const uint16_t* __restrict__ kv,
+                                                    const int32_t* __restrict__ page_table, int n_pages, void* xb, int layer, int L, int H,
+                                                    int KV, int nqkv) {
+    constexpr int JT = HD / 16;
+    extern __shared__ u32x4 aw_lds[];
+    u32x4* sK = aw_lds;            // [2 pages][hi, lo][plane]
+    u32x4* sV = aw_lds + 4 * kPlaneWords<HD>;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, cq = lane & 15;
+    // consecutive workgroups go round the eight XCDs: with eight kv heads each head's keys and values stay in one L2
+    const int gkv = blockIdx.x % KV, grp = gridDim.x / KV - 1 - blockIdx.x / KV;   // the groups with the most ranges first
+    const int w = desc->w, pos0 = desc->pos0, G = H / KV, R = w * G;
+    if (grp * 64 >= R) return;
+    const int tile = grp * 4 + wave, row0 = tile * 16;
+    const int nsp = (pos0 + (min(R, grp * 64 + 64) - 1) / G) / kAttnSplit + 1;                        // ranges of the workgroup
+    const int my_nsp = row0 < R ? (pos0 + (min(R, row0 + 16) - 1) / G) / kAttnSplit + 1 : 0;   // and of this wave's tile
+    SweepStage<HD, 256> st;
+    st.load(kv, page_table, n_pages, layer, L, gkv, KV, 0, 0);
+    const int rho = row0 + cq;
+    u32x4 qh[HD / 32], ql[HD / 32];
+    sweep_queries<HD>(qkv, nqkv, rho, R, G, gkv, g, qh, ql);
+    const int qpos = rho < R ? pos0 + rho / G : -1, qpos_first = pos0 + row0 / G;
+    float M = -INFINITY, Lsum = 0.f;
+    f32x4 o[JT];
+#pragma unroll
+    for (int j = 0; j < JT; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    st.put(sK);
+    __syncthreads();
+    for (int s = 0; s < nsp; ++s) {
+        st.load(kv, page_table, n_pages, layer, L, gkv, KV, s, 1);
+        const bool live = s < my_nsp;
+        f32x4 S[4][2];
+        float mv[4], Ms;
+        if (live) sweep_scores<HD>(sK, qh, ql, s * kAttnSplit, qpos, qpos_first, S, mv, Ms);
+        st.put(sV);
+        __syncthreads();
+        if (s + 1 < nsp) st.load(kv, page_table, n_pages, layer, L, gkv, KV, s + 1, 0);
+        if (live) {
+            float Ls;
+            f32x4 os[JT];
+            sweep_values<HD>(sV, [&](int v, u32x4& Ph, u32x4& Pl, float& l) { attn_probs(S[v], mv[v] == -INFINITY ? 0.f : mv[v], Ph, Pl, l); }, mv, Ms, Ls, os);
+            sweep_merge<JT>(Ms, Ls, os, M, Lsum, o);
+        }
+        if (s + 1 < nsp) st.put(sK);   // everybody is past this range's K since the barrier above
+        __syncthreads();
+    }
+    sweep_store<JT>(xb, row0, R, G, gkv, Lsum, o);
+}
+
+// planes of a range's pages straight into LDS, by T threads: lane l's 16 bytes land at the wave's destination + 16 l
+template <int HD, int T>
+__device__ inline void sweep_fetch(u32x4* dst, const uint16_t* __restrict__ kv, const int32_t* __restrict__ page_table, int n_pages, int layer, int L, int gkv,
+                                   int KV, int s, int half) {
+    constexpr int PW = kPlaneWords<HD>, NP = 2 * PW / T;   // words of a page per thread
+    const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int page = page_table[min(2 * s + p, n_pages - 1)];
+        const u32x4* src = reinterpret_cast<const u32x4*>(kv + kv_plane(page, layer, L, gkv, KV, 2 * half, HD)) + threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + i * T),
+                                             (__attribute__((address_space(3))) void*)(dst + p * 2 * PW + w0 + i * T), 16, 0, 0);
+    }
+}
+// One step's work on LDS.  The areas are told apart for the compiler: without that it waits for the fetches before the first read.
+template <typename Fetch, typename Work>
+__device__ __forceinline__ void apart(u32x4* __restrict__ to_k, u32x4* __restrict__ to_v, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
+                                      f32x4* __restrict__ o, float2* __restrict__ ml, Fetch fetch, Work work) {
+    fetch(to_k, to_v);
+    work(k, v, o, ml);
+}
+// The sweep of attn_wide with two waves per tile, for head dims up to 64: one takes the even key ranges, the other the odd ones, a step
+// apart, so that on every SIMD one wave multiplies by keys and takes exponentials while the other multiplies by values.  In step p
+// range p is scored and range p - 1 is summed; K of range p + 1 and V of range p come in meanwhile, straight into LDS (two
+// buffers each, so one barrier a step).  The second wave hands its ranges' sums to the first, which merges all of them in
+// order: same bits.  144.5 KB of LDS at head dim 64 (one workgroup per CU); at 128 the buffers do not fit.
+// Bound: the two waves' vector and matrix instructions, 1.8 us a range if nothing waited, and LDS (1.1 us).  us a launch of 1024 tiles, one
+// wave per tile / this, 4, 8, 12, 16, 20 ranges: 18.2 / 16.2, 31.6 / 27.0, 50.6 / 38.6, 66.5 / 50.9, 83.0 / 63.6.  On the way: two waves
+// that split every range's keys 72.5 at 20 ranges, this with the buffers filled through registers 70.7-72.4 (with no loads at all
+// 56), filled straight but with the exponentials beside the values' products, or with the fetches waited for at the first read, slower.
+template <int HD>
+constexpr int kAttnPairLds = 16 * kPage * HD * 2 + 4 * (HD / 16 * 64 * 16 + 2 * 16 * 4);
+template <int HD>
+__global__ __launch_bounds__(512, 1) void attn_pair(const float* __restrict__ qkv, const PassDesc* desc, const uint16_t* __restrict__ kv,
+                                                    const int32_t* __restrict__ page_table, int n_pages, void* xb, int layer, int L, int H,
+                                                    int KV, int nqkv) {
+    constexpr int JT = HD / 16, PW = kPlaneWords<HD>;
+    extern __shared__ u32x4 aw_lds[];
+    u32x4* sK = aw_lds;            // [2 buffers][2 pages][hi, lo][plane]
+    u32x4* sV = aw_lds + 8 * PW;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4, cq = lane & 15;
+    const int tw = wave & 3, odd = wave >> 2;   // the wave's tile in the workgroup, and whether it takes the odd ranges
+    f32x4* sO = reinterpret_cast<f32x4*>(aw_lds + 16 * PW) + tw * JT * 64 + lane;                    // handed over: sums,
+    float2* sML = reinterpret_cast<float2*>(aw_lds + 16 * PW + 4 * JT * 64) + tw * 16 + cq;   // maximum and sum of exponentials
+    // consecutive workgroups go round the eight XCDs: with eight kv heads each head's keys and values stay in one L2
+    const int gkv = blockIdx.x % KV, grp = gridDim.x / KV - 1 - blockIdx.x / KV;   // the groups with the most ranges first
+    const int w = desc->w, pos0 = desc->pos0, G = H / KV, R = w * G;
+    if (grp * 64 >= R) return;
+    const int row0 = (grp * 4 + tw) * 16;
+    const int nsp = (pos0 + (min(R, grp * 64 + 64) - 1) / G) / kAttnSplit + 1;                        // ranges of the workgroup
+    const int my_nsp = row0 < R ? (pos0 + (min(R, row0 + 16) - 1) / G) / kAttnSplit + 1 : 0;   // and of this wave's tile
+    auto fetch = [&](u32x4* dst, int r, int half) {   // K or V of range r
+        sweep_fetch<HD, 512>(dst, kv, page_table, n_pages, layer, L, gkv, KV, r, half);
+    };
+    fetch(sK, 0, 0);
+    const int rho = row0 + cq;
+    u32x4 qh[HD / 32], ql[HD / 32];
+    sweep_queries<HD>(qkv, nqkv, rho, R, G, gkv, g, qh, ql);
+    const int qpos = rho < R ? pos0 + rho / G : -1, qpos_first = pos0 + row0 / G;
+    float M = -INFINITY, Lsum = 0.f;
+    f32x4 o[JT];
+    u32x4 Ph[4], Pl[4];   // of the range that the wave scored last, as attn_probs
+    float lv[4], mv[4], Ms = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < JT; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) { Ph[v] = Pl[v] = u32x4{0u, 0u, 0u, 0u}; lv[v] = 0.f; mv[v] = -INFINITY; }
+    auto take_odd = [&](const f32x4* sO, const float2* sML) {   // the other wave's range, handed over before the last barrier
+        f32x4 os[JT];
+#pragma unroll
+        for (int j = 0; j < JT; ++j) os[j] = sO[j * 64];
+        const float2 ml = *sML;
+        sweep_merge<JT>(ml.x, ml.y, os, M, Lsum, o);
+    };
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    for (int p = 0; p <= nsp; ++p) {
+        // into buffers that were read in the step before the last barrier
+        auto next = [&](u32x4* to_k, u32x4* to_v) {
+            if (p + 1 < nsp) fetch(to_k, p + 1, 0);
+            if (p < nsp) fetch(to_v, p, 1);
+        };
+        auto work = [&](const u32x4* k, const u32x4* v, f32x4* sO, float2* sML) {
+            if ((p & 1) == odd) {
+                if (p >= my_nsp) return;
+                f32x4 S[4][2];
+                sweep_scores<HD>(k, qh, ql, p * kAttnSplit, qpos, qpos_first, S, mv, Ms);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) attn_probs(S[u], mv[u] == -INFINITY ? 0.f : mv[u], Ph[u], Pl[u], lv[u]);
+                return;
+            }
+            if (odd == 0 && p >= 3 && p - 2 < my_nsp) take_odd(sO, sML);
+            if (p == 0 || p - 1 >= my_nsp) return;
+            float Ls;
+            f32x4 os[JT];
+            sweep_values<HD>(v, [&](int u, u32x4& ph, u32x4& pl, float& l) { ph = Ph[u]; pl = Pl[u]; l = lv[u]; }, mv, Ms, Ls, os);
+            if (odd) {
+#pragma unroll
+                for (int j = 0; j < JT; ++j) sO[j * 64] = os[j];
+                if (g == 0) *sML = make_float2(Ms, Ls);
+            } else {
+                sweep_merge<JT>(Ms, Ls, os, M, Lsum, o);
+            }
+        };
+        apart(sK + ((p + 1) & 1) * 4 * PW, sV + (p & 1) * 4 * PW, sK + (p & 1) * 4 * PW, sV + ((p + 1) & 1) * 4 * PW, sO, sML, next, work);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    if (odd) return;
+    if ((nsp & 1) == 0 && nsp - 1 < my_nsp) take_odd(sO, sML);   // the last range, if it is the other wave's
+    sweep_store<JT>(xb, row0, R, G, gkv, Lsum, o);
 }
 
 // ---- fp32 models -------------------------------------------------------------------------------------------
@@ -2434,6 +2590,8 @@ int model_kernels_init(char* err) {
                                 attn_lds_bytes(128)), err);
     PSD_HIP(hipFuncSetAttribute((const void*)attn_wide<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnWideLds<128>), err);
     PSD_HIP(hipFuncSetAttribute((const void*)attn_wide<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnWideLds<64>), err);
+    PSD_HIP(hipFuncSetAttribute((const void*)attn_pair<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnPairLds<64>), err);
+    PSD_HIP(hipFuncSetAttribute((const void*)attn_pair<32>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttnPairLds<32>), err);
     int rc;
     if ((rc = lb_kernels_init<EPI_RESID>(err)) != PSD_OK) return rc;
     if ((rc = lb_kernels_init<EPI_LOGITS>(err)) != PSD_OK) return rc;
@@ -2971,7 +3129,9 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
     //   512 tiles   7: 33 / 28 |           14: 55 / 50 | 91 / 82   25: 75 / 84 | 137 / 138
     //   768 tiles  27: 104 / 86 | 205 / 145
     // (a sweep takes 10 us and 3 for every range after the first | 13 and 5; the other route starts at 18-23 us and grows with
-    // tiles times ranges).
+    // tiles times ranges).  Head dims up to 64 sweep with two waves per tile since, where there is a second range for the second
+    // wave (attn_wide / attn_pair, us a launch of 64 tiles: one range 7.7-8.3 / 8.3-8.9, two 11.0-11.6 / 10.8-11.3, three 14.2-14.5 / 13.4-13.6); the
+    // lines above are left where head dim 128 has them.
     const int tiles = KV * ((wmax * G + 15) / 16), ranges = (std::min(M.max_seq, M.len + wmax) + kAttnSplit - 1) / kAttnSplit;
     const bool sweep = c128 && (tiles >= 512 || ranges <= (tiles >= 384 ? 6 : tiles >= 256 ? 4 : 3));
     const bool fold_merge = wmax <= 4 && d <= 2048 && d / 16 <= 256 && H * hd == d && nsplit <= kFoldSplits;
@@ -2991,7 +3151,8 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
         const uint16_t* kvp = (const uint16_t*)M.kv;
 #define PSD_ATTN(HD_)                                                                                                            \
     do {                                                                                                                         \
-        if (sweep) attn_wide<HD_><<<((wmax * G + 63) / 64) * KV, 256, kAttnWideLds<HD_>, stream>>>(M.qkv, M.desc, kvp, M.page_table, M.n_pages, xb2, l, M.L, H, KV, M.nqkv); \
+        if (sweep && HD_ <= 64 && ranges >= 2) attn_pair<HD_ <= 64 ? HD_ : 64><<<((wmax * G + 63) / 64) * KV, 512, kAttnPairLds<HD_>, stream>>>(M.qkv, M.desc, kvp, M.page_table, M.n_pages, xb2, l, M.L, H, KV, M.nqkv); \
+        else if (sweep) attn_wide<HD_><<<((wmax * G + 63) / 64) * KV, 256, kAttnWideLds<HD_>, stream>>>(M.qkv, M.desc, kvp, M.page_table, M.n_pages, xb2, l, M.L, H, KV, M.nqkv); \
         else attn_mfma<HD_><<<agrid, 256, 0, stream>>>(M.qkv, M.desc, kvp, M.page_table, M.n_pages, M.attn_part, l, M.L, H, KV, M.nqkv, qt_per_wg); \
     } while (0)
         if (hd == 128) PSD_ATTN(128); else if (hd == 64) PSD_ATTN(64); else PSD_ATTN(32);

@@ -244,6 +244,27 @@ def test_bf16_wide_attention_is_bit_exact(which, n):
     ref = oracle.Model(SWEEP[which], blobs[which], synth.DTYPE_BF16, 10000.0, 1408).forward(toks, 0)[n:]
     assert np.abs(out[0] - ref).max() <= TOL_BF16
 
+# head dims 64 and 32 sweep with two waves per query tile that take the key ranges in turn, from the second range on: one range (one
+# wave a tile), an even and an odd number of them, tiles of one workgroup that end in different ranges, a workgroup with tiles beyond the last row
+@pytest.mark.parametrize("shape", [ModelShape(1, 512, 8, 8, 512, 200), ModelShape(1, 512, 16, 8, 512, 200)])
+@pytest.mark.parametrize("n", [33, 128, 129, 300, 384, 509])
+def test_bf16_two_wave_sweep_is_bit_exact(shape, n):
+    stub = ModelShape(1, 64, 2, 1, 64, 200)
+    small = synth.target_weights(stub, 85, synth.DTYPE_BF16, sigma=0.03)
+    blob = synth.target_weights(shape, 86, synth.DTYPE_BF16, sigma=0.05)
+    ctx = _ctx((stub, stub, shape), (small, small, blob), synth.DTYPE_BF16, 10000.0, 640, k1=1, k2=1, flags=0x100)
+    toks = synth.tokens(23, 0, n + 3, 200)
+    out = []
+    for step in (512, 32):
+        for pos in range(0, n, step):
+            ctx.forward(2, toks[pos:min(pos + step, n)], pos, want_logits=False)
+        out.append(ctx.forward(2, toks[n:n + 3], n))
+    ctx.close()
+    assert np.array_equal(out[0], out[1])
+    ref = oracle.Model(shape, blob, synth.DTYPE_BF16, 10000.0, 640).forward(toks, 0)[n:]
+    assert np.abs(out[0] - ref).max() <= TOL_BF16
+
+
 # more than 64 key ranges: narrow passes then merge their partials in two turns of a wave's lanes, wide ones merge range by range
 MANY = (ModelShape(2, 1024, 32, 8, 512, 200), ModelShape(2, 1024, 16, 16, 512, 200), ModelShape(2, 2048, 16, 16, 512, 200))
 
