@@ -248,10 +248,37 @@ static int upload_pieces(psd_ctx* c, std::initializer_list<Piece> pieces) {
 static bool passes_expired(psd_ctx* c) {
     if (!__atomic_load_n(&c->res->stuck, __ATOMIC_ACQUIRE)) return false;
     __atomic_store_n(&c->res->stuck, 0u, __ATOMIC_RELEASE);
-    for (auto& M : c->M) M.one_launch = false;
+    for (auto& M : c->M) M.one_launch = M.room = false;
     note_wait_expired();
     return true;
 }
+
+// Room for the one-launch passes of a round: places for the largest of them (they run one after the other), or none of them is one
+// launch.  From before the passes are stamped until their end is known.
+struct PassRoom {
+    struct Pass { int model, wcls; };
+    psd_ctx* c;
+    Places* places = nullptr;
+    int n = 0;
+    PassRoom(psd_ctx* ctx, std::initializer_list<Pass> passes) : c(ctx) {
+        Places* of = nullptr;
+        for (const Pass& p : passes) {
+            n = std::max(n, model_places(c->M[p.model], p.wcls));
+            if (c->M[p.model].one_launch) of = c->M[p.model].places;   // the same for all
+        }
+        if (n == 0 || !of->take(n)) return;
+        places = of;
+        for (const Pass& p : passes) c->M[p.model].room = c->M[p.model].one_launch;
+    }
+    PassRoom(const PassRoom&) = delete;
+    PassRoom& operator=(const PassRoom&) = delete;
+    void give() {
+        if (places) places->give(n);
+        places = nullptr;
+        for (auto& M : c->M) M.room = false;
+    }
+    ~PassRoom() { give(); }
+};
 
 // Enqueues the round's result for the host and waits for it: the host watches its own memory (a stream synchronisation costs
 // 10-20 us more per round) and asks the stream now and then, so that an error or a result that never comes ends the wait.
@@ -672,12 +699,14 @@ extern "C" int psd_forward(psd_ctx* c, int32_t which, const int32_t* tokens, int
     PassDesc d;
     fill_desc(d, tokens, 0, w, 0, logits_out ? w : 0, 0);
     d.pos0 = pos0;
+    PassRoom room(c, {{which, wclass(w)}});
     do {
         if ((rc = model_stamp(M, d, 1, c->stream, c->err)) != PSD_OK) return rc;
         if ((rc = upload(c, M.desc, &d, desc_bytes(d))) != PSD_OK) return rc;
         if ((rc = run_pass(c, which, wclass(w), logits_out ? c->HL : nullptr, false)) != PSD_OK) return rc;
         if ((rc = stage_sync(c)) != PSD_OK) return rc;
     } while (passes_expired(c));
+    room.give();
     M.len = pos0 + w;
     if (logits_out) PSD_HIP(hipMemcpy(logits_out, c->HL, (size_t)w * c->V * sizeof(float), hipMemcpyDeviceToHost), c->err);
     return PSD_OK;
@@ -740,6 +769,7 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
             fill_desc(dd, seq.data(), D.len, L, 0, 1, 0);
             fill_desc(qd, seq.data(), Q.len, L, m, m + 1, nbuf);
             SampleCtl sc{seed, L, 0, hq, 0};
+            PassRoom room(c, {{0, wclass(L - D.len)}, {0, 1}, {1, wclass(hq + m)}});
             if ((rc = model_stamp(D, dd, m, c->stream, c->err)) != PSD_OK || (rc = model_stamp(Q, qd, 1, c->stream, c->err)) != PSD_OK) return rc;
             if ((rc = upload_pieces(c, {{D.desc, &dd, desc_bytes(dd)}, {Q.desc, &qd, desc_bytes(qd)}, {c->chain, &sc, sizeof(sc)}})) != PSD_OK) return rc;
             c->timer.begin(c->stream, 0);
@@ -754,6 +784,7 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
             rc = accept_sync(c, "accept stage1", c->QL + (size_t)nbuf * V, c->DL, c->round_tok, m, T_q, seed, (uint32_t)L, 1u, bonus, assisted, m);
             if (rc == kPassExpired) continue;
             if (rc != PSD_OK) return rc;
+            room.give();
             st.passes_d += m;
             st.passes_q++;
             if ((rc = note_rows(c, 0, c->DL, m)) != PSD_OK) return rc;
@@ -783,6 +814,7 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
         if ((rc = map_pages(c, T, T.len, C + k2)) != PSD_OK) return rc;
         PassDesc td;
         fill_desc(td, seq.data(), T.len, C + k2, 0, k2 + 1, 0);
+        PassRoom room(c, {{2, wclass(wT)}});
         do {
             if ((rc = model_stamp(T, td, 1, c->stream, c->err)) != PSD_OK) return rc;
             if ((rc = upload_pieces(c, {{T.desc, &td, desc_bytes(td)}, {c->win_tok, seq.data() + C, k2 * sizeof(int32_t)}})) != PSD_OK) return rc;
@@ -792,6 +824,7 @@ extern "C" int psd_generate(psd_ctx* c, const int32_t* prompt, int32_t n_prompt,
             rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->win_tok, k2, T_t, seed, (uint32_t)C, 2u, 1, greedy ? 2 : 0, 0);
         } while (rc == kPassExpired);
         if (rc != PSD_OK) return rc;
+        room.give();
         st.passes_t++;
         if ((rc = note_rows(c, 2, c->TL, k2 + 1)) != PSD_OK) return rc;
         const int n = c->res->acc.n_accepted, y = c->res->acc.next_token;
@@ -928,6 +961,7 @@ extern "C" int psd_generate_sd(psd_ctx* c, int32_t proposer, int32_t k, float ta
         fill_desc(pd, seq.data(), P.len, C, 0, 1, 0);
         fill_desc(td, seq.data(), T.len, C, k, k + 1, 0);
         SampleCtl sc{seed, C, 0, ht, 0};
+        PassRoom room(c, {{proposer, wclass(C - P.len)}, {proposer, 1}, {2, wclass(ht + k)}});
         if ((rc = model_stamp(P, pd, k, c->stream, c->err)) != PSD_OK || (rc = model_stamp(T, td, 1, c->stream, c->err)) != PSD_OK) return rc;
         if ((rc = upload_pieces(c, {{P.desc, &pd, desc_bytes(pd)}, {T.desc, &td, desc_bytes(td)}, {c->chain, &sc, sizeof(sc)}})) != PSD_OK) return rc;
         c->timer.begin(c->stream, proposer);
@@ -940,6 +974,7 @@ extern "C" int psd_generate_sd(psd_ctx* c, int32_t proposer, int32_t k, float ta
         rc = accept_sync(c, "accept stage2", c->TL, c->QL, c->round_tok, k, tau, seed, (uint32_t)C, 2u, 1, greedy ? 2 : 0, k);
         if (rc == kPassExpired) continue;
         if (rc != PSD_OK) return rc;
+        room.give();
         (proposer == 0 ? st.passes_d : st.passes_q) += k;
         st.passes_t++;
         if ((rc = note_rows(c, proposer, c->QL, k)) != PSD_OK) return rc;
@@ -1000,6 +1035,7 @@ extern "C" int psd_generate_plain(psd_ctx* c, int32_t which, const int32_t* prom
         if ((rc = map_pages(c, M, M.len, L)) != PSD_OK) return rc;
         PassDesc d;
         fill_desc(d, seq.data(), M.len, L, 0, 1, 0);
+        PassRoom room(c, {{which, wclass(L - M.len)}});
         do {
             if ((rc = model_stamp(M, d, 1, c->stream, c->err)) != PSD_OK) return rc;
             if ((rc = upload_pieces(c, {{M.desc, &d, desc_bytes(d)}})) != PSD_OK) return rc;

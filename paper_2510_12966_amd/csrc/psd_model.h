@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "psd_host.h"
+#include "psd_places.h"
 
 namespace psd {
 
@@ -143,7 +144,10 @@ struct Model {
     PanelScratch panel_qkv, panel_res;   // wide passes, sums of the K quarters of the q/k/v, and of the o and down, projections
     float* panel_rs = nullptr;   // wide passes: [512] rms scale per column, for gate/up (in attn_part)
     float* gu = nullptr;      // fp32 models: [32][F], the SwiGLU's output
-    bool one_launch = false;  // fp32 models small enough for it: passes with logits over few key ranges are one launch
+    bool one_launch = false;  // fp32 models small enough for it: passes with logits over few key ranges may be one launch
+    bool room = false;        // and are, while the caller holds places for their workgroups
+    int grid_max = 0;         // widest such launch
+    Places* places = nullptr; // of the model's device
     uint32_t tag_last = 0;    // last tag handed out to a pass
     uint32_t* stuck = nullptr;   // pinned host memory as the device addresses it: a one-launch pass whose bounded wait expired sets it
     PassDesc* desc = nullptr;
@@ -174,9 +178,12 @@ int model_stamp(Model& M, PassDesc& d, int passes, hipStream_t stream, char* err
 // logits: device [rows][V] destination (may be null when the pass produces none).
 int model_forward(Model& M, int wmax, float* logits, hipStream_t stream, Profiler* prof, char* err);
 
+// Places that a pass with logits of launch class wcls takes if it is one launch; 0: it is not
+int model_places(const Model& M, int wcls);
+
 // Whether the pass that model_forward would enqueue now is one launch (M.ctx_bucket is set, the others as there)
 bool model_one_launch(const Model& M, int wcls, const float* logits);
 
-int model_kernels_init(char* err);  // one-time function attributes
+int model_kernels_init(char* err);  // one-time function attributes, and the current device's places
 
 }  // namespace psd

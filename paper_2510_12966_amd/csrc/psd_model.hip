@@ -13,6 +13,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <type_traits>
 
 namespace psd {
@@ -2584,6 +2585,44 @@ static int lb_kernels_init(char* err) {
     return PSD_OK;
 }
 
+// Places for the workgroups of one-launch passes: three quarters of what the device holds of them, whatever the mix of
+// instantiations (each takes at most 1 / n of a compute unit if n of the largest fit into one).  The last quarter is left to launches
+// whose workgroups wait for a few neighbours only (a row of an ACCEPT sweep: 64): with room for those, everything else ends by itself.
+constexpr int kMaxDevices = 64;   // devices beyond take the chains
+struct DevicePlaces {
+    Places places;
+    int cus = 0;
+};
+static DevicePlaces g_pass_places[kMaxDevices];
+
+template <int HD>
+static hipError_t pass_f32_fit(int* least) {
+    for (const void* f : {(const void*)pass_f32<HD, 1>, (const void*)pass_f32<HD, 4>, (const void*)pass_f32<HD, 8>}) {
+        int n = 0;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 256, 0);
+        if (e != hipSuccess) return e;
+        *least = std::min(*least, n);
+    }
+    return hipSuccess;
+}
+static int pass_places_init(char* err) {
+    static std::mutex once;
+    std::lock_guard<std::mutex> hold(once);
+    int dev = 0, least = 1 << 20;
+    PSD_HIP(hipGetDevice(&dev), err);
+    if (dev >= kMaxDevices || g_pass_places[dev].cus > 0) return PSD_OK;
+    DevicePlaces& d = g_pass_places[dev];
+    PSD_HIP(pass_f32_fit<16>(&least), err);
+    PSD_HIP(pass_f32_fit<32>(&least), err);
+    PSD_HIP(pass_f32_fit<64>(&least), err);
+    PSD_HIP(pass_f32_fit<128>(&least), err);
+    int cus = 0;
+    PSD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), err);
+    d.places.open(cus * least * 3 / 4);
+    d.cus = cus;
+    return PSD_OK;
+}
+
 int model_kernels_init(char* err) {
     // attention stages two pages of K and V as fp32 in LDS: up to ~135 KB of the 160 KB a gfx950 CU has
     PSD_HIP(hipFuncSetAttribute((const void*)attn_partial, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -2595,7 +2634,7 @@ int model_kernels_init(char* err) {
     int rc;
     if ((rc = lb_kernels_init<EPI_RESID>(err)) != PSD_OK) return rc;
     if ((rc = lb_kernels_init<EPI_LOGITS>(err)) != PSD_OK) return rc;
-    return PSD_OK;
+    return pass_places_init(err);
 }
 
 // bytes of the four K quarters' sums of one group of tcw column tiles
@@ -2697,7 +2736,7 @@ static int f32_pass_grid(const Model& M, int wcls) {
     for (int i = 0; i < 6; ++i) most = std::max(most, nux[i] * (i == 1 ? wcls : groups));
     return most;
 }
-// A pass in one launch: models whose projections a workgroup per CU can hold (16 weights per lane of a row, no more than the 2 M
+// A pass in one launch, of a workgroup per CU at most (grid_max): models whose projections that many can hold (16 weights per lane of a row, no more than the 2 M
 // weights of a projection up to which proj_f32 gives every group of columns workgroups of its own).
 static bool f32_one_launch(const Model& M) {
     const size_t most = (size_t)2 << 20;
@@ -2819,15 +2858,26 @@ int model_init(Model& M, const psd_model_desc& m, const char* tag, int max_seq, 
     }
     M.pages_mapped = 0;
     M.len = 0;
-    M.one_launch = f32_one_launch(M);
+    int dev = 0;
+    PSD_HIP(hipGetDevice(&dev), err);
+    M.one_launch = f32_one_launch(M) && dev < kMaxDevices;
+    if (M.one_launch) {
+        M.places = &g_pass_places[dev].places;
+        M.grid_max = std::min(g_pass_places[dev].cus, M.places->total());
+    }
     M.tag_last = 0;
     PSD_HIP(hipStreamSynchronize(stream), err);
     PSD_HIP(hipGetLastError(), err);
     return PSD_OK;
 }
 
+int model_places(const Model& M, int wcls) {
+    const int grid = M.one_launch ? f32_pass_grid(M, wcls) : 0;
+    return grid <= M.grid_max ? Places::of(grid) : 0;
+}
+
 bool model_one_launch(const Model& M, int wcls, const float* logits) {
-    return M.one_launch && logits && f32_pass_grid(M, wcls) <= 256 && std::min(M.nsplit_max, kCtxBuckets[M.ctx_bucket]) <= kF32OneSplits;
+    return M.room && logits && model_places(M, wcls) > 0 && std::min(M.nsplit_max, kCtxBuckets[M.ctx_bucket]) <= kF32OneSplits;
 }
 
 int model_map_pages(Model& M, int keep, int upto, int* first_changed, int* n_changed, char* err) {
@@ -2896,7 +2946,7 @@ static void launch_proj_f32(Launch& L, const char* family, F32Args a) {
 }
 
 int model_stamp(Model& M, PassDesc& d, int passes, hipStream_t stream, char* err) {
-    if (!M.one_launch) return PSD_OK;
+    if (!M.room) return PSD_OK;
     d.tag_step = 5 * M.L;
     const uint32_t span = (uint32_t)passes * d.tag_step;
     if (M.tag_last > 0xffffffffu - span) {   // used up: the slots forget them

@@ -1,4 +1,6 @@
 """GPU parity of the two-stage loop against the CPU oracle, through psd_generate."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -336,6 +338,32 @@ def test_rounds_are_run_again_after_an_expired_pass(tiny_stack, kind):
     if kind == "row_stats":
         for m in res[0][2]:
             assert np.allclose(res[0][2][m], res[1][2][m], rtol=1e-12), m   # sums of the same numbers in the same order
+
+
+def test_contexts_on_their_own_threads_share_the_device(tiny_stack):
+    # one-launch passes of up to 192 workgroups (verify passes of nine tokens) and of 256 (of 32) by six contexts at a time: all of them together
+    # would not fit, so some rounds go as chains; nobody's wait expires and everybody's tokens are those of a context that runs alone
+    cfg, d, q, t, prompt = tiny_stack
+    windows = [(4, 8), (4, 8), (30, 31), (4, 8), (2, 4), (30, 31)]
+    ctxs = [_ctx(cfg, (d, q, t), 16 + 64 + 40, 0.3, 0.2, k1, k2) for k1, k2 in windows]
+    alone = [c.generate(prompt, 64, 5 + i)[0] for i, c in enumerate(ctxs)]
+    before = psd.get_accept_expiries()
+    got = [[] for _ in ctxs]
+
+    def work(i):
+        for _ in range(6):
+            got[i].append(ctxs[i].generate(prompt, 64, 5 + i)[0])
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(ctxs))]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert psd.get_accept_expiries() == before and psd.get_accept_path() == 0
+    for i, runs in enumerate(got):
+        assert len(runs) == 6 and all(np.array_equal(r, alone[i]) for r in runs), i
+    for c in ctxs:
+        c.close()
 
 
 @pytest.mark.parametrize("case", range(18))
