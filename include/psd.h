@@ -292,7 +292,8 @@ int psd_accept_batch_noalloc(const float* logits_p, const float* logits_q, const
  *      a stuck kernel
  * Both sweeps give bit-identical results.  When a wait expires, psd_accept, psd_generate and psd_generate_sd
  * switch the process to path 1 and run the stage again; psd_get_accept_path tells which path is in force.  When one expires in a
- * pass, the context runs that pass again, and all later ones, as a launch per projection (bit-identical as well).
+ * pass, the context runs that pass again, and the next thousand or so rounds (twice as many after each further one), as a launch
+ * per projection (bit-identical as well).
  * The switch may be flipped while other threads run stages (they pick it up at their next stage).  Returns PSD_EINVAL
  * for other values. */
 int psd_set_accept_path(int32_t path);

@@ -30,6 +30,9 @@ struct RoundResult {  // pinned host memory that publish_round fills with what a
     uint32_t stuck;   // set by a one-launch pass whose bounded wait expired
 };
 constexpr int kPassExpired = 1;   // (internal) the round's passes have to be run again
+// Rounds that run as chains of launches after an expired wait, doubled each time.  The wait cost 50 ms, a pass in one launch saves 0.03 to
+// 0.2 ms, so what kept the first launch from being resident may pass at little loss, and what stays costs next to nothing.
+constexpr int kPassPause = 1024, kPassPauseMost = 1 << 20;
 
 // Adaptive controller (the header states the rule).  Pure host arithmetic on accept counts between outer iterations.
 struct Controller {
@@ -153,6 +156,7 @@ struct psd_ctx {
     char* stage_dev = nullptr;       // the same two as the device addresses them
     RoundResult* res_dev = nullptr;
     uint32_t res_seq = 0;
+    int pass_pause = 0, pass_pause_next = kPassPause;   // rounds for which one-launch passes stay chains; after the next expired wait
     // graphs: [model][width class 4 / 16 / 32]
     GraphSlot graphs[3][kNumNarrowClasses][kNumCtxBuckets];   // [model][launch class][context bucket]
     GraphSlot chain_graphs[3][3][kNumNarrowClasses][kNumCtxBuckets];  // sampling steps: [proposer][model whose pass descriptor receives the tokens][launch class][context bucket]
@@ -244,11 +248,13 @@ static int upload_pieces(psd_ctx* c, std::initializer_list<Piece> pieces) {
 }
 
 // The stream has been waited for: whether the bounded wait of a one-launch pass has expired since this was last asked.  Passes are
-// chains of launches in this context from then on; nothing the host keeps has moved, so the caller runs the passes again.
+// chains of launches for a while then; nothing the host keeps has moved, so the caller runs the passes again.
 static bool passes_expired(psd_ctx* c) {
     if (!__atomic_load_n(&c->res->stuck, __ATOMIC_ACQUIRE)) return false;
     __atomic_store_n(&c->res->stuck, 0u, __ATOMIC_RELEASE);
-    for (auto& M : c->M) M.one_launch = M.room = false;
+    for (auto& M : c->M) M.room = false;
+    c->pass_pause = c->pass_pause_next;
+    c->pass_pause_next = std::min(2 * c->pass_pause_next, kPassPauseMost);
     note_wait_expired();
     return true;
 }
@@ -266,7 +272,9 @@ struct PassRoom {
             n = std::max(n, model_places(c->M[p.model], p.wcls));
             if (c->M[p.model].one_launch) of = c->M[p.model].places;   // the same for all
         }
-        if (n == 0 || !of->take(n)) return;
+        if (n == 0) return;
+        if (c->pass_pause > 0) { --c->pass_pause; return; }
+        if (!of->take(n)) return;
         places = of;
         for (const Pass& p : passes) c->M[p.model].room = c->M[p.model].one_launch;
     }

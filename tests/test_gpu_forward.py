@@ -384,6 +384,41 @@ def test_fp32_one_launch_passes_equal_the_chain_of_launches(layers, d, h, kv, f,
     assert np.abs(got[0][:160] - ref).max() <= TOL_F32
 
 
+def test_fp32_passes_return_to_one_launch_after_an_expired_wait():
+    # what kept one launch from being resident may be over: after a pause of 1024 passes the context tries again
+    shape = ModelShape(2, 64, 4, 2, 256, 512)
+    blob = synth.target_weights(shape, 61, synth.DTYPE_F32, sigma=0.06)
+    ctx = _ctx((shape,) * 3, (blob,) * 3, synth.DTYPE_F32, 10000.0, 300)
+    toks = synth.tokens(24, 0, 8, 512)
+
+    def route():
+        ctx.profile(True)
+        out = ctx.forward(0, toks, 0)
+        rows = [r["name"] for r in ctx.kernel_stats() if r["launches"]]
+        ctx.profile(False)
+        return out, any(r.startswith("pass_f32") for r in rows)
+
+    ref, one = route()
+    assert one
+    before = psd.get_accept_expiries()
+    try:
+        psd.set_accept_path(3)
+        first = ctx.forward(0, toks, 0)
+    finally:
+        psd.set_accept_path(0)
+    assert psd.get_accept_expiries() - before == 1
+    paused, one = route()
+    assert not one
+    for _ in range(1022):
+        ctx.forward(0, toks[:1], 0)
+    assert not route()[1]
+    after, one = route()
+    assert one and psd.get_accept_expiries() - before == 1
+    ctx.close()
+    for out in (first, paused, after):
+        assert np.array_equal(out, ref)
+
+
 def test_bf16_ingestion_at_page_split_and_pass_boundaries():
     # prompt lengths around the KV page (64), the attention key range (128) and the pass widths (128, 512):
     # the widest passes, 32-token passes and a ragged mix leave identical logits for the tokens that follow
