@@ -988,8 +988,9 @@ __device__ inline void chain_advance(const ChainStep& s, int t) {
     s.samp_tok[0] = t;
     if (step < kMaxW) s.round_tok[step] = t;
     if (s.q_desc && s.chain->q_base >= 0 && s.chain->q_base + step < kMaxW) s.q_desc->tok[s.chain->q_base + step] = t;
-    s.d_desc->pos0 += s.d_desc->w;
-    s.d_desc->w = 1;
+    const int w = s.d_desc->w;
+    s.d_desc->pos0 += max(w, 0);
+    s.d_desc->w = min(w, 1);   // kPassGone stays: the steps behind an expired pass have no tokens either
     s.d_desc->tok[0] = t;
     s.d_desc->logit_row0 = step + 1;
     s.d_desc->tag0 += s.d_desc->tag_step;

@@ -27,7 +27,7 @@ struct RoundResult {  // pinned host memory that publish_round fills with what a
     int32_t tok[kMaxW];
     float div[kMaxW];
     uint32_t seq;     // written last: the result with this number is there
-    uint32_t stuck;   // set by a one-launch pass whose bounded wait expired
+    uint32_t gone;    // the bounded wait of a one-launch pass has expired
 };
 constexpr int kPassExpired = 1;   // (internal) the round's passes have to be run again
 // Rounds that run as chains of launches after an expired wait, doubled each time.  The wait cost 50 ms, a pass in one launch saves 0.03 to
@@ -187,10 +187,15 @@ __global__ __launch_bounds__(256) void scatter_pieces(const uint32_t* __restrict
     }
 }
 
+struct PassDescs { PassDesc* of[3]; };
 // what the host needs of a round, into pinned host memory; its number goes last.  One wave.
 __global__ __launch_bounds__(64) void publish_round(const AcceptOut* acc, const int32_t* tok, int n_tok, const float* div, int n_div,
-                                                    RoundResult* res, uint32_t seq) {
+                                                    PassDescs descs, RoundResult* res, uint32_t seq) {
     const int i = threadIdx.x;
+    if (i < 3 && descs.of[i]->w == kPassGone) {
+        descs.of[i]->w = 0;   // told once
+        res->gone = 1;
+    }
     if (i < n_tok) res->tok[i] = tok[i];
     if (i < n_div) res->div[i] = div[i];
     if (acc && i == 0) res->acc = *acc;
@@ -247,12 +252,12 @@ static int upload_pieces(psd_ctx* c, std::initializer_list<Piece> pieces) {
     return PSD_OK;
 }
 
-// The stream has been waited for: whether the bounded wait of a one-launch pass has expired since this was last asked.  Passes are
+// A round's result is there: whether the bounded wait of a one-launch pass has expired since this was last asked.  Passes are
 // chains of launches for a while then; nothing the host keeps has moved, so the caller runs the passes again.
 static bool passes_expired(psd_ctx* c) {
-    if (!__atomic_load_n(&c->res->stuck, __ATOMIC_ACQUIRE)) return false;
-    __atomic_store_n(&c->res->stuck, 0u, __ATOMIC_RELEASE);
-    for (auto& M : c->M) M.room = false;
+    if (!__atomic_load_n(&c->res->gone, __ATOMIC_ACQUIRE)) return false;
+    __atomic_store_n(&c->res->gone, 0u, __ATOMIC_RELEASE);
+    for (auto& M : c->M) M.room = M.short_passes = false;
     c->pass_pause = c->pass_pause_next;
     c->pass_pause_next = std::min(2 * c->pass_pause_next, kPassPauseMost);
     note_wait_expired();
@@ -293,7 +298,7 @@ struct PassRoom {
 // Everything enqueued before is then done.  kPassExpired: it has to be run again.
 static int fetch_round(psd_ctx* c, const AcceptOut* acc, const int32_t* tok, int n_tok, int n_div) {
     const uint32_t seq = ++c->res_seq;
-    publish_round<<<1, 64, 0, c->stream>>>(acc, tok, n_tok, c->acc_div, n_div, c->res_dev, seq);
+    publish_round<<<1, 64, 0, c->stream>>>(acc, tok, n_tok, c->acc_div, n_div, PassDescs{{c->M[0].desc, c->M[1].desc, c->M[2].desc}}, c->res_dev, seq);
     PSD_HIP(hipGetLastError(), c->err);
     auto there = [&] { return __atomic_load_n(&c->res->seq, __ATOMIC_ACQUIRE) == seq; };
     for (unsigned spin = 1; !there(); ++spin) {
@@ -618,8 +623,8 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     c->res = (RoundResult*)(c->stage + kRingBytes);
     c->res_dev = (RoundResult*)(c->stage_dev + kRingBytes);
     c->res->seq = 0;
-    c->res->stuck = 0;
-    for (auto& M : c->M) M.stuck = &c->res_dev->stuck;
+    c->res->gone = 0;
+    for (auto& M : c->M) M.short_passes = (params->flags & PSD_FLAG_SHORT_PASSES) != 0;
     for (auto& e : c->ev) CK(hipEventCreate(&e));
     for (auto& st : c->aux) CK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
     for (auto& e : c->aux_ready) CK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -712,8 +717,9 @@ extern "C" int psd_forward(psd_ctx* c, int32_t which, const int32_t* tokens, int
         if ((rc = model_stamp(M, d, 1, c->stream, c->err)) != PSD_OK) return rc;
         if ((rc = upload(c, M.desc, &d, desc_bytes(d))) != PSD_OK) return rc;
         if ((rc = run_pass(c, which, wclass(w), logits_out ? c->HL : nullptr, false)) != PSD_OK) return rc;
-        if ((rc = stage_sync(c)) != PSD_OK) return rc;
-    } while (passes_expired(c));
+        rc = M.room ? fetch_round(c, nullptr, nullptr, 0, 0) : stage_sync(c);
+    } while (rc == kPassExpired);
+    if (rc != PSD_OK) return rc;
     room.give();
     M.len = pos0 + w;
     if (logits_out) PSD_HIP(hipMemcpy(logits_out, c->HL, (size_t)w * c->V * sizeof(float), hipMemcpyDeviceToHost), c->err);

@@ -2035,21 +2035,21 @@ __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qk
 //   written again only by work that needs, through the all-to-all stages in between, the results of everybody who read them.
 //   The new keys and values of a layer are read by the attention of later tokens too, whose groups may lag behind: they have
 //   slots of their own for every layer.
-// Every wait is bounded by the 100 MHz clock: a workgroup whose wait expires (the launch is not resident as a whole) says so in
-// *stuck and ends, the others follow, and the host runs the pass again as a chain of launches.
+// Every wait is bounded by the 100 MHz clock: a workgroup whose wait expires (the launch is not resident as a whole) says so in the
+// descriptor (kPassGone tokens) and ends, the others follow, and the host runs the round again as chains of launches.  The draft steps
+// behind such a pass have no tokens either and end at once: 30 of them would wait 1.5 s in turn.
 typedef unsigned long long slot_t;
 struct F32Pass {
     const float *embed, *final_norm;
     LayerW w;            // of layer 0; those of layer l lie l * layer_bytes further
     size_t layer_bytes;
-    const PassDesc* desc;
+    PassDesc* desc;
     const float2* rope;
     float* kv;
     const int32_t* page_table;
     int n_pages;
     slot_t *X, *Q, *A, *G, *KVn;   // [32][d] residual stream, [32][d] queries, [32][d] attention output, [32][F] SwiGLU output, [L][32][2 KV hd] new keys and values
     float* logits;
-    uint32_t* stuck;
     unsigned long long wait_ticks;
     float eps, inv_d;
     int L, d, H, KV, F, V, hd_log;
@@ -2485,7 +2485,7 @@ __global__ __launch_bounds__(256, 2) void pass_f32(const F32Pass a) {
     __shared__ __align__(16) float zeros[4];
     __shared__ int bad, pages[2 * kF32OneSplits];
     if (threadIdx.x < 4) zeros[threadIdx.x] = 0.f;
-    const F32PassVals dv{a.desc->w, a.desc->pos0, a.desc->n_logit, a.desc->logit_row0, a.desc->tag0};
+    const F32PassVals dv{a.desc->w, a.desc->pos0, min(a.desc->n_logit, a.desc->w), a.desc->logit_row0, a.desc->tag0};
     if (threadIdx.x == 0) bad = 0;
     if (threadIdx.x < 2 * kF32OneSplits) pages[threadIdx.x] = a.page_table[min((int)threadIdx.x, a.n_pages - 1)];
     const auto qkv = f32_part<kStQkv, NC>(a, dv);
@@ -2523,7 +2523,7 @@ __global__ __launch_bounds__(256, 2) void pass_f32(const F32Pass a) {
         else if (ok) ok = f32_project<kStDown, NC>(a, lds, zeros, bad, dv, down, l, f, rot, page, fetch_next);
     }
     if (lm.mine && ok) ok = f32_project<kStLogits, NC>(a, lds, zeros, bad, dv, lm, a.L, f, rot, page, [] {});
-    if (!ok && threadIdx.x == 0) __hip_atomic_store(a.stuck, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (!ok && threadIdx.x == 0) __hip_atomic_store(&a.desc->w, kPassGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---- profiler ---------------------------------------------------------------------------------------
@@ -2974,14 +2974,13 @@ static void launch_pass_f32(Launch& L, float* logits) {
     a.G = a.A + (size_t)kMaxW * d;
     a.KVn = (slot_t*)(M.qkv + (size_t)kMaxW * M.nqkv);
     a.logits = logits;
-    a.stuck = M.stuck;
     a.wait_ticks = wait_ticks();
     a.eps = M.eps;
     a.inv_d = 1.f / (float)d;
     a.L = M.L; a.d = d; a.H = M.H; a.KV = M.KV; a.F = F; a.V = M.V;
     a.hd_log = HD == 16 ? 4 : HD == 32 ? 5 : HD == 64 ? 6 : 7;
     f32_pass_parts(M, a.nux);
-    const int grid = f32_pass_grid(M, L.wcls);
+    const int grid = std::max(1, f32_pass_grid(M, L.wcls) - (M.short_passes ? 1 : 0));
     L.begin("pass_f32", (double)M.weight_bytes);
     if (L.wcls == 1) pass_f32<HD, 1><<<grid, 256, 0, L.s>>>(a);
     else if (L.wcls <= 16) pass_f32<HD, 4><<<grid, 256, 0, L.s>>>(a);

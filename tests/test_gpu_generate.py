@@ -340,6 +340,33 @@ def test_rounds_are_run_again_after_an_expired_pass(tiny_stack, kind):
             assert np.allclose(res[0][2][m], res[1][2][m], rtol=1e-12), m   # sums of the same numbers in the same order
 
 
+@pytest.mark.parametrize("kind", ["psd", "sd", "plain", "forward"])
+def test_draft_steps_behind_an_expired_pass_end_at_once(tiny_stack, kind):
+    # a workgroup of the one-launch passes stays away until a wait of 50 ms has expired: the first draft step waits that long, the 29 (or 19)
+    # behind it have nothing to do, the pass that judges them waits once more; then the round is run again
+    cfg, d, q, t, prompt = tiny_stack
+    res = []
+    for flags in (0, 0x200):
+        ctx = _ctx(cfg, (d, q, t), 16 + 32 + 40, 0.3, 0.2, 30, 31, flags=flags)
+        before = psd.get_accept_expiries()
+        st = {}
+        if kind == "psd":
+            out, st = ctx.generate(prompt, 24, 5)
+        elif kind == "sd":
+            out, st = ctx.generate_sd(0, 20, 0.02, prompt, 24, 5)
+        elif kind == "plain":
+            out, st = ctx.generate_plain(2, prompt, 24, 5)
+        else:
+            out = ctx.forward(2, prompt, 0)
+        assert psd.get_accept_expiries() - before == (1 if flags else 0) and psd.get_accept_path() == 0
+        if flags and kind in ("psd", "sd"):
+            print(kind, st, flush=True)
+            assert 45.0 < st["ms_d"] < 95.0
+        res.append(out)
+        ctx.close()
+    assert np.array_equal(res[0], res[1])
+
+
 def test_contexts_on_their_own_threads_share_the_device(tiny_stack):
     # one-launch passes of up to 192 workgroups (verify passes of nine tokens) and of 256 (of 32) by six contexts at a time: all of them together
     # would not fit, so some rounds go as chains; nobody's wait expires and everybody's tokens are those of a context that runs alone
