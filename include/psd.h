@@ -97,8 +97,9 @@ enum {
     PSD_FLAG_ROW_STATS = 4,         /* collect entropy and largest probability of every logits row the loops produce
                                        (Section 4, model behaviour analysis); read with psd_get_row_stats */
     PSD_FLAG_SCRAMBLE_PAGES = 0x100, /* test aid: hand out physical KV pages in a shuffled order */
-    PSD_FLAG_SHORT_PASSES = 0x200    /* test aid: until a bounded wait has expired (see psd_set_accept_path), one-launch passes of
+    PSD_FLAG_SHORT_PASSES = 0x200,   /* test aid: until a bounded wait has expired (see psd_set_accept_path), one-launch passes of
                                         small fp32 models are launched without their last workgroup */
+    PSD_FLAG_LAST_TAGS = 0x400       /* test aid: after seven of those passes a model's tags are used up and start again */
 };
 
 typedef struct {

@@ -625,6 +625,9 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     c->res->seq = 0;
     c->res->gone = 0;
     for (auto& M : c->M) M.short_passes = (params->flags & PSD_FLAG_SHORT_PASSES) != 0;
+    if (params->flags & PSD_FLAG_LAST_TAGS)
+        for (auto& M : c->M)
+            if ((rc = model_near_last_tag(M, 7, c->stream, c->err)) != PSD_OK) return fail(rc);
     for (auto& e : c->ev) CK(hipEventCreate(&e));
     for (auto& st : c->aux) CK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
     for (auto& e : c->aux_ready) CK(hipEventCreateWithFlags(&e, hipEventDisableTiming));

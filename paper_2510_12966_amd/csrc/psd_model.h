@@ -173,6 +173,9 @@ int model_map_pages(Model& M, int keep, int upto, int* first_changed, int* n_cha
 
 // Gives a descriptor tags of its own for `passes` passes in a row (a draft chain); in stream order, before the descriptor travels.
 int model_stamp(Model& M, PassDesc& d, int passes, hipStream_t stream, char* err);
+// Test aid: as after long service, tags for `passes` more passes are left, and the slots hold one of the first again (tag 1, that of
+// the first layer's queries, keys and values: whoever finds it takes a number for them that is none of theirs).
+int model_near_last_tag(Model& M, int passes, hipStream_t stream, char* err);
 
 // Enqueues one pass described by *M.desc (already on the device).  wmax: one of kNarrowClasses = widest pass the launch must cover;
 // 128, 256, 384 or 512 (bf16 models, logits == nullptr, at most ingest_max): prompt ingestion.

@@ -2945,6 +2945,14 @@ static void launch_proj_f32(Launch& L, const char* family, F32Args a) {
     L.end();
 }
 
+int model_near_last_tag(Model& M, int passes, hipStream_t stream, char* err) {
+    if (!M.one_launch) return PSD_OK;
+    PSD_HIP(hipMemsetD32Async(M.x + (size_t)kMaxW * M.d, 1, (size_t)(kCols - kMaxW) * M.d, stream), err);
+    PSD_HIP(hipMemsetD32Async(M.qkv + (size_t)kMaxW * M.nqkv, 1, (size_t)(kCols - kMaxW) * M.nqkv, stream), err);
+    M.tag_last = 0xffffffffu - (uint32_t)(passes * 5 * M.L);
+    return PSD_OK;
+}
+
 int model_stamp(Model& M, PassDesc& d, int passes, hipStream_t stream, char* err) {
     if (!M.room) return PSD_OK;
     d.tag_step = 5 * M.L;

@@ -384,6 +384,26 @@ def test_fp32_one_launch_passes_equal_the_chain_of_launches(layers, d, h, kv, f,
     assert np.abs(got[0][:160] - ref).max() <= TOL_F32
 
 
+@pytest.mark.parametrize("widths", [(3, 1, 1, 5, 2, 1, 4, 32, 1, 17, 8, 24, 1), (1,) * 30])
+def test_fp32_tags_start_again_when_they_are_used_up(widths):
+    # seven passes before the end of the tags; the slots hold tag 1, which the first pass after it waits for, with a wrong value
+    shape = ModelShape(3, 64, 4, 2, 256, 300)
+    blob = synth.target_weights(shape, 62, synth.DTYPE_F32, sigma=0.06)
+    toks = synth.tokens(25, 0, 128, 300)
+    got = []
+    for flags in (0, 0x400):
+        ctx = _ctx((shape,) * 3, (blob,) * 3, synth.DTYPE_F32, 10000.0, 128, flags=flags)
+        before = psd.get_accept_expiries()
+        out, pos = [], 0
+        for w in widths:
+            out.append(ctx.forward(0, toks[pos:pos + w], pos))
+            pos += w
+        assert psd.get_accept_expiries() == before
+        got.append(np.concatenate(out))
+        ctx.close()
+    assert np.array_equal(got[0], got[1])
+
+
 def test_fp32_passes_return_to_one_launch_after_an_expired_wait():
     # what kept one launch from being resident may be over: after a pause of 1024 passes the context tries again
     shape = ModelShape(2, 64, 4, 2, 256, 512)

@@ -367,6 +367,19 @@ def test_draft_steps_behind_an_expired_pass_end_at_once(tiny_stack, kind):
     assert np.array_equal(res[0], res[1])
 
 
+def test_tags_start_again_within_a_draft_chain(tiny_stack):
+    # rounds of four draft steps: three tags' worth are left when the second round asks for four
+    cfg, d, q, t, prompt = tiny_stack
+    res = []
+    for flags in (0, 0x400):
+        ctx = _ctx(cfg, (d, q, t), 16 + 64 + 10, 0.004, 0.012, 4, 8, flags=flags)
+        before = psd.get_accept_expiries()
+        res.append(ctx.generate(prompt, 64, 5)[0])
+        assert psd.get_accept_expiries() == before
+        ctx.close()
+    assert np.array_equal(res[0], res[1])
+
+
 def test_contexts_on_their_own_threads_share_the_device(tiny_stack):
     # one-launch passes of up to 192 workgroups (verify passes of nine tokens) and of 256 (of 32) by six contexts at a time: all of them together
     # would not fit, so some rounds go as chains; nobody's wait expires and everybody's tokens are those of a context that runs alone
