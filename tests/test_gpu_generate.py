@@ -340,6 +340,33 @@ def test_rounds_are_run_again_after_an_expired_pass(tiny_stack, kind):
             assert np.allclose(res[0][2][m], res[1][2][m], rtol=1e-12), m   # sums of the same numbers in the same order
 
 
+# which of the three models fit one launch (d_ffn 1024; 1056 does not), and how many expiries a run with waits that end at once has to
+# report: greedy stages wait for nobody, so it is the pass's one; the fuzzy rule's decision expires too, once, and is counted as well
+@pytest.mark.parametrize("kind,greedy,fits,expiries", [("psd", 1, (1, 1, 1), 1), ("psd", 1, (0, 1, 0), 1), ("psd", 1, (0, 0, 1), 1), ("psd", 1, (0, 0, 0), 0),
+                                                       ("psd", 0, (0, 1, 0), 2), ("psd", 0, (0, 0, 1), 2), ("psd", 0, (0, 0, 0), 1),
+                                                       ("sd", 1, (1, 1, 1), 1), ("sd", 1, (0, 0, 1), 1), ("sd", 0, (0, 0, 1), 2), ("sd", 1, (1, 1, 0), 1)])
+def test_every_retry_of_an_expired_pass_is_taken(kind, greedy, fits, expiries):
+    # the draft's steps, the qualifier's pass behind good steps, the target's pass of its own loop, the verifier's pass of the two-model loop
+    shapes = [synth.ModelShape(2, 256, 8, 4, 1024 if f else 1056, 512) for f in fits]
+    blobs = [synth.target_weights(s, 70 + i, synth.DTYPE_F32, sigma=0.06) for i, s in enumerate(shapes)]
+    prompt = synth.tokens(26, 0, 16, 512)
+    res = []
+    for expire in (False, True):
+        ctx = psd.Context(*[_desc(s, b, synth.DTYPE_F32, 10000.0) for s, b in zip(shapes, blobs)], 0.02, 0.03, 4, 8, 16 + 24 + 10,
+                          flags=psd.FLAG_GREEDY if greedy else 0)
+        before = psd.get_accept_expiries()
+        try:
+            if expire:
+                psd.set_accept_path(3)
+            out, st = ctx.generate(prompt, 24, 5) if kind == "psd" else ctx.generate_sd(0, 4, 0.02, prompt, 24, 5)
+        finally:
+            psd.set_accept_path(0)
+        assert psd.get_accept_expiries() - before == (expiries if expire else 0)
+        res.append((out, {k: v for k, v in st.items() if not k.startswith("ms_")}))
+        ctx.close()
+    assert np.array_equal(res[0][0], res[1][0]) and res[0][1] == res[1][1]
+
+
 @pytest.mark.parametrize("kind", ["psd", "sd", "plain", "forward"])
 def test_draft_steps_behind_an_expired_pass_end_at_once(tiny_stack, kind):
     # a workgroup of the one-launch passes stays away until a wait of 50 ms has expired: the first draft step waits that long, the 29 (or 19)
