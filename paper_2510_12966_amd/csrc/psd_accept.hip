@@ -781,7 +781,7 @@ __device__ inline void stage_race(const AcceptShape& s, const AcceptWs& w, const
 // it; the last of them to finish picks the token and is the only one to write the result.  Two launches: SWEEP_PARTIALS stops after the
 // first half, SWEEP_DIVERGENCE repeats the first half without publishing and reads the finished partials.
 // The workgroups of a row are neighbours in launch order and consecutive ids go round the 8 accelerator dies, so
-// the chunks a workgroup waits for are resident with it; nobody waits for a workgroup that is launched after it.
+// the chunks a workgroup waits for are resident with it; deciding and racing workgroups wait only for some that are launched before them.
 template <int MODE, bool VEC>
 __global__ __launch_bounds__(kAccThreads, ((MODE == SWEEP_ONE_LAUNCH || MODE == SWEEP_AND_DECIDE || MODE == SWEEP_STAGE) && VEC) ? 8 : 6) void accept_sweep(AcceptShape s, AcceptWs w, DecideArgs da, int take_bonus) {
     __shared__ float4 lds[kSweepWaves];

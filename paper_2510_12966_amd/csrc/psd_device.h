@@ -40,17 +40,6 @@ __device__ inline void draw4(uint64_t seed, uint32_t block, uint32_t position, u
 }
 
 // ---- reductions: fixed tree, so results never depend on scheduling --------
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-__device__ inline float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 // (key, index) maximum; equal keys -> lowest index
 struct KeyIdx { float key; int idx; };
 __device__ inline KeyIdx better(KeyIdx a, KeyIdx b) {
@@ -79,31 +68,7 @@ __device__ inline KeyIdx wave_best(KeyIdx v) {
     return better(KeyIdx{__uint_as_float(k[0]), (int)i[0]}, KeyIdx{__uint_as_float(k[1]), (int)i[1]});
 }
 
-// block-wide versions for blockDim.x = 64 * NW (NW <= 16); `sm` needs NW slots; result valid in all threads
-template <int NW>
-__device__ inline float block_sum(float v, float* sm) {
-    v = wave_sum(v);
-    if constexpr (NW == 1) return v;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float r = 0.f;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) r += sm[i];
-    return r;
-}
-template <int NW>
-__device__ inline float block_max(float v, float* sm) {
-    v = wave_max(v);
-    if constexpr (NW == 1) return v;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float r = sm[0];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) r = fmaxf(r, sm[i]);
-    return r;
-}
+// block-wide, for blockDim.x = 64 * NW (NW <= 16); `sm` needs NW slots; result valid in all threads
 template <int NW>
 __device__ inline KeyIdx block_best(KeyIdx v, KeyIdx* sm) {
     v = wave_best(v);

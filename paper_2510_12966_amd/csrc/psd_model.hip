@@ -2057,11 +2057,10 @@ struct F32Pass {
 };
 constexpr int kF32PassK = 1024;   // largest K of a projection: 16 weights per lane of a row
 
-__device__ inline slot_t slot_load(const slot_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void slot_store(slot_t* p, uint32_t tag, float v) {
     __hip_atomic_store(p, (slot_t)tag << 32 | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Pairs of slots in one 16-byte load that goes past the caches, as slot_load does; either half of it is as it was stored.  Buffer
+// Pairs of slots in one 16-byte load that goes past the caches, as an agent-scope atomic load does; either half of it is as it was stored.  Buffer
 // addressing: one register of offset per load, the base in scalar registers.
 typedef __amdgpu_buffer_rsrc_t buf_t;
 __device__ inline buf_t buf_of(const void* p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000); }
