@@ -485,6 +485,8 @@ __device__ inline void decide(const AcceptShape& s, const AcceptWs& w, const Dec
                 }
                 if (!__any(missing)) break;
                 if (wall_clock64() - t0 >= s.wait_ticks) { good = false; break; }
+                // two sleeps between polls / eight, us a call: one trial, k = 10 at V 32000 13.2 / 13.3, at 128256 15.0 / 15.1; trials x k,
+                // 4 x 10 at 128256 24.0 / 24.0, 16 x 8 45.3 / 45.7, 48 x 8 106.0 / 106.5; 256 x 2 at 32000 50.1 / 50.4
                 __builtin_amdgcn_s_sleep(2);
             }
             if (!__all(good) && lane == 0) {
