@@ -3148,6 +3148,26 @@ static void launch_gemm_bf16(Launch& L, const char* family, GemmArgs a) {
     L.end();
 }
 
+// Wide passes: one sweep per query tile (attn_wide, attn_pair) where there are enough tiles to fill the device or few key ranges to
+// walk; few tiles over a long context keep a workgroup per key range and the merge kernel.  The most ranges for which a pass of
+// `tiles` query tiles sweeps.  us a layer, ranges + merge / sweep, over the key ranges that the pass's last position has:
+//   head dim 128 (attn_wide: 13 us and 5 for every range after the first)
+//     64 tiles   1: 23 / 13    2: 23 / 19    3: 23 / 23    4: 23 / 28      384 tiles   5: 39 / 34    6: 44 / 39    7: 46 / 43    8: 46 / 48
+//    256 tiles   3: 29 / 25    4: 29 / 30    5: 30 / 34    8: 32 / 50      512 tiles  14: 91 / 82   25: 137 / 138    768 tiles  27: 205 / 145
+//   head dim 64 | 32 (attn_pair: 12 us and 2.3 for every range after the second)
+//    128 tiles   4: 18 / 17 | 16 / 13      5: 18 / 20 | 16 / 15      6: 18 / 21 | 16 / 16      160 tiles   5: 21 / 19    6: 21 / 21    9: 23 / 28
+//    192 tiles   5: 21 / 20                6: 21 / 22                256 tiles   5: 21 / 20 | 17 / 15    6: 22 / 21 | 18 / 16    7: 22 / 24 | 18 / 18
+//    320 tiles  10: 35 / 30               14: 40 / 40               20: 51 / 53
+//    384 tiles   7: 26 / 24 | 21 / 18     15: 45 / 42 | 36 / 31     21: 55 / 56 | 42 / 41     28: 66 / 72 | 48 / 52
+//    480 tiles  28: 81 / 71               39: 97 / 97      512 tiles  29: 85 / 74 | 58 / 54    40: 105 / 99 | 67 / 71    67: 166 / 162 | 95 / 114
+//    640 tiles  67: 200 / 160            768 tiles  66: 243 / 162
+static int sweep_ranges(int hd, int tiles) {
+    constexpr int all = 1 << 30;
+    if (hd > 64) return tiles >= 512 ? all : tiles >= 384 ? 6 : tiles >= 256 ? 4 : 3;
+    if (tiles >= (hd == 64 ? 512 : 640)) return all;
+    return tiles >= 512 ? 39 : tiles >= 448 ? 32 : tiles >= 384 ? 19 : tiles >= 320 ? 13 : tiles >= 256 ? 6 : tiles >= 160 ? 5 : 4;
+}
+
 static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
     hipStream_t stream = L.s;
     const int d = M.d, F = M.F, H = M.H, KV = M.KV, hd = M.hd, G = H / KV;
@@ -3176,20 +3196,10 @@ static int forward_bf16(Model& M, int wmax, float* logits, Launch& L) {
     // algorithmic bytes of one layer's attention: K and V of every key the pass can see, as bf16 (the cache holds a hi and a
     // lo plane per value, so the kernels move twice that), plus the queries in and the outputs back
     const double kv_bytes = (double)std::min(M.max_seq, M.len + wmax) * KV * hd * 2 * 2 + (double)wmax * H * hd * 4 * 2;
-    // Wide passes: one sweep per query tile (attn_wide) where there are enough tiles to fill the device or few key ranges to
-    // walk; few tiles over a long context keep a workgroup per key range and the merge kernel.  us a layer, ranges + merge / sweep,
-    // head dim 64 | 128, over the key ranges that the pass's last position has:
-    //    64 tiles   1: 18 / 10 | 23 / 13    2: 18 / 13 | 23 / 19    3: 18 / 16 | 23 / 23    4: 18 / 19 | 23 / 28    8: 19 / 31 | 23 / 48
-    //   256 tiles   3: 21 / 16 | 29 / 25    4: 21 / 19 | 29 / 30    5: 21 / 22 | 30 / 34    8: 22 / 31 | 32 / 50
-    //   384 tiles   5: 26 / 22 | 39 / 34    6: 26 / 25 | 44 / 39    7: 26 / 29 | 46 / 43    8: 26 / 32 | 46 / 48
-    //   512 tiles   7: 33 / 28 |           14: 55 / 50 | 91 / 82   25: 75 / 84 | 137 / 138
-    //   768 tiles  27: 104 / 86 | 205 / 145
-    // (a sweep takes 10 us and 3 for every range after the first | 13 and 5; the other route starts at 18-23 us and grows with
-    // tiles times ranges).  Head dims up to 64 sweep with two waves per tile since, where there is a second range for the second
-    // wave (attn_wide / attn_pair, us a launch of 64 tiles: one range 7.7-8.3 / 8.3-8.9, two 11.0-11.6 / 10.8-11.3, three 14.2-14.5 / 13.4-13.6); the
-    // lines above are left where head dim 128 has them.
     const int tiles = KV * ((wmax * G + 15) / 16), ranges = (std::min(M.max_seq, M.len + wmax) + kAttnSplit - 1) / kAttnSplit;
-    const bool sweep = c128 && (tiles >= 512 || ranges <= (tiles >= 384 ? 6 : tiles >= 256 ? 4 : 3));
+    const bool sweep = c128 && ranges <= sweep_ranges(hd, tiles);
+    // head dims up to 64 sweep with two waves per tile where there is a second range for the second wave (attn_wide / attn_pair, us a
+    // launch of 64 tiles: one range 7.7-8.3 / 8.3-8.9, two 11.0-11.6 / 10.8-11.3, three 14.2-14.5 / 13.4-13.6)
     const bool fold_merge = wmax <= 4 && d <= 2048 && d / 16 <= 256 && H * hd == d && nsplit <= kFoldSplits;
     GemmArgs base{};
     base.ss_in = ss; base.ss_tiles = d / 16; base.inv_d = inv_d; base.eps = M.eps;

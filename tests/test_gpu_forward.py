@@ -265,6 +265,27 @@ def test_bf16_two_wave_sweep_is_bit_exact(shape, n):
     assert np.abs(out[0] - ref).max() <= TOL_BF16
 
 
+# passes of one width over a growing context: where they stop sweeping and take a workgroup per key range (384, 256 and 128 query tiles: beyond 19,
+# 6 and 4 ranges) the bits stay
+@pytest.mark.parametrize("shape", [ModelShape(1, 1024, 16, 4, 512, 200), ModelShape(1, 512, 16, 4, 512, 200)])
+def test_bf16_wide_attention_routes_agree_where_the_rule_changes(shape):
+    stub = ModelShape(1, 64, 2, 1, 64, 200)
+    small = synth.target_weights(stub, 85, synth.DTYPE_BF16, sigma=0.03)
+    blob = synth.target_weights(shape, 88, synth.DTYPE_BF16, sigma=0.05)
+    n = 2700
+    ctx = _ctx((stub, stub, shape), (small, small, blob), synth.DTYPE_BF16, 10000.0, 2816, k1=1, k2=1, flags=0x100)
+    toks = synth.tokens(27, 0, n + 3, 200)
+    out = []
+    for step in (32, 384, 256, 128, 512):
+        for pos in range(0, n, step):
+            ctx.forward(2, toks[pos:min(pos + step, n)], pos, want_logits=False)
+        out.append(ctx.forward(2, toks[n:n + 3], n))
+    ctx.close()
+    assert np.isfinite(out[0]).all()
+    for o in out[1:]:
+        assert np.array_equal(o, out[0])
+
+
 # more than 64 key ranges: narrow passes then merge their partials in two turns of a wave's lanes, wide ones merge range by range
 MANY = (ModelShape(2, 1024, 32, 8, 512, 200), ModelShape(2, 1024, 16, 16, 512, 200), ModelShape(2, 2048, 16, 16, 512, 200))
 
