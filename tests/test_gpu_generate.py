@@ -1,4 +1,5 @@
 """GPU parity of the two-stage loop against the CPU oracle, through psd_generate."""
+import ctypes
 import threading
 
 import numpy as np
@@ -412,7 +413,13 @@ def test_contexts_on_their_own_threads_share_the_device(tiny_stack):
     # would not fit, so some rounds go as chains; nobody's wait expires and everybody's tokens are those of a context that runs alone
     cfg, d, q, t, prompt = tiny_stack
     windows = [(4, 8), (4, 8), (30, 31), (4, 8), (2, 4), (30, 31)]
-    ctxs = [_ctx(cfg, (d, q, t), 16 + 64 + 40, 0.3, 0.2, k1, k2) for k1, k2 in windows]
+    # a context has four streams and streams go round the process's four hardware queues: one more in between puts the contexts' passes
+    # on different ones
+    hip, spare, ctxs = ctypes.CDLL("libamdhip64.so"), [], []
+    for k1, k2 in windows:
+        ctxs.append(_ctx(cfg, (d, q, t), 16 + 64 + 40, 0.3, 0.2, k1, k2))
+        spare.append(ctypes.c_void_p())
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(spare[-1]), 1) == 0   # hipStreamNonBlocking
     alone = [c.generate(prompt, 64, 5 + i)[0] for i, c in enumerate(ctxs)]
     before = psd.get_accept_expiries()
     got = [[] for _ in ctxs]
@@ -431,6 +438,8 @@ def test_contexts_on_their_own_threads_share_the_device(tiny_stack):
         assert len(runs) == 6 and all(np.array_equal(r, alone[i]) for r in runs), i
     for c in ctxs:
         c.close()
+    for s in spare:
+        assert hip.hipStreamDestroy(s) == 0
 
 
 @pytest.mark.parametrize("case", range(18))
