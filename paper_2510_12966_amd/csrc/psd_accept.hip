@@ -986,13 +986,13 @@ __global__ __launch_bounds__(64) void sample_final(const KeyIdx* parts, int nch,
 
 // one thread: publishes draft token t to the next draft pass and to the verifier's
 __device__ inline void chain_advance(const ChainStep& s, int t) {
-    const int step = s.chain->row;
+    const int step = s.chain->row, gone = s.chain->gone;
     s.samp_tok[0] = t;
     if (step < kMaxW) s.round_tok[step] = t;
     if (s.q_desc && s.chain->q_base >= 0 && s.chain->q_base + step < kMaxW) s.q_desc->tok[s.chain->q_base + step] = t;
-    const int w = s.d_desc->w;
-    s.d_desc->pos0 += max(w, 0);
-    s.d_desc->w = min(w, 1);   // kPassGone stays: the steps behind an expired pass have no tokens either
+    s.d_desc->pos0 += s.d_desc->w;
+    s.d_desc->w = gone ? 0 : 1;   // the steps behind an expired pass have nothing to do
+    if (gone) s.d_desc->n_logit = 0;
     s.d_desc->tok[0] = t;
     s.d_desc->logit_row0 = step + 1;
     s.d_desc->tag0 += s.d_desc->tag_step;

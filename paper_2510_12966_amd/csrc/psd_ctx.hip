@@ -187,18 +187,25 @@ __global__ __launch_bounds__(256) void scatter_pieces(const uint32_t* __restrict
     }
 }
 
-struct PassDescs { PassDesc* of[3]; };
-// what the host needs of a round, into pinned host memory; its number goes last.  One wave.
+// what the host needs of a round, into pinned host memory; its number goes last.  One wave; everything is asked for before anything is
+// waited for.
 __global__ __launch_bounds__(64) void publish_round(const AcceptOut* acc, const int32_t* tok, int n_tok, const float* div, int n_div,
-                                                    PassDescs descs, RoundResult* res, uint32_t seq) {
+                                                    SampleCtl* chain, RoundResult* res, uint32_t seq) {
     const int i = threadIdx.x;
-    if (i < 3 && descs.of[i]->w == kPassGone) {
-        descs.of[i]->w = 0;   // told once
+    int32_t t = 0;
+    float d = 0.f;
+    AcceptOut a{};
+    const int32_t gone = chain->gone;
+    if (i < n_tok) t = tok[i];
+    if (i < n_div) d = div[i];
+    if (acc && i == 0) a = *acc;
+    if (i < n_tok) res->tok[i] = t;
+    if (i < n_div) res->div[i] = d;
+    if (acc && i == 0) res->acc = a;
+    if (gone && i == 0) {
+        chain->gone = 0;   // told once
         res->gone = 1;
     }
-    if (i < n_tok) res->tok[i] = tok[i];
-    if (i < n_div) res->div[i] = div[i];
-    if (acc && i == 0) res->acc = *acc;
     __threadfence_system();   // all of the wave's stores
     if (i == 0) __hip_atomic_store(&res->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -298,7 +305,7 @@ struct PassRoom {
 // Everything enqueued before is then done.  kPassExpired: it has to be run again.
 static int fetch_round(psd_ctx* c, const AcceptOut* acc, const int32_t* tok, int n_tok, int n_div) {
     const uint32_t seq = ++c->res_seq;
-    publish_round<<<1, 64, 0, c->stream>>>(acc, tok, n_tok, c->acc_div, n_div, PassDescs{{c->M[0].desc, c->M[1].desc, c->M[2].desc}}, c->res_dev, seq);
+    publish_round<<<1, 64, 0, c->stream>>>(acc, tok, n_tok, c->acc_div, n_div, c->chain, c->res_dev, seq);
     PSD_HIP(hipGetLastError(), c->err);
     auto there = [&] { return __atomic_load_n(&c->res->seq, __ATOMIC_ACQUIRE) == seq; };
     for (unsigned spin = 1; !there(); ++spin) {
@@ -624,7 +631,11 @@ extern "C" int psd_create(const psd_model_desc* draft, const psd_model_desc* qua
     c->res_dev = (RoundResult*)(c->stage_dev + kRingBytes);
     c->res->seq = 0;
     c->res->gone = 0;
-    for (auto& M : c->M) M.short_passes = (params->flags & PSD_FLAG_SHORT_PASSES) != 0;
+    CK(hipMemsetAsync(c->chain, 0, sizeof(SampleCtl), c->stream));
+    for (auto& M : c->M) {
+        M.gone = &c->chain->gone;
+        M.short_passes = (params->flags & PSD_FLAG_SHORT_PASSES) != 0;
+    }
     if (params->flags & PSD_FLAG_LAST_TAGS)
         for (auto& M : c->M)
             if ((rc = model_near_last_tag(M, 7, c->stream, c->err)) != PSD_OK) return fail(rc);

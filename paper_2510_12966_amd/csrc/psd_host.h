@@ -68,7 +68,7 @@ struct SampleCtl {
     int32_t position;  // absolute position of the token the next sample decides
     int32_t row;       // logits row the next sample reads (= index of the draft step in its round)
     int32_t q_base;    // slot of the qualifier pass descriptor that receives the first draft token (-1: none)
-    int32_t pad;
+    int32_t gone;      // the bounded wait of a one-launch pass has expired: the round is void
 };
 
 // Fresh samples: row r -> token for position position0 + r.  partial: n_rows * accept_chunks(vocab) * 8 bytes.

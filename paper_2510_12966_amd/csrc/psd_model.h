@@ -41,11 +41,10 @@ inline int narrow_class_index(int w) {   // -1 when w is wider than the widest c
     return -1;
 }
 
-constexpr int32_t kPassGone = -1;   // PassDesc::w as a one-launch pass leaves it whose bounded wait has expired
 // What one forward pass has to do; lives in DEVICE memory so that a captured graph can be replayed
 // with new contents.  Written by the host before a pass, or by the sampling kernel for the draft chain.
 struct PassDesc {
-    int32_t w;           // tokens in this pass (1..32; up to 512 while ingesting a prompt), or kPassGone
+    int32_t w;           // tokens in this pass (1..32; up to 512 while ingesting a prompt; 0: a one-launch pass with nothing to do)
     int32_t pos0;        // position of the first token == number of valid KV rows before the pass
     int32_t n_logit;     // the last n_logit tokens get logit rows (0 = none)
     int32_t logit_row0;  // first destination row in the logits buffer
@@ -150,6 +149,7 @@ struct Model {
     int grid_max = 0;         // widest such launch
     Places* places = nullptr; // of the model's device
     uint32_t tag_last = 0;    // last tag handed out to a pass
+    int32_t* gone = nullptr;     // SampleCtl::gone of the context
     bool short_passes = false;   // test aid: a workgroup of every one-launch pass stays away
     PassDesc* desc = nullptr;
     // host mirror

@@ -2035,21 +2035,22 @@ __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qk
 //   written again only by work that needs, through the all-to-all stages in between, the results of everybody who read them.
 //   The new keys and values of a layer are read by the attention of later tokens too, whose groups may lag behind: they have
 //   slots of their own for every layer.
-// Every wait is bounded by the 100 MHz clock: a workgroup whose wait expires (the launch is not resident as a whole) says so in the
-// descriptor (kPassGone tokens) and ends, the others follow, and the host runs the round again as chains of launches.  The draft steps
-// behind such a pass have no tokens either and end at once: 30 of them would wait 1.5 s in turn.
+// Every wait is bounded by the 100 MHz clock: a workgroup whose wait expires (the launch is not resident as a whole) says so in *gone
+// and ends, the others follow, and the host runs the round again as chains of launches.  The draft steps behind such a pass get no
+// tokens (chain_advance) and end at once: 30 of them would wait 1.5 s in turn.
 typedef unsigned long long slot_t;
 struct F32Pass {
     const float *embed, *final_norm;
     LayerW w;            // of layer 0; those of layer l lie l * layer_bytes further
     size_t layer_bytes;
-    PassDesc* desc;
+    const PassDesc* desc;
     const float2* rope;
     float* kv;
     const int32_t* page_table;
     int n_pages;
     slot_t *X, *Q, *A, *G, *KVn;   // [32][d] residual stream, [32][d] queries, [32][d] attention output, [32][F] SwiGLU output, [L][32][2 KV hd] new keys and values
     float* logits;
+    int32_t* gone;
     unsigned long long wait_ticks;
     float eps, inv_d;
     int L, d, H, KV, F, V, hd_log;
@@ -2484,7 +2485,7 @@ __global__ __launch_bounds__(256, 2) void pass_f32(const F32Pass a) {
     __shared__ __align__(16) float zeros[4];
     __shared__ int bad, pages[2 * kF32OneSplits];
     if (threadIdx.x < 4) zeros[threadIdx.x] = 0.f;
-    const F32PassVals dv{a.desc->w, a.desc->pos0, min(a.desc->n_logit, a.desc->w), a.desc->logit_row0, a.desc->tag0};
+    const F32PassVals dv{a.desc->w, a.desc->pos0, a.desc->n_logit, a.desc->logit_row0, a.desc->tag0};
     if (threadIdx.x == 0) bad = 0;
     if (threadIdx.x < 2 * kF32OneSplits) pages[threadIdx.x] = a.page_table[min((int)threadIdx.x, a.n_pages - 1)];
     const auto qkv = f32_part<kStQkv, NC>(a, dv);
@@ -2522,7 +2523,7 @@ __global__ __launch_bounds__(256, 2) void pass_f32(const F32Pass a) {
         else if (ok) ok = f32_project<kStDown, NC>(a, lds, zeros, bad, dv, down, l, f, rot, page, fetch_next);
     }
     if (lm.mine && ok) ok = f32_project<kStLogits, NC>(a, lds, zeros, bad, dv, lm, a.L, f, rot, page, [] {});
-    if (!ok && threadIdx.x == 0) __hip_atomic_store(&a.desc->w, kPassGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!ok && threadIdx.x == 0) __hip_atomic_store(a.gone, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---- profiler ---------------------------------------------------------------------------------------
@@ -2981,6 +2982,7 @@ static void launch_pass_f32(Launch& L, float* logits) {
     a.G = a.A + (size_t)kMaxW * d;
     a.KVn = (slot_t*)(M.qkv + (size_t)kMaxW * M.nqkv);
     a.logits = logits;
+    a.gone = M.gone;
     a.wait_ticks = wait_ticks();
     a.eps = M.eps;
     a.inv_d = 1.f / (float)d;
