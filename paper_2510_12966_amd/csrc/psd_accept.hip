@@ -18,8 +18,9 @@
 //   accept_pick    per trial: winner of the race; in small calls the race's last workgroup does it
 // In calls of one trial the race's workgroups are part of the sweep's launch too and wait for the decision, with the race over the
 // bonus row done meanwhile: two launches.  Bound: the chain loads - row exchange - divergence exchange - decision - race -
-// count - pick, 12.7 us of which 7.5 are trips through memory between workgroups (k = 10: 18.0 us a call with the race as a launch of
-// its own and reductions by shuffles, 15.1 now).  Race workgroups that read the divergences and decide for themselves instead of
+// count - pick, 12.7 us of which 7.5 are trips through memory between workgroups.  k = 10 at V 128256, calls one after the other: with the
+// race as a launch of its own and reductions by shuffles 17.9 us where a position is rejected, 16.9 to 17.9 where all are accepted; now
+// 15.4 and 13.7.  Race workgroups that read the divergences and decide for themselves instead of
 // waiting for the decision: 17.6, polls of the lines that are being written hold the writers up.
 // Bulk arithmetic runs in base 2 on the hardware exp2 / log2 units; the two probabilities the coin
 // compares are evaluated with the accurate library functions.  No floating-point atomics: every

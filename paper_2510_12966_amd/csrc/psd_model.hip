@@ -2027,8 +2027,9 @@ __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qk
 // has the value (an all-gather of 512 slots among 32 workgroups: 1.1 us, on one die or across all eight).  A stage asks for its
 // weights first and polls its input while they travel.  The pieces of work and the arithmetic are those of proj_f32 and
 // attn_one_f32, so the results have the same bits.  Bound: the chain of exchanges and the instructions of one wave per SIMD between them, 2-4 us a
-// stage.  Tiny stack, us a pass between events: draft step with its sampling (2 layers, d 64) 61 -> 30, qualifier (4, d 128, 5 tokens)
-// 120 -> 68, target (6, d 256, 9 tokens) 201 -> 118.
+// stage: the exchange is 1.1 us of it among 32 workgroups and 2 to 2.5 among 192, the rest are instructions (340 to 450 spilled scalar
+// registers that the stages read back are a part of them).  Tiny stack, us a pass between events: draft step with its sampling (2
+// layers, d 64) 61 -> 30, qualifier (4, d 128, 5 tokens) 120 -> 68, target (6, d 256, 9 tokens) 201 -> 118.
 // Tags are the pass's own, one per stage (tag0 + 5 l + 1 ..: q/k/v, attention, o, SwiGLU, down), and no slot is written again
 // while somebody may still wait for its former tag:
 //   X, Q, A, G hold one row per token and are handled in groups of NC tokens by every projection.  A group's slots of one buffer are
@@ -2736,8 +2737,13 @@ static int f32_pass_grid(const Model& M, int wcls) {
     for (int i = 0; i < 6; ++i) most = std::max(most, nux[i] * (i == 1 ? wcls : groups));
     return most;
 }
-// A pass in one launch, of a workgroup per CU at most (grid_max): models whose projections that many can hold (16 weights per lane of a row, no more than the 2 M
-// weights of a projection up to which proj_f32 gives every group of columns workgroups of its own).
+// A pass in one launch, of a workgroup per CU at most (grid_max): models whose projections that many can hold (16 weights per lane of a
+// row: d and d_ffn up to 1024; no more than the 2 M weights of a projection up to which proj_f32 gives every group of columns
+// workgroups of its own) and whose slots fit (d_ffn up to 4.5 d, layers up to 3.75 (H / KV + 2)).  The LM head counts in the grid: on 256
+// CUs the vocabulary may have 8192 entries (2048 where d > 256) in passes of up to four tokens, a quarter of that in passes of 13-16 and
+// 25-32; one model's classes may go either way.  Nowhere slower than the chain as a graph, over 13 shapes up to these limits, 20 to 900
+// tokens of context and 1 to 31 tokens a pass; us a draft step, one launch / chain: d 64, 2 layers 30 / 58; d 256, 6 layers 90 / 168; d 512, 4
+// layers 78 / 111; d 1024 in 64 heads, 4 layers 82 / 126; d 256, 8 layers, head dim 128 behind 900 tokens 335 / 509.
 static bool f32_one_launch(const Model& M) {
     const size_t most = (size_t)2 << 20;
     return M.dtype == PSD_F32 && M.d <= kF32PassK && M.F <= kF32PassK && (size_t)2 * M.F * M.d <= most && (size_t)M.nqkv * M.d <= most &&
