@@ -2067,10 +2067,14 @@ __device__ inline void slot_store(slot_t* p, uint32_t tag, float v) {
 typedef __amdgpu_buffer_rsrc_t buf_t;
 __device__ inline buf_t buf_of(const void* p, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000); }
 __device__ inline u32x4 pair_load(buf_t b, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 16 | (int)0x80000000); }   // sc1, volatile
-// Waits for N pairs of slots at byte offsets off(u), until all of them carry `tag`; false when the wait expired
+// Bound of all the waiting that a stage does: lanes whose first wait ended well beside lanes whose wait expired do not wait once more
+struct WaitBound {
+    unsigned long long t0, ticks;
+    __device__ bool over() const { return wall_clock64() - t0 >= ticks; }
+};
+// Waits for N pairs of slots at byte offsets off(u), until all of them carry `tag`; false when the bound was over
 template <int N, typename O>
-__device__ inline bool pairs_wait(buf_t b, O off, uint32_t tag, unsigned long long ticks, u32x4 (&v)[N]) {
-    const unsigned long long t0 = wall_clock64();
+__device__ inline bool pairs_wait(buf_t b, O off, uint32_t tag, const WaitBound& bound, u32x4 (&v)[N]) {
     for (;;) {
         uint32_t diff = 0;
 #pragma unroll
@@ -2078,28 +2082,28 @@ __device__ inline bool pairs_wait(buf_t b, O off, uint32_t tag, unsigned long lo
 #pragma unroll
         for (int u = 0; u < N; ++u) diff |= (v[u].y ^ tag) | (v[u].w ^ tag);
         if (diff == 0) return true;
-        if (wall_clock64() - t0 >= ticks) return false;
+        if (bound.over()) return false;
     }
 }
 // n slots (even, at least two) from the start of b into LDS, by 256 threads
 template <int N>
-__device__ inline bool slots_gather_as(int tid, buf_t b, int n, uint32_t tag, unsigned long long ticks, float* dst) {
+__device__ inline bool slots_gather_as(int tid, buf_t b, int n, uint32_t tag, const WaitBound& bound, float* dst) {
     u32x4 v[N];
-    const bool ok = pairs_wait<N>(b, [&](int u) { return (uint32_t)min(2 * tid + 512 * u, n - 2) * 8; }, tag, ticks, v);
+    const bool ok = pairs_wait<N>(b, [&](int u) { return (uint32_t)min(2 * tid + 512 * u, n - 2) * 8; }, tag, bound, v);
 #pragma unroll
     for (int u = 0; u < N; ++u)
         if (2 * tid + 512 * u < n) *reinterpret_cast<float2*>(dst + 2 * tid + 512 * u) = make_float2(__uint_as_float(v[u].x), __uint_as_float(v[u].z));
     return ok;
 }
-__device__ inline bool slots_gather(int tid, const slot_t* p, int n, uint32_t tag, unsigned long long ticks, float* dst) {
+__device__ inline bool slots_gather(int tid, const slot_t* p, int n, uint32_t tag, const WaitBound& bound, float* dst) {
     if (2 * tid >= n) return true;
     const buf_t b = buf_of(p, n * 8);
-    if (n <= 512) return slots_gather_as<1>(tid, b, n, tag, ticks, dst);
-    if (n <= 1024) return slots_gather_as<2>(tid, b, n, tag, ticks, dst);
+    if (n <= 512) return slots_gather_as<1>(tid, b, n, tag, bound, dst);
+    if (n <= 1024) return slots_gather_as<2>(tid, b, n, tag, bound, dst);
     bool ok = true;
     for (int i = 0; i < n && ok; i += 4096) {
         if (2 * tid >= n - i) break;
-        ok = slots_gather_as<8>(tid, buf_of(p + i, (n - i) * 8), n - i, tag, ticks, dst + i);
+        ok = slots_gather_as<8>(tid, buf_of(p + i, (n - i) * 8), n - i, tag, bound, dst + i);
     }
     return ok;
 }
@@ -2210,6 +2214,7 @@ __device__ inline bool f32_project(const F32Pass& a, float* xs, const float* zer
         }
     }
     __syncthreads();   // the last stage's LDS has been read
+    const WaitBound bound{(unsigned long long)wall_clock64(), a.wait_ticks};
     bool ok = true;
     if (K_ == kStQkv && layer == 0) {
         for (int cc = 0; cc < nc; ++cc) {
@@ -2218,12 +2223,12 @@ __device__ inline bool f32_project(const F32Pass& a, float* xs, const float* zer
         }
     } else {
         const slot_t* src = (K_ == kStO ? a.A : K_ == kStDown ? a.G : a.X) + c0 * K;
-        ok = slots_gather(tid, src, nc * K, tag_in, a.wait_ticks, xs);
+        ok = slots_gather(tid, src, nc * K, tag_in, bound, xs);
     }
     if (kStResid<K_> && fin && !embedded && ok) {
         if (r.y != old || r.w != old) {
             u32x4 again[1];
-            ok = pairs_wait<1>(res, [&](int) { return res_off; }, old, a.wait_ticks, again);
+            ok = pairs_wait<1>(res, [&](int) { return res_off; }, old, bound, again);
             r = again[0];
         }
         y1 = __uint_as_float(r.x);
@@ -2363,6 +2368,7 @@ __device__ inline bool f32_attend(const F32Pass& a, float* lds, int& bad, const 
         const buf_t kn = buf_of(a.KVn + ((size_t)layer * kMaxW * 2 * a.KV + g) * HD, row * (c + 1)), q = buf_of(a.Q + c * a.d + h * HD, HD * 8);
         u32x4 q0 = u32x4{0u, 0u, 0u, 0u};
         if (tid < HD / 2) q0 = pair_load(q, tid * 16);
+        const WaitBound bound{(unsigned long long)wall_clock64(), a.wait_ticks};
         bool ok = true;
         auto gather = [&](auto n, int i0) {
             constexpr int N = decltype(n)::value;
@@ -2370,7 +2376,7 @@ __device__ inline bool f32_attend(const F32Pass& a, float* lds, int& bad, const 
             if (!pairs_wait<N>(kn, [&](int u) {
                     const int i = min(i0 + 256 * u, npairs - 1);
                     return (uint32_t)((i / HD) * row + (i & (HD / 2) ? a.KV * HD * 8 : 0) + (i & (HD / 2 - 1)) * 16);
-                }, tag_in, a.wait_ticks, v)) ok = false;
+                }, tag_in, bound, v)) ok = false;
 #pragma unroll
             for (int u = 0; u < N; ++u) {
                 const int i = i0 + 256 * u;
@@ -2384,7 +2390,7 @@ __device__ inline bool f32_attend(const F32Pass& a, float* lds, int& bad, const 
         if (tid < HD / 2) {
             if (q0.y != tag_in || q0.w != tag_in) {
                 u32x4 again[1];
-                if (!pairs_wait<1>(q, [&](int) { return (uint32_t)tid * 16; }, tag_in, a.wait_ticks, again)) ok = false;
+                if (!pairs_wait<1>(q, [&](int) { return (uint32_t)tid * 16; }, tag_in, bound, again)) ok = false;
                 q0 = again[0];
             }
             *reinterpret_cast<float2*>(s_q + 2 * tid) = make_float2(__uint_as_float(q0.x), __uint_as_float(q0.z));

@@ -390,6 +390,7 @@ def test_draft_steps_behind_an_expired_pass_end_at_once(tiny_stack, kind):
         if flags and kind in ("psd", "sd"):
             print(kind, st, flush=True)
             assert 45.0 < st["ms_d"] < 95.0
+            assert 45.0 < st["ms_q" if kind == "psd" else "ms_t"] < 95.0   # a workgroup does not wait twice
         res.append(out)
         ctx.close()
     assert np.array_equal(res[0], res[1])
