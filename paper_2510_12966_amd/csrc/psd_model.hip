@@ -2027,7 +2027,7 @@ __global__ __launch_bounds__(256) void attn_one_f32(const float* __restrict__ qk
 // has the value (an all-gather of 512 slots among 32 workgroups: 1.1 us, on one die or across all eight).  A stage asks for its
 // weights first and polls its input while they travel.  The pieces of work and the arithmetic are those of proj_f32 and
 // attn_one_f32, so the results have the same bits.  Bound: the chain of exchanges and the instructions of one wave per SIMD between them, 2-4 us a
-// stage: the exchange is 1.1 us of it among 32 workgroups and 2 to 2.5 among 192, the rest are instructions (340 to 450 spilled scalar
+// stage: the exchange is 1.1 us of it among 32 workgroups and 2 to 2.5 among 192, the rest are instructions (350 to 400 spilled scalar
 // registers that the stages read back are a part of them).  Tiny stack, us a pass between events: draft step with its sampling (2
 // layers, d 64) 61 -> 30, qualifier (4, d 128, 5 tokens) 120 -> 68, target (6, d 256, 9 tokens) 201 -> 118.
 // Tags are the pass's own, one per stage (tag0 + 5 l + 1 ..: q/k/v, attention, o, SwiGLU, down), and no slot is written again
